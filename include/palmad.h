@@ -38,9 +38,7 @@
  *     had failed (PALMAD_EDEVICE, no device work); "converge" allows one
  *     range search per length, so a search reports a range search that did
  *     not converge (PALMAD_EDEVICE after device work).
- *   - One context per host thread at a time.  The context caches the
- *     hipGraph of one round of the search for the last workspace and
- *     configuration it saw, and replays it while they stay the same.
+ *   - One context per host thread at a time.
  */
 #ifndef PALMAD_H
 #define PALMAD_H
@@ -93,8 +91,8 @@ typedef struct {
    time per kernel class in palmad_stats (adds two event records per timed
    launch). */
 #define PALMAD_FLAG_TIME_KERNELS 1u
-/* Launch every kernel of a round directly instead of replaying the
-   context's cached round graph (set implicitly by PALMAD_FLAG_TIME_KERNELS). */
+/* Accepted for callers of versions that replayed a captured graph of a
+   round; every kernel is launched directly in any case. */
 #define PALMAD_FLAG_NO_GRAPH 2u
 
 /* Kernel classes of palmad_stats.kernel_* (one entry each). */
@@ -443,7 +441,7 @@ void palmad_stream_destroy(palmad_stream* st);
  * calls from different processes use different copies.  A call returns only
  * once its device work is complete.
  */
-#define PALMAD_STATIC_WORKSPACE_BYTES ((size_t)32 << 20)
+#define PALMAD_STATIC_WORKSPACE_BYTES ((size_t)40 << 20)
 int palmad_discords_static(palmad_ctx* ctx, const double* T, int64_t n, int32_t minL,
                            int32_t maxL, int32_t k, const palmad_options* opts, int64_t* idx,
                            int32_t* len, double* nn_dist, int64_t* nn_idx, int32_t* count,

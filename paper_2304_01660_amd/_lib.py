@@ -80,7 +80,7 @@ class TuneReport(ctypes.Structure):
 
 
 # PALMAD_STATIC_WORKSPACE_BYTES: the static workspace of palmad_discords_static
-STATIC_WORKSPACE_BYTES = 32 << 20
+STATIC_WORKSPACE_BYTES = 40 << 20
 FLAG_TIME_KERNELS = 1
 FLAG_NO_GRAPH = 2
 KERNEL_CLASSES = ("select_near", "select_far", "refine", "polish")

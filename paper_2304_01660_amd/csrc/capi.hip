@@ -4,9 +4,10 @@
 // driver loop (Alg. 1).  Every search runs the same engine over a batch of
 // series (one series for the plain entry points): per round, every series
 // with work left performs one range search (one DRAG call of Alg. 2,
-// parallelised as in Sec. 3.2-3.3) at its own length.  The driver replays
-// a few rounds at a time as a hipGraph on the context's stream and then
-// reads one counter to learn whether any series still has work.
+// parallelised as in Sec. 3.2-3.3) at its own length.  The driver queues
+// a few rounds at a time on the context's stream and then reads the round
+// counters to learn whether any series still has work, or waits for a round
+// with sweeps.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -33,9 +34,6 @@ struct palmad_ctx {
     hipEvent_t ev_in, ev_out;    // order the work stream after / before the caller's
     hipEvent_t ev[KCLASSES][2];  // per-kernel timing
     bool have_events;
-    hipGraph_t graph;            // cached round graph
-    hipGraphExec_t graph_exec;
-    std::string graph_key;
     void* scratch;               // device address of this device's static workspace
 };
 
@@ -221,7 +219,7 @@ struct Plan {
     int B;
     std::vector<Layout> lay;
     std::vector<size_t> base;
-    size_t off_pfx, off_rem, off_sums, total;
+    size_t off_pfx, off_rem, off_sums, off_ipfx, total;
     int64_t totals[PFX_KINDS];
     std::vector<int64_t> pfx;  // [PFX_KINDS][B+1]
     int32_t maxL_all;
@@ -247,7 +245,8 @@ void make_plan(int B, const int64_t* n, const int32_t* minL, const int32_t* maxL
     p->off_pfx = al256(sizeof(SeriesDev) * (size_t)B);
     p->off_rem = al256(p->off_pfx + sizeof(int64_t) * (size_t)PFX_KINDS * (size_t)(B + 1));
     p->off_sums = p->off_rem + 64;
-    size_t o = al256(p->off_sums + 16 * sizeof(unsigned long long));
+    p->off_ipfx = al256(p->off_sums + 16 * sizeof(unsigned long long));
+    size_t o = al256(p->off_ipfx + sizeof(int64_t) * 2 * (size_t)(B + 1));
     p->pfx.assign((size_t)PFX_KINDS * (B + 1), 0);
     p->maxL_all = 0;
     p->Nmax_all = 0;
@@ -330,6 +329,8 @@ int upload(palmad_ctx* ctx, const Plan& p, void* ws, const double* const* Tin, c
     bt->maxL_all = p.maxL_all;
     bt->Nmax_all = p.Nmax_all;
     bt->remaining = (int32_t*)((char*)ws + p.off_rem);
+    bt->ipfx = (int64_t*)((char*)ws + p.off_ipfx);
+    bt->heat = outs && outs[0].heat;
     bt->sums = (unsigned long long*)((char*)ws + p.off_sums);
     return PALMAD_OK;
 }
@@ -394,69 +395,21 @@ int prepare(palmad_ctx* ctx, const Batch& bt, const Plan& p)
     return PALMAD_OK;
 }
 
-std::string graph_key(const Batch& bt, const SweepCfg& c, const Plan& p)
-{
-    char buf[256];
-    snprintf(buf, sizeof buf, "%p|%d|%d|%lld|%d|%d|%d|%d|%d|%d|%d|%a|%d|%d|", (void*)bt.s, bt.B,
-             bt.maxL_all, (long long)bt.Nmax_all,
-             c.near_cols, c.chunk_cols, c.dist_bits, c.far_grid, c.q_near, c.q_far, c.q_ref,
-             (double)c.guard, c.max_attempts, c.band);
-    std::string k = buf;
-    for (int q = 0; q < PFX_KINDS; ++q) k += std::to_string(p.totals[q]) + ",";
-    return k;
-}
-
-void drop_graph(palmad_ctx* ctx)
-{
-    if (ctx->graph_exec) (void)hipGraphExecDestroy(ctx->graph_exec);
-    if (ctx->graph) (void)hipGraphDestroy(ctx->graph);
-    ctx->graph_exec = nullptr;
-    ctx->graph = nullptr;
-    ctx->graph_key.clear();
-}
-
-// Rounds replayed per host check: a finished series makes every kernel of
-// a round return at once, so a few rounds past the end cost little, while
-// each check is a device-to-host copy and a stream synchronisation.
+// Rounds without sweeps issued per host check: a finished series makes
+// every kernel of a round return at once, so a few rounds past the end cost
+// little, while each check is a device-to-host copy and a stream
+// synchronisation.
 constexpr int ROUNDS_PER_CHECK = 4;
 
-// ROUNDS_PER_CHECK rounds replayed from the context's cached graph (captured
-// on first use for this workspace and configuration), or one round launched
-// directly.  Returns the number of rounds issued in *issued.
-int run_rounds(palmad_ctx* ctx, const Batch& bt, const SweepCfg& cfg, const Plan& p, bool graphs,
-               int* issued)
+// One round with sweeps, or ROUNDS_PER_CHECK rounds without them.  (Launched
+// directly: a round is a few kernels of 5-60 us, so the host stays ahead of
+// the device, and a captured graph, bound to one workspace, measured the same
+// on it and cost its capture, 0.4 ms, on every other.)
+int run_rounds(palmad_ctx* ctx, const Batch& bt, const SweepCfg& cfg, const Plan& p, bool full)
 {
-    if (!graphs) {
-        HIP_TRY(launch_round(bt, cfg, p.totals, ctx->work));
-        *issued = 1;
-        return PALMAD_OK;
-    }
-    *issued = ROUNDS_PER_CHECK;
-    const std::string key = graph_key(bt, cfg, p);
-    if (ctx->graph_exec == nullptr || ctx->graph_key != key) {
-        drop_graph(ctx);
-        HIP_TRY(hipStreamBeginCapture(ctx->work, hipStreamCaptureModeThreadLocal));
-        hipError_t e = hipSuccess;
-        for (int r = 0; r < ROUNDS_PER_CHECK && e == hipSuccess; ++r)
-            e = launch_round(bt, cfg, p.totals, ctx->work);
-        hipGraph_t g = nullptr;
-        const hipError_t e2 = hipStreamEndCapture(ctx->work, &g);
-        if (e != hipSuccess || e2 != hipSuccess) {
-            if (g) (void)hipGraphDestroy(g);
-            return fail(ctx, PALMAD_EDEVICE, "round capture failed: %s",
-                        hipGetErrorString(e != hipSuccess ? e : e2));
-        }
-        ctx->graph = g;
-        const hipError_t e3 = hipGraphInstantiate(&ctx->graph_exec, g, nullptr, nullptr, 0);
-        if (e3 != hipSuccess) {
-            ctx->graph_exec = nullptr;
-            drop_graph(ctx);
-            return fail(ctx, PALMAD_EDEVICE, "round graph instantiation failed: %s",
-                        hipGetErrorString(e3));
-        }
-        ctx->graph_key = key;
-    }
-    HIP_TRY(hipGraphLaunch(ctx->graph_exec, ctx->work));
+    const int rounds = full || cfg.timer->on ? 1 : ROUNDS_PER_CHECK;
+    for (int r = 0; r < rounds; ++r)
+        HIP_TRY(launch_round(bt, cfg, p.totals, full, true, ctx->work));
     return PALMAD_OK;
 }
 
@@ -509,26 +462,26 @@ int search(palmad_ctx* ctx, const Plan& p, const Opts& o, void* ws, const double
     if (rc) return rc;
     rc = prepare(ctx, bt, p);
     if (rc) return rc;
-    const bool graphs = !timer.on && !(o.flags & PALMAD_FLAG_NO_GRAPH);
-    int64_t max_rounds = 0;
-    for (int b = 0; b < p.B; ++b) max_rounds = std::max<int64_t>(max_rounds, p.lay[b].L);
-    max_rounds = max_rounds * cfg.max_attempts + 2;
-    for (int64_t round = 0;;) {
-        if (round > max_rounds) return fail(ctx, PALMAD_EDEVICE, "search did not terminate");
-        int issued = 0;
-        rc = run_rounds(ctx, bt, cfg, p, graphs, &issued);
+    HIP_TRY(launch_start(bt, cfg, ctx->work));
+    // every issue of rounds completes a range search of at least one series
+    int64_t max_checks = 2;
+    for (int b = 0; b < p.B; ++b) max_checks += (int64_t)p.lay[b].L * cfg.max_attempts * 2;
+    bool full = true;  // the first length has no witnesses yet
+    for (int64_t check = 0;; ++check) {
+        if (check > max_checks) return fail(ctx, PALMAD_EDEVICE, "search did not terminate");
+        rc = run_rounds(ctx, bt, cfg, p, full);
         if (rc) return rc;
-        round += issued;
-        HIP_TRY(hipMemcpyAsync(ctx->pinned, bt.remaining, 2 * sizeof(int32_t),
+        HIP_TRY(hipMemcpyAsync(ctx->pinned, bt.remaining, REM_COUNT * sizeof(int32_t),
                                hipMemcpyDeviceToHost, ctx->work));
         HIP_TRY(hipStreamSynchronize(ctx->work));
         rc = accumulate(ctx, timer);
         if (rc) return rc;
-        if (ctx->pinned[1])
+        if (ctx->pinned[REM_ERROR])
             return fail(ctx, PALMAD_EDEVICE,
                         "%d series: a range search did not converge within %d attempts",
-                        ctx->pinned[1], cfg.max_attempts);
-        if (ctx->pinned[0] == 0) break;
+                        ctx->pinned[REM_ERROR], cfg.max_attempts);
+        if (ctx->pinned[REM_LEFT] == 0) break;
+        full = ctx->pinned[REM_PENDING] > 0 || ctx->pinned[REM_FIRST] > 0;
     }
     const double secs =
         std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
@@ -592,7 +545,7 @@ void make_probe(int B, const int64_t* n, const int32_t* minL, const int32_t* max
 }
 
 // Best wall time of `reps` searches of the probe under options `o` (after
-// one untimed run, which also captures the round graph).
+// one untimed run).
 int time_probe(palmad_ctx* ctx, const Probe& pr, int32_t k, const Opts& o, void* ws,
                const std::vector<const double*>& tin, const std::vector<Outputs>& outs, int reps,
                void* stream, double* best)
@@ -679,8 +632,6 @@ int palmad_create(palmad_ctx** out, int device)
     ctx->pinned = nullptr;
     ctx->work = nullptr;
     ctx->ev_in = ctx->ev_out = nullptr;
-    ctx->graph = nullptr;
-    ctx->graph_exec = nullptr;
     e = hipHostMalloc((void**)&ctx->pinned, 256, hipHostMallocDefault);
     if (e == hipSuccess) e = hipStreamCreateWithFlags(&ctx->work, hipStreamNonBlocking);
     if (e == hipSuccess) e = hipEventCreateWithFlags(&ctx->ev_in, hipEventDisableTiming);
@@ -722,7 +673,6 @@ void palmad_destroy(palmad_ctx* ctx)
     if (!ctx) return;
     (void)hipSetDevice(ctx->device);
     (void)hipStreamSynchronize(ctx->work);
-    drop_graph(ctx);
     if (ctx->have_events)
         for (int k = 0; k < KCLASSES; ++k)
             for (int q = 0; q < 2; ++q) (void)hipEventDestroy(ctx->ev[k][q]);
@@ -791,8 +741,6 @@ int palmad_discords_static(palmad_ctx* ctx, const double* T, int64_t n, int32_t 
                     p.total, (size_t)PALMAD_STATIC_WORKSPACE_BYTES);
     if (!ctx->scratch)
         return fail(ctx, PALMAD_EUNSUPPORTED, "no static workspace on device %d", ctx->device);
-    // graph instantiation may allocate: every kernel is launched directly
-    o.flags |= PALMAD_FLAG_NO_GRAPH;
     const Outputs out = {idx, len, nn_dist, nn_idx, count};
     // search() returns after its device work completed, so holding the
     // device's lock for the call keeps calls from this process apart
@@ -932,7 +880,8 @@ int palmad_range_discords(palmad_ctx* ctx, const double* T, int64_t n, int32_t m
     rc = prepare(ctx, bt, p);
     if (rc) return rc;
     HIP_TRY(launch_set_fixed_r(bt, r, ctx->work));
-    HIP_TRY(launch_round(bt, cfg, p.totals, ctx->work));
+    HIP_TRY(launch_start(bt, cfg, ctx->work));
+    HIP_TRY(launch_round(bt, cfg, p.totals, true, false, ctx->work));
     const int64_t N = n - m + 1;
     HIP_TRY(launch_range_out(bt, N, (unsigned long long*)alive, nn_dist, ctx->work));
     const Ctrl* c = (const Ctrl*)((char*)workspace + p.base[0] + p.lay[0].off_ctrl);
@@ -1327,8 +1276,9 @@ int palmad_stream_discords(palmad_stream* st, int64_t* idx, int32_t* len, double
     Batch bt;
     rc = stream_batch(st, &out, &bt);
     if (rc) return rc;
-    HIP_TRY(launch_stream_query(bt, st->p.totals, st->minL, st->maxL, st->prof,
-                                64 * cfg_of(st->o, nullptr).q_near, ctx->work));
+    const KernelTimer timer = {};
+    HIP_TRY(launch_stream_query(bt, cfg_of(st->o, &timer), st->p.totals, st->minL, st->maxL, st->prof,
+                                ctx->work));
     HIP_TRY(hipStreamSynchronize(ctx->work));
     return leave(ctx, stream);
 }

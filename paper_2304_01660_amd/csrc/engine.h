@@ -21,13 +21,41 @@ constexpr int R_MAX = 512;   // tallest row tile (64 lanes x 8 rows)
 constexpr int KP_EXTRA = 4;  // candidates polished beyond k
 constexpr int K_MAX = 64;
 constexpr int KP_MAX = K_MAX + KP_EXTRA;
-constexpr int POLISH_COLS = 512;  // columns per exact-pass block (one partial each)
+// The exact pass: most candidates of one round, taken in groups; columns per
+// exact block and per screening chunk; workgroups of the two kernels; the
+// screening is left out below SCREEN_MIN subsequences.
+constexpr int CAND_MAX = 1024;
+constexpr int CAND_GROUP = 16;
+constexpr int CAND_GROUPS = CAND_MAX / CAND_GROUP;
+constexpr int EXACT_COLS = 128;
+constexpr int SCREEN_COLS = 512;
+constexpr int EXACT_GRID = 512;
+constexpr int SCREEN_GRID = 512;
+constexpr int64_t SCREEN_MIN = 8192;
+// A round without sweeps takes at most LEAN_PAIRS (rows, columns) pairs.
+constexpr int64_t LEAN_PAIRS = 600000000;
+// Lists of rows whose witness failed: block b of k_advance appends to list
+// b % FAIL_LISTS (many counters, so that their atomics do not serialise).
+constexpr int FAIL_LISTS = 64;
+// (blocks of 256 rows over Npad + 64 rows; fewer lists than blocks)
+__host__ __device__ constexpr int64_t fail_blocks(int64_t Npad) { return (Npad + 64 + 255) / 256; }
+__host__ __device__ constexpr int fail_lists(int64_t Npad)
+{
+    int l = FAIL_LISTS;
+    while (l > fail_blocks(Npad)) l >>= 1;
+    return l;
+}
+__host__ __device__ constexpr int64_t fail_cap(int64_t Npad)
+{
+    return ((fail_blocks(Npad) + fail_lists(Npad) - 1) / fail_lists(Npad)) * 256;
+}
+constexpr int RESCUE_GRID = 2048, RESCUE_BLOCK = 256;
 constexpr int TOPK_BLOCK = 1024;
 constexpr int RED_BLOCKS = 256;   // series reductions: blocks of 256 threads
 constexpr int MAX_ATTEMPTS = 5000;
 // A round whose selection leaves at most this many live subsequences skips
 // the refinement sweep: the exact pass evaluates all of them directly.
-constexpr int DIRECT_MAX = KP_MAX;
+constexpr int DIRECT_MAX = CAND_MAX;
 // Row tiles that held survivors at the end of a round, or whose first-pass
 // items swept at least 1/HOT_FRAC of the series' columns in all, lead the
 // next round's first selection pass (at most HOT_MAX of them).
@@ -39,6 +67,10 @@ constexpr int HOT_FRAC = 8;
 constexpr int EV_CLASSES = 5;  // first selection pass, split pass, refinement, exact pass, band pre-pass
 constexpr int EV_SLOTS = 64;
 enum { EV_NEAR = 0, EV_FAR = 1, EV_REF = 2, EV_POL = 3, EV_BAND = 4 };
+
+// Host counters of a round: series with work left, series in error, series
+// waiting for a round with sweeps, series at their first length.
+enum { REM_LEFT = 0, REM_ERROR, REM_PENDING, REM_FIRST, REM_COUNT };
 
 // Device-resident control block of one series (the MERLIN state of Alg. 1
 // plus the work counters of the current round).  Fields that work items
@@ -71,12 +103,18 @@ struct Ctrl {
     int32_t hot_r;     // tile height the hot list was built for
     int32_t exact_ref; // 1: refinement sweeps both sides of every tile (set by k_round_end)
     int32_t band_over; // 1: more rows than KP_MAX may hold the k best exact values
+    int32_t pending;   // 1: the range search waits for a round with sweeps
+    uint32_t lean_max; // most rows of a round without sweeps
+    int32_t heat_m;    // length whose heatmap row k_heat writes (0: none)
     // work lists of the current round (built by k_tiles, read by the queued passes)
     alignas(128) uint32_t nlive_sel, maxc_sel;  // live selection tiles, most chunks of one tile
     uint32_t nlive_ref, maxc_ref;
     uint32_t live_ref;     // live subsequences entering refinement this round
     uint32_t nsurv;
     uint32_t ncand;
+    alignas(128) uint32_t nlive;   // rows the witnesses left (> CAND_MAX: too many to list)
+    uint32_t pcnt[CAND_GROUPS];    // exact-pass partials of each candidate group
+    alignas(128) uint32_t nfail[FAIL_LISTS];  // rows in each list of failed witnesses
     // counters accumulated over the call
     alignas(128) unsigned long long rounds, survivors;
     unsigned long long rows_near, rows_far;  // live rows entering the split / refinement passes
@@ -85,7 +123,7 @@ struct Ctrl {
 // Static geometry and buffers of one series (host computes, device reads).
 struct SeriesDev {
     // geometry
-    int64_t n, Nmax, Npad, Tlen, nwords, npart;
+    int64_t n, Nmax, Npad, Tlen, nwords, pcap;
     int32_t minL, maxL, k, kp, L, pad0;
     // input and workspace buffers
     const double* Tin;   // caller's series
@@ -108,9 +146,13 @@ struct SeriesDev {
     int32_t* tref;       // live refinement tiles
     int32_t* hot;        // hot tiles of the last round, ascending [HOT_MAX]
     uint32_t* twork;     // 64-column blocks swept by each first-pass tile this round [nwords]
-    int64_t* cand;       // polished candidates [KP_MAX]
-    double* part;        // polish partials [KP_MAX * npart * 2 + tail]
-    double* xc;          // centred candidate windows [KP_MAX][maxL + 8], then their sums
+    int64_t* cand;       // candidates of the exact pass [CAND_MAX]
+    double* part;        // its partials [pcap][CAND_GROUP][2]
+    float* lbp;          // lower bounds of the screening's workgroups [lbcap][CAND_GROUP]
+    float* ub;           // upper bounds [CAND_GROUPS][blocks][CAND_GROUP] (shares df64 .. rhs)
+    int32_t* wit;        // witness of every row (see k_advance) [Npad+64]
+    double* wc;          // its covariance with the row [Npad+64]
+    int32_t* fail;       // lists of rows whose witness failed (shares the FP32 helpers)
     double* hist;        // nnDist history per length [L]
     unsigned long long* evc;  // pair evaluations [EV_CLASSES][EV_SLOTS]
     double* red;         // reduction scratch [2 * RED_BLOCKS]
@@ -131,10 +173,10 @@ struct SeriesDev {
 
 // Per-series layout (host side; offsets relative to the series' base).
 struct Layout {
-    int64_t n, Nmax, Npad, Tlen, nwords, npart;
+    int64_t n, Nmax, Npad, Tlen, nwords, pcap, lbcap;
     int32_t minL, maxL, k, L, kp;
     size_t off_T, off_mu, off_var, off_mu2, off_var2, off_h32, off_h64, off_alive, off_rho, off_rhs, off_unc,
-        off_tsel, off_tref, off_hot, off_twork, off_cand, off_part, off_xc, off_hist, off_evc, off_ctrl, off_red,
+        off_tsel, off_tref, off_hot, off_twork, off_cand, off_part, off_lbp, off_wit, off_wc, off_hist, off_evc, off_ctrl, off_red,
         off_sgm, total;
 };
 bool make_layout(int64_t n, int32_t minL, int32_t maxL, int32_t k, Layout* out);
@@ -147,7 +189,6 @@ enum PrefixKind {
     PFX_NEAR,       // first-pass selection items: tiles x chunks
     PFX_TSEL,       // blocks of 256 over selection tiles (compaction)
     PFX_TREF,       // blocks of 256 over refinement tiles (compaction)
-    PFX_POLISH,     // blocks of POLISH_COLS columns (polish)
     PFX_BAND,       // row segments of the diagonal band pre-pass
     PFX_KINDS
 };
@@ -158,7 +199,9 @@ struct Batch {
     int32_t B;
     int32_t maxL_all;                // largest length over the batch (LDS sizing)
     int64_t Nmax_all;                // most subsequences of any series
-    int32_t* remaining;              // device [2]: series with work left, series in error
+    int64_t* ipfx;                   // device [2][B+1]: first exact-pass items of each series
+    bool heat;                       // the search writes a discord heatmap
+    int32_t* remaining;              // device [REM_COUNT]
     unsigned long long* sums;        // device [9]: counters summed over the batch
 };
 
@@ -200,7 +243,9 @@ void series_blocks(const Layout& lay, const SweepCfg& cfg, int64_t out[PFX_KINDS
 
 // ---- launchers (all asynchronous on `st`); `total[kind]` = pfx[kind][B] ----
 hipError_t launch_prepare(const Batch& bt, const int64_t* total, hipStream_t st);
-hipError_t launch_round(const Batch& bt, const SweepCfg& cfg, const int64_t* total, hipStream_t st);
+hipError_t launch_start(const Batch& bt, const SweepCfg& cfg, hipStream_t st);
+hipError_t launch_round(const Batch& bt, const SweepCfg& cfg, const int64_t* total, bool full,
+                        bool more, hipStream_t st);
 hipError_t launch_set_fixed_r(const Batch& bt, double r, hipStream_t st);
 hipError_t launch_range_out(const Batch& bt, int64_t N, unsigned long long* alive_out,
                             double* nn_out, hipStream_t st);
@@ -228,8 +273,9 @@ hipError_t launch_adjoint(const double* Tpad, int64_t n, int64_t K, int32_t maxm
 hipError_t launch_stream_update(const Batch& bt, const SweepCfg& cfg, const int64_t* total,
                                 int32_t minL, int32_t maxL, unsigned long long* prof,
                                 int64_t n_old, hipStream_t st);
-hipError_t launch_stream_query(const Batch& bt, const int64_t* total, int32_t minL, int32_t maxL,
-                               const unsigned long long* prof, int hot_rows, hipStream_t st);
+hipError_t launch_stream_query(const Batch& bt, const SweepCfg& cfg, const int64_t* total,
+                               int32_t minL, int32_t maxL, const unsigned long long* prof,
+                               hipStream_t st);
 hipError_t launch_stream_profile(const Batch& bt, const int64_t* total, int32_t minL, int32_t m,
                                  const unsigned long long* prof, double* nn, hipStream_t st);
 hipError_t launch_fill_u64(unsigned long long* p, int64_t count, unsigned long long v,

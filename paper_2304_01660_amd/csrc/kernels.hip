@@ -37,6 +37,7 @@
 #include <math.h>
 
 #include <algorithm>
+#include <type_traits>
 
 namespace palmad {
 
@@ -52,6 +53,29 @@ template <>
 __device__ __forceinline__ float f_inf<float>() { return __int_as_float(0x7f800000); }
 template <>
 __device__ __forceinline__ double f_inf<double>() { return __longlong_as_double(0x7ff0000000000000ll); }
+
+// A margin no pair reaches (finite, so that its low bits can carry a step
+// index: infinity with low bits set would be a NaN).
+template <typename F>
+__device__ __forceinline__ F f_low();
+template <>
+__device__ __forceinline__ float f_low<float>() { return -3.0e38f; }
+template <>
+__device__ __forceinline__ double f_low<double>() { return -1.0e300; }
+
+// v with its six lowest mantissa bits replaced by the step index s < 64: the
+// largest such value of a block tells the step it came from, for one extra
+// instruction per pair.
+__device__ __forceinline__ float pack_step(float v, int s)
+{
+    return __int_as_float((__float_as_int(v) & ~63) | s);
+}
+__device__ __forceinline__ double pack_step(double v, int s)
+{
+    return __longlong_as_double((__double_as_longlong(v) & ~63ll) | (long long)s);
+}
+__device__ __forceinline__ int step_of(float v) { return __float_as_int(v) & 63; }
+__device__ __forceinline__ int step_of(double v) { return (int)(__double_as_longlong(v) & 63ll); }
 
 __device__ __forceinline__ float f_fma(float a, float b, float c) { return fmaf(a, b, c); }
 __device__ __forceinline__ double f_fma(double a, double b, double c) { return fma(a, b, c); }
@@ -157,14 +181,8 @@ __device__ __forceinline__ unsigned long long pair_count(long long ilo, long lon
 
 // ---------------------------------------------------------------------------
 // round preparation: MERLIN's walk over the lengths and its choice of r
-// (Alg. 1), for every series (one block)
+// (Alg. 1)
 // ---------------------------------------------------------------------------
-// Advance every series: the first round starts at minL; after a successful
-// round the next length starts; after a failed one the same length is
-// searched again with the r that k_round_end lowered.  Then set the range of
-// this round, its pruning threshold and reset the round's work counters.
-// rem[0] (series with work left after the round, counted by k_round_end) and
-// rem[1] (series that gave up, now or in an earlier round) start at zero here.
 // Guard band of the FP32 selection sweep.  An FP32 correlation drifts from
 // the exact one by rounding: the centred recurrence accumulates one rounding
 // of the covariance per step over chains of at most R_MAX - 1 steps, and a
@@ -234,59 +252,64 @@ __device__ void begin_range(const SeriesDev& s, Ctrl* c, float guard)
     c->nsurv = 0;
     c->ncand = 0;
     c->live_ref = 0;
+    c->nlive = 0;
+    for (int q = 0; q < FAIL_LISTS; ++q) c->nfail[q] = 0;
     c->band_over = 0;
+    // Most rows the exact pass takes without a sweep: its screening costs
+    // about 4e-12 s per row and column (1e6 columns: 4 us per row), a round of
+    // sweeps 250-400 us.
+    const int64_t N = s.n - m + 1;
+    c->lean_max = (uint32_t)std::min<int64_t>(CAND_MAX, std::max<int64_t>(128, LEAN_PAIRS / N));
     if (c->new_len) {
         c->flat_min = 0x7fffffffffffffffll;
         c->flat_max = -1;
     }
 }
 
-__global__ void k_round_prep(SeriesDev* S, int B, float guard, int max_attempts, int32_t* rem)
+// The next range search of a series (one thread): the first length, the next
+// one after a success, or the same length again with the r that k_round_end
+// lowered.
+__device__ void next_range(const SeriesDev& s, Ctrl* c, float guard, int max_attempts, int32_t* rem)
 {
-    if (threadIdx.x == 0) {
-        rem[0] = 0;
-        rem[1] = 0;
-    }
-    __syncthreads();
-    for (int b = threadIdx.x; b < B; b += blockDim.x) {
-        const SeriesDev& s = S[b];
-        Ctrl* c = s.ctrl;
-        if (c->finished) {
+    if (!c->started) {
+        c->started = 1;
+        c->m = s.minL;
+        c->li = 0;
+        c->attempt = 0;
+        c->new_len = 2;
+    } else if (c->done) {
+        if (c->m >= s.maxL) {
+            c->finished = 1;
             c->active = 0;
-            if (c->error) atomicAdd(&rem[1], 1);  // stays visible in later rounds
-            continue;
+            return;
         }
-        if (!c->started) {
-            c->started = 1;
-            c->m = s.minL;
-            c->li = 0;
-            c->attempt = 0;
-            c->new_len = 2;
-        } else if (c->done) {
-            if (c->m >= s.maxL) {
-                c->finished = 1;
-                c->active = 0;
-                continue;
-            }
-            c->m += 1;
-            c->li += 1;
-            c->attempt = 0;
-            c->new_len = 1;
-        } else {
-            c->attempt += 1;
-            c->new_len = 0;
-            if (c->attempt >= max_attempts) {
-                c->error = 1;
-                c->finished = 1;
-                c->active = 0;
-                atomicAdd(&rem[1], 1);
-                continue;
-            }
+        c->m += 1;
+        c->li += 1;
+        c->attempt = 0;
+        c->new_len = 1;
+    } else {
+        c->attempt += 1;
+        c->new_len = 0;
+        if (c->attempt >= max_attempts) {
+            c->error = 1;
+            c->finished = 1;
+            c->active = 0;
+            atomicAdd(&rem[REM_ERROR], 1);
+            return;
         }
-        c->done = 0;
-        c->active = 1;
-        begin_range(s, c, guard);
     }
+    c->done = 0;
+    c->active = 1;
+    begin_range(s, c, guard);
+    atomicAdd(&rem[REM_LEFT], 1);
+    if (c->li == 0) atomicAdd(&rem[REM_FIRST], 1);
+}
+
+// Before the first round of a search.
+__global__ void k_start(SeriesDev* S, int B, float guard, int max_attempts, int32_t* rem)
+{
+    for (int b = blockIdx.x * blockDim.x + threadIdx.x; b < B; b += gridDim.x * blockDim.x)
+        next_range(S[b], S[b].ctrl, guard, max_attempts, rem);
 }
 
 // ---------------------------------------------------------------------------
@@ -308,6 +331,8 @@ __device__ __forceinline__ const double* cur_var(const SeriesDev& s, const Ctrl*
 // A round whose selection left at most DIRECT_MAX live subsequences: the
 // refinement sweep is skipped and the exact pass evaluates every one of them.
 __device__ __forceinline__ bool direct_round(const Ctrl* c) { return c->live_ref <= DIRECT_MAX; }
+// Few enough rows left by the witnesses for the exact pass without a sweep.
+__device__ __forceinline__ bool lean_round(const Ctrl* c) { return c->nlive <= c->lean_max; }
 
 // Mean and variance of window p at length m: two passes (Eq. (4)).
 __device__ __forceinline__ void direct_stats(const double* __restrict__ T, int64_t p, int32_t m,
@@ -373,7 +398,7 @@ __global__ __launch_bounds__(GUARD_BLOCK) void k_guard(SeriesDev* S, float guard
 {
     const SeriesDev& s = S[blockIdx.x];
     Ctrl* c = s.ctrl;
-    if (!c->active || !c->new_len || guard <= 0.0f) return;
+    if (!c->active || lean_round(c) || guard <= 0.0f) return;
     __shared__ double red[GUARD_BLOCK / 64];
     const int64_t nb = (s.n - c->m + 1 + 255) / 256;
     double g = 0.0;
@@ -472,6 +497,361 @@ __global__ void k_length(SeriesDev* S, int B, const int64_t* __restrict__ pfx)
 }
 
 // ---------------------------------------------------------------------------
+// witnesses: the per-length step of a search
+// ---------------------------------------------------------------------------
+// A subsequence pruned at one length by a neighbour closer than r is almost
+// always pruned by the same neighbour at the next length: distances and r
+// both move slowly with m.  Every row therefore keeps its last witness j and
+// the centred covariance C of the pair in FP64.  From length m - 1 to m,
+//     C += (m-1)/m (t[i+m-1] - mu_i) (t[j+m-1] - mu_j)      (means at m - 1),
+// the two-window form of Eq. (8), so a row costs a few operations instead of
+// the hundreds to thousands of pairs a selection sweep evaluates before it
+// prunes the row (k_advance).  A row whose witness fails tries its witness's
+// witness and the diagonal extensions of its nearest pruned neighbours'
+// (k_rescue).  What is left, a handful to a few hundred rows, goes to the
+// exact pass; only when more than Ctrl::lean_max rows are left (the first
+// length, mostly) does a round sweep.
+//
+// Soundness: a row is pruned only by an FP64 correlation above thr64 by more
+// than WIT_GUARD; rows nearer to the threshold are left to the exact pass.  C
+// starts from a direct dot product (or the exact pass's value), and m sigma^2
+// never shrinks as m grows, so the relative rounding of the chained updates
+// stays of the order m 2^-53, four orders below the guard.
+constexpr double WIT_GUARD = 1e-9;
+constexpr int32_t WIT_NONE = (int32_t)0x80000000;  // j >= 0: C known; ~j: C to be computed
+
+__device__ __forceinline__ double inv_of(double var, double sqm, double feps)
+{
+    const double sg = sqrt(var);
+    return sg <= feps ? 0.0 : 1.0 / (sqm * sg);
+}
+
+// Correlation of a pair (R11: flat windows correlate 1 with each other, 0 with others).
+__device__ __forceinline__ double pair_rho(double C, double ii, double ij)
+{
+    if (ii == 0.0 || ij == 0.0) return (ii == 0.0 && ij == 0.0) ? 1.0 : 0.0;
+    return C * ii * ij;
+}
+
+// Direct centred dot product of windows i and j.
+__device__ __forceinline__ double direct_cov(const double* __restrict__ T, int64_t i, int64_t j,
+                                             int32_t m, double mi, double mj)
+{
+    const double* __restrict__ x = T + i;
+    const double* __restrict__ y = T + j;
+    double a0 = 0.0, a1 = 0.0;
+    int k = 0;
+    for (; k + 8 <= m; k += 8) {
+        double u[8], v[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            u[e] = x[k + e];
+            v[e] = y[k + e];
+        }
+#pragma unroll
+        for (int e = 0; e < 8; e += 2) {
+            a0 = fma(u[e] - mi, v[e] - mj, a0);
+            a1 = fma(u[e + 1] - mi, v[e + 1] - mj, a1);
+        }
+    }
+    for (; k < m; ++k) a0 = fma(x[k] - mi, y[k] - mj, a0);
+    return a0 + a1;
+}
+
+// Statistics of a new length (Eq. (4) at minL, Eq. (7)-(8) after), the
+// witness test, the bitmap of live rows and the lists of those whose witness
+// failed.  One thread per subsequence, one wave per bitmap word.  Bound by
+// HBM: about 90 bytes per subsequence and length.  A repeat of the same
+// length at a smaller r only repeats the test.  rem: the round's host
+// counters restart.
+constexpr int ADV_BLOCK = 256;
+__global__ __launch_bounds__(ADV_BLOCK) void k_advance(SeriesDev* S, int B,
+                                                       const int64_t* __restrict__ pfx, int32_t* rem)
+{
+    __shared__ unsigned int wcnt[ADV_BLOCK / 64];
+    __shared__ unsigned int base_s;
+    if (blockIdx.x == 0 && threadIdx.x < REM_COUNT) rem[threadIdx.x] = 0;
+    const int b = B == 1 ? 0 : series_of(pfx, B, blockIdx.x);
+    const SeriesDev& s = S[b];
+    Ctrl* c = s.ctrl;
+    if (!c->active || c->pending) return;
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int64_t lb = blockIdx.x - (B == 1 ? 0 : pfx[b]);
+    if (lb == 0 && threadIdx.x < CAND_GROUPS) c->pcnt[threadIdx.x] = 0;
+    const int64_t i = lb * (int64_t)ADV_BLOCK + threadIdx.x;
+    const int32_t m = c->m;
+    const int64_t N = s.n - m + 1;
+    const int new_len = c->new_len;
+    const bool prune = c->prune != 0;
+    const double feps = c->flat_eps, sqm = sqrt((double)m);
+    const double kill = c->thr64 + WIT_GUARD;
+    const double* __restrict__ T = s.T;
+    const bool odd = (c->li & 1) != 0;
+    double* mu_n = odd ? s.mu2 : s.mu;
+    double* var_n = odd ? s.var2 : s.var;
+    const double* __restrict__ mu_o = odd ? s.mu : s.mu2;
+    const double* __restrict__ var_o = odd ? s.var : s.var2;
+    const bool in = i < N;
+    const int32_t w0 = in && new_len != 2 ? s.wit[i] : WIT_NONE;
+    double mi = 0.0, vi = 0.0, ii = 0.0, moi = 0.0;
+    if (new_len) {
+        if (in) {
+            if (new_len == 2) {
+                direct_stats(T, i, m, mi, vi);
+            } else {
+                moi = mu_o[i];
+                grow_stats(T, i, m, moi, var_o[i], mi, vi);
+            }
+            ii = inv_of(vi, sqm, feps);
+            if (ii == 0.0) {
+                atomicMin((long long*)&c->flat_min, (long long)i);
+                atomicMax((long long*)&c->flat_max, (long long)i);
+            }
+        }
+        if (i < s.Npad + 64) {
+            mu_n[i] = mi;
+            var_n[i] = vi;
+            s.inv64[i] = ii;
+        }
+    } else if (in) {
+        mi = mu_n[i];
+        ii = s.inv64[i];
+    }
+    bool dead = false;
+    if (new_len == 2) {
+        if (in) s.wit[i] = WIT_NONE;
+    } else if (w0 != WIT_NONE) {
+        const bool fresh = w0 < 0;
+        const int64_t j = fresh ? ~w0 : w0;
+        if (j < N && (j - i >= m || i - j >= m)) {
+            double mj, ij, moj = 0.0;
+            if (new_len) {
+                double vj;
+                moj = mu_o[j];
+                grow_stats(T, j, m, moj, var_o[j], mj, vj);
+                ij = inv_of(vj, sqm, feps);
+            } else {
+                mj = mu_n[j];
+                ij = s.inv64[j];
+            }
+            double C;
+            if (fresh) {
+                C = direct_cov(T, i, j, m, mi, mj);
+                s.wit[i] = (int32_t)j;
+                s.wc[i] = C;
+            } else {
+                C = s.wc[i];
+                if (new_len) {
+                    C += (double)(m - 1) / (double)m * (T[i + m - 1] - moi) * (T[j + m - 1] - moj);
+                    s.wc[i] = C;
+                }
+            }
+            dead = prune && pair_rho(C, ii, ij) > kill;
+        } else {  // no longer a window, or now a self match
+            s.wit[i] = WIT_NONE;
+        }
+    }
+    const unsigned long long live = __ballot(in && !dead);
+    if (lane == 0 && (i >> 6) < s.nwords) s.alive[i >> 6] = live;
+    if (s.heat) {  // range discords are written by k_round_end and k_heat
+        double* hrow = s.heat + (int64_t)c->li * s.heat_ld;
+        for (int64_t q = i; q < s.heat_ld; q += s.Npad + 64) hrow[q] = 0.0;
+    }
+    if (new_len == 2 || !prune) {
+        if (i == 0) c->nlive = 0x7fffffffu;
+        return;
+    }
+    if (lane == 0) wcnt[wv] = (unsigned int)__popcll(live);
+    __syncthreads();
+    const int list = (int)(lb & (fail_lists(s.Npad) - 1));
+    if (threadIdx.x == 0) {
+        unsigned int tot = 0;
+        for (int q = 0; q < ADV_BLOCK / 64; ++q) tot += wcnt[q];
+        base_s = tot ? atomicAdd(&c->nfail[list], tot) : 0u;
+    }
+    __syncthreads();
+    if (in && !dead) {
+        unsigned int p = base_s + (unsigned int)__popcll(live & ((1ull << lane) - 1ull));
+        for (int q = 0; q < wv; ++q) p += wcnt[q];
+        s.fail[list * fail_cap(s.Npad) + p] = (int32_t)i;
+    }
+}
+
+// Second chances for the rows whose witness failed, one wave per row: up to
+// RESCUE_TRIES batches of four candidates, sixteen lanes each, compared by
+// direct FP64 dot products; the best one above the threshold prunes the row
+// and becomes its witness.  Candidates: the witness's witness and that one's,
+// the diagonal extensions of the nearest pruned rows' witnesses on either
+// side; then the same of rows at growing distance.  (ECG-like series at
+// lengths past one beat, where r falls and up to a fifth of the witnesses
+// fail in one length: all but about one row in a thousand of them are pruned
+// here, most by the first batch.)  Rows that stay are the round's candidates.
+// Bound by latency: a few dependent loads per batch.
+constexpr int RESCUE_TRIES = 4;
+__global__ __launch_bounds__(RESCUE_BLOCK) void k_rescue(SeriesDev* S, int B)
+{
+    const int lane = threadIdx.x & 63;
+    const int sub = lane & 15, cq = lane >> 4;
+    const int64_t wave = (int64_t)blockIdx.x * (RESCUE_BLOCK / 64) + (threadIdx.x >> 6);
+    const int64_t nwaves = (int64_t)gridDim.x * (RESCUE_BLOCK / 64);
+    // the waves are shared out evenly among the series
+    const int64_t nper = std::max<int64_t>(1, nwaves / B);
+    const int64_t w = wave % nper;
+    for (int64_t b = wave / nper; b < B; b += nwaves / nper) {
+        const SeriesDev& s = S[b];
+        Ctrl* c = s.ctrl;
+        if (!c->active || c->pending || c->new_len == 2 || !c->prune) continue;
+        const int32_t m = c->m;
+        const int64_t N = s.n - m + 1;
+        const unsigned int mine = c->nfail[lane];
+        unsigned int total = mine;
+#pragma unroll
+        for (int o = 32; o >= 1; o >>= 1) total += __shfl_xor(total, o);
+        if ((int64_t)total * 2 > N && total > c->lean_max) {
+            // (a new threshold altogether, e.g. the first length's next r)
+            if (w == 0 && lane == 0) c->nlive = 0x7fffffffu;
+            continue;
+        }
+        const int64_t cap = fail_cap(s.Npad);
+        const double* __restrict__ T = s.T;
+        const double* __restrict__ mu = cur_mu(s, c);
+        const double* __restrict__ inv = s.inv64;
+        const double kill = c->thr64 + WIT_GUARD;
+        // the series' waves spread over its lists, then over a list's rows
+        const int nl = fail_lists(s.Npad);
+        const int64_t per = std::max<int64_t>(1, nper / nl);  // waves per list
+        if (w >= per * nl) continue;
+        for (int64_t e = w;; e += nper) {
+            const int64_t list = e % nl, p0 = e / nl;
+            if (e != w && nper >= nl) break;
+            if (nper < nl && e >= nl) break;
+            const unsigned int cnt = (unsigned int)__builtin_amdgcn_readlane((int)mine, (int)list);
+        for (int64_t p = p0; p < cnt; p += per) {
+            const int64_t i = s.fail[list * cap + p];
+            const double mi = mu[i], ii = inv[i];
+            // a row's witness, whatever its state (a candidate is always recomputed)
+            auto wit_of = [&](int64_t q) -> int64_t {
+                if (q < 0 || q >= N) return -1;
+                const int32_t v = __hip_atomic_load(&s.wit[q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                return v == WIT_NONE ? -1 : v < 0 ? (int64_t)~v : (int64_t)v;
+            };
+            bool done = false;
+            for (int t = 0; t < RESCUE_TRIES && !done; ++t) {
+                // candidate of this lane's quarter
+                int64_t j = -1;
+                if (t == 0) {
+                    if (cq < 2) {
+                        j = wit_of(wit_of(i));
+                        if (cq == 1) j = wit_of(j);
+                    } else {
+                        // the nearest pruned row on the left (cq 2) or right (cq 3),
+                        // within 63 rows
+                        const int64_t base = cq == 2 ? i - 63 : i;
+                        int64_t q = -1;
+                        if (base >= 0) {
+                            const int off = (int)(base & 63);
+                            unsigned long long bits = load_word(&s.alive[base >> 6]) >> off;
+                            if (off) bits |= load_word(&s.alive[(base >> 6) + 1]) << (64 - off);
+                            unsigned long long z = ~bits;  // bit e: row base + e is pruned (or past the end)
+                            if (z) q = base + (cq == 2 ? 63 - __clzll((long long)z) : __ffsll((long long)z) - 1);
+                        }
+                        const int64_t v = q >= 0 && q < N ? wit_of(q) : -1;
+                        j = v >= 0 ? v + (i - q) : -1;
+                    }
+                } else {
+                    // rows at distance 2^(2t) and 2^(2t+1), both sides: their
+                    // witnesses' witnesses
+                    const int64_t d = (int64_t)1 << (2 * t + (cq >> 1));
+                    const int64_t q = (cq & 1) ? i + d : i - d;
+                    const int64_t v = wit_of(wit_of(q));
+                    j = v >= 0 ? v + (i - q) : -1;
+                }
+                if (j >= N || (j < i + m && j > i - m)) j = -1;
+                if (j < 0) j = -1;
+                double rho = -4.0, C = 0.0;
+                if (j >= 0) {
+                    const double mj = mu[j];
+                    for (int k = sub; k < m; k += 16) C = fma(T[i + k] - mi, T[j + k] - mj, C);
+                }
+#pragma unroll
+                for (int o = 8; o >= 1; o >>= 1) C += __shfl_xor(C, o);
+                if (j >= 0) rho = pair_rho(C, ii, inv[j]);
+                // the best of the four
+                double br = rho;
+                int bq = cq;
+#pragma unroll
+                for (int o = 16; o <= 32; o <<= 1) {
+                    const double r2 = __shfl_xor(br, o);
+                    const int q2 = __shfl_xor(bq, o);
+                    if (r2 > br || (r2 == br && q2 < bq)) {
+                        br = r2;
+                        bq = q2;
+                    }
+                }
+                done = br > kill;
+                if (done && sub == 0 && cq == bq) {
+                    __hip_atomic_store(&s.wit[i], (int32_t)j, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    s.wc[i] = C;
+                    atomicAnd(&s.alive[i >> 6], ~(1ull << (i & 63)));
+                }
+                done = __builtin_amdgcn_readfirstlane((int)done) != 0;
+            }
+            if (!done && lane == 0) {
+                const unsigned int have =
+                    __hip_atomic_load(&c->nlive, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                if (have <= (unsigned int)CAND_MAX) {  // abandoned once it overflows
+                    const unsigned int slot = atomicAdd(&c->nlive, 1u);
+                    if (slot < (unsigned int)CAND_MAX) s.cand[slot] = i;
+                }
+            }
+        }
+        }
+    }
+}
+
+// Helpers of a round that sweeps (Eq. (10)'s centred form): df[i] =
+// (t_{i+m} - t_i)/2, dg[i] = (t_{i+m} - mu_{i+1}) + (t_i - mu_i) for i < N-1
+// (zero beyond) in both precisions, the spread extremes that set the FP32
+// guard band, and the resets of the row maxima.
+__global__ __launch_bounds__(ADV_BLOCK) void k_helpers(SeriesDev* S, int B,
+                                                       const int64_t* __restrict__ pfx)
+{
+    const int b = series_of(pfx, B, blockIdx.x);
+    const SeriesDev& s = S[b];
+    Ctrl* c = s.ctrl;
+    if (!c->active || lean_round(c)) return;
+    const int64_t lb = blockIdx.x - pfx[b];
+    const int64_t i = lb * (int64_t)ADV_BLOCK + threadIdx.x;
+    const int32_t m = c->m;
+    const int64_t N = s.n - m + 1;
+    const double* __restrict__ mu = cur_mu(s, c);
+    double smax = 0.0, smin = f_inf<double>();
+    if (i < s.Npad + 64) {
+        double df = 0.0, dg = 0.0, inv = 0.0;
+        if (i < N - 1) {
+            const double a = s.T[i + m], e = s.T[i];
+            df = (a - e) * 0.5;
+            dg = (a - mu[i + 1]) + (e - mu[i]);
+        }
+        if (i < N) {
+            inv = s.inv64[i];
+            if (inv > 0.0) smax = smin = sqrt(cur_var(s, c)[i]);
+        }
+        s.df64[i] = df;
+        s.dg64[i] = dg;
+        s.df32[i] = (float)df;
+        s.dg32[i] = (float)dg;
+        s.inv32[i] = (float)inv;
+    }
+    spread_extremes(s, lb, smax, smin);
+    if (i < s.nwords) s.unc[i] = 0ull;
+    if (i < s.Npad) {
+        s.rho[i] = 0x000fffffffffffffull;  // ordered bits of -inf
+        s.rhs[i] = 0x000fffffffffffffull;
+    }
+}
+
+// ---------------------------------------------------------------------------
 // the sweeps
 // ---------------------------------------------------------------------------
 template <typename F>
@@ -486,6 +866,7 @@ struct SweepArgs {
     unsigned long long* rhs;
     unsigned long long* unc;
     uint32_t* twork;
+    int32_t* wit;  // witnesses of the rows this item prunes
     Ctrl* ctrl;
     int64_t N;
     int32_t m;
@@ -794,6 +1175,15 @@ __device__ __forceinline__ void kill_columns(unsigned long long* alive, int64_t 
     }
 }
 
+// The alive bits of columns j0 .. j0 + 63.
+__device__ __forceinline__ unsigned long long live_columns(const unsigned long long* alive, int64_t j0)
+{
+    const int64_t w0 = j0 >> 6;
+    const int off = (int)(j0 & 63);
+    const unsigned long long lo = load_word(&alive[w0]) >> off;
+    return uniform64(off ? lo | (load_word(&alive[w0 + 1]) << (64 - off)) : lo);
+}
+
 // One step of the diagonal recurrence for all Q slots of every lane.
 // Registers rotate: before step u of a group of Q steps, slot q lives in
 // C[(q - u) mod Q]; each register is updated in place, so the shift from
@@ -819,36 +1209,64 @@ __device__ __forceinline__ int slot_reg(int q)
 }
 
 // ----- selection sweep -----
+// A pair closer than r prunes both of its subsequences, and each remembers
+// the other as its witness (SeriesDev::wit, stored as ~index: the pair's
+// covariance is not known in FP64 yet).  At the next lengths k_advance tests
+// a subsequence against its witness first, which prunes nearly all of them
+// again without a sweep.
+//
+// Witness of a column hit in step s: the row of the lowest hit lane (mg: that
+// lane's margins), kept in lane s of wcol until the block ends.
+template <typename F, int Q>
+__device__ __forceinline__ void col_witness(unsigned long long bal, const F (&mg)[Q], int32_t row0,
+                                            int s, int32_t& wcol)
+{
+    const int l = __ffsll((long long)bal) - 1;
+    int slot = 0;
+#pragma unroll
+    for (int q = 1; q < Q; ++q)
+        if ((__ballot(mg[q] > F(0)) >> l) & 1ull) slot = q;
+    wcol = (int)threadIdx.x == s ? row0 + Q * l + slot : wcol;
+}
+
 // One step U of a group: advance, then the pruning margin of every slot,
 // C * inv_j - th = (rho - thr) / inv_i, which is > 0 exactly when the pair is
-// closer than r.  The row keeps its largest margin (folded into the dead
-// masks once per block); the column is hit when any slot's margin is > 0.
+// closer than r.  The row keeps its largest margin (rm) and the block's
+// largest with its step (bm; folded into the dead masks once per block); the
+// column is hit when any slot's margin is > 0.
 // MASK: only pairs with j >= i + m count (the triangle next to the band).
-template <typename F, int Q, int U, bool MASK>
+template <typename F, int Q, int U, bool MASK, bool WIT>
 __device__ __forceinline__ void sel_step(F (&C)[Q], const F (&a)[Q], const F (&b)[Q],
-                                         const F (&nth)[Q], F (&rm)[Q], const int32_t (&ri)[Q],
-                                         F dfj, F dgj, F invj, F Bv, int32_t jm,
-                                         unsigned long long& colbits, int s)
+                                         const F (&nth)[Q], F (&rm)[Q], F (&bm)[Q],
+                                         const int32_t (&ri)[Q], F dfj, F dgj, F invj, F Bv,
+                                         int32_t jm, int32_t row0, unsigned long long& colbits,
+                                         int32_t& wcol, int s)
 {
     advance<F, Q, U>(C, a, b, dfj, dgj, Bv);
     F mg[Q];
 #pragma unroll
     for (int q = 0; q < Q; ++q) {
         mg[q] = f_fma(C[slot_reg<Q, U>(q)], invj, nth[q]);
-        if (MASK) mg[q] = (jm >= ri[q]) ? mg[q] : -f_inf<F>();
+        if (MASK) mg[q] = (jm >= ri[q]) ? mg[q] : f_low<F>();
         rm[q] = fmax(rm[q], mg[q]);
+        if (WIT) bm[q] = fmax(bm[q], pack_step(mg[q], s));
     }
     F cm = mg[0];
 #pragma unroll
     for (int q = 1; q < Q; ++q) cm = fmax(cm, mg[q]);
-    if (uniform64(__ballot(cm > F(0))) != 0ull) colbits |= 1ull << s;
+    const unsigned long long bal = uniform64(__ballot(cm > F(0)));
+    if (bal != 0ull) {
+        colbits |= 1ull << s;
+        if (WIT) col_witness<F, Q>(bal, mg, row0, s, wcol);
+    }
 }
 
-template <typename F, int Q, bool MASK>
+template <typename F, int Q, bool MASK, bool WIT>
 __device__ __forceinline__ void sel_block(const SweepArgs<F>& A, int64_t j0, int nst, F (&C)[Q],
                                           const F (&a)[Q], const F (&b)[Q], const F (&nth)[Q],
-                                          F (&rm)[Q], const int32_t (&ri)[Q], const H4<F>* hs,
-                                          unsigned long long& colbits)
+                                          F (&rm)[Q], F (&bm)[Q], const int32_t (&ri)[Q],
+                                          const H4<F>* hs, int32_t row0,
+                                          unsigned long long& colbits, int32_t& wcol)
 {
     for (int s0 = 0; s0 < nst; s0 += Q) {
         const int64_t jg = j0 + s0;
@@ -859,9 +1277,9 @@ __device__ __forceinline__ void sel_block(const SweepArgs<F>& A, int64_t j0, int
         const int left = nst - s0;
 #define SEL_STEP(U)                                                                            \
     if ((U) < left)                                                                            \
-        sel_step<F, Q, ((U) < Q ? (U) : 0), MASK>(C, a, b, nth, rm, ri, hv[(U) % Q].df,       \
-                                                  hv[(U) % Q].dg, hv[(U) % Q].inv,             \
-                                                  hv[(U) % Q].B, jm + (U), colbits, s0 + (U));
+        sel_step<F, Q, ((U) < Q ? (U) : 0), MASK, WIT>(                                       \
+            C, a, b, nth, rm, bm, ri, hv[(U) % Q].df, hv[(U) % Q].dg, hv[(U) % Q].inv,         \
+            hv[(U) % Q].B, jm + (U), row0, colbits, wcol, s0 + (U));
         static_assert(Q == 2 || Q == 4 || Q == 8, "Q must be 2, 4 or 8");
         SEL_STEP(0)
         SEL_STEP(1)
@@ -894,20 +1312,38 @@ __device__ __forceinline__ F sel_margins(F (&C)[Q], const F (&a)[Q], const F (&b
     return cm;
 }
 
-template <typename F, int Q>
+template <typename F, int Q, bool WIT>
 __device__ __forceinline__ void sel_group(F (&C)[Q], const F (&a)[Q], const F (&b)[Q],
-                                          const F (&nth)[Q], F (&rm)[Q], const H4<F> (&hv)[Q],
-                                          unsigned long long& colbits, int s0)
+                                          const F (&nth)[Q], F (&rm)[Q], F (&bm)[Q],
+                                          const H4<F> (&hv)[Q], int32_t row0,
+                                          unsigned long long& colbits, int32_t& wcol, int s0)
 {
     unsigned long long bal[Q];
 #define SEL_PAIR(U)                                                                    \
     {                                                                                  \
         F m0[Q], m1[Q];                                                                \
         const F c0 = sel_margins<F, Q, (U)>(C, a, b, nth, hv[(U)], m0);                \
-        bal[(U)] = __ballot(c0 > F(0));                                                \
+        const unsigned long long b0 = uniform64(__ballot(c0 > F(0)));                  \
         const F c1 = sel_margins<F, Q, (U) + 1>(C, a, b, nth, hv[(U) + 1], m1);        \
-        bal[(U) + 1] = __ballot(c1 > F(0));                                            \
-        _Pragma("unroll") for (int q = 0; q < Q; ++q) rm[q] = fmax(rm[q], fmax(m0[q], m1[q])); \
+        const unsigned long long b1 = uniform64(__ballot(c1 > F(0)));                  \
+        _Pragma("unroll") for (int q = 0; q < Q; ++q) {                                \
+            rm[q] = fmax(rm[q], fmax(m0[q], m1[q]));                                   \
+            if (WIT)                                                                   \
+                bm[q] = fmax(bm[q], fmax(pack_step(m0[q], s0 + (U)), pack_step(m1[q], s0 + (U) + 1))); \
+        }                                                                              \
+        if (WIT) {                                                                     \
+            if (b0 != 0ull) {                                                          \
+                colbits |= 1ull << (s0 + (U));                                         \
+                col_witness<F, Q>(b0, m0, row0, s0 + (U), wcol);                       \
+            }                                                                          \
+            if (b1 != 0ull) {                                                          \
+                colbits |= 1ull << (s0 + (U) + 1);                                     \
+                col_witness<F, Q>(b1, m1, row0, s0 + (U) + 1, wcol);                   \
+            }                                                                          \
+        } else {                                                                       \
+            bal[(U)] = b0;                                                             \
+            bal[(U) + 1] = b1;                                                         \
+        }                                                                              \
     }
     static_assert(Q == 2 || Q == 4 || Q == 8, "Q must be 2, 4 or 8");
     SEL_PAIR(0)
@@ -917,32 +1353,36 @@ __device__ __forceinline__ void sel_group(F (&C)[Q], const F (&a)[Q], const F (&
         SEL_PAIR((Q > 4 ? 6 : 0))
     }
 #undef SEL_PAIR
-    unsigned long long g = 0ull;
+    if (!WIT) {
+        unsigned long long g = 0ull;
 #pragma unroll
-    for (int u = 0; u < Q; ++u)
-        if (bal[u] != 0ull) g |= 1ull << u;
-    colbits |= g << s0;
+        for (int u = 0; u < Q; ++u)
+            if (bal[u] != 0ull) g |= 1ull << u;
+        colbits |= g << s0;
+    }
 }
 
 // A full block of 64 steps with every pair a non-self match, in groups of Q
-// steps without per-step tests: row maxima fold two steps per max, column
-// tests are kept as ballots and folded into colbits once per group.  (Reading
+// steps without per-step tests: row maxima fold two steps per max.  (Reading
 // the next group's helpers ahead costs registers, hence occupancy, and
 // measured slower.)
-template <typename F, int Q>
+template <typename F, int Q, bool WIT>
 __device__ __forceinline__ void sel_block_full(F (&C)[Q], const F (&a)[Q], const F (&b)[Q],
-                                               const F (&nth)[Q], F (&rm)[Q], const H4<F>* hs,
-                                               unsigned long long& colbits)
+                                               const F (&nth)[Q], F (&rm)[Q], F (&bm)[Q],
+                                               const H4<F>* hs, int32_t row0,
+                                               unsigned long long& colbits, int32_t& wcol)
 {
     for (int s0 = 0; s0 < 64; s0 += Q) {
         H4<F> hv[Q];
 #pragma unroll
         for (int u = 0; u < Q; ++u) hv[u] = hs[s0 + u];
-        sel_group<F, Q>(C, a, b, nth, rm, hv, colbits, s0);
+        sel_group<F, Q, WIT>(C, a, b, nth, rm, bm, hv, row0, colbits, wcol, s0);
     }
 }
 
-template <typename F, int Q>
+// WIT: keep the witnesses of the rows and columns it prunes (a search; a bare
+// range search has no next length and saves the instructions).
+template <typename F, int Q, bool WIT>
 __device__ void sel_item(const SweepArgs<F>& A, int64_t i0, int64_t jbeg, int64_t jend, F thr,
                          double* lds, unsigned long long& evals, uint32_t* work)
 {
@@ -954,6 +1394,7 @@ __device__ void sel_item(const SweepArgs<F>& A, int64_t i0, int64_t jbeg, int64_
     const int32_t m = A.m;
     const int64_t N = A.N;
     const int64_t rbase = i0 + (int64_t)Q * lane;
+    const int32_t row0 = (int32_t)i0;
 
     unsigned long long dm[Q];
     rows_from_bitmap<Q>(A.alive, rbase, dm);
@@ -985,22 +1426,42 @@ __device__ void sel_item(const SweepArgs<F>& A, int64_t i0, int64_t jbeg, int64_
         b[q] = top ? F(0) : A.dg[ip];
         const F invi = A.inv[i];
         // margin offset: C * inv_j - thr / inv_i > 0  <=>  rho > thr
-        nth[q] = (i < N && invi > F(0)) ? -(thr / invi) : -f_inf<F>();
+        nth[q] = (i < N && invi > F(0)) ? -(thr / invi) : f_low<F>();
         ri[q] = (int32_t)i;
-        rm[q] = -f_inf<F>();
+        rm[q] = f_low<F>();
     }
+    // Rows of block [j0, j0 + 64) that fell in it keep the step as witness.
+    auto row_witness = [&](const F (&bm)[Q], int64_t j0) {
+#pragma unroll
+        for (int q = 0; q < Q; ++q)
+            if (bm[q] > F(0) && !((dm[q] >> lane) & 1ull))
+                A.wit[rbase + q] = ~(int32_t)(j0 + step_of(bm[q]));
+    };
     // column jbeg
     {
         const F invj = A.inv[jbeg];
-        F cm = -f_inf<F>();
+        F mg[Q], bm[Q];
+        F cm = f_low<F>();
 #pragma unroll
         for (int q = 0; q < Q; ++q) {
-            F mg = f_fma(C[q], invj, nth[q]);
-            mg = ((int32_t)(jbeg - m) >= ri[q]) ? mg : -f_inf<F>();
-            rm[q] = fmax(rm[q], mg);
-            cm = fmax(cm, mg);
+            mg[q] = f_fma(C[q], invj, nth[q]);
+            mg[q] = ((int32_t)(jbeg - m) >= ri[q]) ? mg[q] : f_low<F>();
+            rm[q] = fmax(rm[q], mg[q]);
+            bm[q] = pack_step(mg[q], 0);
+            cm = fmax(cm, mg[q]);
         }
-        kill_columns(A.alive, jbeg, uniform64(__ballot(cm > F(0))) ? 1ull : 0ull);
+        const unsigned long long bal = uniform64(__ballot(cm > F(0)));
+        if (!WIT) {
+            kill_columns(A.alive, jbeg, bal ? 1ull : 0ull);
+        } else if (bal != 0ull) {
+            int32_t wcol = 0;
+            col_witness<F, Q>(bal, mg, row0, 0, wcol);
+            if (live_columns(A.alive, jbeg) & 1ull) {
+                if (lane == 0) A.wit[jbeg] = ~wcol;
+                kill_columns(A.alive, jbeg, 1ull);
+            }
+            row_witness(bm, jbeg);
+        }
 #pragma unroll
         for (int q = 0; q < Q; ++q) dm[q] |= uniform64(__ballot(rm[q] > F(0)));
     }
@@ -1019,14 +1480,26 @@ __device__ void sel_item(const SweepArgs<F>& A, int64_t i0, int64_t jbeg, int64_
             const H4<F>* hb = hs + 64 * sb;
             const unsigned long long word = load_word(&A.alive[rbase >> 6]);
             unsigned long long colbits = 0ull;
+            int32_t wcol = 0;
+            F bm[Q];
+#pragma unroll
+            for (int q = 0; q < Q; ++q) bm[q] = f_low<F>();
             const bool full = (j - (i0 + R - 1)) >= m;
             if (Q <= 4 && full && nst == 64)  // taller tiles: the general path keeps fewer registers
-                sel_block_full<F, Q>(C, a, b, nth, rm, hb, colbits);
+                sel_block_full<F, Q, WIT>(C, a, b, nth, rm, bm, hb, row0, colbits, wcol);
             else if (full)
-                sel_block<F, Q, false>(A, j, nst, C, a, b, nth, rm, ri, hb, colbits);
+                sel_block<F, Q, false, WIT>(A, j, nst, C, a, b, nth, rm, bm, ri, hb, row0, colbits, wcol);
             else
-                sel_block<F, Q, true>(A, j, nst, C, a, b, nth, rm, ri, hb, colbits);
-            kill_columns(A.alive, j, colbits);
+                sel_block<F, Q, true, WIT>(A, j, nst, C, a, b, nth, rm, bm, ri, hb, row0, colbits, wcol);
+            if (!WIT) {
+                kill_columns(A.alive, j, colbits);
+            } else if (colbits != 0ull) {
+                // only columns still alive: the others keep the witness they have
+                colbits &= live_columns(A.alive, j);
+                if ((colbits >> lane) & 1ull) A.wit[j + lane] = ~wcol;
+                row_witness(bm, j);
+                kill_columns(A.alive, j, colbits);
+            }
 #pragma unroll
             for (int q = 0; q < Q; ++q) dm[q] |= uniform64(__ballot(rm[q] > F(0)));
             ev += pair_count(i0, std::min<int64_t>(i0 + R, N), j, nst, m, false);
@@ -1047,7 +1520,7 @@ __device__ void sel_item(const SweepArgs<F>& A, int64_t i0, int64_t jbeg, int64_
     for (int q = 0; q < Q; ++q) {
         const int64_t i = rbase + q;
         bool u = false;
-        if (!((dm[q] >> lane) & 1ull) && i < N && rm[q] > -f_inf<F>()) {
+        if (!((dm[q] >> lane) & 1ull) && i < N && rm[q] > F(0.5) * f_low<F>()) {
             const double rt = (double)rm[q] * (double)A.inv[i] + (double)thr;
             atomicMax(&A.rhs[i], ord_of(rt));
             u = rt > ulim;
@@ -1099,6 +1572,7 @@ __device__ __forceinline__ SweepArgs<float> args_of<float>(const SeriesDev& s, C
     A.rhs = s.rhs;
     A.unc = s.unc;
     A.twork = s.twork;
+    A.wit = s.wit;
     A.ctrl = c;
     A.m = c->m;
     A.N = s.n - A.m + 1;
@@ -1118,6 +1592,7 @@ __device__ __forceinline__ SweepArgs<double> args_of<double>(const SeriesDev& s,
     A.rhs = s.rhs;
     A.unc = s.unc;
     A.twork = s.twork;
+    A.wit = s.wit;
     A.ctrl = c;
     A.m = c->m;
     A.N = s.n - A.m + 1;
@@ -1210,7 +1685,46 @@ __device__ __forceinline__ void ref_block_full(double (&C)[Q], const double (&a)
     }
 }
 
-template <int Q, int NC = batch_cols<double>()>
+// The block of nst steps from j0 again (same operations, same values): every
+// slot keeps the first column of the block that prunes it.
+template <int Q>
+__device__ __forceinline__ void ref_replay(const SweepArgs<double>& A, int64_t j0, int nst, bool left,
+                                           double (&C)[Q], const double (&a)[Q],
+                                           const double (&b)[Q], const double (&iv)[Q],
+                                           const int32_t (&ri)[Q], double thr,
+                                           const H4<double>* hs, int32_t (&wj)[Q])
+{
+    for (int s0 = 0; s0 < nst; s0 += Q) {
+        auto step = [&](auto U) {
+            constexpr int u = decltype(U)::value;
+            if (u < Q && s0 + u < nst) {
+                const H4<double> h = hs[s0 + u];
+                advance<double, Q, (u < Q ? u : 0)>(C, a, b, h.df, h.dg, h.B);
+                const int32_t j = (int32_t)(j0 + s0 + u);
+#pragma unroll
+                for (int q = 0; q < Q; ++q) {
+                    const double v = C[slot_reg<Q, (u < Q ? u : 0)>(q)] * h.inv;
+                    const bool ok = left ? j + A.m <= ri[q] : j - A.m >= ri[q];
+                    if (ok && v * iv[q] > thr && wj[q] < 0) wj[q] = j;
+                }
+            }
+        };
+        step(std::integral_constant<int, 0>());
+        step(std::integral_constant<int, 1>());
+        if (Q > 2) {
+            step(std::integral_constant<int, 2>());
+            step(std::integral_constant<int, 3>());
+        }
+        if (Q > 4) {
+            step(std::integral_constant<int, 4>());
+            step(std::integral_constant<int, 5>());
+            step(std::integral_constant<int, 6>());
+            step(std::integral_constant<int, 7>());
+        }
+    }
+}
+
+template <int Q, int NC = batch_cols<double>(), bool WIT = false>
 __device__ void ref_item(const SweepArgs<double>& A, int64_t i0, int64_t jbeg, int64_t jend,
                          bool left, double thr, int prune, double* lds, unsigned long long& evals)
 {
@@ -1271,6 +1785,11 @@ __device__ void ref_item(const SweepArgs<double>& A, int64_t i0, int64_t jbeg, i
             const int nst = (int)std::min<int64_t>(64, jb_end - j);
             const H4<double>* hb = hs + 64 * sb;
             const unsigned long long word = load_word(&A.alive[rbase >> 6]);
+            double C0[Q];
+            if (WIT) {
+#pragma unroll
+                for (int q = 0; q < Q; ++q) C0[q] = C[q];
+            }
             bool full;
             if (left) full = (i0 - (j + nst - 1)) >= m;
             else full = (j - (i0 + R - 1)) >= m;
@@ -1281,10 +1800,27 @@ __device__ void ref_item(const SweepArgs<double>& A, int64_t i0, int64_t jbeg, i
             ev += pair_count(i0, std::min<int64_t>(i0 + R, N), j, nst, m, left);
             j += nst;
             if (prune) {
+                unsigned long long fell = 0ull;
+                double iv[Q];
+                bool now[Q];
 #pragma unroll
                 for (int q = 0; q < Q; ++q) {
-                    const double iv = rowinv[Q * lane + q];
-                    dm[q] |= uniform64(__ballot(iv > 0.0 && mx[q] * iv > thr));
+                    iv[q] = rowinv[Q * lane + q];
+                    now[q] = iv[q] > 0.0 && mx[q] * iv[q] > thr && !((dm[q] >> lane) & 1ull);
+                    const unsigned long long k = uniform64(__ballot(now[q]));
+                    fell |= k;
+                    dm[q] |= k;
+                }
+                if (WIT && fell != 0ull) {
+                    // the rows that fell in this block: their witnesses
+                    // (one found in the item's first column falls here too)
+                    int32_t wj[Q];
+#pragma unroll
+                    for (int q = 0; q < Q; ++q) wj[q] = -1;
+                    ref_replay<Q>(A, j - nst, nst, left, C0, a, b, iv, ri, thr, hb, wj);
+#pragma unroll
+                    for (int q = 0; q < Q; ++q)
+                        if (now[q]) A.wit[rbase + q] = ~(wj[q] >= 0 ? wj[q] : (int32_t)jbeg);
                 }
             }
             go = sync_rows_with<Q>(A.alive, rbase, word, dm);
@@ -1301,8 +1837,11 @@ __device__ void ref_item(const SweepArgs<double>& A, int64_t i0, int64_t jbeg, i
         const int64_t i = rbase + q;
         flat[q] = (i < N) && !(invi[q] > 0.0);
         if (flat[q]) {
-            const bool partner = (flo >= 0 && flo <= i - m) || (fhi >= 0 && fhi >= i + m);
+            const bool lo_ok = flo >= 0 && flo <= i - m, hi_ok = fhi >= 0 && fhi >= i + m;
+            const bool partner = lo_ok || hi_ok;
             mx[q] = partner ? 1.0 : 0.0;
+            if (WIT && prune && mx[q] > thr)
+                A.wit[i] = ~(int32_t)(lo_ok ? flo : hi_ok ? fhi : i + m < N ? i + m : i - m);
         }
         if (prune) dm[q] |= uniform64(__ballot(flat[q] && mx[q] > thr));
     }
@@ -1409,7 +1948,7 @@ __global__ __launch_bounds__(64) void k_select_band(SeriesDev* S, int B, const i
     const int b = series_of(pfx, B, blockIdx.x);
     const SeriesDev& s = S[b];
     Ctrl* c = s.ctrl;
-    if (!c->active || !c->prune) return;
+    if (!c->active || !c->prune || lean_round(c)) return;
     const SweepArgs<F> A = args_of<F>(s, c);
     const int32_t m = A.m;
     const int64_t i0 = (int64_t)(blockIdx.x - pfx[b]) * BAND_S;
@@ -1536,6 +2075,13 @@ __global__ __launch_bounds__(64) void k_select_band(SeriesDev* S, int B, const i
 #pragma unroll
         for (int q = 0; q < BAND_Q; ++q) {
             const unsigned int v = __builtin_bitreverse32(km[q]);
+            // every hit is a witness of both its subsequences
+            for (unsigned int h = v; h; h &= h - 1u) {
+                const int32_t t = t0 + __ffs((int)h) - 1;
+                const int32_t i = (int32_t)i0 + t, j = (int32_t)j0 + t + BAND_Q * lane + q;
+                A.wit[i] = ~j;
+                A.wit[j] = ~i;
+            }
             if (v) {
                 const int cb = off + t0 + BAND_Q * lane + q;
                 atomicOr(&kb[cb >> 5], v << (cb & 31));
@@ -1563,7 +2109,7 @@ __global__ __launch_bounds__(64) void k_select_band(SeriesDev* S, int B, const i
 // First selection pass: every row tile's nearest near_cols columns, split
 // into chunks of `chunk` columns that run concurrently; each stops as soon
 // as the whole tile is dead.
-template <typename F, int Q>
+template <typename F, int Q, bool WIT>
 __global__ __launch_bounds__(64) void k_select_near(SeriesDev* S, int B,
                                                     const int64_t* __restrict__ pfx, int near_cols,
                                                     int chunk)
@@ -1572,7 +2118,7 @@ __global__ __launch_bounds__(64) void k_select_near(SeriesDev* S, int B,
     const int b = series_of(pfx, B, blockIdx.x);
     const SeriesDev& s = S[b];
     Ctrl* c = s.ctrl;
-    if (!c->active || !c->prune) return;
+    if (!c->active || !c->prune || lean_round(c)) return;
     constexpr int R = 64 * Q;
     const int64_t lb = blockIdx.x - pfx[b];
     const SweepArgs<F> A = args_of<F>(s, c);
@@ -1615,7 +2161,7 @@ __global__ __launch_bounds__(64) void k_select_near(SeriesDev* S, int B,
     const int64_t jend = std::min<int64_t>(std::min<int64_t>(A.N, jbeg + chunk), j00 + near_cols);
     const F thr = sel_threshold<F>(c);
     unsigned long long ev = 0;
-    sel_item<F, Q>(A, i0, jbeg, jend, thr, lds, ev, &A.twork[tile]);
+    sel_item<F, Q, WIT>(A, i0, jbeg, jend, thr, lds, ev, &A.twork[tile]);
     if (threadIdx.x == 0 && ev) {
         atomicAdd(&s.evc[EV_NEAR * EV_SLOTS + (blockIdx.x & (EV_SLOTS - 1))], ev);
     }
@@ -1625,7 +2171,7 @@ __global__ __launch_bounds__(64) void k_select_near(SeriesDev* S, int B,
 // from each series' counter; a workgroup drains the series in rotated order.
 // The FP32 two-row tile fits 128 registers, so four waves share a SIMD
 // (three otherwise): the pass is bound by how many items are resident.
-template <typename F, int Q>
+template <typename F, int Q, bool WIT>
 __global__ __launch_bounds__(64, (sizeof(F) == 4 && Q <= 2) ? 4 : 1) void k_select_far(
     SeriesDev* S, int B, int near_cols, int chunk, int near_rows)
 {
@@ -1639,7 +2185,7 @@ __global__ __launch_bounds__(64, (sizeof(F) == 4 && Q <= 2) ? 4 : 1) void k_sele
     for (int b = 0; b < B; ++b) {
         const SeriesDev& s = S[b];
         Ctrl* c = s.ctrl;
-        if (!c->active || !c->prune) continue;
+        if (!c->active || !c->prune || lean_round(c)) continue;
         const unsigned int nlive = c->nlive_sel;
         const unsigned long long total = (unsigned long long)nlive * c->maxc_sel;
         if (total == 0) continue;
@@ -1658,7 +2204,7 @@ __global__ __launch_bounds__(64, (sizeof(F) == 4 && Q <= 2) ? 4 : 1) void k_sele
             const int64_t jbeg = (i0 / near_rows) * near_rows + A.m + near_cols + (int64_t)cc * chunk;
             if (jbeg >= A.N) continue;
             const int64_t jend = std::min<int64_t>(A.N, jbeg + chunk);
-            sel_item<F, Q>(A, i0, jbeg, jend, thr, lds, ev, nullptr);
+            sel_item<F, Q, WIT>(A, i0, jbeg, jend, thr, lds, ev, nullptr);
         }
         if (threadIdx.x == 0 && ev) {
             atomicAdd(&s.evc[EV_FAR * EV_SLOTS + (blockIdx.x & (EV_SLOTS - 1))], ev);
@@ -1684,7 +2230,7 @@ __global__ __launch_bounds__(TILES_BLOCK) void k_tiles(SeriesDev* S, int B,
     const int b = series_of(pfx, B, blockIdx.x);
     const SeriesDev& s = S[b];
     Ctrl* c = s.ctrl;
-    if (!c->active) return;
+    if (!c->active || lean_round(c)) return;
     if (mode == 0 && !c->prune) return;
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int64_t t = (blockIdx.x - pfx[b]) * (int64_t)TILES_BLOCK + threadIdx.x;
@@ -1775,7 +2321,9 @@ __global__ __launch_bounds__(TILES_BLOCK) void k_tiles(SeriesDev* S, int B,
 
 // Refinement: exact FP64 row maximum of rho over both sides for every tile
 // holding survivors; items drawn nearest-first, alternating right and left.
-template <int Q>
+// WIT: the rows it prunes keep their witnesses (a search); a bare range
+// search has no next length.
+template <int Q, bool WIT>
 __global__ __launch_bounds__(64, (Q <= 4 ? 3 : 1)) void k_refine(SeriesDev* S, int B,
                                                                          int chunk)
 {
@@ -1785,7 +2333,7 @@ __global__ __launch_bounds__(64, (Q <= 4 ? 3 : 1)) void k_refine(SeriesDev* S, i
     for (int b = 0; b < B; ++b) {
         const SeriesDev& s = S[b];
         Ctrl* c = s.ctrl;
-        if (!c->active || direct_round(c)) continue;
+        if (!c->active || lean_round(c) || direct_round(c)) continue;
         const unsigned int nlive = c->nlive_ref;
         const unsigned long long total = (unsigned long long)nlive * c->maxc_ref;
         if (total == 0) continue;
@@ -1825,7 +2373,7 @@ __global__ __launch_bounds__(64, (Q <= 4 ? 3 : 1)) void k_refine(SeriesDev* S, i
                 jend = std::min<int64_t>(A.N, jbeg + chunk);
             }
             if (jbeg >= jend) continue;
-            ref_item<Q>(A, i0, jbeg, jend, left, thr, prune, lds, ev);
+            ref_item<Q, batch_cols<double>(), WIT>(A, i0, jbeg, jend, left, thr, prune, lds, ev);
         }
         if (threadIdx.x == 0 && ev)
             atomicAdd(&s.evc[EV_REF * EV_SLOTS + (blockIdx.x & (EV_SLOTS - 1))], ev);
@@ -1860,8 +2408,7 @@ __device__ __forceinline__ Key wave_min_key(Key k)
 // wave first extracts the best of the bitmap words it owns by rounds of
 // wave-wide minimum (no block barriers), then wave 0 extracts the best of
 // the pooled per-wave lists.  In a direct round (no refinement sweep) every
-// live subsequence becomes a candidate.  Finally write the candidates'
-// centred windows x_k = t_{i+k} - mu_i and their sums for the exact pass.
+// live subsequence becomes a candidate.
 // fn(q, word) for every nonzero word q of the bitmap taken by this thread
 // (q = threadIdx.x + TOPK_BLOCK j): sixteen words are loaded before any is
 // scanned, so one memory latency covers them.
@@ -1895,10 +2442,9 @@ __global__ __launch_bounds__(TOPK_BLOCK) void k_select_top(SeriesDev* S)
     __shared__ int kp_s;
     const SeriesDev& s = S[blockIdx.x];
     Ctrl* c = s.ctrl;
-    if (!c->active) return;
+    if (!c->active || lean_round(c)) return;
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    const int32_t m = c->m;
-    const int64_t N = s.n - m + 1;
+    const int64_t N = s.n - c->m + 1;
     const int64_t nw = (N + 63) / 64;
     const unsigned long long* __restrict__ alive = s.alive;
     const unsigned long long* __restrict__ rho = s.rho;
@@ -1920,22 +2466,14 @@ __global__ __launch_bounds__(TOPK_BLOCK) void k_select_top(SeriesDev* S)
                 const int t = __ffsll((long long)bits) - 1;
                 bits &= bits - 1ull;
                 const unsigned int slot = atomicAdd(&nc_s, 1u);
-                if (slot < (unsigned int)KP_MAX) cand_s[slot] = q * 64 + t;
+                if (slot < (unsigned int)CAND_MAX) s.cand[slot] = q * 64 + t;
             }
         });
         __syncthreads();
-        kp = (int)min(nc_s, (unsigned int)KP_MAX);
-        if (kp < k) {
-            if (tid == 0) {
-                c->nsurv = (unsigned int)kp;
-                c->ncand = 0;
-            }
-            return;
-        }
-        if (tid < kp) s.cand[tid] = cand_s[tid];
+        kp = (int)min(nc_s, (unsigned int)CAND_MAX);
         if (tid == 0) {
             c->nsurv = (unsigned int)kp;  // refined by k_round_end
-            c->ncand = (unsigned int)kp;
+            c->ncand = kp < k ? 0u : (unsigned int)kp;
         }
     } else {
         unsigned int cnt = 0;
@@ -1946,7 +2484,8 @@ __global__ __launch_bounds__(TOPK_BLOCK) void k_select_top(SeriesDev* S)
         __syncthreads();
         unsigned int ns = 0;
         for (int q = 0; q < NW; ++q) ns += cnt_s[q];
-        if (ns < (unsigned int)k) {
+        // (a bare range search wants the count only)
+        if (ns < (unsigned int)k || (c->mode == 3 && s.idx == nullptr)) {
             if (tid == 0) {
                 c->nsurv = ns;
                 c->ncand = 0;
@@ -2060,74 +2599,492 @@ __global__ __launch_bounds__(TOPK_BLOCK) void k_select_top(SeriesDev* S)
             c->ncand = (unsigned int)kp;
         }
     }
-    __syncthreads();
-    const double* __restrict__ mu = cur_mu(s, c);
-    const int64_t stride = (int64_t)s.maxL + 8;
-    for (int r = w; r < kp; r += NW) {
-        const int64_t i = cand_s[r];
-        const double mui = mu[i];
-        double* x = s.xc + r * stride;
-        double sx = 0.0;
-        for (int kk = lane; kk < m; kk += 64) {
-            const double v = s.T[i + kk] - mui;
-            x[kk] = v;
-            sx += v;
+}
+
+// ---------------------------------------------------------------------------
+// the exact pass: nearest neighbours of the candidate rows over every column
+// ---------------------------------------------------------------------------
+// Candidates are taken in groups of PM_G = 16.  The reported values come from
+// direct centred FP64 dot products on the FP64 matrix cores (k_exact); a
+// screening pass (k_screen) first bounds every pair's correlation on the FP16
+// matrix cores and leaves to k_exact only the blocks of EX_COLS columns that
+// can hold a candidate's largest correlation.
+constexpr int PM_G = 16;       // candidates per group
+constexpr int EX_COLS = EXACT_COLS;  // columns per exact block
+constexpr int EX_WAVES = 4;    // waves per workgroup, EX_COLS / EX_WAVES columns each
+constexpr int EX_CT = EX_COLS / EX_WAVES / 16;  // 16-column tiles per wave
+constexpr int PM_KC = 256;     // window offsets per LDS chunk
+constexpr int PM_XS = PM_KC + 1;  // LDS row stride of a candidate window (odd: no bank conflicts)
+constexpr int SC_WAVES = 4;
+constexpr int SC_COLS = SCREEN_COLS;  // columns per screening chunk, EX_COLS per wave
+static_assert(SC_COLS == SC_WAVES * EX_COLS, "a wave screens one exact block");
+constexpr int SC_AS = PM_KC + 8;  // LDS row stride of a screened window, in halves
+constexpr int SC_SLOTS = (SC_COLS + PM_KC) / 8;  // 16-byte slots of one shifted copy
+
+// Candidates of a series in this round (0: nothing to evaluate).
+__device__ __forceinline__ int cand_count(const SeriesDev& s, const Ctrl* c, int full)
+{
+    if (!c->active) return 0;
+    if (lean_round(c)) return c->nlive >= (uint32_t)s.k ? (int)c->nlive : 0;
+    return full ? (int)c->ncand : 0;
+}
+__device__ __forceinline__ int64_t exact_blocks(int64_t N) { return (N + EX_COLS - 1) / EX_COLS; }
+__device__ __forceinline__ int64_t screen_chunks(int64_t N) { return (N + SC_COLS - 1) / SC_COLS; }
+
+// Work items of the two kernels: (candidate group, chunk or block) of every
+// series, group-major, numbered across the batch; each workgroup takes one
+// contiguous range, so that it stays with a group's windows.  ipfx[b]: first
+// item of series b (one series needs no table).
+__device__ __forceinline__ int64_t items_of(const SeriesDev& s, int full, bool screen)
+{
+    const Ctrl* c = s.ctrl;
+    const int64_t ng = (cand_count(s, c, full) + PM_G - 1) / PM_G;
+    const int64_t N = s.n - c->m + 1;
+    return ng * (screen ? screen_chunks(N) : exact_blocks(N));
+}
+constexpr int ITEMS_BLOCK = 1024;
+__global__ __launch_bounds__(ITEMS_BLOCK) void k_items(SeriesDev* S, int B, int full, int64_t* ipfx_s,
+                                                       int64_t* ipfx_e)
+{
+    __shared__ long long ws[2][ITEMS_BLOCK / 64];
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    long long base[2] = {0, 0};
+    for (int b0 = 0; b0 < B; b0 += ITEMS_BLOCK) {
+        const int b = b0 + tid;
+        long long v[2] = {0, 0}, x[2];
+        if (b < B) {
+            v[0] = items_of(S[b], full, true);
+            v[1] = items_of(S[b], full, false);
         }
-        sx = wave_sum(sx);
-        if (lane == 0) s.xc[KP_MAX * stride + r] = sx;
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            x[q] = v[q];
+            for (int o = 1; o < 64; o <<= 1) {
+                const long long y = __shfl_up(x[q], o);
+                if (lane >= o) x[q] += y;
+            }
+            if (lane == 63) ws[q][w] = x[q];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            long long before = 0, tot = 0;
+            for (int e = 0; e < ITEMS_BLOCK / 64; ++e) {
+                before += e < w ? ws[q][e] : 0;
+                tot += ws[q][e];
+            }
+            if (b < B) (q ? ipfx_e : ipfx_s)[b] = base[q] + before + x[q] - v[q];
+            base[q] += tot;
+        }
+        __syncthreads();
+    }
+    if (tid == 0) {
+        ipfx_s[B] = base[0];
+        ipfx_e[B] = base[1];
     }
 }
 
-// Exact FP64 nearest-neighbour correlation of the candidate rows against
-// every column: direct centred dot products (no recurrence), the reference
-// the reported distances and neighbour indices come from.  It is a dense
-// contraction X (candidates x m) . H (m x columns) with H[k][j] = t_{j+k},
-// so it runs on the FP64 matrix cores: V_MFMA_F64_16X16X4F64 multiplies a
-// 16 x 4 block of candidate values by a 4 x 16 block of the series, lane l
-// supplying X[l % 16][l / 16] and H[l / 16][l % 16] and receiving
-// D[l / 16 + 4 r][l % 16], r < 4.  A block is POLISH_COLS consecutive
-// columns of one series (PM_CT tiles of 16 per wave) for one group of PM_G
-// candidates (grid.y); the columns' values and chunks of PM_KC offsets of
-// the candidates' centred windows are staged in LDS, so a lane reads one
-// value per matrix instruction (1024 FMAs).  One (max rho, argmax j)
-// partial per candidate and workgroup.
-constexpr int PM_WAVES = POLISH_COLS / 128;   // waves per block
-constexpr int PM_CT = 8;                      // 16-column tiles per wave
-constexpr int PM_G = 16;                      // candidates per block
-constexpr int PM_KC = 256;                    // window offsets per LDS chunk
-constexpr int PM_XS = PM_KC + 1;              // LDS row stride of a candidate window (odd: no bank conflicts)
-constexpr int PM_GRID = 512;                  // workgroups per candidate group (each sweeps blocks in turn)
-// A workgroup sweeps the column blocks g, g + G, ... of the flat block space
-// (all series, prefix table pfx); the candidates' windows stay in LDS while
-// consecutive blocks belong to the same series and the window fits one chunk.
-__global__ __launch_bounds__(64 * PM_WAVES) void k_polish(SeriesDev* S, int B,
-                                                          const int64_t* __restrict__ pfx,
-                                                          int64_t nblocks)
+// The share of a workgroup: items [lo, hi) of total, per items each.
+struct Share {
+    int64_t lo, hi, per;
+};
+__device__ __forceinline__ Share share_of(int64_t total)
 {
-    static_assert(PM_WAVES * PM_CT * 16 == POLISH_COLS, "polish block geometry");
-    extern __shared__ double lds[];
-    __shared__ double red_v[PM_WAVES][PM_G];
-    __shared__ long long red_j[PM_WAVES][PM_G];
+    Share r;
+    r.per = (total + gridDim.x - 1) / gridDim.x;
+    r.lo = std::min<int64_t>(total, r.per * blockIdx.x);
+    r.hi = std::min<int64_t>(total, r.lo + r.per);
+    return r;
+}
+
+// Partials of a series: a workgroup that evaluated something for group g
+// leaves one, in one of the slots from part_base(g) on (as many as there are
+// workgroups whose share meets the group).
+__device__ __forceinline__ int64_t part_base(int64_t per, int64_t first, int64_t nblk, int g)
+{
+    return (first + g * nblk) / per - first / per + g;
+}
+
+typedef _Float16 half8_t __attribute__((ext_vector_type(8)));
+typedef float acc4f_t __attribute__((ext_vector_type(4)));
+
+// Screening.  Every candidate window x (centred, scaled to unit norm) and
+// every stretch of the series w (offset and scaled by a power of two per
+// chunk) is rounded to FP16 and x.w accumulated in FP32 by
+// V_MFMA_F32_16X16X32_F16, 32 times the rate of the FP64 instruction.  The
+// values only bound the correlation; every value that is reported or decides
+// anything comes from k_exact.  The Hankel operand B[k][c] = w[c' + k] is read
+// in aligned groups of eight values: tile u of a wave holds the columns
+// 8 c + u (c < 16) and reads the copy of w shifted by u, so eight copies of
+// the stretch stand in LDS.
+//
+// Bound: |rho~ - rho| <= e_j = e0 sqrt(1 + m ((mu_j - off) inv_j)^2) + floor,
+// by Cauchy-Schwarz on |x| = 1 and |w_j - off|: e0 holds the two roundings
+// (2^-11 each) and the FP32 accumulation (one rounding of 2^-23 per product),
+// floor the smallest normal FP16 value (should the matrix cores flush
+// subnormals), all rounded up.  A candidate's lower bound is the largest
+// rho~ - e_j over all columns; only blocks whose largest rho~ + e_j reaches
+// it can hold its maximum, so k_exact finds the same value and the same
+// smallest argmax as over all columns.  (A split into two FP16 values per
+// operand, 2^-22 instead of 2^-11, takes three times the matrix work and
+// leaves few blocks fewer.)
+__global__ __launch_bounds__(64 * SC_WAVES) void k_screen(SeriesDev* S, int B, int full,
+                                                          const int64_t* __restrict__ ipfx)
+{
+    __shared__ half8_t wcopy[8][SC_SLOTS];
+    __shared__ __align__(16) _Float16 xa[PM_G * SC_AS];
+    __shared__ double cmu[PM_G], cinv[PM_G];
+    __shared__ int64_t cidx[PM_G];
+    __shared__ double rlo[SC_WAVES], rhi[SC_WAVES];
+    __shared__ float lbw[SC_WAVES][PM_G];
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const int ca = lane & 15, ka = lane >> 4;
-    const int colbase = w * 16 * PM_CT;
-    const int g0 = (int)blockIdx.y * PM_G;
-    double* xg = lds;                   // [PM_G][PM_XS] candidate window chunk
-    double* ts = lds + PM_G * PM_XS;    // t[j0 .. j0 + POLISH_COLS + m + 4)
-    int loaded = -1;                    // series whose single-chunk windows are in xg
-    // running (max rho, smallest argmax j) of the lane's candidate rows over
-    // the blocks of series `cur` this workgroup has swept; the blocks of one
-    // series come in ascending order, so a strict > keeps the smaller j
-    int cur = -1;
-    int64_t cslot = 0;
-    double best[4];
-    long long bj[4];
-    unsigned long long evb = 0;
-    // one partial per (candidate, workgroup): slot = the workgroup's first
-    // block of the series, which is below the grid size
-    auto flush = [&]() {
-        const SeriesDev& s = S[cur];
-        const int ncand = (int)s.ctrl->ncand;
+    const int64_t total = B == 1 ? items_of(S[0], full, true) : ipfx[B];
+    const Share sh = share_of(total);
+    for (int64_t it = sh.lo; it < sh.hi;) {
+        const int b = B == 1 ? 0 : series_of(ipfx, B, it);
+        const int64_t first = B == 1 ? 0 : ipfx[b];
+        const SeriesDev& s = S[b];
+        const Ctrl* c = s.ctrl;
+        const int ncand = cand_count(s, c, full);
+        const int32_t m = c->m;
+        const int64_t N = s.n - m + 1;
+        const int64_t nch = screen_chunks(N), nblk = exact_blocks(N);
+        const int g = (int)((it - first) / nch);
+        const int64_t c0 = (it - first) - g * nch;
+        const int64_t c1 = std::min<int64_t>(nch, c0 + (sh.hi - it));
+        it += c1 - c0;
+        const double* __restrict__ T = s.T;
+        const double* __restrict__ mu = cur_mu(s, c);
+        const double* __restrict__ inv = s.inv64;
+        __syncthreads();
+        if (tid < PM_G) {
+            const int cid = PM_G * g + tid;
+            const int64_t i = s.cand[min(cid, ncand - 1)];
+            cidx[tid] = i;
+            cmu[tid] = mu[i];
+            cinv[tid] = inv[i];
+        }
+        __syncthreads();
+        int64_t ci[4];
+        bool flat[4];
+        float lbr[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            ci[r] = cidx[4 * ka + r];
+            flat[r] = cinv[4 * ka + r] == 0.0;
+            lbr[r] = -4.0f;
+        }
+        const float e0 = 1.05f * (2.0f * 0x1p-11f + 0x1p-22f + (float)(m + 32) * 0x1p-23f +
+                                  sqrtf((float)m) * 0x1p-23f);
+        const bool single = m <= PM_KC;
+        bool staged = false;
+        for (int64_t ch = c0; ch < c1; ++ch) {
+            const int64_t j0 = ch * SC_COLS;
+            // offset and scale of the chunk's stretch
+            double lo = f_inf<double>(), hi = -f_inf<double>();
+            const int span = (int)std::min<int64_t>(SC_COLS + m, s.n - j0);
+            for (int t = tid; t < span; t += 64 * SC_WAVES) {
+                const double v = T[j0 + t];
+                lo = fmin(lo, v);
+                hi = fmax(hi, v);
+            }
+#pragma unroll
+            for (int o = 32; o >= 1; o >>= 1) {
+                lo = fmin(lo, __shfl_xor(lo, o));
+                hi = fmax(hi, __shfl_xor(hi, o));
+            }
+            if (lane == 0) {
+                rlo[w] = lo;
+                rhi[w] = hi;
+            }
+            __syncthreads();  // (the previous chunk's operands are consumed)
+            for (int q = 0; q < SC_WAVES; ++q) {
+                lo = fmin(lo, rlo[q]);
+                hi = fmax(hi, rhi[q]);
+            }
+            const double off = 0.5 * (lo + hi);
+            const double range = 0.5 * (hi - lo);
+            // power of two with range * sw in (512, 1024] (1 for a constant stretch)
+            int ex = 0;
+            if (range > 0.0) (void)frexp(range, &ex);
+            const double sw = range > 0.0 ? ldexp(1.0, min(10 - ex, 900)) : 1.0;
+            acc4f_t acc[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) acc[u] = (acc4f_t){0.f, 0.f, 0.f, 0.f};
+            for (int kb = 0; kb < m; kb += PM_KC) {
+                const int kn = min(PM_KC, m - kb);
+                if (kb) __syncthreads();
+                // slot t of copy u: w[8 t + u .. 8 t + u + 7]
+                for (int e = tid; e < 2 * SC_SLOTS; e += 64 * SC_WAVES) {
+                    const int t = e >> 1, u0 = (e & 1) * 4;
+                    const double* __restrict__ src = T + j0 + kb + 8 * t + u0;
+                    _Float16 h[11];
+#pragma unroll
+                    for (int q = 0; q < 11; ++q) {
+                        const double v = (src[q] - off) * sw;
+                        // values past the windows of this chunk may exceed the scale
+                        h[q] = (_Float16)(float)fmin(2048.0, fmax(-2048.0, v));
+                    }
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        half8_t ph;
+#pragma unroll
+                        for (int q = 0; q < 8; ++q) ph[q] = h[u + q];
+                        wcopy[u0 + u][t] = ph;
+                    }
+                }
+                if (!single || !staged) {
+                    for (int gq = w; gq < PM_G; gq += SC_WAVES) {
+                        const int64_t i = cidx[gq];
+                        const double mi = cmu[gq], sc = cinv[gq] * 1024.0;
+                        for (int k = lane; k < SC_AS; k += 64) {
+                            const double v = k < kn ? (T[i + kb + k] - mi) * sc : 0.0;
+                            xa[gq * SC_AS + k] = (_Float16)(float)v;
+                        }
+                    }
+                    staged = true;
+                }
+                __syncthreads();
+                const int steps = (kn + 31) >> 5;
+                const _Float16* ah = &xa[ca * SC_AS + 8 * ka];
+                const int slot = w * (EX_COLS / 8) + ca + ka;
+                for (int st = 0; st < steps; ++st) {
+                    const half8_t vh = *(const half8_t*)(ah + 32 * st);
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) {
+                        const half8_t bh = wcopy[u][slot + 4 * st];
+                        acc[u] = __builtin_amdgcn_mfma_f32_16x16x32_f16(vh, bh, acc[u], 0, 0, 0);
+                    }
+                }
+            }
+            // epilogue: lane holds candidate 4 ka + r, columns jb + 8 ca + u
+            const int64_t jb = j0 + w * EX_COLS;
+            bool edge = jb + EX_COLS > N;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) edge = edge || (jb < ci[r] + m && jb + EX_COLS > ci[r] - m);
+            const bool masked = __ballot(edge) != 0ull;
+            const double usw = 1.0 / sw;
+            const float fl = sqrtf((float)m) * 0x1p-13f;
+            float ubm[4], lbm[4];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) ubm[r] = lbm[r] = -4.0f;
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const int64_t j = jb + 8 * ca + u;
+                const double ivd = inv[j];
+                const float iv = (float)(ivd * usw);
+                const float dn = (float)((mu[j] - off) * ivd);
+                const float ej = 1.02f * (e0 * sqrtf(1.0f + (float)m * dn * dn) + fl * iv) + 1e-12f;
+                const float gj = iv * 0x1p-10f;
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const float t = acc[u][r] * gj;
+                    const bool ok = !masked || (j < N && (j <= ci[r] - m || j >= ci[r] + m));
+                    ubm[r] = fmaxf(ubm[r], ok ? t + ej : -4.0f);
+                    lbm[r] = fmaxf(lbm[r], ok ? t - ej : -4.0f);
+                }
+            }
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                lbr[r] = fmaxf(lbr[r], lbm[r]);
+#pragma unroll
+                for (int o = 8; o >= 1; o >>= 1) ubm[r] = fmaxf(ubm[r], __shfl_xor(ubm[r], o));
+                if (flat[r]) ubm[r] = 4.0f;  // every block of a flat candidate is evaluated
+            }
+            const int64_t blk = ch * SC_WAVES + w;
+            if (ca == 0 && blk < nblk)
+                *(float4*)(s.ub + ((int64_t)g * nblk + blk) * PM_G + 4 * ka) =
+                    make_float4(ubm[0], ubm[1], ubm[2], ubm[3]);
+        }
+        // the workgroup's lower bounds of this group
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+#pragma unroll
+            for (int o = 8; o >= 1; o >>= 1) lbr[r] = fmaxf(lbr[r], __shfl_xor(lbr[r], o));
+            if (ca == 0) lbw[w][4 * ka + r] = flat[r] ? -4.0f : lbr[r];
+        }
+        __syncthreads();
+        if (tid < PM_G) {
+            float v = lbw[0][tid];
+            for (int q = 1; q < SC_WAVES; ++q) v = fmaxf(v, lbw[q][tid]);
+            const int64_t e = (int64_t)blockIdx.x - first / sh.per + g;
+            s.lbp[e * PM_G + tid] = v;
+        }
+    }
+}
+
+// Exact FP64 nearest-neighbour correlation of the candidate rows: direct
+// centred dot products (no recurrence), the reference the reported distances
+// and neighbour indices come from.  X (candidates x m) . H (m x columns) with
+// H[k][j] = t_{j+k} on the FP64 matrix cores: V_MFMA_F64_16X16X4F64
+// multiplies a 16 x 4 block of candidate values by a 4 x 16 block of the
+// series, lane l supplying X[l % 16][l / 16] and H[l / 16][l % 16] and
+// receiving D[l / 16 + 4 r][l % 16], r < 4.  A block is EX_COLS columns, EX_CT
+// tiles per wave: small, because after the screening a group has a few blocks
+// and their latency counts.  With `screened` only the marked blocks run.  One
+// (max rho, argmax j) partial per candidate, group and workgroup, in the
+// order the workgroups finish (slots from one counter per group).
+__global__ __launch_bounds__(64 * EX_WAVES) void k_exact(SeriesDev* S, int B, int full, int screened,
+                                                         int screen_grid,
+                                                         const int64_t* __restrict__ ipfx_s,
+                                                         const int64_t* __restrict__ ipfx_e)
+{
+    extern __shared__ double lds[];
+    __shared__ double red_v[EX_WAVES][PM_G];
+    __shared__ long long red_j[EX_WAVES][PM_G];
+    __shared__ double sxs[PM_G], civ[PM_G];
+    __shared__ int64_t cidx[PM_G];
+    __shared__ float lbs[EX_WAVES * 4][PM_G];
+    __shared__ unsigned long long mark_s[EX_WAVES];
+    __shared__ unsigned int slot_s;
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const int ca = lane & 15, ka = lane >> 4;
+    double* xg = lds;                 // [PM_G][PM_XS] candidate window chunk
+    double* ts = lds + PM_G * PM_XS;  // t[j0 .. j0 + EX_COLS + m + 4)
+    const int64_t total = B == 1 ? items_of(S[0], full, false) : ipfx_e[B];
+    const Share sh = share_of(total);
+    for (int64_t it = sh.lo; it < sh.hi;) {
+        const int b = B == 1 ? 0 : series_of(ipfx_e, B, it);
+        const int64_t first = B == 1 ? 0 : ipfx_e[b];
+        const SeriesDev& s = S[b];
+        Ctrl* c = s.ctrl;
+        const int ncand = cand_count(s, c, full);
+        const int32_t m = c->m;
+        const int64_t N = s.n - m + 1;
+        const int64_t nblk = exact_blocks(N);
+        const int g = (int)((it - first) / nblk);
+        const int64_t b0 = (it - first) - g * nblk;
+        const int64_t b1 = std::min<int64_t>(nblk, b0 + (sh.hi - it));
+        it += b1 - b0;
+        const int g0 = PM_G * g;
+        const double* __restrict__ T = s.T;
+        const double* __restrict__ mu = cur_mu(s, c);
+        const double* __restrict__ inv = s.inv64;  // 1/(sqrt(m) sigma), 0 for a flat window
+        const bool single = m <= PM_KC;
+        bool have_meta = false, loaded = false, any = false;
+        double best[4];
+        long long bj[4];
+        unsigned int evb = 0;
+        int64_t ci[4];
+        double sxv[4], ivi[4];
+        __syncthreads();
+        float lb = -8.0f;  // lower bound of candidate tid % 16
+        if (screened) {
+            // the lower bounds the screening's workgroups left
+            const int64_t nch = screen_chunks(N);
+            const int64_t firsts = B == 1 ? 0 : ipfx_s[b];
+            const int64_t tots = B == 1 ? items_of(s, full, true) : ipfx_s[B];
+            const int64_t pers = (tots + screen_grid - 1) / screen_grid;
+            const int64_t w0 = firsts / pers;
+            const int64_t e0 = (firsts + g * nch) / pers - w0 + g;
+            const int64_t e1 = (firsts + (g + 1) * nch - 1) / pers - w0 + g;
+            for (int64_t e = e0 + (tid >> 4); e <= e1; e += EX_WAVES * 4)
+                lb = fmaxf(lb, s.lbp[e * PM_G + (tid & 15)]);
+            lbs[tid >> 4][tid & 15] = lb;
+            __syncthreads();
+            for (int q = 0; q < EX_WAVES * 4; ++q) lb = fmaxf(lb, lbs[q][tid & 15]);
+        }
+        for (int64_t bb = b0; bb < b1; bb += EX_WAVES * 4) {
+            // sixteen blocks at a time: which of them hold a column that counts
+            {
+                const int64_t q = bb + (tid >> 4);
+                const int cid = tid & 15;
+                bool mk = q < b1 && g0 + cid < ncand;
+                if (mk && screened) mk = s.ub[((int64_t)g * nblk + q) * PM_G + cid] >= lb;
+                const unsigned long long bal = __ballot(mk);
+                __syncthreads();
+                if (lane == 0) mark_s[w] = bal;
+                __syncthreads();
+            }
+            for (int e = 0; e < EX_WAVES * 4; ++e) {
+                if (((mark_s[e >> 2] >> (16 * (e & 3))) & 0xffffull) == 0ull) continue;
+                const int64_t blk = bb + e;
+                if (!have_meta) {
+                    // candidates' indices, spreads and sums of centred values
+                    for (int gq = w; gq < PM_G; gq += EX_WAVES) {
+                        const int64_t i = s.cand[min(g0 + gq, ncand - 1)];
+                        const double mi = mu[i];
+                        double sx = 0.0;
+                        for (int k = lane; k < m; k += 64) sx += T[i + k] - mi;
+                        sx = wave_sum(sx);
+                        if (lane == 0) {
+                            cidx[gq] = i;
+                            sxs[gq] = sx;
+                            civ[gq] = inv[i];
+                        }
+                    }
+                    __syncthreads();
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        ci[r] = cidx[ka + 4 * r];
+                        sxv[r] = sxs[ka + 4 * r];
+                        ivi[r] = civ[ka + 4 * r];
+                        best[r] = -f_inf<double>();
+                        bj[r] = 0x7fffffffffffffffll;
+                    }
+                    have_meta = true;
+                }
+                any = true;
+                const int64_t j0 = blk * EX_COLS;
+                const int colbase = w * (EX_COLS / EX_WAVES);
+                pm_acc_t acc[EX_CT];
+#pragma unroll
+                for (int ct = 0; ct < EX_CT; ++ct) acc[ct] = (pm_acc_t){0.0, 0.0, 0.0, 0.0};
+                for (int kb = 0; kb < m; kb += PM_KC) {
+                    const int kn = min(PM_KC, m - kb);
+                    __syncthreads();  // the previous chunk and block are consumed
+                    if (kb == 0) lds_fill(ts, T + j0, EX_COLS + m + 4);
+                    if (!single || !loaded) {
+                        for (int gq = w; gq < PM_G; gq += EX_WAVES) {
+                            const int64_t i = cidx[gq];
+                            const double mi = mu[i];
+#pragma unroll
+                            for (int q = 0; q < PM_KC / 64; ++q) {
+                                const int k = lane + 64 * q;
+                                xg[gq * PM_XS + k] = k < kn ? T[i + kb + k] - mi : 0.0;
+                            }
+                        }
+                        loaded = true;
+                    }
+                    __syncthreads();
+                    const double* xp = xg + ca * PM_XS + ka;
+                    const double* tb = ts + colbase + kb + ka + ca;
+                    for (int k4 = 0; k4 < kn; k4 += 4) {
+                        const double av = xp[k4];
+#pragma unroll
+                        for (int ct = 0; ct < EX_CT; ++ct)
+                            acc[ct] = __builtin_amdgcn_mfma_f64_16x16x4f64(av, tb[k4 + 16 * ct],
+                                                                           acc[ct], 0, 0, 0);
+                    }
+                }
+                // epilogue: lane holds D[ka + 4 r][16 ct + ca]; rho = C inv_i inv_j
+#pragma unroll
+                for (int ct = 0; ct < EX_CT; ++ct) {
+                    const int64_t j = j0 + colbase + 16 * ct + ca;
+                    if (j >= N) continue;
+                    const double ivj = inv[j], muj = mu[j];
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        if (j <= ci[r] - m || j >= ci[r] + m) {
+                            double rh;
+                            if (ivi[r] == 0.0 || ivj == 0.0) {  // a flat window (R11)
+                                rh = (ivi[r] == 0.0 && ivj == 0.0) ? 1.0 : 0.0;
+                            } else {
+                                const double Cv = acc[ct][r] - muj * sxv[r];
+                                rh = fmin(1.0, fmax(-1.0, Cv * ivi[r] * ivj));
+                            }
+                            if (rh > best[r]) {  // a lane's columns ascend with ct and with the block
+                                best[r] = rh;
+                                bj[r] = j;
+                            }
+                            if (g0 + ka + 4 * r < ncand) ++evb;
+                        }
+                    }
+                }
+            }
+        }
+        if (!any) continue;  // (uniform over the workgroup)
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
 #pragma unroll
@@ -2144,171 +3101,93 @@ __global__ __launch_bounds__(64 * PM_WAVES) void k_polish(SeriesDev* S, int B,
                 red_j[w][ka + 4 * r] = bj[r];
             }
         }
+        if (tid == 0) slot_s = atomicAdd(&c->pcnt[g], 1u);
         __syncthreads();
-        if (tid < PM_G && g0 + tid < ncand) {
+        if (tid < PM_G) {
             double bv = red_v[0][tid];
             long long bjj = red_j[0][tid];
-            for (int q = 1; q < PM_WAVES; ++q)
+            for (int q = 1; q < EX_WAVES; ++q)
                 if (red_v[q][tid] > bv || (red_v[q][tid] == bv && red_j[q][tid] < bjj)) {
                     bv = red_v[q][tid];
                     bjj = red_j[q][tid];
                 }
-            const int64_t slot = ((int64_t)(g0 + tid) * s.npart + cslot) * 2;
-            s.part[slot] = bv;
-            s.part[slot + 1] = (double)bjj;
+            const int64_t p = ((part_base(sh.per, first, nblk, g) + slot_s) * PM_G + tid) * 2;
+            s.part[p] = bv;
+            s.part[p + 1] = (double)bjj;
         }
         const unsigned long long e = (unsigned long long)wave_sum((double)evb);
         if (lane == 0 && e)
-            atomicAdd(&s.evc[EV_POL * EV_SLOTS + ((blockIdx.x + blockIdx.y + w) & (EV_SLOTS - 1))], e);
-        __syncthreads();  // red_v / red_j are free again
-        cur = -1;
-    };
-    for (int64_t fb = blockIdx.x; fb < nblocks; fb += gridDim.x) {
-        const int b = series_of(pfx, B, fb);
-        if (cur >= 0 && b != cur) flush();
-        const SeriesDev& s = S[b];
-        Ctrl* c = s.ctrl;
-        if (!c->active) continue;
-        const int ncand = (int)c->ncand;
-        if (g0 >= ncand) continue;
-        const int32_t m = c->m;
-        const int64_t N = s.n - m + 1;
-        const double* __restrict__ mu = cur_mu(s, c);
-        const double* __restrict__ inv = s.inv64;  // 1/(sqrt(m) sigma), 0 for a flat window
-        const int64_t blk = fb - pfx[b];
-        if (cur < 0) {
-            cur = b;
-            cslot = blk;
-            evb = 0;
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                best[r] = -f_inf<double>();
-                bj[r] = 0x7fffffffffffffffll;
-            }
-        }
-        const int64_t j0 = blk * POLISH_COLS;
-        const int64_t stride = (int64_t)s.maxL + 8;
-        const double* __restrict__ xc = s.xc;
-        pm_acc_t acc[PM_CT];
-#pragma unroll
-        for (int ct = 0; ct < PM_CT; ++ct) acc[ct] = (pm_acc_t){0.0, 0.0, 0.0, 0.0};
-        const bool single = m <= PM_KC;
-        for (int kb = 0; kb < m; kb += PM_KC) {
-            const int kn = min(PM_KC, m - kb);
-            __syncthreads();  // the previous chunk and block are consumed
-            if (kb == 0) lds_fill(ts, s.T + j0, POLISH_COLS + m + 4);
-            if (!single || loaded != b) {
-                // eight loads in flight per thread before their stores
-                for (int e0 = 0; e0 < PM_G * PM_KC; e0 += 8 * 64 * PM_WAVES) {
-                    double v[8];
-#pragma unroll
-                    for (int u = 0; u < 8; ++u) {
-                        const int e = e0 + tid + 64 * PM_WAVES * u;
-                        const int g = e / PM_KC, k = e - g * PM_KC;
-                        const int cid = min(g0 + g, ncand - 1);
-                        v[u] = k < kn ? xc[cid * stride + kb + k] : 0.0;  // zero past m
-                    }
-#pragma unroll
-                    for (int u = 0; u < 8; ++u) {
-                        const int e = e0 + tid + 64 * PM_WAVES * u;
-                        const int g = e / PM_KC, k = e - g * PM_KC;
-                        xg[g * PM_XS + k] = v[u];
-                    }
-                }
-                loaded = single ? b : -1;
-            }
-            __syncthreads();
-            const double* xa = xg + ca * PM_XS + ka;
-            const double* tb = ts + colbase + kb + ka + ca;
-            for (int k4 = 0; k4 < kn; k4 += 4) {
-                const double av = xa[k4];
-#pragma unroll
-                for (int ct = 0; ct < PM_CT; ++ct)
-                    acc[ct] = __builtin_amdgcn_mfma_f64_16x16x4f64(av, tb[k4 + 16 * ct], acc[ct], 0, 0, 0);
-            }
-        }
-        // epilogue: lane holds D[ka + 4 r][16 ct + ca]; rho = C inv_i inv_j
-        const double* __restrict__ sxs = xc + KP_MAX * stride;
-        int64_t ci[4];
-        double sxv[4], ivi[4];
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int cid = min(g0 + ka + 4 * r, ncand - 1);
-            ci[r] = s.cand[cid];
-            sxv[r] = sxs[cid];
-            ivi[r] = inv[ci[r]];
-        }
-#pragma unroll
-        for (int ct = 0; ct < PM_CT; ++ct) {
-            const int64_t j = j0 + colbase + 16 * ct + ca;
-            if (j >= N) continue;
-            const double ivj = inv[j], muj = mu[j];
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                if (j <= ci[r] - m || j >= ci[r] + m) {
-                    double rh;
-                    if (ivi[r] == 0.0 || ivj == 0.0) {  // a flat window (R11)
-                        rh = (ivi[r] == 0.0 && ivj == 0.0) ? 1.0 : 0.0;
-                    } else {
-                        const double Cv = acc[ct][r] - muj * sxv[r];
-                        rh = fmin(1.0, fmax(-1.0, Cv * ivi[r] * ivj));
-                    }
-                    if (rh > best[r]) {  // a lane's columns ascend with ct and with the block
-                        best[r] = rh;
-                        bj[r] = j;
-                    }
-                    if (g0 + ka + 4 * r < ncand) ++evb;
-                }
-            }
-        }
+            atomicAdd(&s.evc[EV_POL * EV_SLOTS + ((blockIdx.x + w) & (EV_SLOTS - 1))], e);
     }
-    if (cur >= 0) flush();
 }
 
-// Close the round of every series (one block each): reduce the polish
-// partials to each candidate's exact (rho, j), rank the candidates, write the
-// length's top-k rows when the round found at least k range discords, and
-// lower MERLIN's r otherwise; count the series with work left in rem[0].
+// Close the round of every series (one block each): reduce the exact pass's
+// partials to each candidate's (rho, j), rank the candidates, write the
+// length's top-k rows when the round found at least k range discords, lower
+// MERLIN's r otherwise, and set up the series' next range search.  A round
+// without sweeps (full = 0) that turned out to need them is left pending.
 constexpr int END_BLOCK = 1024;
 __global__ __launch_bounds__(END_BLOCK) void k_round_end(SeriesDev* S, int32_t* rem, int hot_rows,
-                                                          int npol)
+                                                          int full, int more, float guard,
+                                                          int max_attempts, int B,
+                                                          const int64_t* __restrict__ ipfx_e)
 {
-    __shared__ double nn_s[KP_MAX];
-    __shared__ long long id_s[KP_MAX];
-    __shared__ long long jj_s[KP_MAX];
+    __shared__ double nn_s[CAND_MAX];
+    __shared__ long long id_s[CAND_MAX];
+    __shared__ long long jj_s[CAND_MAX];
+    __shared__ int valid_s[CAND_MAX];  // the valid candidates, nvalid_s of them
+    __shared__ unsigned int nvalid_s;
     const SeriesDev& s = S[blockIdx.x];
     Ctrl* c = s.ctrl;
-    if (!c->active) return;
-    __shared__ int valid_s[KP_MAX];
-    __shared__ unsigned int nvalid_s;
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    if (!c->active) {
+        if (tid == 0 && c->error) atomicAdd(&rem[REM_ERROR], 1);  // stays visible in later rounds
+        return;
+    }
+    const bool lean = lean_round(c);
+    if (!full && !lean) {
+        if (tid == 0) {
+            c->pending = 1;
+            atomicAdd(&rem[REM_LEFT], 1);
+            atomicAdd(&rem[REM_PENDING], 1);
+            if (c->li == 0) atomicAdd(&rem[REM_FIRST], 1);
+        }
+        return;
+    }
     const int k = s.k;
     const int32_t m = c->m;
     const int li = c->li;
-    const int kp = (int)c->ncand;
+    const int kp = lean ? (int)c->nlive : (int)c->ncand;
     const bool direct = direct_round(c);
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    if (tid == 0) nvalid_s = 0;
+    __syncthreads();
     if (kp >= k) {
         // tpc threads per candidate (all candidates at once, tpc as large as
         // the block allows, at most a wave): strided partials loaded eight at
         // a time before they are compared (they come from other XCDs' caches,
         // so each batch costs a full memory latency), then a reduction over
-        // the tpc threads.  k_polish's npol workgroups left one partial each
-        // in the slots below min(blocks of this length, npol).
-        const int64_t npart = s.npart;
-        const int64_t nblk = std::min<int64_t>((s.n - m + 1 + POLISH_COLS - 1) / POLISH_COLS, npol);
+        // the tpc threads.
         int tpc = 64;
         while (tpc > 1 && tpc * kp > END_BLOCK) tpc >>= 1;
         const int sub = tid & (tpc - 1);
+        const int64_t nblk = exact_blocks(s.n - m + 1);
+        const int64_t first = B == 1 ? 0 : ipfx_e[blockIdx.x];
+        const int64_t total =
+            B == 1 ? (int64_t)((kp + CAND_GROUP - 1) / CAND_GROUP) * nblk : ipfx_e[B];
+        const int64_t per = (total + EXACT_GRID - 1) / EXACT_GRID;
         for (int cid = tid / tpc; cid < kp; cid += END_BLOCK / tpc) {
             double best = -f_inf<double>(), bj = 1e300;
-            const double* pc = s.part + (int64_t)cid * npart * 2;
-            for (int64_t p0 = sub; p0 < nblk; p0 += 8 * (int64_t)tpc) {
+            const int g = cid / CAND_GROUP;
+            const int np = (int)c->pcnt[g];
+            const double* pc =
+                s.part + (part_base(per, first, nblk, g) * CAND_GROUP + cid % CAND_GROUP) * 2;
+            for (int p0 = sub; p0 < np; p0 += 8 * tpc) {
                 double v[8], jj[8];
 #pragma unroll
                 for (int u = 0; u < 8; ++u) {
-                    const int64_t p = p0 + (int64_t)u * tpc;
-                    v[u] = p < nblk ? pc[p * 2] : -f_inf<double>();
-                    jj[u] = p < nblk ? pc[p * 2 + 1] : 1e300;
+                    const int64_t p = p0 + u * tpc;
+                    v[u] = p < np ? pc[p * 2 * CAND_GROUP] : -f_inf<double>();
+                    jj[u] = p < np ? pc[p * 2 * CAND_GROUP + 1] : 1e300;
                 }
 #pragma unroll
                 for (int u = 0; u < 8; ++u)
@@ -2328,9 +3207,10 @@ __global__ __launch_bounds__(END_BLOCK) void k_round_end(SeriesDev* S, int32_t* 
             if (sub == 0) {
                 const double d2 = 2.0 * (double)m * (1.0 - best);
                 const long long i = s.cand[cid];
+                const long long j = bj < 1e299 ? (long long)bj : -1;  // every candidate has a neighbour
                 nn_s[cid] = sqrt(fmin(4.0 * (double)m, fmax(0.0, d2)));
                 id_s[cid] = i;
-                jj_s[cid] = (long long)bj;
+                jj_s[cid] = j;
                 // a direct round decides here which live subsequences are range
                 // discords (distance >= r, i.e. rho <= thr64), as refinement would
                 int ok_i = 1;
@@ -2338,67 +3218,60 @@ __global__ __launch_bounds__(END_BLOCK) void k_round_end(SeriesDev* S, int32_t* 
                     ok_i = !(c->prune && best > c->thr64);
                     if (ok_i) s.rho[i] = ord_of(best);
                     else atomicAnd(&s.alive[i >> 6], ~(1ull << (i & 63)));
+                    if (s.heat && ok_i)
+                        s.heat[(int64_t)li * s.heat_ld + i] = fmin(2.0, fmax(0.0, 1.0 - best));
                 }
-                valid_s[cid] = ok_i;
+                if (ok_i) valid_s[atomicAdd(&nvalid_s, 1u)] = cid;
+                if (more && j >= 0) {  // the nearest neighbour is the best witness
+                    const double ii = s.inv64[i], ij = s.inv64[j];
+                    s.wit[i] = (int32_t)j;
+                    s.wc[i] = ii > 0.0 && ij > 0.0 ? best / (ii * ij) : 0.0;
+                }
             }
         }
     }
-    if (s.heat) __threadfence();  // the direct round's bitmap and rho updates, read below
     __syncthreads();
-    if (tid == 0) {
-        unsigned int nv = 0;
-        for (int q = 0; q < kp; ++q) nv += (unsigned int)valid_s[q];
-        nvalid_s = nv;
-    }
-    __syncthreads();
-    const unsigned int ns = direct ? (kp >= k ? nvalid_s : (unsigned int)kp) : c->nsurv;
+    const unsigned int ns = direct ? (kp >= k ? nvalid_s : (lean ? c->nlive : c->nsurv)) : c->nsurv;
     // the candidates could not be narrowed to KP_MAX: same r again, with both
     // sides of every tile refined exactly
-    const bool redo = c->band_over != 0;
+    const bool redo = !lean && c->band_over != 0;
     const bool ok = ns >= (unsigned int)k && kp >= k && !redo;
-    if (ok && tid < kp && valid_s[tid]) {
+    const int nv = kp >= k ? (int)nvalid_s : 0;
+    if (ok && tid < nv) {
+        const int t = valid_s[tid];
         int rank = 0;
-        for (int q = 0; q < kp; ++q)
-            if (valid_s[q] &&
-                (nn_s[q] > nn_s[tid] || (nn_s[q] == nn_s[tid] && id_s[q] < id_s[tid])))
-                ++rank;
+        for (int e = 0; e < nv; ++e) {
+            const int q = valid_s[e];
+            if (nn_s[q] > nn_s[t] || (nn_s[q] == nn_s[t] && id_s[q] < id_s[t])) ++rank;
+        }
         if (rank < k) {
             const int64_t row = (int64_t)li * k + rank;
             if (s.idx) {
-                s.idx[row] = id_s[tid];
+                s.idx[row] = id_s[t];
                 s.len[row] = m;
-                s.nn[row] = nn_s[tid];
-                s.nnidx[row] = jj_s[tid];
+                s.nn[row] = nn_s[t];
+                s.nnidx[row] = jj_s[t];
             }
-            if (rank == k - 1) s.hist[li] = nn_s[tid];
+            if (rank == k - 1) s.hist[li] = nn_s[t];
         }
     }
     __syncthreads();
-    if (ok && s.heat) {
-        // the discord heatmap row of this length (Eq. (11)): every range
-        // discord (the alive bits) with its exact nearest-neighbour
-        // correlation, as ED^2 / (2m) = 1 - rho; 0 elsewhere
-        const int64_t N = s.n - m + 1;
-        double* hrow = s.heat + (int64_t)li * s.heat_ld;
-        for (int64_t i = tid; i < s.heat_ld; i += END_BLOCK) {
-            double v = 0.0;
-            if (i < N && ((load_word(&s.alive[i >> 6]) >> (i & 63)) & 1ull)) {
-                const double rh =
-                    dbl_of(__hip_atomic_load(&s.rho[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-                v = fmin(2.0, fmax(0.0, 1.0 - rh));
-            }
-            hrow[i] = v;
-        }
-        if (tid == 0) s.rlen[li] = c->r;
-    }
     if (tid == 0) {
         c->rounds += 1;
         c->nsurv = ns;
+        if (lean) {
+            c->rows_near += c->nlive;
+            c->rows_far += c->nlive;
+        }
         c->exact_ref = redo ? 1 : 0;
+        c->pending = 0;
+        // (a heatmap row of a round that refined: the bitmap's rows, by k_heat)
+        c->heat_m = ok && !direct ? m : 0;
         if (ok) {
             c->done = 1;
             c->survivors += ns;
             if (s.count) s.count[li] = (int32_t)ns;
+            if (s.rlen) s.rlen[li] = c->r;
         } else if (!redo) {
             c->done = 0;
             if (c->mode == 0) c->r *= 0.5;
@@ -2407,53 +3280,71 @@ __global__ __launch_bounds__(END_BLOCK) void k_round_end(SeriesDev* S, int32_t* 
         } else {
             c->done = 0;
         }
-        if (!(c->done && c->m >= s.maxL)) atomicAdd(&rem[0], 1);
     }
-    // Hot tiles of hot_rows rows, in ascending order (the first HOT_MAX of
-    // them): those that still hold survivors or whose first-pass items swept
-    // at least N / HOT_FRAC columns this round.  The next round's first
-    // selection pass dispatches all their chunks before any other tile's, so
-    // that the longest work items of the pass start first.  The per-tile
-    // work counters restart.
-    __shared__ unsigned int wcnt_s[END_BLOCK / 64];
-    __shared__ unsigned int base_s;
-    // (the bitmap atomics of this block completed before the barrier; the
-    // scan reads the bitmap with agent-scope loads)
-    __syncthreads();
-    if (tid == 0) base_s = 0;
-    const int64_t ntl = (s.n - m + 1 + hot_rows - 1) / hot_rows;
-    const int wpt = hot_rows / 64;
-    const uint32_t hot_work = (uint32_t)((s.n - m + 1 + 64 * HOT_FRAC - 1) / (64 * HOT_FRAC));
-    for (int64_t t0 = 0; t0 < ntl; t0 += END_BLOCK) {
+    if (full && !lean) {
+        // Hot tiles of hot_rows rows, in ascending order (the first HOT_MAX of
+        // them): those that still hold survivors or whose first-pass items swept
+        // at least N / HOT_FRAC columns this round.  The next sweep's first
+        // selection pass dispatches all their chunks before any other tile's, so
+        // that the longest work items of the pass start first.  The per-tile
+        // work counters restart.
+        __shared__ unsigned int wcnt_s[END_BLOCK / 64];
+        __shared__ unsigned int base_s;
+        // (the bitmap atomics of this block completed before the barrier; the
+        // scan reads the bitmap with agent-scope loads)
         __syncthreads();
-        const unsigned int base = base_s;
-        const int64_t t = t0 + tid;
-        bool hot = false;
-        if (t < ntl) {
-            unsigned long long any = 0ull;
-            for (int w2 = 0; w2 < wpt; ++w2) any |= load_word(&s.alive[t * wpt + w2]);
-            hot = any != 0ull || s.twork[t] >= hot_work;
-            s.twork[t] = 0u;
+        if (tid == 0) base_s = 0;
+        const int64_t ntl = (s.n - m + 1 + hot_rows - 1) / hot_rows;
+        const int wpt = hot_rows / 64;
+        const uint32_t hot_work = (uint32_t)((s.n - m + 1 + 64 * HOT_FRAC - 1) / (64 * HOT_FRAC));
+        for (int64_t t0 = 0; t0 < ntl; t0 += END_BLOCK) {
+            __syncthreads();
+            const unsigned int base = base_s;
+            const int64_t t = t0 + tid;
+            bool hot = false;
+            if (t < ntl) {
+                unsigned long long any = 0ull;
+                for (int w2 = 0; w2 < wpt; ++w2) any |= load_word(&s.alive[t * wpt + w2]);
+                hot = any != 0ull || s.twork[t] >= hot_work;
+                s.twork[t] = 0u;
+            }
+            const unsigned long long bal = __ballot(hot);
+            if (lane == 0) wcnt_s[w] = (unsigned int)__popcll(bal);
+            __syncthreads();
+            unsigned int before = 0, total = 0;
+            for (int q = 0; q < END_BLOCK / 64; ++q) {
+                before += (q < w) ? wcnt_s[q] : 0u;
+                total += wcnt_s[q];
+            }
+            const unsigned int pos =
+                base + before + (unsigned int)__popcll(bal & ((1ull << lane) - 1ull));
+            if (hot && pos < (unsigned int)HOT_MAX) s.hot[pos] = (int32_t)t;
+            __syncthreads();
+            if (tid == 0) base_s = base + total;
         }
-        const unsigned long long bal = __ballot(hot);
-        if (lane == 0) wcnt_s[w] = (unsigned int)__popcll(bal);
         __syncthreads();
-        unsigned int before = 0, total = 0;
-        for (int q = 0; q < END_BLOCK / 64; ++q) {
-            before += (q < w) ? wcnt_s[q] : 0u;
-            total += wcnt_s[q];
+        if (tid == 0) {
+            c->nhot = base_s < (unsigned int)HOT_MAX ? base_s : (unsigned int)HOT_MAX;
+            c->hot_r = hot_rows;
         }
-        const unsigned int pos =
-            base + before + (unsigned int)__popcll(bal & ((1ull << lane) - 1ull));
-        if (hot && pos < (unsigned int)HOT_MAX) s.hot[pos] = (int32_t)t;
-        __syncthreads();
-        if (tid == 0) base_s = base + total;
     }
-    __syncthreads();
-    if (tid == 0) {
-        c->nhot = base_s < (unsigned int)HOT_MAX ? base_s : (unsigned int)HOT_MAX;
-        c->hot_r = hot_rows;
-    }
+    if (more && tid == 0) next_range(s, c, guard, max_attempts, rem);
+}
+
+// The heatmap row (Eq. (11)) of a successful round that refined: every range
+// discord (the alive bits) with its exact nearest-neighbour correlation, as
+// ED^2 / (2m) = 1 - rho; k_advance cleared the row.  (Launched after
+// k_round_end: the control block already holds the next range search.)
+__global__ void k_heat(SeriesDev* S, int B, const int64_t* __restrict__ pfx)
+{
+    const int b = series_of(pfx, B, blockIdx.x);
+    const SeriesDev& s = S[b];
+    const int32_t m = s.ctrl->heat_m;
+    if (s.heat == nullptr || m == 0) return;
+    const int64_t i = (blockIdx.x - pfx[b]) * (int64_t)ADV_BLOCK + threadIdx.x;
+    if (i >= s.n - m + 1) return;
+    if (!((s.alive[i >> 6] >> (i & 63)) & 1ull)) return;
+    s.heat[(int64_t)(m - s.minL) * s.heat_ld + i] = fmin(2.0, fmax(0.0, 1.0 - dbl_of(s.rho[i])));
 }
 
 // ---------------------------------------------------------------------------
@@ -2659,9 +3550,11 @@ __global__ void k_stream_query(SeriesDev* S, const unsigned long long* __restric
         c->exact_ref = 0;
         c->band_over = 0;
         c->live_ref = 0xffffffffu;  // not a direct round
+        c->nlive = 0xffffffffu;
         c->nsurv = c->ncand = 0;
         c->done = 0;
     }
+    if (blockIdx.x == 0 && threadIdx.x < CAND_GROUPS) c->pcnt[threadIdx.x] = 0;
 }
 
 // The exact profile of the current length as distances (Eq. (6)):
@@ -2691,42 +3584,42 @@ __global__ void k_fill_u64(unsigned long long* p, int64_t count, unsigned long l
 // ---------------------------------------------------------------------------
 // launchers
 // ---------------------------------------------------------------------------
-template <typename F, int Q>
+template <typename F, int Q, bool WIT>
 static void launch_near(const Batch& bt, const SweepCfg& cfg, const int64_t* total, hipStream_t st)
 {
     const size_t lds = sizeof(double) * sweep_lds_doubles(bt.maxL_all, 64 * Q, (int)sizeof(F), false);
     if (total[PFX_NEAR] == 0) return;
     cfg.timer->begin(0, st);
-    hipLaunchKernelGGL((k_select_near<F, Q>), dim3((unsigned int)total[PFX_NEAR]), dim3(64), lds,
+    hipLaunchKernelGGL((k_select_near<F, Q, WIT>), dim3((unsigned int)total[PFX_NEAR]), dim3(64), lds,
                        st, bt.s, bt.B, bt.pfx[PFX_NEAR], cfg.near_cols, cfg.chunk_cols);
     cfg.timer->end(0, st);
 }
 
-template <typename F, int Q>
+template <typename F, int Q, bool WIT>
 static void launch_far(const Batch& bt, const SweepCfg& cfg, const int64_t* total, hipStream_t st)
 {
     const size_t lds = sizeof(double) * sweep_lds_doubles(bt.maxL_all, 64 * Q, (int)sizeof(F), false);
     hipLaunchKernelGGL(k_tiles, dim3((unsigned int)total[PFX_TSEL]), dim3(TILES_BLOCK), 0, st, bt.s, bt.B,
                        bt.pfx[PFX_TSEL], 64 * Q, 0, cfg.near_cols, cfg.chunk_cols, 64 * cfg.q_near);
     cfg.timer->begin(1, st);
-    hipLaunchKernelGGL((k_select_far<F, Q>), dim3(cfg.far_grid), dim3(64), lds, st, bt.s, bt.B,
+    hipLaunchKernelGGL((k_select_far<F, Q, WIT>), dim3(cfg.far_grid), dim3(64), lds, st, bt.s, bt.B,
                        cfg.near_cols, cfg.chunk_cols, 64 * cfg.q_near);
     cfg.timer->end(1, st);
 }
 
-template <int Q>
+template <int Q, bool WIT>
 static void launch_refine(const Batch& bt, const SweepCfg& cfg, const int64_t* total, hipStream_t st)
 {
     hipLaunchKernelGGL(k_tiles, dim3((unsigned int)total[PFX_TREF]), dim3(TILES_BLOCK), 0, st, bt.s, bt.B,
                        bt.pfx[PFX_TREF], 64 * Q, 1, 0, cfg.chunk_cols, 64 * cfg.q_near);
     const size_t lds = sizeof(double) * sweep_lds_doubles(bt.maxL_all, 64 * Q, (int)sizeof(double), true);
     cfg.timer->begin(2, st);
-    hipLaunchKernelGGL((k_refine<Q>), dim3(cfg.far_grid), dim3(64), lds, st, bt.s, bt.B,
+    hipLaunchKernelGGL((k_refine<Q, WIT>), dim3(cfg.far_grid), dim3(64), lds, st, bt.s, bt.B,
                        cfg.chunk_cols);
     cfg.timer->end(2, st);
 }
 
-template <typename F>
+template <typename F, bool WIT>
 static void launch_select(const Batch& bt, const SweepCfg& cfg, const int64_t* total,
                           hipStream_t st)
 {
@@ -2737,49 +3630,92 @@ static void launch_select(const Batch& bt, const SweepCfg& cfg, const int64_t* t
         cfg.timer->end(5, st);
     }
     switch (cfg.q_near) {
-    case 2: launch_near<F, 2>(bt, cfg, total, st); break;
-    case 4: launch_near<F, 4>(bt, cfg, total, st); break;
-    default: launch_near<F, 8>(bt, cfg, total, st); break;
+    case 2: launch_near<F, 2, WIT>(bt, cfg, total, st); break;
+    case 4: launch_near<F, 4, WIT>(bt, cfg, total, st); break;
+    default: launch_near<F, 8, WIT>(bt, cfg, total, st); break;
     }
     if ((int64_t)cfg.near_cols >= bt.Nmax_all) {
         // the first pass already covers every column of every series
         return;
     }
     switch (cfg.q_far) {
-    case 2: launch_far<F, 2>(bt, cfg, total, st); break;
-    case 4: launch_far<F, 4>(bt, cfg, total, st); break;
-    default: launch_far<F, 8>(bt, cfg, total, st); break;
+    case 2: launch_far<F, 2, WIT>(bt, cfg, total, st); break;
+    case 4: launch_far<F, 4, WIT>(bt, cfg, total, st); break;
+    default: launch_far<F, 8, WIT>(bt, cfg, total, st); break;
     }
+}
+
+template <bool WIT>
+static void launch_refine_q(const Batch& bt, const SweepCfg& cfg, const int64_t* total, hipStream_t st)
+{
+    switch (cfg.q_ref) {
+    case 4: launch_refine<4, WIT>(bt, cfg, total, st); break;
+    case 8: launch_refine<8, WIT>(bt, cfg, total, st); break;
+    default: launch_refine<2, WIT>(bt, cfg, total, st); break;
+    }
+}
+
+// The exact pass over the rounds' candidates.  Up to SCREEN_MIN subsequences
+// a launch of the screening costs more than the blocks it saves.
+static void launch_exact(const Batch& bt, const SweepCfg& cfg, int full, hipStream_t st)
+{
+    cfg.timer->begin(3, st);
+    if (bt.B > 1)
+        hipLaunchKernelGGL(k_items, dim3(1), dim3(ITEMS_BLOCK), 0, st, bt.s, bt.B, full, bt.ipfx,
+                           bt.ipfx + bt.B + 1);
+    const bool screened = bt.Nmax_all > SCREEN_MIN;
+    if (screened)
+        hipLaunchKernelGGL(k_screen, dim3(SCREEN_GRID), dim3(64 * SC_WAVES), 0, st, bt.s, bt.B, full,
+                           bt.ipfx);
+    const size_t lds = sizeof(double) * (size_t)(PM_G * PM_XS + EX_COLS + bt.maxL_all + 4);
+    hipLaunchKernelGGL(k_exact, dim3(EXACT_GRID), dim3(64 * EX_WAVES), lds, st, bt.s, bt.B, full,
+                       screened ? 1 : 0, SCREEN_GRID, bt.ipfx, bt.ipfx + bt.B + 1);
+    cfg.timer->end(3, st);
+}
+
+hipError_t launch_start(const Batch& bt, const SweepCfg& cfg, hipStream_t st)
+{
+    hipLaunchKernelGGL(k_start, dim3(1), dim3(256), 0, st, bt.s, bt.B, cfg.guard, cfg.max_attempts,
+                       bt.remaining);
+    return hipGetLastError();
 }
 
 // One round: every series with work does one range search at its current
 // length (a fixed launch sequence; all parameters come from the device).
-hipError_t launch_round(const Batch& bt, const SweepCfg& cfg, const int64_t* total, hipStream_t st)
+// Without `full` the sweeps are left out: a series that needs them waits for
+// the next full round.  more = 0: a bare range search.
+hipError_t launch_round(const Batch& bt, const SweepCfg& cfg, const int64_t* total, bool full,
+                        bool more, hipStream_t st)
 {
     const unsigned int elem = (unsigned int)total[PFX_ELEM];
-    hipLaunchKernelGGL(k_round_prep, dim3(1), dim3(256), 0, st, bt.s, bt.B, cfg.guard,
-                       cfg.max_attempts, bt.remaining);
     cfg.timer->begin(4, st);
-    hipLaunchKernelGGL(k_length, dim3(elem), dim3(256), 0, st, bt.s, bt.B, bt.pfx[PFX_ELEM]);
+    hipLaunchKernelGGL(k_advance, dim3(elem), dim3(ADV_BLOCK), 0, st, bt.s, bt.B, bt.pfx[PFX_ELEM],
+                       bt.remaining);
+    if (more)
+        hipLaunchKernelGGL(k_rescue, dim3(RESCUE_GRID), dim3(RESCUE_BLOCK), 0, st, bt.s, bt.B);
+    if (full)
+        hipLaunchKernelGGL(k_helpers, dim3(elem), dim3(ADV_BLOCK), 0, st, bt.s, bt.B,
+                           bt.pfx[PFX_ELEM]);
     cfg.timer->end(4, st);
-    hipLaunchKernelGGL(k_guard, dim3(bt.B), dim3(GUARD_BLOCK), 0, st, bt.s, cfg.guard);
-    if (cfg.dist_bits == 64) launch_select<double>(bt, cfg, total, st);
-    else launch_select<float>(bt, cfg, total, st);
-    switch (cfg.q_ref) {
-    case 4: launch_refine<4>(bt, cfg, total, st); break;
-    case 8: launch_refine<8>(bt, cfg, total, st); break;
-    default: launch_refine<2>(bt, cfg, total, st); break;
+    if (full) {
+        hipLaunchKernelGGL(k_guard, dim3(bt.B), dim3(GUARD_BLOCK), 0, st, bt.s, cfg.guard);
+        if (more) {
+            if (cfg.dist_bits == 64) launch_select<double, true>(bt, cfg, total, st);
+            else launch_select<float, true>(bt, cfg, total, st);
+            launch_refine_q<true>(bt, cfg, total, st);
+        } else {
+            if (cfg.dist_bits == 64) launch_select<double, false>(bt, cfg, total, st);
+            else launch_select<float, false>(bt, cfg, total, st);
+            launch_refine_q<false>(bt, cfg, total, st);
+        }
+        hipLaunchKernelGGL(k_select_top, dim3(bt.B), dim3(TOPK_BLOCK), 0, st, bt.s);
     }
-    hipLaunchKernelGGL(k_select_top, dim3(bt.B), dim3(TOPK_BLOCK), 0, st, bt.s);
-    const size_t lds = sizeof(double) * (size_t)(PM_G * PM_XS + POLISH_COLS + bt.maxL_all + 4);
-    cfg.timer->begin(3, st);
-    const int npol = (int)std::min<int64_t>(total[PFX_POLISH], PM_GRID);
-    hipLaunchKernelGGL(k_polish, dim3((unsigned int)npol, (KP_MAX + PM_G - 1) / PM_G),
-                       dim3(64 * PM_WAVES), lds, st, bt.s, bt.B, bt.pfx[PFX_POLISH],
-                       total[PFX_POLISH]);
-    cfg.timer->end(3, st);
+    launch_exact(bt, cfg, full ? 1 : 0, st);
     hipLaunchKernelGGL(k_round_end, dim3(bt.B), dim3(END_BLOCK), 0, st, bt.s, bt.remaining,
-                       64 * cfg.q_near, npol);
+                       64 * cfg.q_near, full ? 1 : 0, more ? 1 : 0, cfg.guard, cfg.max_attempts, bt.B,
+                       bt.ipfx + bt.B + 1);
+    if (full && bt.heat)
+        hipLaunchKernelGGL(k_heat, dim3(elem), dim3(ADV_BLOCK), 0, st, bt.s, bt.B, bt.pfx[PFX_ELEM]);
     return hipGetLastError();
 }
 
@@ -2831,22 +3767,19 @@ hipError_t launch_stream_update(const Batch& bt, const SweepCfg& cfg, const int6
     return hipGetLastError();
 }
 
-hipError_t launch_stream_query(const Batch& bt, const int64_t* total, int32_t minL, int32_t maxL,
-                               const unsigned long long* prof, int hot_rows, hipStream_t st)
+hipError_t launch_stream_query(const Batch& bt, const SweepCfg& cfg, const int64_t* total,
+                               int32_t minL, int32_t maxL, const unsigned long long* prof,
+                               hipStream_t st)
 {
-    const size_t lds = sizeof(double) * (size_t)(PM_G * PM_XS + POLISH_COLS + bt.maxL_all + 4);
-    const int npol = (int)std::min<int64_t>(total[PFX_POLISH], PM_GRID);
     for (int32_t m = minL; m <= maxL; ++m) {
         hipLaunchKernelGGL(k_set_len, dim3(1), dim3(1), 0, st, bt.s, m, m == minL ? 2 : 1);
         hipLaunchKernelGGL(k_length, dim3((unsigned int)total[PFX_ELEM]), dim3(256), 0, st, bt.s, 1,
                            bt.pfx[PFX_ELEM]);
         hipLaunchKernelGGL(k_stream_query, dim3(256), dim3(256), 0, st, bt.s, prof);
         hipLaunchKernelGGL(k_select_top, dim3(1), dim3(TOPK_BLOCK), 0, st, bt.s);
-        hipLaunchKernelGGL(k_polish, dim3((unsigned int)npol, (KP_MAX + PM_G - 1) / PM_G),
-                           dim3(64 * PM_WAVES), lds, st, bt.s, 1, bt.pfx[PFX_POLISH],
-                           total[PFX_POLISH]);
-        hipLaunchKernelGGL(k_round_end, dim3(1), dim3(END_BLOCK), 0, st, bt.s, bt.remaining, hot_rows,
-                           npol);
+        launch_exact(bt, cfg, 1, st);
+        hipLaunchKernelGGL(k_round_end, dim3(1), dim3(END_BLOCK), 0, st, bt.s, bt.remaining,
+                           64 * cfg.q_near, 1, 0, 0.0f, 0, 1, bt.ipfx + bt.B + 1);
     }
     return hipGetLastError();
 }
@@ -2887,6 +3820,7 @@ __global__ void k_set_len(SeriesDev* S, int32_t m, int32_t new_len)
     c->li = m - s.minL;
     c->new_len = new_len;
     c->active = 1;
+    c->nlive = 0x7fffffffu;
     if (new_len) {
         c->flat_min = 0x7fffffffffffffffll;
         c->flat_max = -1;
@@ -3118,7 +4052,10 @@ bool make_layout(int64_t n, int32_t minL, int32_t maxL, int32_t k, Layout* out)
     l.Npad = ((l.Nmax + 1 + R_MAX - 1) / R_MAX) * R_MAX + R_MAX;
     l.Tlen = l.Npad + maxL + 256;
     l.nwords = l.Npad / 64 + 1;
-    l.npart = (l.Nmax + POLISH_COLS - 1) / POLISH_COLS;
+    const int64_t nblk = (l.Nmax + EXACT_COLS - 1) / EXACT_COLS;
+    const int64_t nch = (l.Nmax + SCREEN_COLS - 1) / SCREEN_COLS;
+    l.pcap = std::min<int64_t>(EXACT_GRID, CAND_GROUPS * nblk) + 2 * CAND_GROUPS;
+    l.lbcap = std::min<int64_t>(SCREEN_GRID, CAND_GROUPS * nch) + 2 * CAND_GROUPS;
     const size_t hl = (size_t)(l.Npad + 64);
     size_t o = 0;
     l.off_T = o;     o = al256(o + sizeof(double) * (size_t)l.Tlen);
@@ -3127,18 +4064,24 @@ bool make_layout(int64_t n, int32_t minL, int32_t maxL, int32_t k, Layout* out)
     l.off_mu2 = o;   o = al256(o + sizeof(double) * hl);
     l.off_var2 = o;  o = al256(o + sizeof(double) * hl);
     l.off_h32 = o;   o = al256(o + 3 * al256(sizeof(float) * hl));
+    // inv64, df64, dg64, rho, rhs: the last four, contiguous, hold at least
+    // 32 Npad bytes and serve the screening's bounds outside a sweep (64 bytes
+    // per group and exact block: CAND_GROUPS / 2 bytes per row)
+    static_assert(CAND_GROUPS * CAND_GROUP * sizeof(float) <= 32 * EXACT_COLS, "bounds fit");
     l.off_h64 = o;   o = al256(o + 3 * al256(sizeof(double) * hl));
-    l.off_alive = o; o = al256(o + sizeof(unsigned long long) * (size_t)l.nwords);
     l.off_rho = o;   o = al256(o + sizeof(unsigned long long) * (size_t)l.Npad);
     l.off_rhs = o;   o = al256(o + sizeof(unsigned long long) * (size_t)l.Npad);
+    l.off_alive = o; o = al256(o + sizeof(unsigned long long) * (size_t)l.nwords);
     l.off_unc = o;   o = al256(o + sizeof(unsigned long long) * (size_t)l.nwords);
     l.off_tsel = o;  o = al256(o + sizeof(int32_t) * (size_t)(l.Npad / 64 + 1));
     l.off_tref = o;  o = al256(o + sizeof(int32_t) * (size_t)(l.Npad / 64 + 1));
     l.off_hot = o;   o = al256(o + sizeof(int32_t) * (size_t)HOT_MAX);
     l.off_twork = o; o = al256(o + sizeof(uint32_t) * (size_t)l.nwords);
-    l.off_cand = o;  o = al256(o + sizeof(int64_t) * (size_t)KP_MAX);
-    l.off_part = o;  o = al256(o + sizeof(double) * (size_t)(2 * KP_MAX * (l.npart + 1)));
-    l.off_xc = o;    o = al256(o + sizeof(double) * (size_t)KP_MAX * (size_t)(maxL + 9));
+    l.off_cand = o;  o = al256(o + sizeof(int64_t) * (size_t)CAND_MAX);
+    l.off_part = o;  o = al256(o + sizeof(double) * (size_t)(2 * CAND_GROUP) * (size_t)l.pcap);
+    l.off_lbp = o;   o = al256(o + sizeof(float) * (size_t)(CAND_GROUP * l.lbcap));
+    l.off_wit = o;   o = al256(o + sizeof(int32_t) * hl);
+    l.off_wc = o;    o = al256(o + sizeof(double) * hl);
     l.off_hist = o;  o = al256(o + sizeof(double) * (size_t)(l.L > 0 ? l.L : 1));
     l.off_evc = o;   o = al256(o + sizeof(unsigned long long) * EV_CLASSES * EV_SLOTS);
     l.off_ctrl = o;  o = al256(o + sizeof(Ctrl));
@@ -3159,7 +4102,7 @@ SeriesDev carve(void* base, const Layout& l)
     s.Npad = l.Npad;
     s.Tlen = l.Tlen;
     s.nwords = l.nwords;
-    s.npart = l.npart;
+    s.pcap = l.pcap;
     s.minL = l.minL;
     s.maxL = l.maxL;
     s.k = l.k;
@@ -3173,9 +4116,9 @@ SeriesDev carve(void* base, const Layout& l)
     s.df32 = (float*)(p + l.off_h32);
     s.dg32 = (float*)(p + l.off_h32 + al256(sizeof(float) * hl));
     s.inv32 = (float*)(p + l.off_h32 + 2 * al256(sizeof(float) * hl));
-    s.df64 = (double*)(p + l.off_h64);
-    s.dg64 = (double*)(p + l.off_h64 + al256(sizeof(double) * hl));
-    s.inv64 = (double*)(p + l.off_h64 + 2 * al256(sizeof(double) * hl));
+    s.inv64 = (double*)(p + l.off_h64);
+    s.df64 = (double*)(p + l.off_h64 + al256(sizeof(double) * hl));
+    s.dg64 = (double*)(p + l.off_h64 + 2 * al256(sizeof(double) * hl));
     s.alive = (unsigned long long*)(p + l.off_alive);
     s.rho = (unsigned long long*)(p + l.off_rho);
     s.rhs = (unsigned long long*)(p + l.off_rhs);
@@ -3186,7 +4129,11 @@ SeriesDev carve(void* base, const Layout& l)
     s.twork = (uint32_t*)(p + l.off_twork);
     s.cand = (int64_t*)(p + l.off_cand);
     s.part = (double*)(p + l.off_part);
-    s.xc = (double*)(p + l.off_xc);
+    s.lbp = (float*)(p + l.off_lbp);
+    s.ub = (float*)s.df64;         // free outside a round's sweeps (see make_layout)
+    s.fail = (int32_t*)s.df32;     // likewise
+    s.wit = (int32_t*)(p + l.off_wit);
+    s.wc = (double*)(p + l.off_wc);
     s.hist = (double*)(p + l.off_hist);
     s.evc = (unsigned long long*)(p + l.off_evc);
     s.ctrl = (Ctrl*)(p + l.off_ctrl);
@@ -3205,7 +4152,6 @@ void series_blocks(const Layout& l, const SweepCfg& cfg, int64_t out[PFX_KINDS])
     out[PFX_NEAR] = ((l.Nmax + rn - 1) / rn) * nsub;
     out[PFX_TSEL] = ((l.Nmax + rf - 1) / rf + 255) / 256;
     out[PFX_TREF] = ((l.Nmax + rr - 1) / rr + 255) / 256;
-    out[PFX_POLISH] = l.npart;
     out[PFX_BAND] = (l.Nmax + BAND_S - 1) / BAND_S;
 }
 

@@ -37,11 +37,13 @@ __global__ void k_ctrl_init(SeriesDev* S)
 {
     const SeriesDev& s = S[blockIdx.y];
     const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (g == 0) {
-        Ctrl z = {};
-        z.flat_min = -1;
-        z.flat_max = -1;
-        *s.ctrl = z;
+    // (word by word: a zeroed Ctrl value would go through scratch memory)
+    static_assert(sizeof(Ctrl) % 4 == 0, "Ctrl is cleared in words");
+    if (blockIdx.x == 0) {
+        uint32_t* z = (uint32_t*)s.ctrl;
+        for (int e = threadIdx.x; e < (int)(sizeof(Ctrl) / 4); e += blockDim.x) z[e] = 0u;
+        __syncthreads();
+        if (threadIdx.x == 0) s.ctrl->flat_min = s.ctrl->flat_max = -1;
     }
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     for (int64_t i = g; i < s.L; i += stride) s.hist[i] = 0.0;

@@ -1,0 +1,151 @@
+"""Rounds without sweeps: the witness test, the second chances and the
+screened exact pass, at the sizes where they can go wrong -- series around the
+screening's smallest size and around multiples of its 512-column chunks and
+128-column blocks, windows around the 256-offset staging chunk, flat
+stretches, a series with a huge spike (which widens the screening's error
+bound) -- against profiles in FP64 by plain matrix products
+of the reference's z-normalised windows: the top-k rows, and through the
+heatmap every length's range discords with their exact distances.  Tolerance
+as in the other parity tests (ED^2 = 2m (1 - rho), rho to 1e-12)."""
+
+import sys
+
+import numpy as np
+import pytest
+
+from oracle import bruteforce as bf
+from paper_2304_01660_amd import synth
+from parity_helpers import close_ed
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+SCREEN_MIN = 8192  # subsequences; longer series are screened
+
+
+def _dev():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    return torch.device("cuda:0")
+
+
+def _say(*a):
+    print("[case]", *a, file=sys.stderr, flush=True)
+
+
+def _series(kind, n, seed):
+    rng = np.random.default_rng([seed, n])
+    if kind in ("rw", "ecg", "noise"):
+        return synth.small_random(seed, n, kind)
+    if kind == "flat":  # plateaus of up to 150 points between walks
+        T = np.cumsum(rng.standard_normal(n))
+        for _ in range(max(2, n // 1500)):
+            p = int(rng.integers(0, n - 200))
+            T[p:p + int(rng.integers(60, 150))] = T[p]
+        return T
+    if kind == "spike":
+        T = synth.small_random(seed, n, "ecg")
+        T[n // 3] += 1.0e6
+        return T
+    raise ValueError(kind)
+
+
+def _profile(T, m, dev):
+    """Distance of every subsequence to its nearest non-self match."""
+    Z, _, _, flat = bf.znorm_windows(T, m)
+    Z = torch.from_numpy(np.ascontiguousarray(Z)).to(dev)
+    f = torch.from_numpy(flat).to(dev)
+    N = Z.shape[0]
+    Zt = Z.t().contiguous()
+    i = torch.arange(N, device=dev)
+    best = []
+    for a in range(0, N, 2048):
+        rows = i[a:a + 2048]
+        rho = Z[a:a + 2048] @ Zt / m
+        rho[f[a:a + 2048][:, None] & f[None, :]] = 1.0
+        rho[(i[None, :] - rows[:, None]).abs() < m] = -2.0
+        best.append(rho.max(1).values)
+    rho = torch.cat(best).clamp(-1.0, 1.0)
+    return torch.sqrt(2.0 * m * (1.0 - rho)).cpu().numpy()
+
+
+CASES = [
+    # kind, N at minL, minL, maxL, k
+    ("rw", SCREEN_MIN, 20, 23, 3),
+    ("ecg", SCREEN_MIN + 1, 31, 35, 2),
+    ("noise", SCREEN_MIN + 1, 17, 20, 1),
+    ("rw", 8704, 64, 67, 1),            # 17 chunks of 512
+    ("ecg", 8705 + 2, 64, 67, 3),       # N crosses 8705 -> 8704 on the way
+    ("ecg", 8833, 255, 258, 2),         # windows around 256 offsets
+    ("rw", 9000, 511, 513, 2),
+    ("flat", 8400, 40, 44, 2),
+    ("flat", 1500, 12, 16, 3),
+    ("spike", 8300, 50, 54, 2),
+    ("rw", 400, 3, 6, 64),              # k at its largest
+]
+
+
+@pytest.mark.parametrize("dist_bits", [32, 64])
+@pytest.mark.parametrize("case", range(len(CASES)))
+def test_search_and_heatmap_match_bruteforce(case, dist_bits):
+    from paper_2304_01660_amd import api
+    dev = _dev()
+    kind, N, minL, maxL, k = CASES[case]
+    n = N + minL - 1
+    T = _series(kind, n, 700 + case)
+    _say("witness", dist_bits, case, CASES[case], n)
+    Td = torch.from_numpy(T).to(dev)
+    out = api.discord_heatmap(Td, minL, maxL, k, dist_bits=dist_bits, return_stats=True)
+    plain = api.discords(Td, minL, maxL, k, dist_bits=dist_bits)
+    for key in ("idx", "len", "nn_dist", "nn_idx", "count"):
+        assert torch.equal(out[key], plain[key]), key
+    heat = out["heat"].cpu().numpy()
+    rng = out["range"].cpu().numpy()
+    cnt = out["count"].cpu().numpy()
+    nn = out["nn_dist"].cpu().numpy()
+    idx = out["idx"].cpu().numpy()
+    nbr = out["nn_idx"].cpu().numpy()
+    for m in range(minL, maxL + 1):
+        li = m - minL
+        Nm = n - m + 1
+        P = _profile(T, m, dev)
+        r = rng[li]
+        row = heat[li, :Nm]
+        assert np.all(heat[li, Nm:] == 0.0)
+        top = np.sort(P)[::-1][:k]
+        rows = slice(li * k, (li + 1) * k)
+        assert np.all(close_ed(nn[rows], top, m))
+        assert np.all(close_ed(nn[rows], P[idx[rows]], m))
+        assert np.all(np.abs(nbr[rows] - idx[rows]) >= m)
+        for i, j, d in zip(idx[rows], nbr[rows], nn[rows]):
+            x, y = T[i:i + m], T[j:j + m]
+            if x.std() > 0.0 and y.std() > 0.0:
+                rho = np.mean((x - x.mean()) * (y - y.mean())) / (x.std() * y.std())
+                assert close_ed(d, np.sqrt(max(0.0, 2.0 * m * (1.0 - rho))), m)
+        if r <= 0:
+            continue
+        member = row > 0.0
+        far = ~close_ed(P, np.full_like(P, r), m)
+        np.testing.assert_array_equal(member[far], (P >= r)[far])
+        assert int(member.sum()) == int(cnt[li])
+        assert np.all(close_ed(np.sqrt(2.0 * m * row[member]), P[member], m))
+
+
+def test_batch_of_screened_and_small_series_equals_single_searches():
+    """Candidate groups numbered across series of uneven size."""
+    from paper_2304_01660_amd import api
+    dev = _dev()
+    spec = [("rw", 300, 10, 14), ("ecg", 9500, 60, 66), ("noise", 2000, 12, 14),
+            ("rw", 12000, 33, 37), ("flat", 5000, 20, 24), ("ecg", 700, 40, 41)]
+    vals = [torch.from_numpy(_series(kind, n, 800 + q)).to(dev)
+            for q, (kind, n, _, _) in enumerate(spec)]
+    lo = [x[2] for x in spec]
+    hi = [x[3] for x in spec]
+    for band in (0, 1):
+        _say("witness batch", band)
+        res = api.discords_batched(vals, lo, hi, 2, band_pass=band)
+        for b in range(len(spec)):
+            one = api.discords(vals[b], lo[b], hi[b], 2)
+            for key in ("idx", "len", "nn_dist", "nn_idx", "count"):
+                assert torch.equal(res[b][key], one[key]), (b, key)
