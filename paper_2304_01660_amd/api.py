@@ -58,6 +58,11 @@ def _workspace(nbytes: int, dev) -> torch.Tensor:
     return ws
 
 
+def _stats_arg(st, wanted: bool):
+    """The counters cost a kernel and a copy: gathered only when asked for."""
+    return ctypes.byref(st) if wanted else None
+
+
 def discords(T: torch.Tensor, minL: int, maxL: int, k: int, *, dist_bits: int = 0,
              guard: float = 0.0, near_cols: int = 0, chunk_cols: int = 0, workspace=None,
              return_stats: bool = False, time_kernels: bool = False, rows_near: int = 0,
@@ -94,7 +99,7 @@ def discords(T: torch.Tensor, minL: int, maxL: int, k: int, *, dist_bits: int = 
         ctypes.c_void_p(ws.data_ptr()), ws.numel(), ctypes.c_void_p(out["idx"].data_ptr()),
         ctypes.c_void_p(out["len"].data_ptr()), ctypes.c_void_p(out["nn_dist"].data_ptr()),
         ctypes.c_void_p(out["nn_idx"].data_ptr()), ctypes.c_void_p(out["count"].data_ptr()),
-        ctypes.byref(st), _stream(dev))
+        _stats_arg(st, return_stats), _stream(dev))
     _lib.check(rc, ctx)
     if return_stats:
         out["stats"] = st.as_dict()
@@ -140,7 +145,7 @@ def discord_heatmap(T: torch.Tensor, minL: int, maxL: int, k: int, *, dist_bits:
         ctypes.c_void_p(out["len"].data_ptr()), ctypes.c_void_p(out["nn_dist"].data_ptr()),
         ctypes.c_void_p(out["nn_idx"].data_ptr()), ctypes.c_void_p(out["count"].data_ptr()),
         ctypes.c_void_p(out["heat"].data_ptr()), ld, ctypes.c_void_p(out["range"].data_ptr()),
-        ctypes.byref(st), _stream(dev))
+        _stats_arg(st, return_stats), _stream(dev))
     _lib.check(rc, ctx)
     if return_stats:
         out["stats"] = st.as_dict()
@@ -247,8 +252,8 @@ def discords_batched(series, minL, maxL, k: int, *, dist_bits: int = 0, guard: f
         ctx, ctypes.c_void_p(values.data_ptr()), offs, B, c_lo, c_hi, int(k), ctypes.byref(o),
         ctypes.c_void_p(ws.data_ptr()), ws.numel(), ctypes.c_void_p(idx.data_ptr()),
         ctypes.c_void_p(ln.data_ptr()), ctypes.c_void_p(nn.data_ptr()),
-        ctypes.c_void_p(nnj.data_ptr()), ctypes.c_void_p(cnt.data_ptr()), ctypes.byref(st),
-        _stream(dev))
+        ctypes.c_void_p(nnj.data_ptr()), ctypes.c_void_p(cnt.data_ptr()),
+        _stats_arg(st, return_stats), _stream(dev))
     _lib.check(rc, ctx)
     res = []
     r0 = c0 = 0
@@ -333,7 +338,7 @@ def range_discords(T: torch.Tensor, m: int, r: float, *, dist_bits: int = 0, gua
     rc = _lib.lib().palmad_range_discords(
         ctx, ctypes.c_void_p(T.data_ptr()), n, m, float(r), ctypes.byref(o),
         ctypes.c_void_p(ws.data_ptr()), ws.numel(), ctypes.c_void_p(words.data_ptr()),
-        ctypes.c_void_p(nn.data_ptr()), ctypes.byref(cnt), ctypes.byref(st), _stream(dev))
+        ctypes.c_void_p(nn.data_ptr()), ctypes.byref(cnt), _stats_arg(st, return_stats), _stream(dev))
     _lib.check(rc, ctx)
     bits = torch.arange(64, device=dev, dtype=torch.int64)
     mask = ((words[:, None] >> bits[None, :]) & 1).reshape(-1)[:N].bool()

@@ -26,10 +26,13 @@
 
 using namespace palmad;
 
+constexpr size_t STAGE_BYTES = 64 << 10;
+
 struct palmad_ctx {
     int device;
     std::string err;
     int32_t* pinned;             // pinned host mirror of small device counters
+    char* stage;                 // pinned staging of small plans [STAGE_BYTES]
     hipStream_t work;            // the library's stream (default priority)
     hipEvent_t ev_in, ev_out;    // order the work stream after / before the caller's
     hipEvent_t ev[KCLASSES][2];  // per-kernel timing
@@ -301,8 +304,12 @@ struct Outputs {
 int upload(palmad_ctx* ctx, const Plan& p, void* ws, const double* const* Tin, const Outputs* outs,
            Batch* bt, const int64_t* n_now = nullptr)
 {
-    std::vector<char> blob(p.off_rem, 0);
-    SeriesDev* d = (SeriesDev*)blob.data();
+    // small plans go through the context's pinned buffer, without a wait: the
+    // entry points that upload return only after the work stream has drained
+    const bool staged = p.off_rem <= STAGE_BYTES;
+    std::vector<char> pageable(staged ? 0 : p.off_rem, 0);
+    char* blob = staged ? ctx->stage : pageable.data();
+    SeriesDev* d = (SeriesDev*)blob;
     for (int b = 0; b < p.B; ++b) {
         SeriesDev s = carve((char*)ws + p.base[b], p.lay[b]);
         s.Tin = Tin ? Tin[b] : nullptr;
@@ -319,9 +326,9 @@ int upload(palmad_ctx* ctx, const Plan& p, void* ws, const double* const* Tin, c
         }
         d[b] = s;
     }
-    std::memcpy(blob.data() + p.off_pfx, p.pfx.data(), sizeof(int64_t) * p.pfx.size());
-    HIP_TRY(hipMemcpyAsync(ws, blob.data(), blob.size(), hipMemcpyHostToDevice, ctx->work));
-    HIP_TRY(hipStreamSynchronize(ctx->work));
+    std::memcpy(blob + p.off_pfx, p.pfx.data(), sizeof(int64_t) * p.pfx.size());
+    HIP_TRY(hipMemcpyAsync(ws, blob, p.off_rem, hipMemcpyHostToDevice, ctx->work));
+    if (!staged) HIP_TRY(hipStreamSynchronize(ctx->work));
     bt->s = (SeriesDev*)ws;
     for (int q = 0; q < PFX_KINDS; ++q)
         bt->pfx[q] = (const int64_t*)((char*)ws + p.off_pfx) + (size_t)q * (p.B + 1);
@@ -379,20 +386,32 @@ int leave(palmad_ctx* ctx, void* stream)
     return PALMAD_OK;
 }
 
-// Padded copies, finiteness check and the flat-window threshold.
-int prepare(palmad_ctx* ctx, const Batch& bt, const Plan& p)
+// The verdict of the finiteness check in the round counters read back.
+int check_finite(palmad_ctx* ctx, const Plan& p)
+{
+    if (ctx->pinned[REM_BAD] == 0) return PALMAD_OK;
+    if (p.B == 1) return fail(ctx, PALMAD_ENONFINITE, "the series holds NaN or Inf values");
+    return fail(ctx, PALMAD_ENONFINITE, "%d series hold NaN or Inf values (first: series %d)",
+                ctx->pinned[REM_BAD], ctx->pinned[REM_BAD_SERIES]);
+}
+
+int read_counters(palmad_ctx* ctx, const Batch& bt)
+{
+    HIP_TRY(hipMemcpyAsync(ctx->pinned, bt.remaining, REM_TOTAL * sizeof(int32_t),
+                           hipMemcpyDeviceToHost, ctx->work));
+    HIP_TRY(hipStreamSynchronize(ctx->work));
+    return PALMAD_OK;
+}
+
+// Padded copies, finiteness check and the flat-window threshold.  A search
+// does not wait here: no range search starts on a series with NaN or Inf, and
+// its first check of the counters reports it.
+int prepare(palmad_ctx* ctx, const Batch& bt, const Plan& p, bool wait = true)
 {
     HIP_TRY(launch_prepare(bt, p.totals, ctx->work));
-    HIP_TRY(launch_nonfinite(bt, bt.remaining, ctx->work));
-    HIP_TRY(hipMemcpyAsync(ctx->pinned, bt.remaining, 2 * sizeof(int32_t), hipMemcpyDeviceToHost,
-                           ctx->work));
-    HIP_TRY(hipStreamSynchronize(ctx->work));
-    if (ctx->pinned[0]) {
-        if (p.B == 1) return fail(ctx, PALMAD_ENONFINITE, "the series holds NaN or Inf values");
-        return fail(ctx, PALMAD_ENONFINITE, "%d series hold NaN or Inf values (first: series %d)",
-                    ctx->pinned[0], ctx->pinned[1]);
-    }
-    return PALMAD_OK;
+    if (!wait) return PALMAD_OK;
+    const int rc = read_counters(ctx, bt);
+    return rc ? rc : check_finite(ctx, p);
 }
 
 // Rounds without sweeps issued per host check: a finished series makes
@@ -460,7 +479,7 @@ int search(palmad_ctx* ctx, const Plan& p, const Opts& o, void* ws, const double
     Batch bt;
     rc = upload(ctx, p, ws, Tin, outs, &bt);
     if (rc) return rc;
-    rc = prepare(ctx, bt, p);
+    rc = prepare(ctx, bt, p, false);
     if (rc) return rc;
     HIP_TRY(launch_start(bt, cfg, ctx->work));
     // every issue of rounds completes a range search of at least one series
@@ -471,10 +490,9 @@ int search(palmad_ctx* ctx, const Plan& p, const Opts& o, void* ws, const double
         if (check > max_checks) return fail(ctx, PALMAD_EDEVICE, "search did not terminate");
         rc = run_rounds(ctx, bt, cfg, p, full);
         if (rc) return rc;
-        HIP_TRY(hipMemcpyAsync(ctx->pinned, bt.remaining, REM_COUNT * sizeof(int32_t),
-                               hipMemcpyDeviceToHost, ctx->work));
-        HIP_TRY(hipStreamSynchronize(ctx->work));
-        rc = accumulate(ctx, timer);
+        rc = read_counters(ctx, bt);
+        if (!rc) rc = check_finite(ctx, p);
+        if (!rc) rc = accumulate(ctx, timer);
         if (rc) return rc;
         if (ctx->pinned[REM_ERROR])
             return fail(ctx, PALMAD_EDEVICE,
@@ -630,15 +648,18 @@ int palmad_create(palmad_ctx** out, int device)
     if (!ctx) return fail(nullptr, PALMAD_ENOMEM, "context allocation failed");
     ctx->device = device;
     ctx->pinned = nullptr;
+    ctx->stage = nullptr;
     ctx->work = nullptr;
     ctx->ev_in = ctx->ev_out = nullptr;
     e = hipHostMalloc((void**)&ctx->pinned, 256, hipHostMallocDefault);
+    if (e == hipSuccess) e = hipHostMalloc((void**)&ctx->stage, STAGE_BYTES, hipHostMallocDefault);
     if (e == hipSuccess) e = hipStreamCreateWithFlags(&ctx->work, hipStreamNonBlocking);
     if (e == hipSuccess) e = hipEventCreateWithFlags(&ctx->ev_in, hipEventDisableTiming);
     if (e == hipSuccess) e = hipEventCreateWithFlags(&ctx->ev_out, hipEventDisableTiming);
     if (e != hipSuccess) {
         if (ctx->ev_in) (void)hipEventDestroy(ctx->ev_in);
         if (ctx->work) (void)hipStreamDestroy(ctx->work);
+        if (ctx->stage) (void)hipHostFree(ctx->stage);
         if (ctx->pinned) (void)hipHostFree(ctx->pinned);
         delete ctx;
         return fail(nullptr, PALMAD_EDEVICE, "context setup failed: %s", hipGetErrorString(e));
@@ -679,6 +700,7 @@ void palmad_destroy(palmad_ctx* ctx)
     (void)hipEventDestroy(ctx->ev_in);
     (void)hipEventDestroy(ctx->ev_out);
     (void)hipStreamDestroy(ctx->work);
+    if (ctx->stage) (void)hipHostFree(ctx->stage);
     if (ctx->pinned) (void)hipHostFree(ctx->pinned);
     delete ctx;
 }
@@ -877,7 +899,7 @@ int palmad_range_discords(palmad_ctx* ctx, const double* T, int64_t n, int32_t m
     Batch bt;
     rc = upload(ctx, p, workspace, &T, nullptr, &bt);
     if (rc) return rc;
-    rc = prepare(ctx, bt, p);
+    rc = prepare(ctx, bt, p, false);
     if (rc) return rc;
     HIP_TRY(launch_set_fixed_r(bt, r, ctx->work));
     HIP_TRY(launch_start(bt, cfg, ctx->work));
@@ -885,10 +907,12 @@ int palmad_range_discords(palmad_ctx* ctx, const double* T, int64_t n, int32_t m
     const int64_t N = n - m + 1;
     HIP_TRY(launch_range_out(bt, N, (unsigned long long*)alive, nn_dist, ctx->work));
     const Ctrl* c = (const Ctrl*)((char*)workspace + p.base[0] + p.lay[0].off_ctrl);
-    HIP_TRY(hipMemcpyAsync(ctx->pinned, &c->nsurv, sizeof(int32_t), hipMemcpyDeviceToHost,
-                           ctx->work));
-    HIP_TRY(hipStreamSynchronize(ctx->work));
-    *count = (int64_t)(uint32_t)ctx->pinned[0];
+    HIP_TRY(hipMemcpyAsync(ctx->pinned + REM_TOTAL, &c->nsurv, sizeof(int32_t),
+                           hipMemcpyDeviceToHost, ctx->work));
+    rc = read_counters(ctx, bt);
+    if (!rc) rc = check_finite(ctx, p);
+    if (rc) return rc;
+    *count = (int64_t)(uint32_t)ctx->pinned[REM_TOTAL];
     rc = accumulate(ctx, timer);
     if (rc) return rc;
     const double secs =
@@ -911,14 +935,12 @@ int palmad_window_stats(palmad_ctx* ctx, const double* T, int64_t n, int32_t min
     if (rc) return rc;
     rc = enter(ctx, stream);
     if (rc) return rc;
-    Batch bt;
-    rc = upload(ctx, p, workspace, &T, nullptr, &bt);
-    if (rc) return rc;
-    rc = prepare(ctx, bt, p);
-    if (rc) return rc;
-    HIP_TRY(launch_stats_to(bt, minL, m, p.totals, ctx->work));
-    HIP_TRY(launch_stats_out(bt, n - m + 1, mu, sigma, ctx->work));
+    int32_t* bad = (int32_t*)workspace;
+    HIP_TRY(launch_check_finite(T, n, bad, ctx->work));
+    HIP_TRY(launch_window_stats(T, n, minL, m, bad, mu, sigma, ctx->work));
+    HIP_TRY(hipMemcpyAsync(ctx->pinned, bad, sizeof(int32_t), hipMemcpyDeviceToHost, ctx->work));
     HIP_TRY(hipStreamSynchronize(ctx->work));
+    if (ctx->pinned[0]) return fail(ctx, PALMAD_ENONFINITE, "the series holds NaN or Inf values");
     return leave(ctx, stream);
 }
 
@@ -1213,6 +1235,8 @@ int palmad_stream_create(palmad_ctx* ctx, int64_t capacity, int32_t minL, int32_
         return fail(ctx, PALMAD_EDEVICE, "stream initialisation failed");
     }
     rc = leave(ctx, stream);
+    if (!rc && hipStreamSynchronize(ctx->work) != hipSuccess)
+        rc = fail(ctx, PALMAD_EDEVICE, "stream initialisation failed");
     if (rc) {
         delete st;
         return rc;

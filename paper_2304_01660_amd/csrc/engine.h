@@ -69,8 +69,10 @@ constexpr int EV_SLOTS = 64;
 enum { EV_NEAR = 0, EV_FAR = 1, EV_REF = 2, EV_POL = 3, EV_BAND = 4 };
 
 // Host counters of a round: series with work left, series in error, series
-// waiting for a round with sweeps, series at their first length.
+// waiting for a round with sweeps, series at their first length; then, once
+// per call, series holding NaN or Inf and the first of them.
 enum { REM_LEFT = 0, REM_ERROR, REM_PENDING, REM_FIRST, REM_COUNT };
+enum { REM_BAD = REM_COUNT, REM_BAD_SERIES, REM_TOTAL };
 
 // Device-resident control block of one series (the MERLIN state of Alg. 1
 // plus the work counters of the current round).  Fields that work items
@@ -201,7 +203,7 @@ struct Batch {
     int64_t Nmax_all;                // most subsequences of any series
     int64_t* ipfx;                   // device [2][B+1]: first exact-pass items of each series
     bool heat;                       // the search writes a discord heatmap
-    int32_t* remaining;              // device [REM_COUNT]
+    int32_t* remaining;              // device [REM_TOTAL]
     unsigned long long* sums;        // device [9]: counters summed over the batch
 };
 
@@ -253,10 +255,11 @@ hipError_t launch_stats_to(const Batch& bt, int32_t minL, int32_t m, const int64
                            hipStream_t st);
 // Per-series counters summed over the batch: 9 values (see k_sum_stats).
 hipError_t launch_sum_stats(const Batch& bt, unsigned long long* out, hipStream_t st);
-// out[0] = series holding NaN/Inf, out[1] = the first of them (or -1).
-hipError_t launch_nonfinite(const Batch& bt, int32_t* out, hipStream_t st);
 hipError_t launch_set_len(const Batch& bt, int32_t m, hipStream_t st);
-hipError_t launch_stats_out(const Batch& bt, int64_t N, double* mu, double* sigma, hipStream_t st);
+// Means and deviations of every window at length m (recurrences from minL),
+// straight from the caller's series; *bad: set when it holds NaN or Inf.
+hipError_t launch_window_stats(const double* T, int64_t n, int32_t minL, int32_t m,
+                               const int32_t* bad, double* mu, double* sigma, hipStream_t st);
 // Interest of every heatmap column (largest value over the lengths, and that
 // length) and the k most interesting columns.
 hipError_t launch_interest(const double* heat, int32_t L, int64_t ld, int64_t ncols, int32_t minL,
@@ -282,7 +285,7 @@ hipError_t launch_fill_u64(unsigned long long* p, int64_t count, unsigned long l
                            hipStream_t st);
 // Control blocks, histories, counters and bitmaps of every series to zero.
 hipError_t launch_ctrl_init(const Batch& bt, hipStream_t st);
-// Appended values: out[0] = 1 if any of src[0 .. count) is not finite.
+// out[0] = 1 if any of src[0 .. count) is not finite, else 0.
 hipError_t launch_check_finite(const double* src, int64_t count, int32_t* out, hipStream_t st);
 // Copy src[0 .. count) into the padded series at n_old and recompute the
 // series' population sigma (flat threshold) over its first s.n points.

@@ -308,6 +308,7 @@ __device__ void next_range(const SeriesDev& s, Ctrl* c, float guard, int max_att
 // Before the first round of a search.
 __global__ void k_start(SeriesDev* S, int B, float guard, int max_attempts, int32_t* rem)
 {
+    if (rem[REM_BAD] > 0) return;  // a series holds NaN or Inf: no range search starts
     for (int b = blockIdx.x * blockDim.x + threadIdx.x; b < B; b += gridDim.x * blockDim.x)
         next_range(S[b], S[b].ctrl, guard, max_attempts, rem);
 }
@@ -335,13 +336,15 @@ __device__ __forceinline__ bool direct_round(const Ctrl* c) { return c->live_ref
 __device__ __forceinline__ bool lean_round(const Ctrl* c) { return c->nlive <= c->lean_max; }
 
 // Mean and variance of window p at length m: two passes (Eq. (4)).
-__device__ __forceinline__ void direct_stats(const double* __restrict__ T, int64_t p, int32_t m,
-                                             double& mean, double& var)
+__device__ __forceinline__ void direct_stats(const double* T, int64_t p, int32_t m, double& mean,
+                                             double& var)
 {
     double acc = 0.0;
+#pragma unroll 8
     for (int k = 0; k < m; ++k) acc += T[p + k];
     mean = acc / (double)m;
     double q = 0.0;
+#pragma unroll 8
     for (int k = 0; k < m; ++k) {
         const double d = T[p + k] - mean;
         q += d * d;
@@ -349,16 +352,36 @@ __device__ __forceinline__ void direct_stats(const double* __restrict__ T, int64
     var = q / (double)m;
 }
 
-// Eq. (7)-(8): window p from length m-1 (mean mu0, variance v0) to m.
-__device__ __forceinline__ void grow_stats(const double* __restrict__ T, int64_t p, int32_t m,
-                                           double mu0, double v0, double& mean, double& var)
+// a / d from rd = 1 / d (correctly rounded): the residual of the first
+// quotient corrects it to the correctly rounded one (Markstein), in three
+// operations instead of a division's dozen.
+__device__ __forceinline__ double div_by(double a, double d, double rd)
 {
-    const int32_t mo = m - 1;
-    const double t = T[p + mo];
-    const double dm = (double)mo;
+    const double q = a * rd;
+    return fma(fma(-q, d, a), rd, q);
+}
+
+// Constants of one length's update: m, 1/m, (m-1)/m.
+struct GrowBy {
+    double m, rm, fm;
+};
+__device__ __forceinline__ GrowBy grow_by(int32_t m)
+{
+    GrowBy g;
+    g.m = (double)m;
+    g.rm = 1.0 / g.m;
+    g.fm = (double)(m - 1) / g.m;
+    return g;
+}
+
+// Eq. (7)-(8): a window from length m-1 (mean mu0, variance v0) to m, t its
+// new last value.
+__device__ __forceinline__ void grow_stats(double t, const GrowBy& g, double mu0, double v0,
+                                           double& mean, double& var)
+{
     const double d = mu0 - t;
-    mean = (dm * mu0 + t) / (dm + 1.0);
-    var = dm / (dm + 1.0) * (v0 + d * d / (dm + 1.0));
+    mean = div_by(fma(g.m - 1.0, mu0, t), g.m, g.rm);
+    var = g.fm * (v0 + div_by(d * d, g.m, g.rm));
 }
 
 // Block extremes of the window spreads (every block of k_length at a new
@@ -451,8 +474,9 @@ __global__ void k_length(SeriesDev* S, int B, const int64_t* __restrict__ pfx)
                 direct_stats(T, i, m, m0, v0);
                 if (i + 1 < N) direct_stats(T, i + 1, m, m1, v1);
             } else {
-                grow_stats(T, i, m, mu_o[i], var_o[i], m0, v0);
-                if (i + 1 < N) grow_stats(T, i + 1, m, mu_o[i + 1], var_o[i + 1], m1, v1);
+                const GrowBy g = grow_by(m);
+                grow_stats(T[i + m - 1], g, mu_o[i], var_o[i], m0, v0);
+                if (i + 1 < N) grow_stats(T[i + m], g, mu_o[i + 1], var_o[i + 1], m1, v1);
             }
         }
         mu_n[i] = m0;
@@ -568,6 +592,7 @@ constexpr int ADV_BLOCK = 256;
 __global__ __launch_bounds__(ADV_BLOCK) void k_advance(SeriesDev* S, int B,
                                                        const int64_t* __restrict__ pfx, int32_t* rem)
 {
+    extern __shared__ double ts[];  // ADV_BLOCK + maxL values
     __shared__ unsigned int wcnt[ADV_BLOCK / 64];
     __shared__ unsigned int base_s;
     if (blockIdx.x == 0 && threadIdx.x < REM_COUNT) rem[threadIdx.x] = 0;
@@ -593,14 +618,21 @@ __global__ __launch_bounds__(ADV_BLOCK) void k_advance(SeriesDev* S, int B,
     const double* __restrict__ var_o = odd ? s.var : s.var2;
     const bool in = i < N;
     const int32_t w0 = in && new_len != 2 ? s.wit[i] : WIT_NONE;
-    double mi = 0.0, vi = 0.0, ii = 0.0, moi = 0.0;
+    const GrowBy gb = grow_by(m);
+    if (new_len == 2) {  // the block's stretch of the series, for the direct sums
+        const int64_t e = std::min<int64_t>(s.Tlen - (i - threadIdx.x), ADV_BLOCK + m);
+        for (int t = threadIdx.x; t < e; t += ADV_BLOCK) ts[t] = T[i - threadIdx.x + t];
+        __syncthreads();
+    }
+    double mi = 0.0, vi = 0.0, ii = 0.0, moi = 0.0, ti = 0.0;
     if (new_len) {
         if (in) {
             if (new_len == 2) {
-                direct_stats(T, i, m, mi, vi);
+                direct_stats(ts, threadIdx.x, m, mi, vi);
             } else {
                 moi = mu_o[i];
-                grow_stats(T, i, m, moi, var_o[i], mi, vi);
+                ti = T[i + m - 1];
+                grow_stats(ti, gb, moi, var_o[i], mi, vi);
             }
             ii = inv_of(vi, sqm, feps);
             if (ii == 0.0) {
@@ -624,11 +656,12 @@ __global__ __launch_bounds__(ADV_BLOCK) void k_advance(SeriesDev* S, int B,
         const bool fresh = w0 < 0;
         const int64_t j = fresh ? ~w0 : w0;
         if (j < N && (j - i >= m || i - j >= m)) {
-            double mj, ij, moj = 0.0;
+            double mj, ij, moj = 0.0, tj = 0.0;
             if (new_len) {
                 double vj;
                 moj = mu_o[j];
-                grow_stats(T, j, m, moj, var_o[j], mj, vj);
+                tj = T[j + m - 1];
+                grow_stats(tj, gb, moj, var_o[j], mj, vj);
                 ij = inv_of(vj, sqm, feps);
             } else {
                 mj = mu_n[j];
@@ -642,7 +675,7 @@ __global__ __launch_bounds__(ADV_BLOCK) void k_advance(SeriesDev* S, int B,
             } else {
                 C = s.wc[i];
                 if (new_len) {
-                    C += (double)(m - 1) / (double)m * (T[i + m - 1] - moi) * (T[j + m - 1] - moj);
+                    C += gb.fm * (ti - moi) * (tj - moj);
                     s.wc[i] = C;
                 }
             }
@@ -3689,8 +3722,9 @@ hipError_t launch_round(const Batch& bt, const SweepCfg& cfg, const int64_t* tot
 {
     const unsigned int elem = (unsigned int)total[PFX_ELEM];
     cfg.timer->begin(4, st);
-    hipLaunchKernelGGL(k_advance, dim3(elem), dim3(ADV_BLOCK), 0, st, bt.s, bt.B, bt.pfx[PFX_ELEM],
-                       bt.remaining);
+    hipLaunchKernelGGL(k_advance, dim3(elem), dim3(ADV_BLOCK),
+                       sizeof(double) * (size_t)(ADV_BLOCK + bt.maxL_all), st, bt.s, bt.B,
+                       bt.pfx[PFX_ELEM], bt.remaining);
     if (more)
         hipLaunchKernelGGL(k_rescue, dim3(RESCUE_GRID), dim3(RESCUE_BLOCK), 0, st, bt.s, bt.B);
     if (full)
@@ -3845,44 +3879,46 @@ hipError_t launch_stats_to(const Batch& bt, int32_t minL, int32_t m, const int64
     return hipGetLastError();
 }
 
-// Sum of the per-series counters of a call (one block):
+// Sum of the per-series counters of a call (one block, a wave per series):
 // out = {evals_sel, evals_ref, evals_pol, rounds, survivors, evals_near, evals_far,
 //        rows_near, rows_far, evals_band}.
-__global__ void k_sum_stats(SeriesDev* S, int B, unsigned long long* out)
+__global__ __launch_bounds__(1024) void k_sum_stats(SeriesDev* S, int B, unsigned long long* out)
 {
+    static_assert(EV_SLOTS == 64, "one slot per lane");
     __shared__ unsigned long long acc[10];
     if (threadIdx.x < 10) acc[threadIdx.x] = 0ull;
     __syncthreads();
-    for (int b = 0; b < B; ++b) {
+    const int lane = threadIdx.x & 63;
+    for (int b = threadIdx.x >> 6; b < B; b += 16) {
         const SeriesDev& s = S[b];
-        for (int e = threadIdx.x; e < EV_CLASSES * EV_SLOTS; e += blockDim.x) {
-            const unsigned long long v = s.evc[e];
-            const int cls = e / EV_SLOTS;
-            if (v) {
-                if (cls == EV_NEAR || cls == EV_FAR || cls == EV_BAND) atomicAdd(&acc[0], v);
-                atomicAdd(&acc[cls == EV_NEAR  ? 5
-                               : cls == EV_FAR ? 6
-                               : cls == EV_REF ? 1
-                               : cls == EV_POL ? 2
-                                               : 9],
-                          v);
-            }
-        }
-        if (threadIdx.x == 0) {
+        unsigned long long v[EV_CLASSES];
+#pragma unroll
+        for (int e = 0; e < EV_CLASSES; ++e) v[e] = s.evc[e * EV_SLOTS + lane];
+#pragma unroll
+        for (int e = 0; e < EV_CLASSES; ++e)
+#pragma unroll
+            for (int o = 32; o >= 1; o >>= 1) v[e] += __shfl_xor(v[e], o);
+        if (lane == 0) {
             const Ctrl* c = s.ctrl;
-            acc[3] += c->rounds;
-            acc[4] += c->survivors;
-            acc[7] += c->rows_near;
-            acc[8] += c->rows_far;
+            atomicAdd(&acc[0], v[EV_NEAR] + v[EV_FAR] + v[EV_BAND]);
+            atomicAdd(&acc[1], v[EV_REF]);
+            atomicAdd(&acc[2], v[EV_POL]);
+            atomicAdd(&acc[3], c->rounds);
+            atomicAdd(&acc[4], c->survivors);
+            atomicAdd(&acc[5], v[EV_NEAR]);
+            atomicAdd(&acc[6], v[EV_FAR]);
+            atomicAdd(&acc[7], c->rows_near);
+            atomicAdd(&acc[8], c->rows_far);
+            atomicAdd(&acc[9], v[EV_BAND]);
         }
-        __syncthreads();
     }
+    __syncthreads();
     if (threadIdx.x < 10) out[threadIdx.x] = acc[threadIdx.x];
 }
 
 hipError_t launch_sum_stats(const Batch& bt, unsigned long long* out, hipStream_t st)
 {
-    hipLaunchKernelGGL(k_sum_stats, dim3(1), dim3(256), 0, st, bt.s, bt.B, out);
+    hipLaunchKernelGGL(k_sum_stats, dim3(1), dim3(1024), 0, st, bt.s, bt.B, out);
     return hipGetLastError();
 }
 
@@ -3890,7 +3926,7 @@ __global__ void k_range_out(SeriesDev* S, int64_t N, unsigned long long* alive_o
 {
     const SeriesDev& s = S[0];
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= N) return;
+    if (i >= N || !s.ctrl->started) return;
     const int32_t m = s.ctrl->m;
     const bool on = (s.alive[i >> 6] >> (i & 63)) & 1ull;
     if ((i & 63) == 0) alive_out[i >> 6] = s.alive[i >> 6];
@@ -3910,19 +3946,56 @@ hipError_t launch_range_out(const Batch& bt, int64_t N, unsigned long long* aliv
     return hipGetLastError();
 }
 
-__global__ void k_stats_out(SeriesDev* S, int64_t N, double* mo, double* so)
+// Statistics of every window at length m by the recurrences from minL on: one
+// thread walks its window through all the lengths in registers, the series'
+// stretch and the lengths' constants in LDS.  (A launch per length, which
+// wrote every helper of a search as well, moved 100 bytes per window and
+// length: 1.66 ms at 10^6 points, m = 128 -> 192.)  Nothing is written when
+// the series holds NaN or Inf (*bad).
+constexpr int STATS_LENGTHS = 256;  // constants staged at a time
+__global__ __launch_bounds__(ADV_BLOCK) void k_window_stats(const double* __restrict__ T, int64_t n,
+                                                            int32_t minL, int32_t m,
+                                                            const int32_t* bad, double* mu,
+                                                            double* sigma)
 {
-    const SeriesDev& s = S[0];
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= N) return;
-    mo[i] = cur_mu(s, s.ctrl)[i];
-    so[i] = sqrt(cur_var(s, s.ctrl)[i]);
+    extern __shared__ double ts[];  // ADV_BLOCK + m values
+    __shared__ double rm[STATS_LENGTHS], fm[STATS_LENGTHS];
+    if (*bad) return;
+    const int64_t i0 = (int64_t)blockIdx.x * ADV_BLOCK;
+    const int tid = threadIdx.x;
+    const int e = (int)std::min<int64_t>(n - i0, ADV_BLOCK + m);
+    for (int t = tid; t < e; t += ADV_BLOCK) ts[t] = T[i0 + t];
+    __syncthreads();
+    const bool in = i0 + tid < n - m + 1;
+    double mean = 0.0, var = 0.0;
+    if (in) direct_stats(ts, tid, minL, mean, var);
+    for (int32_t l0 = minL + 1; l0 <= m; l0 += STATS_LENGTHS) {
+        const int cnt = std::min(STATS_LENGTHS, m - l0 + 1);
+        __syncthreads();
+        for (int q = tid; q < cnt; q += ADV_BLOCK) {
+            const GrowBy g = grow_by(l0 + q);
+            rm[q] = g.rm;
+            fm[q] = g.fm;
+        }
+        __syncthreads();
+        if (in)
+            for (int q = 0; q < cnt; ++q) {
+                const GrowBy g = {(double)(l0 + q), rm[q], fm[q]};
+                grow_stats(ts[tid + l0 + q - 1], g, mean, var, mean, var);
+            }
+    }
+    if (in) {
+        mu[i0 + tid] = mean;
+        sigma[i0 + tid] = sqrt(var);
+    }
 }
 
-hipError_t launch_stats_out(const Batch& bt, int64_t N, double* mu, double* sigma, hipStream_t st)
+hipError_t launch_window_stats(const double* T, int64_t n, int32_t minL, int32_t m,
+                               const int32_t* bad, double* mu, double* sigma, hipStream_t st)
 {
-    hipLaunchKernelGGL(k_stats_out, dim3((unsigned int)((N + 255) / 256)), dim3(256), 0, st, bt.s,
-                       N, mu, sigma);
+    hipLaunchKernelGGL(k_window_stats, dim3((unsigned int)((n - m + 1 + ADV_BLOCK - 1) / ADV_BLOCK)),
+                       dim3(ADV_BLOCK), sizeof(double) * (size_t)(ADV_BLOCK + m), st, T, n, minL, m, bad,
+                       mu, sigma);
     return hipGetLastError();
 }
 

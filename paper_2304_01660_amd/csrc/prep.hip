@@ -33,9 +33,11 @@ __device__ double block_sum_p(double v, double* sh)
     return t;  // valid in thread 0
 }
 
-__global__ void k_ctrl_init(SeriesDev* S)
+__global__ void k_ctrl_init(SeriesDev* S, int32_t* rem)
 {
     const SeriesDev& s = S[blockIdx.y];
+    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x < REM_TOTAL)
+        rem[threadIdx.x] = threadIdx.x == REM_BAD_SERIES ? 0x7fffffff : 0;
     const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     // (word by word: a zeroed Ctrl value would go through scratch memory)
     static_assert(sizeof(Ctrl) % 4 == 0, "Ctrl is cleared in words");
@@ -83,10 +85,10 @@ __global__ void k_sqdev(SeriesDev* S)
     const SeriesDev& s = S[blockIdx.y];
     __shared__ double sh[16];
     __shared__ double mean_s;
-    if (threadIdx.x == 0) {
-        double t = 0.0;
-        for (int i = 0; i < RED_BLOCKS; ++i) t += s.red[i];
-        mean_s = t / (double)s.n;
+    static_assert(RED_BLOCKS == RED_THREADS, "one partial per thread");
+    {
+        const double t = block_sum_p(s.red[threadIdx.x], sh);
+        if (threadIdx.x == 0) mean_s = t / (double)s.n;
     }
     __syncthreads();
     const double mean = mean_s;
@@ -100,31 +102,37 @@ __global__ void k_sqdev(SeriesDev* S)
     if (threadIdx.x == 0) s.red[RED_BLOCKS + blockIdx.x] = t;
 }
 
-__global__ void k_sigma_final(SeriesDev* S)
+// Sigma of every series and its flat threshold; the series holding NaN or Inf
+// are counted in rem (nullptr: a stream, whose appends are checked first).
+__global__ __launch_bounds__(RED_THREADS) void k_sigma_final(SeriesDev* S, int32_t* rem)
 {
     const SeriesDev& s = S[blockIdx.x];
+    __shared__ double sh[16];
+    const double t = block_sum_p(s.red[RED_BLOCKS + threadIdx.x], sh);
     if (threadIdx.x == 0) {
-        double t = 0.0;
-        for (int i = 0; i < RED_BLOCKS; ++i) t += s.red[RED_BLOCKS + i];
         const double sg = sqrt(t / (double)s.n);
         s.ctrl->sigmaT = sg;
         s.ctrl->flat_eps = 1e-12 * (sg > 1.0 ? sg : 1.0);
+        if (rem && s.ctrl->nonfinite) {
+            atomicAdd(&rem[REM_BAD], 1);
+            atomicMin(&rem[REM_BAD_SERIES], (int)blockIdx.x);
+        }
     }
 }
 
 hipError_t launch_ctrl_init(const Batch& bt, hipStream_t st)
 {
-    hipLaunchKernelGGL(k_ctrl_init, dim3(64, bt.B), dim3(256), 0, st, bt.s);
+    hipLaunchKernelGGL(k_ctrl_init, dim3(64, bt.B), dim3(256), 0, st, bt.s, bt.remaining);
     return hipGetLastError();
 }
 
 hipError_t launch_prepare(const Batch& bt, const int64_t* total, hipStream_t st)
 {
     (void)total;
-    hipLaunchKernelGGL(k_ctrl_init, dim3(64, bt.B), dim3(256), 0, st, bt.s);
+    hipLaunchKernelGGL(k_ctrl_init, dim3(64, bt.B), dim3(256), 0, st, bt.s, bt.remaining);
     hipLaunchKernelGGL(k_copy_sum, dim3(RED_BLOCKS, bt.B), dim3(RED_THREADS), 0, st, bt.s);
     hipLaunchKernelGGL(k_sqdev, dim3(RED_BLOCKS, bt.B), dim3(RED_THREADS), 0, st, bt.s);
-    hipLaunchKernelGGL(k_sigma_final, dim3(bt.B), dim3(64), 0, st, bt.s);
+    hipLaunchKernelGGL(k_sigma_final, dim3(bt.B), dim3(RED_THREADS), 0, st, bt.s, bt.remaining);
     return hipGetLastError();
 }
 
@@ -132,16 +140,15 @@ hipError_t launch_prepare(const Batch& bt, const int64_t* total, hipStream_t st)
 // copy into the padded series at n_old, and the sum of the first s.n values
 // in the same order as k_copy_sum, so that sigma of the series (hence the
 // flat threshold) equals that of a search over the same values.
+__global__ void k_clear_flag(int32_t* out) { out[0] = 0; }
+
 __global__ void k_check_finite(const double* __restrict__ src, int64_t count, int32_t* out)
 {
-    __shared__ int bad_s;
-    if (threadIdx.x == 0) bad_s = 0;
-    __syncthreads();
     int bad = 0;
-    for (int64_t i = threadIdx.x; i < count; i += blockDim.x) bad |= !isfinite(src[i]);
-    if (bad) atomicOr(&bad_s, 1);
-    __syncthreads();
-    if (threadIdx.x == 0) out[0] = bad_s;
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < count;
+         i += (int64_t)gridDim.x * blockDim.x)
+        bad |= !isfinite(src[i]);
+    if (bad) atomicOr(out, 1);
 }
 
 __global__ void k_stream_copy(SeriesDev* S, const double* __restrict__ src, int64_t n_old,
@@ -167,7 +174,9 @@ __global__ void k_stream_sum(SeriesDev* S)
 
 hipError_t launch_check_finite(const double* src, int64_t count, int32_t* out, hipStream_t st)
 {
-    hipLaunchKernelGGL(k_check_finite, dim3(1), dim3(1024), 0, st, src, count, out);
+    hipLaunchKernelGGL(k_clear_flag, dim3(1), dim3(1), 0, st, out);
+    hipLaunchKernelGGL(k_check_finite, dim3((unsigned int)std::min<int64_t>(1024, (count + 255) / 256)),
+                       dim3(256), 0, st, src, count, out);
     return hipGetLastError();
 }
 
@@ -177,33 +186,7 @@ hipError_t launch_stream_append(const Batch& bt, const double* src, int64_t n_ol
     hipLaunchKernelGGL(k_stream_copy, dim3(256), dim3(256), 0, st, bt.s, src, n_old, count);
     hipLaunchKernelGGL(k_stream_sum, dim3(RED_BLOCKS, 1), dim3(RED_THREADS), 0, st, bt.s);
     hipLaunchKernelGGL(k_sqdev, dim3(RED_BLOCKS, 1), dim3(RED_THREADS), 0, st, bt.s);
-    hipLaunchKernelGGL(k_sigma_final, dim3(1), dim3(64), 0, st, bt.s);
-    return hipGetLastError();
-}
-
-__global__ void k_nonfinite(SeriesDev* S, int B, int32_t* out)
-{
-    __shared__ int cnt, first;
-    if (threadIdx.x == 0) {
-        cnt = 0;
-        first = 0x7fffffff;
-    }
-    __syncthreads();
-    for (int b = threadIdx.x; b < B; b += blockDim.x)
-        if (S[b].ctrl->nonfinite) {
-            atomicAdd(&cnt, 1);
-            atomicMin(&first, b);
-        }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        out[0] = cnt;
-        out[1] = cnt ? first : -1;
-    }
-}
-
-hipError_t launch_nonfinite(const Batch& bt, int32_t* out, hipStream_t st)
-{
-    hipLaunchKernelGGL(k_nonfinite, dim3(1), dim3(256), 0, st, bt.s, bt.B, out);
+    hipLaunchKernelGGL(k_sigma_final, dim3(1), dim3(RED_THREADS), 0, st, bt.s, (int32_t*)nullptr);
     return hipGetLastError();
 }
 
