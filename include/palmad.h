@@ -73,10 +73,12 @@ typedef struct {
                               the remaining columns go to the queued pass; 0 = 2048.
                               Capped so that the longest series has at most 65536
                               (tile, chunk) items in the first pass. */
-    int32_t chunk_cols;    /* columns per work item of the sweeps; 0 = 1024. */
+    int32_t chunk_cols;    /* columns per work item of the sweeps; 0 = 1024.  Shortened
+                              (to 128 at least) where the first pass would have too few
+                              items to fill the device. */
     uint32_t flags;        /* PALMAD_FLAG_* bits */
     int32_t rows_near;     /* row-tile height of the first selection pass: 128, 256 or
-                              512; 0 = 512 (FP32) / 256 (FP64). */
+                              512; 0 = 256. */
     int32_t rows_far;      /* row-tile height of the split selection pass; 0 = as near. */
     int32_t rows_refine;   /* row-tile height of the refinement pass; 0 = 128. */
     int32_t far_grid;      /* workgroups of the split passes (1..65536); 0 = 2048. */

@@ -30,7 +30,7 @@ constexpr int CAND_GROUPS = CAND_MAX / CAND_GROUP;
 constexpr int EXACT_COLS = 128;
 constexpr int SCREEN_COLS = 512;
 constexpr int EXACT_GRID = 512;
-constexpr int SCREEN_GRID = 512;
+constexpr int SCREEN_GRID = 768;  // three workgroups per CU
 constexpr int64_t SCREEN_MIN = 8192;
 // A round without sweeps takes at most LEAN_PAIRS (rows, columns) pairs.
 constexpr int64_t LEAN_PAIRS = 600000000;

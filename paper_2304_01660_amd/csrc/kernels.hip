@@ -253,7 +253,6 @@ __device__ void begin_range(const SeriesDev& s, Ctrl* c, float guard)
     c->ncand = 0;
     c->live_ref = 0;
     c->nlive = 0;
-    for (int q = 0; q < FAIL_LISTS; ++q) c->nfail[q] = 0;
     c->band_over = 0;
     // Most rows the exact pass takes without a sweep: its screening costs
     // about 4e-12 s per row and column (1e6 columns: 4 us per row), a round of
@@ -711,20 +710,21 @@ __global__ __launch_bounds__(ADV_BLOCK) void k_advance(SeriesDev* S, int B,
 }
 
 // Second chances for the rows whose witness failed, one wave per row: up to
-// RESCUE_TRIES batches of four candidates, sixteen lanes each, compared by
+// RESCUE_TRIES batches of eight candidates, eight lanes each, compared by
 // direct FP64 dot products; the best one above the threshold prunes the row
 // and becomes its witness.  Candidates: the witness's witness and that one's,
 // the diagonal extensions of the nearest pruned rows' witnesses on either
-// side; then the same of rows at growing distance.  (ECG-like series at
-// lengths past one beat, where r falls and up to a fifth of the witnesses
-// fail in one length: all but about one row in a thousand of them are pruned
-// here, most by the first batch.)  Rows that stay are the round's candidates.
-// Bound by latency: a few dependent loads per batch.
-constexpr int RESCUE_TRIES = 4;
+// side, and the witnesses' witnesses of rows a little further off; then those
+// of rows at growing distance.  (ECG-like series at lengths past one beat,
+// where r falls and up to a fifth of the witnesses fail in one length: all but
+// about one row in a thousand of them are pruned here, most by the first
+// batch.)  Rows that stay are the round's candidates.  Bound by latency: a
+// chain of dependent loads per batch, which is why a batch is wide.
+constexpr int RESCUE_TRIES = 2;
 __global__ __launch_bounds__(RESCUE_BLOCK) void k_rescue(SeriesDev* S, int B)
 {
     const int lane = threadIdx.x & 63;
-    const int sub = lane & 15, cq = lane >> 4;
+    const int sub = lane & 7, cq = lane >> 3;
     const int64_t wave = (int64_t)blockIdx.x * (RESCUE_BLOCK / 64) + (threadIdx.x >> 6);
     const int64_t nwaves = (int64_t)gridDim.x * (RESCUE_BLOCK / 64);
     // the waves are shared out evenly among the series
@@ -733,10 +733,10 @@ __global__ __launch_bounds__(RESCUE_BLOCK) void k_rescue(SeriesDev* S, int B)
     for (int64_t b = wave / nper; b < B; b += nwaves / nper) {
         const SeriesDev& s = S[b];
         Ctrl* c = s.ctrl;
+        const unsigned int mine = c->nfail[lane];
         if (!c->active || c->pending || c->new_len == 2 || !c->prune) continue;
         const int32_t m = c->m;
         const int64_t N = s.n - m + 1;
-        const unsigned int mine = c->nfail[lane];
         unsigned int total = mine;
 #pragma unroll
         for (int o = 32; o >= 1; o >>= 1) total += __shfl_xor(total, o);
@@ -751,93 +751,108 @@ __global__ __launch_bounds__(RESCUE_BLOCK) void k_rescue(SeriesDev* S, int B)
         const double* __restrict__ inv = s.inv64;
         const double kill = c->thr64 + WIT_GUARD;
         // the series' waves spread over its lists, then over a list's rows
+        // (fewer waves than lists: several lists per wave)
         const int nl = fail_lists(s.Npad);
         const int64_t per = std::max<int64_t>(1, nper / nl);  // waves per list
-        if (w >= per * nl) continue;
-        for (int64_t e = w;; e += nper) {
-            const int64_t list = e % nl, p0 = e / nl;
-            if (e != w && nper >= nl) break;
-            if (nper < nl && e >= nl) break;
+        for (int64_t e = w; e < (nper >= nl ? per * nl : (int64_t)nl); e += nper) {
+            const int64_t list = e % nl;
             const unsigned int cnt = (unsigned int)__builtin_amdgcn_readlane((int)mine, (int)list);
-        for (int64_t p = p0; p < cnt; p += per) {
-            const int64_t i = s.fail[list * cap + p];
-            const double mi = mu[i], ii = inv[i];
-            // a row's witness, whatever its state (a candidate is always recomputed)
-            auto wit_of = [&](int64_t q) -> int64_t {
-                if (q < 0 || q >= N) return -1;
-                const int32_t v = __hip_atomic_load(&s.wit[q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                return v == WIT_NONE ? -1 : v < 0 ? (int64_t)~v : (int64_t)v;
-            };
-            bool done = false;
-            for (int t = 0; t < RESCUE_TRIES && !done; ++t) {
-                // candidate of this lane's quarter
-                int64_t j = -1;
-                if (t == 0) {
-                    if (cq < 2) {
-                        j = wit_of(wit_of(i));
-                        if (cq == 1) j = wit_of(j);
-                    } else {
-                        // the nearest pruned row on the left (cq 2) or right (cq 3),
-                        // within 63 rows
-                        const int64_t base = cq == 2 ? i - 63 : i;
-                        int64_t q = -1;
-                        if (base >= 0) {
-                            const int off = (int)(base & 63);
-                            unsigned long long bits = load_word(&s.alive[base >> 6]) >> off;
-                            if (off) bits |= load_word(&s.alive[(base >> 6) + 1]) << (64 - off);
-                            unsigned long long z = ~bits;  // bit e: row base + e is pruned (or past the end)
-                            if (z) q = base + (cq == 2 ? 63 - __clzll((long long)z) : __ffsll((long long)z) - 1);
+            for (int64_t p = e / nl; p < cnt; p += per) {
+                const int64_t i = s.fail[list * cap + p];
+                const double mi = mu[i], ii = inv[i];
+                // a row's witness, whatever its state (a candidate is always recomputed)
+                auto wit_of = [&](int64_t q) -> int64_t {
+                    if (q < 0 || q >= N) return -1;
+                    const int32_t v =
+                        __hip_atomic_load(&s.wit[q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    return v == WIT_NONE ? -1 : v < 0 ? (int64_t)~v : (int64_t)v;
+                };
+                bool done = false;
+                for (int t = 0; t < RESCUE_TRIES && !done; ++t) {
+                    // this lane's candidate: row q's witness (hops = 1) or that
+                    // one's witness (2, 3), shifted along the diagonal to row i
+                    int64_t q = i;
+                    int hops = 2;
+                    if (t == 0) {
+                        if (cq == 1) hops = 3;
+                        if (cq == 2 || cq == 3) {
+                            // the nearest pruned row on the left (2) or right (3),
+                            // within 63 rows
+                            hops = 1;
+                            const int64_t base = cq == 2 ? i - 63 : i;
+                            q = -1;
+                            if (base >= 0) {
+                                const int off = (int)(base & 63);
+                                unsigned long long bits = load_word(&s.alive[base >> 6]) >> off;
+                                if (off) bits |= load_word(&s.alive[(base >> 6) + 1]) << (64 - off);
+                                // bit e: row base + e is pruned (or past the end)
+                                const unsigned long long z = ~bits;
+                                if (z)
+                                    q = base + (cq == 2 ? 63 - __clzll((long long)z)
+                                                        : __ffsll((long long)z) - 1);
+                            }
                         }
-                        const int64_t v = q >= 0 && q < N ? wit_of(q) : -1;
-                        j = v >= 0 ? v + (i - q) : -1;
+                        if (cq >= 4) q = i + (cq == 4 ? -4 : cq == 5 ? 4 : cq == 6 ? -16 : 16);
+                    } else {
+                        const int64_t d = (int64_t)32 << (cq >> 1);  // 32 .. 256 rows away
+                        q = (cq & 1) ? i + d : i - d;
                     }
-                } else {
-                    // rows at distance 2^(2t) and 2^(2t+1), both sides: their
-                    // witnesses' witnesses
-                    const int64_t d = (int64_t)1 << (2 * t + (cq >> 1));
-                    const int64_t q = (cq & 1) ? i + d : i - d;
-                    const int64_t v = wit_of(wit_of(q));
-                    j = v >= 0 ? v + (i - q) : -1;
-                }
-                if (j >= N || (j < i + m && j > i - m)) j = -1;
-                if (j < 0) j = -1;
-                double rho = -4.0, C = 0.0;
-                if (j >= 0) {
-                    const double mj = mu[j];
-                    for (int k = sub; k < m; k += 16) C = fma(T[i + k] - mi, T[j + k] - mj, C);
-                }
+                    int64_t j = wit_of(q);
+                    if (hops > 1) j = wit_of(j);
+                    if (hops > 2) j = wit_of(j);
+                    if (j >= 0) j += i - q;
+                    if (j < 0 || j >= N || (j < i + m && j > i - m)) j = -1;
+                    double rho = -4.0, C = 0.0;
+                    if (j >= 0) {
+                        const double mj = mu[j], ij = inv[j];
+                        const double* __restrict__ x = T + i;
+                        const double* __restrict__ y = T + j;
+                        int k = sub;
+                        for (; k + 24 < m; k += 32) {
+                            double u[4], v[4];
 #pragma unroll
-                for (int o = 8; o >= 1; o >>= 1) C += __shfl_xor(C, o);
-                if (j >= 0) rho = pair_rho(C, ii, inv[j]);
-                // the best of the four
-                double br = rho;
-                int bq = cq;
+                            for (int z = 0; z < 4; ++z) {
+                                u[z] = x[k + 8 * z];
+                                v[z] = y[k + 8 * z];
+                            }
 #pragma unroll
-                for (int o = 16; o <= 32; o <<= 1) {
-                    const double r2 = __shfl_xor(br, o);
-                    const int q2 = __shfl_xor(bq, o);
-                    if (r2 > br || (r2 == br && q2 < bq)) {
-                        br = r2;
-                        bq = q2;
+                            for (int z = 0; z < 4; ++z) C = fma(u[z] - mi, v[z] - mj, C);
+                        }
+                        for (; k < m; k += 8) C = fma(x[k] - mi, y[k] - mj, C);
+                        rho = ij;
+                    }
+#pragma unroll
+                    for (int o = 4; o >= 1; o >>= 1) C += __shfl_xor(C, o);
+                    if (j >= 0) rho = pair_rho(C, ii, rho);
+                    // the best of the eight
+                    double br = rho;
+                    int bq = cq;
+#pragma unroll
+                    for (int o = 8; o <= 32; o <<= 1) {
+                        const double r2 = __shfl_xor(br, o);
+                        const int q2 = __shfl_xor(bq, o);
+                        if (r2 > br || (r2 == br && q2 < bq)) {
+                            br = r2;
+                            bq = q2;
+                        }
+                    }
+                    done = __builtin_amdgcn_readfirstlane((int)(br > kill)) != 0;
+                    if (done && sub == 0 && cq == bq) {
+                        __hip_atomic_store(&s.wit[i], (int32_t)j, __ATOMIC_RELAXED,
+                                           __HIP_MEMORY_SCOPE_AGENT);
+                        s.wc[i] = C;
+                        atomicAnd(&s.alive[i >> 6], ~(1ull << (i & 63)));
                     }
                 }
-                done = br > kill;
-                if (done && sub == 0 && cq == bq) {
-                    __hip_atomic_store(&s.wit[i], (int32_t)j, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    s.wc[i] = C;
-                    atomicAnd(&s.alive[i >> 6], ~(1ull << (i & 63)));
-                }
-                done = __builtin_amdgcn_readfirstlane((int)done) != 0;
-            }
-            if (!done && lane == 0) {
-                const unsigned int have =
-                    __hip_atomic_load(&c->nlive, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                if (have <= (unsigned int)CAND_MAX) {  // abandoned once it overflows
-                    const unsigned int slot = atomicAdd(&c->nlive, 1u);
-                    if (slot < (unsigned int)CAND_MAX) s.cand[slot] = i;
+                if (!done && lane == 0) {
+                    const unsigned int have =
+                        __hip_atomic_load(&c->nlive, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    if (have <= (unsigned int)CAND_MAX) {  // abandoned once it overflows
+                        const unsigned int slot = atomicAdd(&c->nlive, 1u);
+                        if (slot < (unsigned int)CAND_MAX) s.cand[slot] = i;
+                    }
                 }
             }
-        }
         }
     }
 }
@@ -2646,6 +2661,7 @@ constexpr int PM_G = 16;       // candidates per group
 constexpr int EX_COLS = EXACT_COLS;  // columns per exact block
 constexpr int EX_WAVES = 4;    // waves per workgroup, EX_COLS / EX_WAVES columns each
 constexpr int EX_CT = EX_COLS / EX_WAVES / 16;  // 16-column tiles per wave
+constexpr int EX_STEPS = 8;    // matrix steps (of 4 offsets) read ahead
 constexpr int PM_KC = 256;     // window offsets per LDS chunk
 constexpr int PM_XS = PM_KC + 1;  // LDS row stride of a candidate window (odd: no bank conflicts)
 constexpr int SC_WAVES = 4;
@@ -2761,7 +2777,7 @@ typedef float acc4f_t __attribute__((ext_vector_type(4)));
 // smallest argmax as over all columns.  (A split into two FP16 values per
 // operand, 2^-22 instead of 2^-11, takes three times the matrix work and
 // leaves few blocks fewer.)
-__global__ __launch_bounds__(64 * SC_WAVES) void k_screen(SeriesDev* S, int B, int full,
+__global__ __launch_bounds__(64 * SC_WAVES, 3) void k_screen(SeriesDev* S, int B, int full,
                                                           const int64_t* __restrict__ ipfx)
 {
     __shared__ half8_t wcopy[8][SC_SLOTS];
@@ -2811,16 +2827,41 @@ __global__ __launch_bounds__(64 * SC_WAVES) void k_screen(SeriesDev* S, int B, i
         const float e0 = 1.05f * (2.0f * 0x1p-11f + 0x1p-22f + (float)(m + 32) * 0x1p-23f +
                                   sqrtf((float)m) * 0x1p-23f);
         const bool single = m <= PM_KC;
-        bool staged = false;
+        auto stage_windows = [&](int kb, int kn) {
+            for (int gq = w; gq < PM_G; gq += SC_WAVES) {
+                const int64_t i = cidx[gq];
+                const double mi = cmu[gq], sc = cinv[gq] * 1024.0;
+                double v[(SC_AS + 63) / 64];
+#pragma unroll
+                for (int q = 0; q < (SC_AS + 63) / 64; ++q) {
+                    const int k = lane + 64 * q;
+                    v[q] = k < kn ? T[i + kb + k] : mi;
+                }
+#pragma unroll
+                for (int q = 0; q < (SC_AS + 63) / 64; ++q) {
+                    const int k = lane + 64 * q;
+                    if (k < SC_AS) xa[gq * SC_AS + k] = (_Float16)(float)((v[q] - mi) * sc);
+                }
+            }
+        };
+        if (single) stage_windows(0, m);
         for (int64_t ch = c0; ch < c1; ++ch) {
             const int64_t j0 = ch * SC_COLS;
             // offset and scale of the chunk's stretch
             double lo = f_inf<double>(), hi = -f_inf<double>();
             const int span = (int)std::min<int64_t>(SC_COLS + m, s.n - j0);
-            for (int t = tid; t < span; t += 64 * SC_WAVES) {
-                const double v = T[j0 + t];
-                lo = fmin(lo, v);
-                hi = fmax(hi, v);
+            for (int t0 = tid; t0 < span; t0 += 4 * 64 * SC_WAVES) {
+                double v[4];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const int t = t0 + q * 64 * SC_WAVES;
+                    v[q] = T[j0 + (t < span ? t : t0)];
+                }
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    lo = fmin(lo, v[q]);
+                    hi = fmax(hi, v[q]);
+                }
             }
 #pragma unroll
             for (int o = 32; o >= 1; o >>= 1) {
@@ -2867,17 +2908,7 @@ __global__ __launch_bounds__(64 * SC_WAVES) void k_screen(SeriesDev* S, int B, i
                         wcopy[u0 + u][t] = ph;
                     }
                 }
-                if (!single || !staged) {
-                    for (int gq = w; gq < PM_G; gq += SC_WAVES) {
-                        const int64_t i = cidx[gq];
-                        const double mi = cmu[gq], sc = cinv[gq] * 1024.0;
-                        for (int k = lane; k < SC_AS; k += 64) {
-                            const double v = k < kn ? (T[i + kb + k] - mi) * sc : 0.0;
-                            xa[gq * SC_AS + k] = (_Float16)(float)v;
-                        }
-                    }
-                    staged = true;
-                }
+                if (!single) stage_windows(kb, kn);
                 __syncthreads();
                 const int steps = (kn + 31) >> 5;
                 const _Float16* ah = &xa[ca * SC_AS + 8 * ka];
@@ -2966,7 +2997,7 @@ __global__ __launch_bounds__(64 * EX_WAVES) void k_exact(SeriesDev* S, int B, in
     extern __shared__ double lds[];
     __shared__ double red_v[EX_WAVES][PM_G];
     __shared__ long long red_j[EX_WAVES][PM_G];
-    __shared__ double sxs[PM_G], civ[PM_G];
+    __shared__ double sxs[PM_G], civ[PM_G], cmu[PM_G];
     __shared__ int64_t cidx[PM_G];
     __shared__ float lbs[EX_WAVES * 4][PM_G];
     __shared__ unsigned long long mark_s[EX_WAVES];
@@ -2974,7 +3005,7 @@ __global__ __launch_bounds__(64 * EX_WAVES) void k_exact(SeriesDev* S, int B, in
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const int ca = lane & 15, ka = lane >> 4;
     double* xg = lds;                 // [PM_G][PM_XS] candidate window chunk
-    double* ts = lds + PM_G * PM_XS;  // t[j0 .. j0 + EX_COLS + m + 4)
+    double* ts = lds + PM_G * PM_XS;  // t[j0 .. j0 + EX_COLS + m + 4 EX_STEPS)
     const int64_t total = B == 1 ? items_of(S[0], full, false) : ipfx_e[B];
     const Share sh = share_of(total);
     for (int64_t it = sh.lo; it < sh.hi;) {
@@ -2995,13 +3026,20 @@ __global__ __launch_bounds__(64 * EX_WAVES) void k_exact(SeriesDev* S, int B, in
         const double* __restrict__ mu = cur_mu(s, c);
         const double* __restrict__ inv = s.inv64;  // 1/(sqrt(m) sigma), 0 for a flat window
         const bool single = m <= PM_KC;
-        bool have_meta = false, loaded = false, any = false;
+        bool loaded = false, any = false;
         double best[4];
         long long bj[4];
         unsigned int evb = 0;
         int64_t ci[4];
         double sxv[4], ivi[4];
         __syncthreads();
+        // the group's indices, means and spreads, fetched while the bounds are
+        if (tid < PM_G) {
+            const int64_t i = s.cand[min(g0 + tid, ncand - 1)];
+            cidx[tid] = i;
+            cmu[tid] = mu[i];
+            civ[tid] = inv[i];
+        }
         float lb = -8.0f;  // lower bound of candidate tid % 16
         if (screened) {
             // the lower bounds the screening's workgroups left
@@ -3012,12 +3050,20 @@ __global__ __launch_bounds__(64 * EX_WAVES) void k_exact(SeriesDev* S, int B, in
             const int64_t w0 = firsts / pers;
             const int64_t e0 = (firsts + g * nch) / pers - w0 + g;
             const int64_t e1 = (firsts + (g + 1) * nch - 1) / pers - w0 + g;
-            for (int64_t e = e0 + (tid >> 4); e <= e1; e += EX_WAVES * 4)
-                lb = fmaxf(lb, s.lbp[e * PM_G + (tid & 15)]);
+            constexpr int EN = EX_WAVES * 4;  // entries per pass of the workgroup
+            for (int64_t e = e0 + (tid >> 4); e <= e1; e += 8 * EN) {
+                float v[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u)
+                    v[u] = e + u * EN <= e1 ? s.lbp[(e + u * EN) * PM_G + (tid & 15)] : -8.0f;
+#pragma unroll
+                for (int u = 0; u < 8; ++u) lb = fmaxf(lb, v[u]);
+            }
             lbs[tid >> 4][tid & 15] = lb;
-            __syncthreads();
-            for (int q = 0; q < EX_WAVES * 4; ++q) lb = fmaxf(lb, lbs[q][tid & 15]);
         }
+        __syncthreads();
+        if (screened)
+            for (int q = 0; q < EX_WAVES * 4; ++q) lb = fmaxf(lb, lbs[q][tid & 15]);
         for (int64_t bb = b0; bb < b1; bb += EX_WAVES * 4) {
             // sixteen blocks at a time: which of them hold a column that counts
             {
@@ -3033,21 +3079,79 @@ __global__ __launch_bounds__(64 * EX_WAVES) void k_exact(SeriesDev* S, int B, in
             for (int e = 0; e < EX_WAVES * 4; ++e) {
                 if (((mark_s[e >> 2] >> (16 * (e & 3))) & 0xffffull) == 0ull) continue;
                 const int64_t blk = bb + e;
-                if (!have_meta) {
-                    // candidates' indices, spreads and sums of centred values
-                    for (int gq = w; gq < PM_G; gq += EX_WAVES) {
-                        const int64_t i = s.cand[min(g0 + gq, ncand - 1)];
-                        const double mi = mu[i];
-                        double sx = 0.0;
-                        for (int k = lane; k < m; k += 64) sx += T[i + k] - mi;
-                        sx = wave_sum(sx);
-                        if (lane == 0) {
-                            cidx[gq] = i;
-                            sxs[gq] = sx;
-                            civ[gq] = inv[i];
+                const int64_t j0 = blk * EX_COLS;
+                const int colbase = w * (EX_COLS / EX_WAVES);
+                // the columns' spreads and means, in flight during the products
+                double ivj[EX_CT], muj[EX_CT];
+#pragma unroll
+                for (int ct = 0; ct < EX_CT; ++ct) {
+                    const int64_t j = j0 + colbase + 16 * ct + ca;  // (inside the padded buffers)
+                    ivj[ct] = inv[j];
+                    muj[ct] = mu[j];
+                }
+                pm_acc_t acc[EX_CT];
+#pragma unroll
+                for (int ct = 0; ct < EX_CT; ++ct) acc[ct] = (pm_acc_t){0.0, 0.0, 0.0, 0.0};
+                for (int kb = 0; kb < m; kb += PM_KC) {
+                    const int kn = min(PM_KC, m - kb);
+                    __syncthreads();  // the previous chunk and block are consumed
+                    const bool fill = !single || !loaded;
+                    if (fill) {
+                        // every load of the chunk's windows before its stores
+                        constexpr int NG = PM_G / EX_WAVES, NQ = PM_KC / 64;
+                        double v[NG][NQ];
+#pragma unroll
+                        for (int u = 0; u < NG; ++u) {
+                            const double* __restrict__ x = T + cidx[w + EX_WAVES * u] + kb;
+#pragma unroll
+                            for (int q = 0; q < NQ; ++q)
+                                v[u][q] = lane + 64 * q < kn ? x[lane + 64 * q] : 0.0;
                         }
+                        if (kb == 0) lds_fill(ts, T + j0, EX_COLS + m + 4 * EX_STEPS);
+#pragma unroll
+                        for (int u = 0; u < NG; ++u) {
+                            const int gq = w + EX_WAVES * u;
+                            const double mi = cmu[gq];
+                            double sx = 0.0;
+#pragma unroll
+                            for (int q = 0; q < NQ; ++q) {
+                                const int k = lane + 64 * q;
+                                const double d = k < kn ? v[u][q] - mi : 0.0;
+                                xg[gq * PM_XS + k] = d;
+                                sx += d;
+                            }
+                            if (!any) {  // the windows' sums (zero up to rounding)
+                                sx = wave_sum(sx);
+                                if (lane == 0) sxs[gq] = kb ? sxs[gq] + sx : sx;
+                            }
+                        }
+                        loaded = true;
+                    } else if (kb == 0) {
+                        lds_fill(ts, T + j0, EX_COLS + m + 4 * EX_STEPS);
                     }
                     __syncthreads();
+                    const double* xp = xg + ca * PM_XS + ka;
+                    const double* tb = ts + colbase + kb + ka + ca;
+                    // eight steps' operands are read before their products (one
+                    // wave per SIMD: nothing else hides the LDS latency); the
+                    // window is zero past kn, the stretch finite
+                    for (int k8 = 0; k8 < kn; k8 += 4 * EX_STEPS) {
+                        double av[EX_STEPS], bv[EX_STEPS][EX_CT];
+#pragma unroll
+                        for (int u = 0; u < EX_STEPS; ++u) {
+                            av[u] = xp[k8 + 4 * u];
+#pragma unroll
+                            for (int ct = 0; ct < EX_CT; ++ct) bv[u][ct] = tb[k8 + 4 * u + 16 * ct];
+                        }
+#pragma unroll
+                        for (int u = 0; u < EX_STEPS; ++u)
+#pragma unroll
+                            for (int ct = 0; ct < EX_CT; ++ct)
+                                acc[ct] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[u], bv[u][ct],
+                                                                               acc[ct], 0, 0, 0);
+                    }
+                }
+                if (!any) {
 #pragma unroll
                     for (int r = 0; r < 4; ++r) {
                         ci[r] = cidx[ka + 4 * r];
@@ -3056,56 +3160,22 @@ __global__ __launch_bounds__(64 * EX_WAVES) void k_exact(SeriesDev* S, int B, in
                         best[r] = -f_inf<double>();
                         bj[r] = 0x7fffffffffffffffll;
                     }
-                    have_meta = true;
-                }
-                any = true;
-                const int64_t j0 = blk * EX_COLS;
-                const int colbase = w * (EX_COLS / EX_WAVES);
-                pm_acc_t acc[EX_CT];
-#pragma unroll
-                for (int ct = 0; ct < EX_CT; ++ct) acc[ct] = (pm_acc_t){0.0, 0.0, 0.0, 0.0};
-                for (int kb = 0; kb < m; kb += PM_KC) {
-                    const int kn = min(PM_KC, m - kb);
-                    __syncthreads();  // the previous chunk and block are consumed
-                    if (kb == 0) lds_fill(ts, T + j0, EX_COLS + m + 4);
-                    if (!single || !loaded) {
-                        for (int gq = w; gq < PM_G; gq += EX_WAVES) {
-                            const int64_t i = cidx[gq];
-                            const double mi = mu[i];
-#pragma unroll
-                            for (int q = 0; q < PM_KC / 64; ++q) {
-                                const int k = lane + 64 * q;
-                                xg[gq * PM_XS + k] = k < kn ? T[i + kb + k] - mi : 0.0;
-                            }
-                        }
-                        loaded = true;
-                    }
-                    __syncthreads();
-                    const double* xp = xg + ca * PM_XS + ka;
-                    const double* tb = ts + colbase + kb + ka + ca;
-                    for (int k4 = 0; k4 < kn; k4 += 4) {
-                        const double av = xp[k4];
-#pragma unroll
-                        for (int ct = 0; ct < EX_CT; ++ct)
-                            acc[ct] = __builtin_amdgcn_mfma_f64_16x16x4f64(av, tb[k4 + 16 * ct],
-                                                                           acc[ct], 0, 0, 0);
-                    }
+                    any = true;
                 }
                 // epilogue: lane holds D[ka + 4 r][16 ct + ca]; rho = C inv_i inv_j
 #pragma unroll
                 for (int ct = 0; ct < EX_CT; ++ct) {
                     const int64_t j = j0 + colbase + 16 * ct + ca;
                     if (j >= N) continue;
-                    const double ivj = inv[j], muj = mu[j];
 #pragma unroll
                     for (int r = 0; r < 4; ++r) {
                         if (j <= ci[r] - m || j >= ci[r] + m) {
                             double rh;
-                            if (ivi[r] == 0.0 || ivj == 0.0) {  // a flat window (R11)
-                                rh = (ivi[r] == 0.0 && ivj == 0.0) ? 1.0 : 0.0;
+                            if (ivi[r] == 0.0 || ivj[ct] == 0.0) {  // a flat window (R11)
+                                rh = (ivi[r] == 0.0 && ivj[ct] == 0.0) ? 1.0 : 0.0;
                             } else {
-                                const double Cv = acc[ct][r] - muj * sxv[r];
-                                rh = fmin(1.0, fmax(-1.0, Cv * ivi[r] * ivj));
+                                const double Cv = acc[ct][r] - muj[ct] * sxv[r];
+                                rh = fmin(1.0, fmax(-1.0, Cv * ivi[r] * ivj[ct]));
                             }
                             if (rh > best[r]) {  // a lane's columns ascend with ct and with the block
                                 best[r] = rh;
@@ -3165,10 +3235,10 @@ __global__ __launch_bounds__(END_BLOCK) void k_round_end(SeriesDev* S, int32_t* 
                                                           int max_attempts, int B,
                                                           const int64_t* __restrict__ ipfx_e)
 {
+    // the valid candidates, nvalid_s of them
     __shared__ double nn_s[CAND_MAX];
     __shared__ long long id_s[CAND_MAX];
     __shared__ long long jj_s[CAND_MAX];
-    __shared__ int valid_s[CAND_MAX];  // the valid candidates, nvalid_s of them
     __shared__ unsigned int nvalid_s;
     const SeriesDev& s = S[blockIdx.x];
     Ctrl* c = s.ctrl;
@@ -3194,6 +3264,7 @@ __global__ __launch_bounds__(END_BLOCK) void k_round_end(SeriesDev* S, int32_t* 
     const bool direct = direct_round(c);
     if (tid == 0) nvalid_s = 0;
     __syncthreads();
+    if (tid < FAIL_LISTS) c->nfail[tid] = 0;  // read by k_rescue only
     if (kp >= k) {
         // tpc threads per candidate (all candidates at once, tpc as large as
         // the block allows, at most a wave): strided partials loaded eight at
@@ -3211,6 +3282,8 @@ __global__ __launch_bounds__(END_BLOCK) void k_round_end(SeriesDev* S, int32_t* 
         for (int cid = tid / tpc; cid < kp; cid += END_BLOCK / tpc) {
             double best = -f_inf<double>(), bj = 1e300;
             const int g = cid / CAND_GROUP;
+            const long long i = s.cand[cid];
+            const double ii = s.inv64[i];
             const int np = (int)c->pcnt[g];
             const double* pc =
                 s.part + (part_base(per, first, nblk, g) * CAND_GROUP + cid % CAND_GROUP) * 2;
@@ -3239,11 +3312,7 @@ __global__ __launch_bounds__(END_BLOCK) void k_round_end(SeriesDev* S, int32_t* 
             }
             if (sub == 0) {
                 const double d2 = 2.0 * (double)m * (1.0 - best);
-                const long long i = s.cand[cid];
                 const long long j = bj < 1e299 ? (long long)bj : -1;  // every candidate has a neighbour
-                nn_s[cid] = sqrt(fmin(4.0 * (double)m, fmax(0.0, d2)));
-                id_s[cid] = i;
-                jj_s[cid] = j;
                 // a direct round decides here which live subsequences are range
                 // discords (distance >= r, i.e. rho <= thr64), as refinement would
                 int ok_i = 1;
@@ -3254,9 +3323,14 @@ __global__ __launch_bounds__(END_BLOCK) void k_round_end(SeriesDev* S, int32_t* 
                     if (s.heat && ok_i)
                         s.heat[(int64_t)li * s.heat_ld + i] = fmin(2.0, fmax(0.0, 1.0 - best));
                 }
-                if (ok_i) valid_s[atomicAdd(&nvalid_s, 1u)] = cid;
+                if (ok_i) {
+                    const unsigned int v = atomicAdd(&nvalid_s, 1u);
+                    nn_s[v] = sqrt(fmin(4.0 * (double)m, fmax(0.0, d2)));
+                    id_s[v] = i;
+                    jj_s[v] = j;
+                }
                 if (more && j >= 0) {  // the nearest neighbour is the best witness
-                    const double ii = s.inv64[i], ij = s.inv64[j];
+                    const double ij = s.inv64[j];
                     s.wit[i] = (int32_t)j;
                     s.wc[i] = ii > 0.0 && ij > 0.0 ? best / (ii * ij) : 0.0;
                 }
@@ -3271,11 +3345,15 @@ __global__ __launch_bounds__(END_BLOCK) void k_round_end(SeriesDev* S, int32_t* 
     const bool ok = ns >= (unsigned int)k && kp >= k && !redo;
     const int nv = kp >= k ? (int)nvalid_s : 0;
     if (ok && tid < nv) {
-        const int t = valid_s[tid];
+        const int t = tid;
+        const double nt = nn_s[t];
+        const long long it = id_s[t];
         int rank = 0;
+#pragma unroll 8
         for (int e = 0; e < nv; ++e) {
-            const int q = valid_s[e];
-            if (nn_s[q] > nn_s[t] || (nn_s[q] == nn_s[t] && id_s[q] < id_s[t])) ++rank;
+            const double ne = nn_s[e];
+            const long long ie = id_s[e];
+            rank += (ne > nt || (ne == nt && ie < it)) ? 1 : 0;
         }
         if (rank < k) {
             const int64_t row = (int64_t)li * k + rank;
@@ -3700,7 +3778,7 @@ static void launch_exact(const Batch& bt, const SweepCfg& cfg, int full, hipStre
     if (screened)
         hipLaunchKernelGGL(k_screen, dim3(SCREEN_GRID), dim3(64 * SC_WAVES), 0, st, bt.s, bt.B, full,
                            bt.ipfx);
-    const size_t lds = sizeof(double) * (size_t)(PM_G * PM_XS + EX_COLS + bt.maxL_all + 4);
+    const size_t lds = sizeof(double) * (size_t)(PM_G * PM_XS + EX_COLS + bt.maxL_all + 4 * EX_STEPS);
     hipLaunchKernelGGL(k_exact, dim3(EXACT_GRID), dim3(64 * EX_WAVES), lds, st, bt.s, bt.B, full,
                        screened ? 1 : 0, SCREEN_GRID, bt.ipfx, bt.ipfx + bt.B + 1);
     cfg.timer->end(3, st);
