@@ -1877,6 +1877,14 @@ __device__ void ref_item(const SweepArgs<double>& A, int64_t i0, int64_t jbeg, i
     double invi[Q];
 #pragma unroll
     for (int q = 0; q < Q; ++q) invi[q] = rowinv[Q * lane + q];
+    if (prune && jend == jbeg + 1) {  // the only column: no block tested it
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            const bool now = invi[q] > 0.0 && mx[q] * invi[q] > thr && !((dm[q] >> lane) & 1ull);
+            if (WIT && now) A.wit[rbase + q] = ~(int32_t)jbeg;
+            dm[q] |= uniform64(__ballot(now));
+        }
+    }
     // flat rows: correlation 1 with another flat window, 0 with any other
     const int64_t flo = c->flat_min, fhi = c->flat_max;
     bool flat[Q];

@@ -149,3 +149,22 @@ def test_batch_of_screened_and_small_series_equals_single_searches():
             one = api.discords(vals[b], lo[b], hi[b], 2)
             for key in ("idx", "len", "nn_dist", "nn_idx", "count"):
                 assert torch.equal(res[b][key], one[key]), (b, key)
+
+
+@pytest.mark.parametrize("one_past", [0, 1])
+def test_refinement_items_of_one_column(one_past):
+    """The last item on the left of the series' last tile holds only column 0,
+    the only neighbour of one row; so the row is no range discord."""
+    from paper_2304_01660_amd import api
+    dev = _dev()
+    N, m = 1088 + one_past, 255
+    T = np.random.default_rng([1088, m]).standard_normal(N + m - 1)
+    T[671:671 + m + 3] = T[671]  # a wide guard: the refinement decides
+    T[5:5 + m] = T[1047:1047 + m]
+    _say("one column", N)
+    out = api.discord_heatmap(torch.from_numpy(T).to(dev), m, m, 2)
+    r = float(out["range"][0])
+    P = _profile(T, m, dev)
+    far = ~close_ed(P, np.full_like(P, r), m)
+    member = out["heat"].cpu().numpy()[0, :N] > 0.0
+    np.testing.assert_array_equal(member[far], (P >= r)[far])
