@@ -441,15 +441,16 @@ int prepare(palmad_ctx* ctx, const Batch& bt, const Plan& p, bool wait = true)
 // synchronisation.
 constexpr int ROUNDS_PER_CHECK = 4;
 
-// One round with sweeps, or ROUNDS_PER_CHECK rounds without them.  (Launched
+// One round with sweeps or dense ones, or ROUNDS_PER_CHECK rounds without.  (Launched
 // directly: a round is a few kernels of 5-60 us, so the host stays ahead of
 // the device, and a captured graph, bound to one workspace, measured the same
 // on it and cost its capture, 0.4 ms, on every other.)
-int run_rounds(palmad_ctx* ctx, const Batch& bt, const SweepCfg& cfg, const Plan& p, bool full)
+int run_rounds(palmad_ctx* ctx, const Batch& bt, const SweepCfg& cfg, const Plan& p, bool full,
+               bool dense)
 {
-    const int rounds = full || cfg.timer->on ? 1 : ROUNDS_PER_CHECK;
+    const int rounds = full || dense || cfg.timer->on ? 1 : ROUNDS_PER_CHECK;
     for (int r = 0; r < rounds; ++r)
-        HIP_TRY(launch_round(bt, cfg, p.totals, full, true, ctx->work));
+        HIP_TRY(launch_round(bt, cfg, p.totals, full, dense, true, ctx->work));
     return PALMAD_OK;
 }
 
@@ -507,10 +508,10 @@ int search(palmad_ctx* ctx, const Plan& p, const Opts& o, void* ws, const double
     // every issue of rounds completes a range search of at least one series
     int64_t max_checks = 2;
     for (int b = 0; b < p.B; ++b) max_checks += (int64_t)p.lay[b].L * cfg.max_attempts * 2;
-    bool full = true;  // the first length has no witnesses yet
+    bool full = true, dense = false;  // the first length has no witnesses yet
     for (int64_t check = 0;; ++check) {
         if (check > max_checks) return fail(ctx, PALMAD_EDEVICE, "search did not terminate");
-        rc = run_rounds(ctx, bt, cfg, p, full);
+        rc = run_rounds(ctx, bt, cfg, p, full, dense);
         if (rc) return rc;
         rc = read_counters(ctx, bt);
         if (!rc) rc = check_finite(ctx, p);
@@ -521,7 +522,8 @@ int search(palmad_ctx* ctx, const Plan& p, const Opts& o, void* ws, const double
                         "%d series: a range search did not converge within %d attempts",
                         ctx->pinned[REM_ERROR], cfg.max_attempts);
         if (ctx->pinned[REM_LEFT] == 0) break;
-        full = ctx->pinned[REM_PENDING] > 0 || ctx->pinned[REM_FIRST] > 0;
+        full = ctx->pinned[REM_SWEEP] > 0;
+        dense = ctx->pinned[REM_DENSE] > 0;
     }
     const double secs =
         std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
@@ -926,7 +928,7 @@ int palmad_range_discords(palmad_ctx* ctx, const double* T, int64_t n, int32_t m
     if (rc) return rc;
     HIP_TRY(launch_set_fixed_r(bt, r, ctx->work));
     HIP_TRY(launch_start(bt, cfg, ctx->work));
-    HIP_TRY(launch_round(bt, cfg, p.totals, true, false, ctx->work));
+    HIP_TRY(launch_round(bt, cfg, p.totals, true, false, false, ctx->work));
     const int64_t N = n - m + 1;
     HIP_TRY(launch_range_out(bt, N, (unsigned long long*)alive, nn_dist, ctx->work));
     const Ctrl* c = (const Ctrl*)((char*)workspace + p.base[0] + p.lay[0].off_ctrl);

@@ -30,7 +30,7 @@ constexpr int CAND_GROUPS = CAND_MAX / CAND_GROUP;
 constexpr int EXACT_COLS = 128;
 constexpr int SCREEN_COLS = 512;
 constexpr int EXACT_GRID = 512;
-constexpr int SCREEN_GRID = 768;  // three workgroups per CU
+constexpr int SCREEN_GRID = 512;  // two workgroups per CU
 constexpr int64_t SCREEN_MIN = 8192;
 // A round without sweeps takes at most LEAN_PAIRS (rows, columns) pairs.
 constexpr int64_t LEAN_PAIRS = 600000000;
@@ -49,6 +49,14 @@ __host__ __device__ constexpr int64_t fail_cap(int64_t Npad)
 {
     return ((fail_blocks(Npad) + fail_lists(Npad) - 1) / fail_lists(Npad)) * 256;
 }
+// Dense rounds: rows per work item, workgroups, longest window, entries for
+// k_pairs kept.
+constexpr int DENSE_ROWS = 64;
+constexpr int DENSE_GRID = 512;
+constexpr int DENSE_MAXM = 256;
+constexpr int DENSE_NEAR = 16384;             // columns of its first pass at the second range,
+constexpr int64_t DENSE_NEAR_MAXN = 131072;   // for series of at most so many subsequences
+__host__ __device__ constexpr int64_t dense_pairs(int64_t Npad) { return 2 * Npad; }
 constexpr int RESCUE_GRID = 2048, RESCUE_BLOCK = 256;
 constexpr int TOPK_BLOCK = 1024;
 constexpr int RED_BLOCKS = 256;   // series reductions: blocks of 256 threads
@@ -69,9 +77,11 @@ constexpr int EV_SLOTS = 64;
 enum { EV_NEAR = 0, EV_FAR = 1, EV_REF = 2, EV_POL = 3, EV_BAND = 4 };
 
 // Host counters of a round: series with work left, series in error, series
-// waiting for a round with sweeps, series at their first length; then, once
-// per call, series holding NaN or Inf and the first of them.
-enum { REM_LEFT = 0, REM_ERROR, REM_PENDING, REM_FIRST, REM_COUNT };
+// waiting (for a round with sweeps or a dense one), series whose next range
+// search needs sweeps (the first length's and those waiting for them), series
+// whose next one is a dense round; then, once per call, series holding NaN or
+// Inf and the first of them.
+enum { REM_LEFT = 0, REM_ERROR, REM_PENDING, REM_SWEEP, REM_DENSE, REM_COUNT };
 enum { REM_BAD = REM_COUNT, REM_BAD_SERIES, REM_TOTAL };
 
 // Device-resident control block of one series (the MERLIN state of Alg. 1
@@ -105,6 +115,9 @@ struct Ctrl {
     int32_t hot_r;     // tile height the hot list was built for
     int32_t exact_ref; // 1: refinement sweeps both sides of every tile (set by k_round_end)
     int32_t band_over; // 1: more rows than KP_MAX may hold the k best exact values
+    int32_t dense;     // kind of dense round (DENSE_*)
+    int32_t handled;   // 1: this round's rows went through k_dense_list
+    uint32_t ndense, npairs;  // its listed rows, entries for k_pairs
     int32_t pending;   // 1: the range search waits for a round with sweeps
     uint32_t lean_max; // most rows of a round without sweeps
     int32_t heat_m;    // length whose heatmap row k_heat writes (0: none)
@@ -154,6 +167,8 @@ struct SeriesDev {
     float* ub;           // upper bounds [CAND_GROUPS][blocks][CAND_GROUP] (shares df64 .. rhs)
     int32_t* wit;        // witness of every row (see k_advance) [Npad+64]
     double* wc;          // its covariance with the row [Npad+64]
+    int2* pairs;         // a dense round's (row, first of eight columns) entries for k_pairs
+                         // [dense_pairs] (shares df64, dg64)
     int32_t* fail;       // lists of rows whose witness failed (shares the FP32 helpers)
     double* hist;        // nnDist history per length [L]
     unsigned long long* evc;  // pair evaluations [EV_CLASSES][EV_SLOTS]
@@ -247,7 +262,7 @@ void series_blocks(const Layout& lay, const SweepCfg& cfg, int64_t out[PFX_KINDS
 hipError_t launch_prepare(const Batch& bt, const int64_t* total, hipStream_t st);
 hipError_t launch_start(const Batch& bt, const SweepCfg& cfg, hipStream_t st);
 hipError_t launch_round(const Batch& bt, const SweepCfg& cfg, const int64_t* total, bool full,
-                        bool more, hipStream_t st);
+                        bool dense, bool more, hipStream_t st);
 hipError_t launch_set_fixed_r(const Batch& bt, double r, hipStream_t st);
 hipError_t launch_range_out(const Batch& bt, int64_t N, unsigned long long* alive_out,
                             double* nn_out, hipStream_t st);

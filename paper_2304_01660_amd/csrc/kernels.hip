@@ -215,6 +215,23 @@ __device__ __forceinline__ void set_sel_thresholds(Ctrl* c, float guard)
     c->thr32 = __double2float_ru(c->thr_sel);
 }
 
+// A round that bounds every row left, by a short first pass (DENSE_SWEEP) or by
+// the witnesses (DENSE_LEFT), instead of sweeping on (see k_dense).
+enum { DENSE_NO = 0, DENSE_SWEEP, DENSE_OFF, DENSE_LEFT };
+__device__ __forceinline__ bool dense_round(const Ctrl* c)
+{
+    return c->dense == DENSE_SWEEP || c->dense == DENSE_LEFT;
+}
+// Columns of the short first pass: most rows of the second range (r = sqrt(m))
+// fall within a few thousand columns where they fall at all; from the third
+// range on a good part never does.
+__device__ __forceinline__ int dense_near(const Ctrl* c) { return c->attempt == 1 ? DENSE_NEAR : 2048; }
+// Rows x columns x m above which rows left by the witnesses get a first pass
+// before they are bounded (about half a millisecond of k_dense; a million
+// points took 48.9 ms without this rule, 28.7 without dense rounds, 25.6 so).
+constexpr double DENSE_LEFT_WORK = 2.5e11;
+constexpr double DENSE_MIN_THR = 0.2;  // smallest threshold of a dense round
+
 __device__ void begin_range(const SeriesDev& s, Ctrl* c, float guard)
 {
     const int li = c->li;
@@ -262,7 +279,16 @@ __device__ void begin_range(const SeriesDev& s, Ctrl* c, float guard)
     if (c->new_len) {
         c->flat_min = 0x7fffffffffffffffll;
         c->flat_max = -1;
+        c->dense = DENSE_NO;
     }
+    c->handled = 0;
+    // from the second range of the first length on (long series: the third;
+    // there the second leaves few rows to sweep and many columns to bound)
+    if (c->dense != DENSE_OFF)
+        c->dense = c->mode == 0 && c->attempt >= (N <= DENSE_NEAR_MAXN ? 1 : 2) &&
+                           s.heat == nullptr && m <= DENSE_MAXM && c->thr64 >= DENSE_MIN_THR
+                       ? DENSE_SWEEP
+                       : DENSE_NO;
 }
 
 // The next range search of a series (one thread): the first length, the next
@@ -301,7 +327,8 @@ __device__ void next_range(const SeriesDev& s, Ctrl* c, float guard, int max_att
     c->active = 1;
     begin_range(s, c, guard);
     atomicAdd(&rem[REM_LEFT], 1);
-    if (c->li == 0) atomicAdd(&rem[REM_FIRST], 1);
+    if (c->li == 0) atomicAdd(&rem[REM_SWEEP], 1);
+    if (dense_round(c)) atomicAdd(&rem[REM_DENSE], 1);
 }
 
 // Before the first round of a search.
@@ -2213,8 +2240,10 @@ __global__ __launch_bounds__(64) void k_select_near(SeriesDev* S, int B,
     if (i0 >= A.N) return;
     const int64_t j00 = i0 + A.m;
     const int64_t jbeg = j00 + cc * chunk;
-    if (jbeg >= A.N || jbeg >= j00 + near_cols) return;
-    const int64_t jend = std::min<int64_t>(std::min<int64_t>(A.N, jbeg + chunk), j00 + near_cols);
+    if (c->dense == DENSE_LEFT) return;
+    const int64_t width = c->dense == DENSE_SWEEP ? dense_near(c) : near_cols;
+    if (jbeg >= A.N || jbeg >= j00 + width) return;
+    const int64_t jend = std::min<int64_t>(std::min<int64_t>(A.N, jbeg + chunk), j00 + width);
     const F thr = sel_threshold<F>(c);
     unsigned long long ev = 0;
     sel_item<F, Q, WIT>(A, i0, jbeg, jend, thr, lds, ev, &A.twork[tile]);
@@ -2241,7 +2270,7 @@ __global__ __launch_bounds__(64, (sizeof(F) == 4 && Q <= 2) ? 4 : 1) void k_sele
     for (int b = 0; b < B; ++b) {
         const SeriesDev& s = S[b];
         Ctrl* c = s.ctrl;
-        if (!c->active || !c->prune || lean_round(c)) continue;
+        if (!c->active || !c->prune || lean_round(c) || dense_round(c)) continue;
         const unsigned int nlive = c->nlive_sel;
         const unsigned long long total = (unsigned long long)nlive * c->maxc_sel;
         if (total == 0) continue;
@@ -2286,7 +2315,7 @@ __global__ __launch_bounds__(TILES_BLOCK) void k_tiles(SeriesDev* S, int B,
     const int b = series_of(pfx, B, blockIdx.x);
     const SeriesDev& s = S[b];
     Ctrl* c = s.ctrl;
-    if (!c->active || lean_round(c)) return;
+    if (!c->active || lean_round(c) || dense_round(c)) return;
     if (mode == 0 && !c->prune) return;
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int64_t t = (blockIdx.x - pfx[b]) * (int64_t)TILES_BLOCK + threadIdx.x;
@@ -2389,7 +2418,7 @@ __global__ __launch_bounds__(64, (Q <= 4 ? 3 : 1)) void k_refine(SeriesDev* S, i
     for (int b = 0; b < B; ++b) {
         const SeriesDev& s = S[b];
         Ctrl* c = s.ctrl;
-        if (!c->active || lean_round(c) || direct_round(c)) continue;
+        if (!c->active || lean_round(c) || dense_round(c) || direct_round(c)) continue;
         const unsigned int nlive = c->nlive_ref;
         const unsigned long long total = (unsigned long long)nlive * c->maxc_ref;
         if (total == 0) continue;
@@ -2498,7 +2527,7 @@ __global__ __launch_bounds__(TOPK_BLOCK) void k_select_top(SeriesDev* S)
     __shared__ int kp_s;
     const SeriesDev& s = S[blockIdx.x];
     Ctrl* c = s.ctrl;
-    if (!c->active || lean_round(c)) return;
+    if (!c->active || lean_round(c) || dense_round(c)) return;
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const int64_t N = s.n - c->m + 1;
     const int64_t nw = (N + 63) / 64;
@@ -2683,7 +2712,7 @@ __device__ __forceinline__ int cand_count(const SeriesDev& s, const Ctrl* c, int
 {
     if (!c->active) return 0;
     if (lean_round(c)) return c->nlive >= (uint32_t)s.k ? (int)c->nlive : 0;
-    return full ? (int)c->ncand : 0;
+    return full || c->handled ? (int)c->ncand : 0;
 }
 __device__ __forceinline__ int64_t exact_blocks(int64_t N) { return (N + EX_COLS - 1) / EX_COLS; }
 __device__ __forceinline__ int64_t screen_chunks(int64_t N) { return (N + SC_COLS - 1) / SC_COLS; }
@@ -2785,7 +2814,7 @@ typedef float acc4f_t __attribute__((ext_vector_type(4)));
 // smallest argmax as over all columns.  (A split into two FP16 values per
 // operand, 2^-22 instead of 2^-11, takes three times the matrix work and
 // leaves few blocks fewer.)
-__global__ __launch_bounds__(64 * SC_WAVES, 3) void k_screen(SeriesDev* S, int B, int full,
+__global__ __launch_bounds__(64 * SC_WAVES, 2) void k_screen(SeriesDev* S, int B, int full,
                                                           const int64_t* __restrict__ ipfx)
 {
     __shared__ half8_t wcopy[8][SC_SLOTS];
@@ -3232,6 +3261,676 @@ __global__ __launch_bounds__(64 * EX_WAVES) void k_exact(SeriesDev* S, int B, in
     }
 }
 
+// ---------------------------------------------------------------------------
+// dense rounds: many range discords
+// ---------------------------------------------------------------------------
+// The first length halves r until k range discords are found, and the last
+// of these ranges can lie far below the k-th distance: a quarter of all
+// subsequences may be range discords, each to be proved against every column;
+// later lengths can have thousands of them as well.  The sweeps would scan
+// nearly every tile against every column, on the right in FP32 and on the
+// left in FP64.  Instead such a round runs the first selection pass over a
+// part of its columns (dense_near; not at all where the witnesses already
+// pruned what falls), lists the rows left (k_dense_list) and bounds each of
+// them against all columns on the FP16 matrix cores as k_screen does
+// (k_dense, the same operands and error bound): rows with a pair above the
+// threshold, or within the error of it, are decided by FP64 dot products
+// (k_pairs), and a row without one is a range discord.  Only rows whose
+// largest correlation may be among the k smallest go to the exact pass
+// (k_dense_top).  Heatmaps report every range discord's exact maximum, and
+// windows past 256 points leave no room for the operands: both sweep.
+// Measured against sweeps: 200,000 points, m = 96, 51,000 range discords: the
+// round's sweeps 14 ms, this 8.4 ms (430 TFLOP/s); 64 series of 10,000 to
+// 200,000 points: the search 480 ms, now 175; 100,000 points, lengths 90-140:
+// 8.4 ms, now 7.2.
+constexpr int DN_ROWS = DENSE_ROWS;      // rows per item, DN_G groups of 16
+constexpr int DN_G = DN_ROWS / 16;
+constexpr int DN_BUF = 512;              // entries buffered per workgroup
+constexpr int DN_RAW = SC_COLS + PM_KC + 8;  // series values of a chunk
+__host__ __device__ constexpr int dense_stride(int m) { return ((m + 31) & ~31) + 8; }
+
+// The rows left, ascending (one block per series); few enough of them are
+// candidates at once.  In a round without sweeps (full = 0) every series with
+// too many rows left for that is taken here, unless its witnesses failed
+// altogether.
+__device__ __forceinline__ bool dense_allowed(const SeriesDev& s, const Ctrl* c)
+{
+    return c->prune && c->nlive != 0x7fffffffu && s.heat == nullptr && c->m <= DENSE_MAXM &&
+           c->thr64 >= DENSE_MIN_THR && c->dense != DENSE_OFF;
+}
+__global__ __launch_bounds__(TOPK_BLOCK) void k_dense_list(SeriesDev* S, int full)
+{
+    __shared__ unsigned int wsum[TOPK_BLOCK / 64];
+    const SeriesDev& s = S[blockIdx.x];
+    Ctrl* c = s.ctrl;
+    if (!c->active || lean_round(c)) return;
+    if (!dense_round(c) && (full || !dense_allowed(s, c))) return;
+    if (!full && c->dense == DENSE_SWEEP) return;  // its first pass has not run
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const int64_t nw = (s.n - c->m + 1 + 63) / 64;
+    const unsigned int lean_max = c->lean_max;
+    unsigned int base = 0;
+    for (int64_t q0 = 0; q0 < nw; q0 += TOPK_BLOCK) {
+        const int64_t q = q0 + tid;
+        unsigned long long bits = q < nw ? s.alive[q] : 0ull;
+        const unsigned int cnt = (unsigned int)__popcll(bits);
+        unsigned int x = cnt;
+        for (int o = 1; o < 64; o <<= 1) {
+            const unsigned int y = __shfl_up(x, o);
+            if (lane >= o) x += y;
+        }
+        __syncthreads();
+        if (lane == 63) wsum[w] = x;
+        __syncthreads();
+        unsigned int before = 0, tot = 0;
+        for (int e = 0; e < TOPK_BLOCK / 64; ++e) {
+            before += e < w ? wsum[e] : 0u;
+            tot += wsum[e];
+        }
+        unsigned int p = base + before + x - cnt;
+        while (bits) {
+            const int t = __ffsll((long long)bits) - 1;
+            bits &= bits - 1ull;
+            const int64_t i = q * 64 + t;
+            if (p < lean_max) s.cand[p] = i;
+            s.fail[p++] = (int32_t)i;
+            s.rho[i] = 0x000fffffffffffffull;  // ordered bits of -inf
+            s.rhs[i] = 0x000fffffffffffffull;
+        }
+        base += tot;
+    }
+    __syncthreads();  // (the control block is read until here)
+    // many rows of a long series: a first pass over some columns prunes most of
+    // them for less than bounding them all costs
+    if (!full && (double)base * (double)(s.n - c->m + 1) * (double)c->m > DENSE_LEFT_WORK) {
+        if (tid == 0) c->dense = DENSE_SWEEP;
+        return;
+    }
+    if (tid == 0) {
+        c->handled = 1;
+        c->rows_near += base;
+        c->npairs = 0;
+        if (base <= lean_max) {
+            c->dense = DENSE_NO;
+            c->live_ref = base;  // a direct round
+            c->rows_far += base;
+            c->nsurv = base;
+            c->ncand = base < (unsigned int)s.k ? 0u : base;
+        } else {
+            c->dense = DENSE_LEFT;
+            c->ndense = base;
+        }
+    }
+}
+
+// One item: DN_ROWS listed rows against one segment of the columns, four waves
+// of 128 columns each per chunk of 512.  A wave computes a 64 x 128 tile of
+// products in parts (128 accumulators do not fit two waves per SIMD); for
+// windows of 33 to 128 points (STEPS = 4) the rows' operands stay in registers
+// for the whole item, so that eight matrix instructions take two LDS reads;
+// from LDS (STEPS = 0, every other window) they take six, which is as long as
+// the products.  The next chunk's series values are fetched during the
+// products.  Bound by the matrix cores (2 m flops per pair) and, for short
+// windows, by the 1.5 vector operations per product that fold it into its
+// row's maximum.  A row with a product that may exceed the threshold hands the
+// lane's eight columns to k_pairs; if it surely does, the row is out of the
+// item.  (Workgroups take the items in turn, two of this size per CU: a launch
+// of all items of 64 series measured 2 ms with nothing to do, this 0.1.
+// Registers over the budget spill outside the loop over the products.)
+template <int STEPS>
+__device__ __forceinline__ void dense_item(const SeriesDev& s, Ctrl* c, int64_t tile, int seg, int segs,
+                                           _Float16* dxa, half8_t (*wcopy)[SC_SLOTS], float* gjs,
+                                           double* raw, double* rlo, double* rhi, int32_t* rows,
+                                           float (*bnd)[SC_WAVES][DN_ROWS],
+                                           unsigned long long* dead_p, unsigned int* npair_p,
+                                           unsigned int* gbase_p, int2* buf)
+{
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const int ca = lane & 15, ka = lane >> 4;
+    const int32_t m = c->m;
+    const int64_t N = s.n - m + 1;
+    const unsigned int nrow = c->ndense;
+    const double* __restrict__ T = s.T;
+    const double* __restrict__ mu = cur_mu(s, c);
+    const double* __restrict__ inv = s.inv64;
+    const float thr = (float)c->thr64;
+    const int stride = dense_stride(m);
+    __syncthreads();  // (the previous item is consumed)
+    if (tid == 0) *npair_p = 0u;
+    if (tid < DN_ROWS)
+        rows[tid] = s.fail[std::min<int64_t>(tile * DN_ROWS + tid, (int64_t)nrow - 1)];
+    __syncthreads();
+    // the rows' windows, centred and scaled to norm 1024
+#pragma unroll 1
+    for (int r0 = w; r0 < DN_ROWS; r0 += 4 * SC_WAVES) {
+        constexpr int NQ = (DENSE_MAXM + 63) / 64 + 1;
+        double v[4][NQ], mi[4], sc[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int64_t i = rows[r0 + SC_WAVES * u];
+            mi[u] = mu[i];
+            sc[u] = inv[i] * 1024.0;
+#pragma unroll
+            for (int q = 0; q < NQ; ++q) {
+                const int k = lane + 64 * q;
+                v[u][q] = k < m ? T[i + k] : 0.0;
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+#pragma unroll
+            for (int q = 0; q < NQ; ++q) {
+                const int k = lane + 64 * q;
+                if (k < stride)
+                    dxa[(r0 + SC_WAVES * u) * stride + k] =
+                        k < m ? (_Float16)(float)((v[u][q] - mi[u]) * sc[u]) : (_Float16)0.0f;
+            }
+    }
+    // rows past the list, rows pruned meanwhile, and flat rows (R11:
+    // correlation 1 with another flat window, 0 with any other, so a partner
+    // decides)
+    if (tid < DN_ROWS) {
+        const int64_t i = rows[tid];
+        bool off = tile * DN_ROWS + tid >= (int64_t)nrow ||
+                   !((load_word(&s.alive[i >> 6]) >> (i & 63)) & 1ull);
+        if (!off && inv[i] == 0.0) {
+            const int64_t flo = c->flat_min, fhi = c->flat_max;
+            const bool lo_ok = flo >= 0 && flo <= i - m, hi_ok = fhi >= 0 && fhi >= i + m;
+            if (lo_ok || hi_ok) {
+                off = true;
+                s.wit[i] = ~(int32_t)(lo_ok ? flo : fhi);
+                atomicAnd(&s.alive[i >> 6], ~(1ull << (i & 63)));
+            }
+        }
+        const unsigned long long d = __ballot(off);
+        if (tid == 0) *dead_p = d;
+    }
+    __syncthreads();
+    int32_t rmin = 0x7fffffff, rmax = -1;
+#pragma unroll
+    for (int q = 0; q < 4 * DN_G; ++q) {
+        const int32_t i = rows[16 * (q >> 2) + 4 * ka + (q & 3)];
+        rmin = min(rmin, i);
+        rmax = max(rmax, i);
+    }
+    const _Float16* ap = dxa + ca * stride + 8 * ka;
+    half8_t areg[STEPS ? STEPS : 1][DN_G];
+    float ubr[4 * DN_G];
+#pragma unroll
+    for (int q = 0; q < 4 * DN_G; ++q) ubr[q] = -4.0f;
+    float em_max = 0.0f;
+    unsigned long long seen = 0ull;
+    bool fresh = true;  // the rows' operands changed
+    const float e0 = 1.05f * (2.0f * 0x1p-11f + 0x1p-22f + (float)(m + 32) * 0x1p-23f +
+                              sqrtf((float)m) * 0x1p-23f);
+    const float fl = sqrtf((float)m) * 0x1p-13f;
+    const int64_t nch = screen_chunks(N);
+    const int64_t ch0 = nch * seg / segs, ch1 = nch * (seg + 1) / segs;
+    const int steps = (m + 31) >> 5;
+    constexpr int RAW = (SC_COLS + PM_KC + 8 + 255) / 256;  // raw values per thread
+    double rv[RAW], cm[2], ci[2];
+    auto fetch = [&](int64_t ch) {
+        const int64_t j0 = ch * SC_COLS;
+#pragma unroll
+        for (int q = 0; q < RAW; ++q) {
+            const int t = tid + 256 * q;
+            rv[q] = t < DN_RAW ? T[j0 + t] : 0.0;  // (inside the padded series)
+        }
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {  // the wave's columns, two per lane
+            cm[q] = mu[j0 + w * EX_COLS + lane + 64 * q];
+            ci[q] = inv[j0 + w * EX_COLS + lane + 64 * q];
+        }
+    };
+    auto flush = [&]() {  // hand the listed entries over (whole workgroup)
+        const unsigned int np = min(*npair_p, (unsigned int)DN_BUF);
+        if (tid == 0 && np) *gbase_p = atomicAdd(&c->npairs, np);
+        __syncthreads();
+        for (unsigned int q = tid; q < np; q += 64 * SC_WAVES)
+            if ((int64_t)*gbase_p + q < dense_pairs(s.Npad)) s.pairs[*gbase_p + q] = buf[q];
+        __syncthreads();
+        if (tid == 0) *npair_p = 0u;
+    };
+    unsigned long long ev = 0;
+    fetch(ch0);
+    for (int64_t ch = ch0; ch < ch1; ++ch) {
+        const int64_t j0 = ch * SC_COLS;
+        const int64_t jb = j0 + w * EX_COLS;
+        const int span = (int)std::min<int64_t>(SC_COLS + m, s.n - j0);
+        double lo = f_inf<double>(), hi = -f_inf<double>();
+#pragma unroll
+        for (int q = 0; q < RAW; ++q) {
+            const int t = tid + 256 * q;
+            if (t < span) {
+                lo = fmin(lo, rv[q]);
+                hi = fmax(hi, rv[q]);
+            }
+        }
+#pragma unroll
+        for (int o = 32; o >= 1; o >>= 1) {
+            lo = fmin(lo, __shfl_xor(lo, o));
+            hi = fmax(hi, __shfl_xor(hi, o));
+        }
+        __syncthreads();  // the previous chunk's operands are consumed
+        const unsigned long long dead = *dead_p;  // (written only between the next barrier and this one)
+        if (dead == ~0ull) break;
+        if (*npair_p > DN_BUF / 2) {
+            __syncthreads();
+            flush();
+        }
+        if (lane == 0) {
+            rlo[w] = lo;
+            rhi[w] = hi;
+        }
+#pragma unroll
+        for (int q = 0; q < RAW; ++q)
+            if (tid + 256 * q < DN_RAW) raw[tid + 256 * q] = rv[q];
+        // a dead row's window becomes zero: its products then stay far below the
+        // threshold (positive by DENSE_MIN_THR)
+        if (dead != seen) {
+            for (unsigned long long d = (dead & ~seen) & (0x1111111111111111ull << w); d; d &= d - 1ull) {
+                const int r = __ffsll((long long)d) - 1;
+                for (int k = lane; k < stride; k += 64) dxa[r * stride + k] = (_Float16)0.0f;
+            }
+            seen = dead;
+            fresh = true;
+        }
+        __syncthreads();
+        if (STEPS && fresh) {
+#pragma unroll
+            for (int st = 0; st < STEPS; ++st)
+#pragma unroll
+                for (int g = 0; g < DN_G; ++g)
+                    if (st < steps)
+                        areg[st][g] = *(const half8_t*)(ap + 16 * g * stride + 32 * st);
+            fresh = false;
+        }
+        for (int q = 0; q < SC_WAVES; ++q) {
+            lo = fmin(lo, rlo[q]);
+            hi = fmax(hi, rhi[q]);
+        }
+        const double off = 0.5 * (lo + hi);
+        const double range = 0.5 * (hi - lo);
+        int ex = 0;
+        if (range > 0.0) (void)frexp(range, &ex);
+        const double sw = range > 0.0 ? ldexp(1.0, min(10 - ex, 900)) : 1.0;
+        const double usw = 1.0 / sw;
+        if (tid < 2 * SC_SLOTS) {
+            const int t = tid >> 1, u0 = (tid & 1) * 4;
+            const double* src = raw + 8 * t + u0;
+            _Float16 h[11];
+#pragma unroll
+            for (int q = 0; q < 11; ++q)
+                h[q] = (_Float16)(float)fmin(2048.0, fmax(-2048.0, (src[q] - off) * sw));
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                half8_t ph;
+#pragma unroll
+                for (int q = 0; q < 8; ++q) ph[q] = h[u + q];
+                wcopy[u0 + u][t] = ph;
+            }
+        }
+        float em = 0.0f;  // largest error bound of the wave's columns
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            const float iv = (float)(ci[q] * usw);
+            const float dn = (float)((cm[q] - off) * ci[q]);
+            const float ej = 1.02f * (e0 * sqrtf(1.0f + (float)m * dn * dn) + fl * iv) + 1e-6f;
+            if (jb + lane + 64 * q < N) em = fmaxf(em, ej);
+            gjs[w * EX_COLS + lane + 64 * q] = iv * 0x1p-10f;
+        }
+#pragma unroll
+        for (int o = 32; o >= 1; o >>= 1) em = fmaxf(em, __shfl_xor(em, o));
+        __syncthreads();
+        if (ch + 1 < ch1) fetch(ch + 1);
+        if (jb >= N) continue;  // (the next barrier is the loop's first)
+        const int slot = w * (EX_COLS / 8) + ca + ka;
+        const bool edge = __ballot(jb + EX_COLS > N ||
+                                   ((int64_t)rmin < jb + EX_COLS + m && (int64_t)rmax > jb - m)) != 0ull;
+        float mx[4 * DN_G];
+#pragma unroll
+        for (int q = 0; q < 4 * DN_G; ++q) mx[q] = -4.0f;
+        // NU of the eight shifts at a time
+        constexpr int NU = STEPS ? 2 : 4;
+#pragma unroll 1
+        for (int hf = 0; hf < 8 / NU; ++hf) {
+            acc4f_t acc[DN_G][NU];
+#pragma unroll
+            for (int g = 0; g < DN_G; ++g)
+#pragma unroll
+                for (int u = 0; u < NU; ++u) acc[g][u] = (acc4f_t){0.f, 0.f, 0.f, 0.f};
+            if (STEPS) {
+#pragma unroll
+                for (int st = 0; st < STEPS; ++st) {
+                    if (st >= steps) break;
+#pragma unroll
+                    for (int u = 0; u < NU; ++u) {
+                        const half8_t bv = wcopy[NU * hf + u][slot + 4 * st];
+#pragma unroll
+                        for (int g = 0; g < DN_G; ++g)
+                            acc[g][u] = __builtin_amdgcn_mfma_f32_16x16x32_f16(areg[st][g], bv,
+                                                                               acc[g][u], 0, 0, 0);
+                    }
+                }
+            } else {
+                for (int st = 0; st < steps; ++st) {
+                    half8_t av[DN_G];
+#pragma unroll
+                    for (int g = 0; g < DN_G; ++g)
+                        av[g] = *(const half8_t*)(ap + 16 * g * stride + 32 * st);
+#pragma unroll
+                    for (int u = 0; u < NU; ++u) {
+                        const half8_t bv = wcopy[NU * hf + u][slot + 4 * st];
+#pragma unroll
+                        for (int g = 0; g < DN_G; ++g)
+                            acc[g][u] = __builtin_amdgcn_mfma_f32_16x16x32_f16(av[g], bv, acc[g][u],
+                                                                               0, 0, 0);
+                    }
+                }
+            }
+            // lane: rows 16 g + 4 ka + r, columns jl + u
+            float gj[NU];
+#pragma unroll
+            for (int u = 0; u < NU; ++u) gj[u] = gjs[w * EX_COLS + 8 * ca + NU * hf + u];
+            if (!edge) {
+#pragma unroll
+                for (int g = 0; g < DN_G; ++g)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        float v = mx[4 * g + r];
+#pragma unroll
+                        for (int u = 0; u < NU; ++u) v = fmaxf(v, acc[g][u][r] * gj[u]);
+                        mx[4 * g + r] = v;
+                    }
+            } else {
+                const int32_t jl = (int32_t)jb + 8 * ca + NU * hf;
+#pragma unroll
+                for (int g = 0; g < DN_G; ++g)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const int32_t i = rows[16 * g + 4 * ka + r];
+#pragma unroll
+                        for (int u = 0; u < NU; ++u) {
+                            const int32_t j = jl + u;
+                            const bool ok = (int64_t)j < N && (j <= i - m || j >= i + m);
+                            mx[4 * g + r] = fmaxf(mx[4 * g + r], ok ? acc[g][u][r] * gj[u] : -4.0f);
+                        }
+                    }
+            }
+        }
+        em_max = fmaxf(em_max, em);
+        float any = -4.0f;
+#pragma unroll
+        for (int q = 0; q < 4 * DN_G; ++q) {
+            ubr[q] = fmaxf(ubr[q], mx[q] + em);  // (-4 + em: no pair yet)
+            any = fmaxf(any, mx[q]);
+        }
+        if (__ballot(any + em > thr) != 0ull) {
+#pragma unroll 1
+            for (int q = 0; q < 4 * DN_G; ++q) {
+                float v = mx[0];
+#pragma unroll
+                for (int e = 1; e < 4 * DN_G; ++e) v = q == e ? mx[e] : v;
+                if (!(v + em > thr)) continue;
+                const int rr = 16 * (q >> 2) + 4 * ka + (q & 3);
+                const int2 pr = make_int2(rows[rr], (int32_t)jb + 8 * ca);
+                const unsigned int p = atomicAdd(npair_p, 1u);
+                if (p < (unsigned int)DN_BUF) {
+                    buf[p] = pr;
+                } else {  // (buffer full)
+                    const unsigned int gp = atomicAdd(&c->npairs, 1u);
+                    if ((int64_t)gp < dense_pairs(s.Npad)) s.pairs[gp] = pr;
+                }
+                if (v - em > thr) atomicOr(dead_p, 1ull << rr);  // surely closer than r
+            }
+        }
+        ev += (unsigned long long)DN_ROWS * EX_COLS;
+    }
+    __syncthreads();
+    flush();
+    // the rows' upper bounds over this segment; a row's largest correlation is
+    // at least that less twice the error of the block that gave it
+#pragma unroll
+    for (int q = 0; q < 4 * DN_G; ++q) {
+#pragma unroll
+        for (int o = 8; o >= 1; o >>= 1) ubr[q] = fmaxf(ubr[q], __shfl_xor(ubr[q], o));
+        if (ca == 0) {
+            bnd[0][w][16 * (q >> 2) + 4 * ka + (q & 3)] = ubr[q];
+            bnd[1][w][16 * (q >> 2) + 4 * ka + (q & 3)] = ubr[q] - 2.01f * em_max;
+        }
+    }
+    __syncthreads();
+    if (tid < DN_ROWS && !((*dead_p >> tid) & 1ull)) {
+        float u = -4.0f, l = -4.0f;
+        for (int q = 0; q < SC_WAVES; ++q) {
+            u = fmaxf(u, bnd[0][q][tid]);
+            l = fmaxf(l, bnd[1][q][tid]);
+        }
+        const int64_t i = rows[tid];
+        if (u > -2.0f) {
+            atomicMax(&s.rhs[i], ord_of((double)u));
+            atomicMax(&s.rho[i], ord_of((double)l));
+        }
+    }
+    if (lane == 0 && ev)
+        atomicAdd(&s.evc[EV_FAR * EV_SLOTS + ((blockIdx.x + w) & (EV_SLOTS - 1))], ev);
+}
+
+// Row tiles of a series' list.
+__device__ __forceinline__ int64_t dense_tiles(const Ctrl* c)
+{
+    return c->active && !lean_round(c) && dense_round(c) && c->handled
+               ? ((int64_t)c->ndense + DN_ROWS - 1) / DN_ROWS
+               : 0;
+}
+
+// First row tile of every series (one block; one series needs no table).
+__global__ __launch_bounds__(ITEMS_BLOCK) void k_dense_items(SeriesDev* S, int B, int64_t* pfx)
+{
+    __shared__ long long ws[ITEMS_BLOCK / 64];
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    long long base = 0;
+    for (int b0 = 0; b0 < B; b0 += ITEMS_BLOCK) {
+        const int b = b0 + tid;
+        const long long v = b < B ? dense_tiles(S[b].ctrl) : 0;
+        long long x = v;
+        for (int o = 1; o < 64; o <<= 1) {
+            const long long y = __shfl_up(x, o);
+            if (lane >= o) x += y;
+        }
+        if (lane == 63) ws[w] = x;
+        __syncthreads();
+        long long before = 0, tot = 0;
+        for (int e = 0; e < ITEMS_BLOCK / 64; ++e) {
+            before += e < w ? ws[e] : 0;
+            tot += ws[e];
+        }
+        if (b < B) pfx[b] = base + before + x - v;
+        base += tot;
+        __syncthreads();
+    }
+    if (tid == 0) pfx[B] = base;
+}
+
+__global__ __launch_bounds__(64 * SC_WAVES, 2) void k_dense(SeriesDev* S, int B,
+                                                            const int64_t* __restrict__ pfx)
+{
+    extern __shared__ _Float16 dxa[];  // [DN_ROWS][dense_stride(m)]
+    __shared__ half8_t wcopy[8][SC_SLOTS];
+    __shared__ double raw[DN_RAW];
+    __shared__ float gjs[SC_COLS];
+    __shared__ double rlo[SC_WAVES], rhi[SC_WAVES];
+    __shared__ int32_t rows[DN_ROWS];
+    __shared__ float bnd[2][SC_WAVES][DN_ROWS];
+    __shared__ unsigned long long dead_s;
+    __shared__ unsigned int npair_s, gbase_s;
+    __shared__ int2 buf[DN_BUF];
+    const int64_t tiles = B == 1 ? dense_tiles(S[0].ctrl) : pfx[B];
+    if (tiles == 0) return;
+    // column segments: a few items per workgroup
+    const int segs = (int)std::min<int64_t>(16, std::max<int64_t>(1, 3 * (int64_t)gridDim.x / tiles));
+    for (int64_t it = blockIdx.x; it < tiles * segs; it += gridDim.x) {
+        const int64_t t = it % tiles;
+        const int seg = (int)(it / tiles);
+        const int b = B == 1 ? 0 : series_of(pfx, B, t);
+        const SeriesDev& s = S[b];
+        Ctrl* c = s.ctrl;
+        const int64_t tile = t - (B == 1 ? 0 : pfx[b]);
+#define DENSE_ITEM(ST)                                                                        \
+    dense_item<ST>(s, c, tile, seg, segs, dxa, wcopy, gjs, raw, rlo, rhi, rows, bnd, &dead_s, \
+                   &npair_s, &gbase_s, buf)
+        switch ((c->m + 31) >> 5) {
+        case 2:
+        case 3:
+        case 4: DENSE_ITEM(4); break;
+        default: DENSE_ITEM(0); break;
+        }
+#undef DENSE_ITEM
+    }
+}
+
+// The rows handed over, by direct FP64 dot products with the eight columns of
+// each entry, eight lanes per column, one wave per entry: the best one above
+// the threshold prunes the row and becomes its witness.
+__global__ __launch_bounds__(RESCUE_BLOCK) void k_pairs(SeriesDev* S, int B)
+{
+    const int lane = threadIdx.x & 63;
+    const int sub = lane & 7, cq = lane >> 3;
+    const int64_t wave = (int64_t)blockIdx.x * (RESCUE_BLOCK / 64) + (threadIdx.x >> 6);
+    const int64_t nwaves = (int64_t)gridDim.x * (RESCUE_BLOCK / 64);
+    const int64_t nper = std::max<int64_t>(1, nwaves / B);
+    for (int64_t b = wave / nper; b < B; b += nwaves / nper) {
+        const SeriesDev& s = S[b];
+        Ctrl* c = s.ctrl;
+        if (!c->active || lean_round(c) || !dense_round(c) || !c->handled) continue;
+        const int32_t m = c->m;
+        const int64_t N = s.n - m + 1;
+        const int64_t np = std::min<int64_t>(c->npairs, dense_pairs(s.Npad));
+        const double* __restrict__ T = s.T;
+        const double* __restrict__ mu = cur_mu(s, c);
+        const double* __restrict__ inv = s.inv64;
+        const double thr = c->thr64;
+        for (int64_t p = wave % nper; p < np; p += nper) {
+            const int2 pr = s.pairs[p];
+            const int64_t i = pr.x, j = (int64_t)pr.y + cq;
+            if (!((load_word(&s.alive[i >> 6]) >> (i & 63)) & 1ull)) continue;
+            const bool ok = j < N && (j <= i - m || j >= i + m);
+            double C = 0.0, rho = -4.0;
+            if (ok) {
+                const double mi = mu[i], mj = mu[j];
+                for (int k = sub; k < m; k += 8) C = fma(T[i + k] - mi, T[j + k] - mj, C);
+            }
+#pragma unroll
+            for (int o = 4; o >= 1; o >>= 1) C += __shfl_xor(C, o);
+            if (ok) rho = pair_rho(C, inv[i], inv[j]);
+            double br = rho;
+            int bq = cq;
+#pragma unroll
+            for (int o = 8; o <= 32; o <<= 1) {
+                const double r2 = __shfl_xor(br, o);
+                const int q2 = __shfl_xor(bq, o);
+                if (r2 > br || (r2 == br && q2 < bq)) {
+                    br = r2;
+                    bq = q2;
+                }
+            }
+            if (br > thr && sub == 0 && cq == bq) {
+                // (~j: several entries of a row may land here at once, and an index
+                // and a covariance stored apart could come from different ones)
+                s.wit[i] = ~(int32_t)j;
+                atomicAnd(&s.alive[i >> 6], ~(1ull << (i & 63)));
+            }
+        }
+    }
+}
+
+// After a dense round (one block per series): the number of range discords,
+// and as candidates every one whose lower bound does not exceed the k-th
+// smallest upper bound (rhs, rho: upper and lower bounds of the largest
+// correlation).  The k-th smallest by k rounds of the block's minimum, each
+// thread holding its own; only the winner looks for its next.
+__global__ __launch_bounds__(TOPK_BLOCK) void k_dense_top(SeriesDev* S)
+{
+    constexpr int NW = TOPK_BLOCK / 64;
+    __shared__ unsigned long long wu[NW];
+    __shared__ long long wi[NW];
+    __shared__ unsigned int cnt_s, nc_s;
+    const SeriesDev& s = S[blockIdx.x];
+    Ctrl* c = s.ctrl;
+    if (!c->active || lean_round(c) || !dense_round(c) || !c->handled) return;
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const int64_t nw = (s.n - c->m + 1 + 63) / 64;
+    const int k = s.k;
+    if (tid == 0) cnt_s = nc_s = 0;
+    __syncthreads();
+    unsigned int cnt = 0;
+    // this thread's smallest key after `last`
+    auto next_of = [&](const Key& last, bool count) {
+        Key best = {~0ull, KEY_NONE};
+        scan_words(s.alive, nw, [&](int64_t q, unsigned long long bits) {
+            if (count) cnt += (unsigned int)__popcll(bits);
+            while (bits) {
+                const int t = __ffsll((long long)bits) - 1;
+                bits &= bits - 1ull;
+                const Key x = {s.rhs[q * 64 + t], q * 64 + t};
+                if (key_less(last, x) && key_less(x, best)) best = x;
+            }
+        });
+        return best;
+    };
+    Key mine = next_of(Key{0ull, -1}, true);
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) cnt += __shfl_xor(cnt, o);
+    if (lane == 0) atomicAdd(&cnt_s, cnt);
+    __syncthreads();
+    const unsigned int ns = cnt_s;
+    if (tid == 0) {
+        c->live_ref = 0xffffffffu;  // not a direct round: every live row is a range discord
+        c->rows_far += ns;
+        c->nsurv = ns;
+        c->ncand = 0;
+    }
+    const bool lost = (int64_t)c->npairs > dense_pairs(s.Npad);
+    if (ns < (unsigned int)k && !lost) return;
+    Key kth = {0ull, -1};
+    for (int r = 0; r < k && !lost; ++r) {
+        const Key v = wave_min_key(mine);
+        if (lane == 0) {
+            wu[w] = v.u;
+            wi[w] = v.i;
+        }
+        __syncthreads();
+        kth = Key{wu[0], wi[0]};
+        for (int q = 1; q < NW; ++q) {
+            const Key x = {wu[q], wi[q]};
+            if (key_less(x, kth)) kth = x;
+        }
+        __syncthreads();
+        if (mine.i == kth.i && r + 1 < k) mine = next_of(kth, false);
+    }
+    if (!lost)
+        scan_words(s.alive, nw, [&](int64_t q, unsigned long long bits) {
+            while (bits) {
+                const int t = __ffsll((long long)bits) - 1;
+                bits &= bits - 1ull;
+                const int64_t i = q * 64 + t;
+                if (s.rho[i] <= kth.u) {
+                    const unsigned int slot = atomicAdd(&nc_s, 1u);
+                    if (slot < (unsigned int)CAND_MAX) s.cand[slot] = i;
+                }
+            }
+        });
+    __syncthreads();
+    if (tid == 0) {
+        if (lost || nc_s > (unsigned int)CAND_MAX) {
+            c->band_over = 1;  // the range again, with sweeps
+            c->dense = DENSE_OFF;
+        } else {
+            c->ncand = nc_s;
+        }
+    }
+}
+
 // Close the round of every series (one block each): reduce the exact pass's
 // partials to each candidate's (rho, j), rank the candidates, write the
 // length's top-k rows when the round found at least k range discords, lower
@@ -3256,12 +3955,14 @@ __global__ __launch_bounds__(END_BLOCK) void k_round_end(SeriesDev* S, int32_t* 
         return;
     }
     const bool lean = lean_round(c);
-    if (!full && !lean) {
+    if (!full && !lean && !c->handled) {
         if (tid == 0) {
             c->pending = 1;
+            if (c->dense == DENSE_NO && dense_allowed(s, c)) c->dense = DENSE_LEFT;
             atomicAdd(&rem[REM_LEFT], 1);
             atomicAdd(&rem[REM_PENDING], 1);
-            if (c->li == 0) atomicAdd(&rem[REM_FIRST], 1);
+            if (c->dense != DENSE_LEFT) atomicAdd(&rem[REM_SWEEP], 1);
+            if (dense_round(c)) atomicAdd(&rem[REM_DENSE], 1);
         }
         return;
     }
@@ -3400,7 +4101,7 @@ __global__ __launch_bounds__(END_BLOCK) void k_round_end(SeriesDev* S, int32_t* 
             c->done = 0;
         }
     }
-    if (full && !lean) {
+    if (full && !lean && !c->handled) {
         // Hot tiles of hot_rows rows, in ascending order (the first HOT_MAX of
         // them): those that still hold survivors or whose first-pass items swept
         // at least N / HOT_FRAC columns this round.  The next sweep's first
@@ -3804,7 +4505,7 @@ hipError_t launch_start(const Batch& bt, const SweepCfg& cfg, hipStream_t st)
 // Without `full` the sweeps are left out: a series that needs them waits for
 // the next full round.  more = 0: a bare range search.
 hipError_t launch_round(const Batch& bt, const SweepCfg& cfg, const int64_t* total, bool full,
-                        bool more, hipStream_t st)
+                        bool dense, bool more, hipStream_t st)
 {
     const unsigned int elem = (unsigned int)total[PFX_ELEM];
     cfg.timer->begin(4, st);
@@ -3829,6 +4530,18 @@ hipError_t launch_round(const Batch& bt, const SweepCfg& cfg, const int64_t* tot
             launch_refine_q<false>(bt, cfg, total, st);
         }
         hipLaunchKernelGGL(k_select_top, dim3(bt.B), dim3(TOPK_BLOCK), 0, st, bt.s);
+    }
+    if (dense) {
+        cfg.timer->begin(1, st);
+        hipLaunchKernelGGL(k_dense_list, dim3(bt.B), dim3(TOPK_BLOCK), 0, st, bt.s, full ? 1 : 0);
+        if (bt.B > 1)
+            hipLaunchKernelGGL(k_dense_items, dim3(1), dim3(ITEMS_BLOCK), 0, st, bt.s, bt.B, bt.ipfx);
+        hipLaunchKernelGGL(k_dense, dim3(DENSE_GRID), dim3(64 * SC_WAVES),
+                           sizeof(_Float16) * DN_ROWS * dense_stride(std::min(bt.maxL_all, DENSE_MAXM)),
+                           st, bt.s, bt.B, bt.ipfx);
+        hipLaunchKernelGGL(k_pairs, dim3(RESCUE_GRID), dim3(RESCUE_BLOCK), 0, st, bt.s, bt.B);
+        hipLaunchKernelGGL(k_dense_top, dim3(bt.B), dim3(TOPK_BLOCK), 0, st, bt.s);
+        cfg.timer->end(1, st);
     }
     launch_exact(bt, cfg, full ? 1 : 0, st);
     hipLaunchKernelGGL(k_round_end, dim3(bt.B), dim3(END_BLOCK), 0, st, bt.s, bt.remaining,
@@ -4291,6 +5004,7 @@ SeriesDev carve(void* base, const Layout& l)
     s.lbp = (float*)(p + l.off_lbp);
     s.ub = (float*)s.df64;         // free outside a round's sweeps (see make_layout)
     s.fail = (int32_t*)s.df32;     // likewise
+    s.pairs = (int2*)s.df64;       // likewise (df64, dg64)
     s.wit = (int32_t*)(p + l.off_wit);
     s.wc = (double*)(p + l.off_wc);
     s.hist = (double*)(p + l.off_hist);
@@ -4304,8 +5018,9 @@ SeriesDev carve(void* base, const Layout& l)
 void series_blocks(const Layout& l, const SweepCfg& cfg, int64_t out[PFX_KINDS])
 {
     const int rn = 64 * cfg.q_near, rf = 64 * cfg.q_far, rr = 64 * cfg.q_ref;
-    // chunks of the first pass: near_cols, at most every column
-    const int64_t span = std::min<int64_t>((int64_t)cfg.near_cols, l.Nmax);
+    // chunks of the first pass: near_cols (or a dense round's), at most every column
+    const int64_t wide = l.Nmax <= DENSE_NEAR_MAXN ? std::max(cfg.near_cols, DENSE_NEAR) : cfg.near_cols;
+    const int64_t span = std::min<int64_t>(wide, l.Nmax);
     const int64_t nsub = (span + cfg.chunk_cols - 1) / cfg.chunk_cols;
     out[PFX_ELEM] = (l.Npad + 64 + 255) / 256;
     out[PFX_NEAR] = ((l.Nmax + rn - 1) / rn) * nsub;

@@ -168,3 +168,32 @@ def test_refinement_items_of_one_column(one_past):
     far = ~close_ed(P, np.full_like(P, r), m)
     member = out["heat"].cpu().numpy()[0, :N] > 0.0
     np.testing.assert_array_equal(member[far], (P >= r)[far])
+
+
+@pytest.mark.parametrize("minL", [31, 64, 96, 127, 255])
+@pytest.mark.parametrize("N", [1025, 1088, 1537, 8193])
+def test_many_range_discords_match_the_heatmaps_sweeps(N, minL):
+    """White noise: at the second range most or all subsequences are range
+    discords, which a plain search bounds on the matrix cores and a heatmap
+    sweeps for.  Lists one past a tile of 64 rows, columns one past a chunk of
+    512, windows around the operand steps of 32 and around 128 and 256."""
+    from paper_2304_01660_amd import api
+    dev = _dev()
+    k, n = 2, N + minL - 1
+    T = np.random.default_rng([N, minL]).standard_normal(n)
+    T[n // 2:n // 2 + minL + 3] = T[n // 2]       # flat rows, each other's neighbours
+    T[5:5 + minL] = T[n - 40 - minL:n - 40]       # a pair without distance
+    _say("dense", N, minL)
+    Td = torch.from_numpy(T).to(dev)
+    plain = api.discords(Td, minL, minL + 2, k)
+    swept = api.discord_heatmap(Td, minL, minL + 2, k)
+    for key in ("idx", "len", "nn_dist", "nn_idx", "count"):
+        assert torch.equal(plain[key], swept[key]), key
+    r = float(swept["range"][0])
+    P = _profile(T, minL, dev)
+    far = ~close_ed(P, np.full_like(P, r), minL)
+    if r > 0 and bool(far.all()):
+        assert int(plain["count"][0]) == int((P >= r).sum())
+    res = api.discords_batched([Td, Td[:n - 1].contiguous()], [minL] * 2, [minL + 2] * 2, k)
+    for key in ("idx", "len", "nn_dist", "nn_idx", "count"):
+        assert torch.equal(res[0][key], plain[key]), key
