@@ -395,7 +395,8 @@ int palmad_selection_drift(palmad_ctx* ctx, const double* T, int64_t n, int32_t 
  * palmad_stream_workspace_size: bytes of device workspace for a stream
  *   (pure host; PALMAD_EINVAL for arguments palmad_workspace_size() would
  *   reject with n = capacity).  About 8 L bytes per point beyond a search's
- *   workspace (L = maxL - minL + 1).
+ *   workspace (L = maxL - minL + 1); below 262,144 points, where several
+ *   lengths are handled together, beyond that of up to 15 searches.
  * palmad_stream_create: a stream on the context's device; workspace (device,
  *   256-byte aligned) must stay valid and unused by anything else until
  *   palmad_stream_destroy().  *out receives the handle (host memory).

@@ -320,8 +320,8 @@ struct Outputs {
 };
 
 // Write the descriptors and prefix tables into the workspace (one upload).
-// n_now (optional): the current length of each series when it is shorter
-// than the length its layout was planned for (a streaming series).
+// n_now (optional): a streaming series, all descriptors of one series whose
+// current length is shorter than the length its layout was planned for.
 int upload(palmad_ctx* ctx, const Plan& p, void* ws, const double* const* Tin, const Outputs* outs,
            Batch* bt, const int64_t* n_now = nullptr)
 {
@@ -334,16 +334,20 @@ int upload(palmad_ctx* ctx, const Plan& p, void* ws, const double* const* Tin, c
     for (int b = 0; b < p.B; ++b) {
         SeriesDev s = carve((char*)ws + p.base[b], p.lay[b]);
         s.Tin = Tin ? Tin[b] : nullptr;
-        if (n_now) s.n = n_now[b];
+        if (n_now) {
+            s.n = *n_now;
+            s.T = b > 0 ? d[0].T : s.T;
+        }
         if (outs) {
-            s.idx = outs[b].idx;
-            s.len = outs[b].len;
-            s.nn = outs[b].nn;
-            s.nnidx = outs[b].nnidx;
-            s.count = outs[b].count;
-            s.heat = outs[b].heat;
-            s.rlen = outs[b].rlen;
-            s.heat_ld = outs[b].heat_ld;
+            const Outputs& o = outs[n_now ? 0 : b];
+            s.idx = o.idx;
+            s.len = o.len;
+            s.nn = o.nn;
+            s.nnidx = o.nnidx;
+            s.count = o.count;
+            s.heat = o.heat;
+            s.rlen = o.rlen;
+            s.heat_ld = o.heat_ld;
         }
         d[b] = s;
     }
@@ -627,8 +631,20 @@ struct palmad_stream {
 
 namespace {
 
-// Workspace of a stream: the search layout of a series of `cap` points,
-// then the L profiles, then a small scratch.
+// Plan of a stream: one descriptor per length handled together (see
+// k_stream_group).  A long series fills the machine with one length, whose
+// workspace then stays that of one search.
+void stream_plan(int64_t cap, int32_t minL, int32_t maxL, int32_t k, const SweepCfg& cfg, Plan* p)
+{
+    const int64_t N = cap - minL + 1, L = maxL - minL + 1;
+    int64_t lanes = std::min<int64_t>({STREAM_LANES, L, (STREAM_ROWS + N - 1) / N});
+    lanes -= lanes % 2 == 0 ? 1 : 0;
+    const std::vector<int64_t> n((size_t)lanes, cap);
+    const std::vector<int32_t> lo((size_t)lanes, minL), hi((size_t)lanes, maxL);
+    make_plan((int)lanes, n.data(), lo.data(), hi.data(), k, cfg, p);
+}
+
+// Workspace of a stream: its plan's, then the L profiles, then a small scratch.
 size_t stream_bytes(const Plan& p, int32_t L, size_t* off_prof, size_t* off_flag)
 {
     *off_prof = al256(p.total);
@@ -638,8 +654,7 @@ size_t stream_bytes(const Plan& p, int32_t L, size_t* off_prof, size_t* off_flag
 
 int stream_batch(palmad_stream* st, const Outputs* outs, Batch* bt)
 {
-    const double* none = nullptr;
-    return upload(st->ctx, st->p, st->ws, &none, outs, bt, &st->n);
+    return upload(st->ctx, st->p, st->ws, nullptr, outs, bt, &st->n);
 }
 
 }  // namespace
@@ -1204,7 +1219,7 @@ int palmad_stream_workspace_size(int64_t capacity, int32_t minL, int32_t maxL, i
     rc = read_opts(nullptr, opts, &o);
     if (rc) return rc;
     Plan p;
-    make_plan(1, &capacity, &minL, &maxL, k, cfg_of(o, nullptr), &p);
+    stream_plan(capacity, minL, maxL, k, cfg_of(o, nullptr), &p);
     size_t a, b;
     *bytes = stream_bytes(p, maxL - minL + 1, &a, &b);
     return PALMAD_OK;
@@ -1231,7 +1246,7 @@ int palmad_stream_create(palmad_ctx* ctx, int64_t capacity, int32_t minL, int32_
     st->minL = minL;
     st->maxL = maxL;
     st->k = k;
-    make_plan(1, &capacity, &minL, &maxL, k, cfg_of(o, nullptr), &st->p);
+    stream_plan(capacity, minL, maxL, k, cfg_of(o, nullptr), &st->p);
     size_t off_prof, off_flag;
     const size_t need = stream_bytes(st->p, maxL - minL + 1, &off_prof, &off_flag);
     rc = check_ws(ctx, workspace, ws_bytes, need);
@@ -1306,7 +1321,7 @@ int palmad_stream_append(palmad_stream* st, const double* values, int64_t count,
     SweepCfg cfg = cfg_of(st->o, nullptr);
     HIP_TRY(launch_stream_append(bt, values, n_old, count, ctx->work));
     HIP_TRY(launch_stream_update(bt, cfg, st->p.totals, st->minL, st->maxL, st->prof, n_old,
-                                 ctx->work));
+                                 st->n, ctx->work));
     HIP_TRY(hipStreamSynchronize(ctx->work));
     return leave(ctx, stream);
 }
@@ -1346,7 +1361,7 @@ int palmad_stream_profile(palmad_stream* st, int32_t m, double* nn_dist, void* s
     Batch bt;
     rc = stream_batch(st, nullptr, &bt);
     if (rc) return rc;
-    HIP_TRY(launch_stream_profile(bt, st->p.totals, st->minL, m, st->prof, nn_dist, ctx->work));
+    HIP_TRY(launch_stream_profile(bt, m, st->prof, nn_dist, ctx->work));
     HIP_TRY(hipStreamSynchronize(ctx->work));
     return leave(ctx, stream);
 }

@@ -57,6 +57,16 @@ constexpr int DENSE_MAXM = 256;
 constexpr int DENSE_NEAR = 16384;             // columns of its first pass at the second range,
 constexpr int64_t DENSE_NEAR_MAXN = 131072;   // for series of at most so many subsequences
 __host__ __device__ constexpr int64_t dense_pairs(int64_t Npad) { return 2 * Npad; }
+// Streaming series: lengths handled together so that one launch holds about
+// STREAM_ROWS rows, an odd number of at most STREAM_LANES; the profile
+// update's longest chunk of columns, the items it should have, and its
+// workgroups (30,000 points, nine lengths: 4096 workgroups and chunks of 512
+// 1.06 ms, 16384 and 2048 0.80).
+constexpr int64_t STREAM_ROWS = 262144;
+constexpr int STREAM_LANES = 15;
+constexpr int STREAM_CHUNK = 2048;
+constexpr int64_t STREAM_ITEMS = 4096;
+constexpr int STREAM_GRID = 16384;
 constexpr int RESCUE_GRID = 2048, RESCUE_BLOCK = 256;
 constexpr int TOPK_BLOCK = 1024;
 constexpr int RED_BLOCKS = 256;   // series reductions: blocks of 256 threads
@@ -290,12 +300,12 @@ hipError_t launch_adjoint(const double* Tpad, int64_t n, int64_t K, int32_t maxm
 // from the profiles, one length's profile as distances, and a fill.
 hipError_t launch_stream_update(const Batch& bt, const SweepCfg& cfg, const int64_t* total,
                                 int32_t minL, int32_t maxL, unsigned long long* prof,
-                                int64_t n_old, hipStream_t st);
+                                int64_t n_old, int64_t n, hipStream_t st);
 hipError_t launch_stream_query(const Batch& bt, const SweepCfg& cfg, const int64_t* total,
                                int32_t minL, int32_t maxL, const unsigned long long* prof,
                                hipStream_t st);
-hipError_t launch_stream_profile(const Batch& bt, const int64_t* total, int32_t minL, int32_t m,
-                                 const unsigned long long* prof, double* nn, hipStream_t st);
+hipError_t launch_stream_profile(const Batch& bt, int32_t m, const unsigned long long* prof,
+                                 double* nn, hipStream_t st);
 hipError_t launch_fill_u64(unsigned long long* p, int64_t count, unsigned long long v,
                            hipStream_t st);
 // Control blocks, histories, counters and bitmaps of every series to zero.

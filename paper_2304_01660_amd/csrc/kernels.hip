@@ -4294,87 +4294,246 @@ __global__ void k_drift_band(SeriesDev* S, float guard, double* out)
 // only re-derives their maxima.  The refinement sweep does the work with
 // pruning off; every row's running maximum of rho stays in its length's
 // profile (ordered bits, prof[(m - minL) Npad + i]).
+//
+// One length of a series of tens of thousands of points does not fill the
+// machine (30,000 points: 3,500 items of 128 rows and 1,024 columns), and a
+// kernel per length and step costs as much as its work, so `lanes` lengths go
+// together: the batch holds one descriptor per lane, which share the series,
+// lane b at length m0 + b.  (30,000 points, 33 lengths, three appends and
+// queries: a length at a time 36 ms, nine 10.9.  The profile update takes 175
+// us per length alone and 93 of nine, of which its FP64 operations, four per
+// pair and side, are 31.)
+
+// The lanes' lengths m0, m0 + 1, ... up to maxL (one block).
+__global__ void k_stream_group(SeriesDev* S, int lanes, int32_t m0, int32_t maxL)
+{
+    const int b = threadIdx.x;
+    if (b >= lanes) return;
+    const SeriesDev& s = S[b];
+    Ctrl* c = s.ctrl;
+    const double eps = S[0].ctrl->flat_eps;
+    c->m = m0 + b;
+    c->li = c->m - s.minL;
+    c->active = c->m <= maxL ? 1 : 0;
+    c->flat_eps = eps;
+    c->flat_min = 0x7fffffffffffffffll;
+    c->flat_max = -1;
+    // a round without pruning whose candidates k_stream_pick chooses
+    c->mode = 3;
+    c->r = 0.0;
+    c->prune = 0;
+    c->thr64 = c->thr_sel = 2.0;
+    c->thr32 = 2.0f;
+    c->exact_ref = 0;
+    c->band_over = 0;
+    c->live_ref = 0xffffffffu;  // not a direct round
+    c->nlive = 0xffffffffu;
+    c->handled = 1;
+    c->nsurv = c->ncand = 0;
+    c->done = 0;
+    for (int g = 0; g < CAND_GROUPS; ++g) c->pcnt[g] = 0;
+}
+
+// Statistics and helpers of the lanes' lengths, as k_length computes them one
+// length at a time: a thread carries window i and its right neighbour through
+// the lengths.  The group before left its last length's mean and variance
+// with the last lane (`lanes` is odd, so that its two buffers alternate).
+__global__ __launch_bounds__(256) void k_stream_stats(SeriesDev* S, int lanes, int32_t m0,
+                                                      int32_t maxL)
+{
+    const SeriesDev& s = S[0];
+    const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    const double* __restrict__ T = s.T;
+    const double feps = s.ctrl->flat_eps;
+    double mean0 = 0.0, v0 = 0.0, mean1 = 0.0, v1 = 0.0;
+    if (m0 > s.minL && i < s.n - m0 + 2) {  // (length m0 - 1)
+        const SeriesDev& p = S[lanes - 1];
+        const bool odd = ((m0 - 1 - s.minL) & 1) != 0;
+        const double* mu_o = odd ? p.mu2 : p.mu;
+        const double* var_o = odd ? p.var2 : p.var;
+        mean0 = mu_o[i];
+        v0 = var_o[i];
+        if (i + 1 < s.n - m0 + 2) {
+            mean1 = mu_o[i + 1];
+            v1 = var_o[i + 1];
+        }
+    }
+    for (int b = 0; b < lanes && m0 + b <= maxL; ++b) {
+        const SeriesDev& sb = S[b];
+        Ctrl* c = sb.ctrl;
+        const int32_t m = m0 + b;
+        const int64_t N = s.n - m + 1;
+        if (i < sb.Npad + 64) {
+            double a0 = 0.0, q0 = 0.0, a1 = 0.0, q1 = 0.0;
+            if (i < N) {
+                if (m == s.minL) {
+                    direct_stats(T, i, m, a0, q0);
+                    if (i + 1 < N) direct_stats(T, i + 1, m, a1, q1);
+                } else {
+                    const GrowBy g = grow_by(m);
+                    grow_stats(T[i + m - 1], g, mean0, v0, a0, q0);
+                    if (i + 1 < N) grow_stats(T[i + m], g, mean1, v1, a1, q1);
+                }
+            }
+            mean0 = a0;
+            v0 = q0;
+            mean1 = a1;
+            v1 = q1;
+            const bool odd = ((m - s.minL) & 1) != 0;
+            (odd ? sb.mu2 : sb.mu)[i] = mean0;
+            if (b == lanes - 1) (odd ? sb.var2 : sb.var)[i] = v0;
+            double df = 0.0, dg = 0.0, inv = 0.0;
+            if (i < N - 1) {
+                const double a = T[i + m], e = T[i];
+                df = (a - e) * 0.5;
+                dg = (a - mean1) + (e - mean0);
+            }
+            if (i < N) {
+                const double sg = sqrt(v0);
+                if (sg <= feps) {
+                    atomicMin((long long*)&c->flat_min, (long long)i);
+                    atomicMax((long long*)&c->flat_max, (long long)i);
+                } else {
+                    inv = 1.0 / (sqrt((double)m) * sg);
+                }
+            }
+            sb.df64[i] = df;
+            sb.dg64[i] = dg;
+            sb.inv64[i] = inv;
+        }
+        if (i < sb.nwords) {
+            const int64_t lo = i * 64;
+            sb.alive[i] = lo + 64 <= N ? ~0ull : lo < N ? (1ull << (N - lo)) - 1ull : 0ull;
+        }
+    }
+}
+
 template <int Q>
-__global__ __launch_bounds__(64, (Q <= 4 ? 3 : 1)) void k_stream_band(SeriesDev* S,
+__global__ __launch_bounds__(64, (Q <= 4 ? 3 : 1)) void k_stream_band(SeriesDev* S, int lanes,
                                                                       unsigned long long* prof,
                                                                       int64_t n_old, int chunk)
 {
     extern __shared__ double lds[];
     constexpr int R = 64 * Q;
-    const SeriesDev& s = S[0];
-    Ctrl* c = s.ctrl;
-    SweepArgs<double> A = args_of<double>(s, c);
-    A.rho = prof + (int64_t)c->li * s.Npad;
-    const int32_t m = A.m;
-    const int64_t N = A.N;
-    const int64_t Nold = std::max<int64_t>(0, n_old - m + 1);
-    if (Nold >= N) return;
-    const int64_t a0 = (Nold / R) * R;
-    const int64_t tA = (N - a0 + R - 1) / R;
-    const int64_t cA = (N + chunk - 1) / chunk;
-    const int64_t itemsA = tA * 2 * cA;
-    const int64_t tB = (Nold + R - 1) / R;
-    const int64_t cB = (N - Nold + chunk - 1) / chunk;
-    const int64_t total = itemsA + tB * cB;
-    unsigned long long ev = 0;
-    for (int64_t it = blockIdx.x; it < total; it += gridDim.x) {
-        int64_t i0, jbeg, jend;
-        bool left;
-        if (it < itemsA) {
-            const int64_t t = it % tA, r = it / tA;
-            const int64_t cc = r >> 1;
-            left = (r & 1) != 0;
-            i0 = a0 + t * R;
-            if (left) {
-                jend = std::min<int64_t>(N, i0 + R - m) - cc * chunk;
-                jbeg = std::max<int64_t>(0, jend - chunk);
+    unsigned long long cum = 0;  // items dealt out as in k_select_far
+    for (int b = 0; b < lanes; ++b) {
+        const SeriesDev& s = S[b];
+        Ctrl* c = s.ctrl;
+        if (!c->active) continue;
+        SweepArgs<double> A = args_of<double>(s, c);
+        A.rho = prof + (int64_t)c->li * s.Npad;
+        const int32_t m = A.m;
+        const int64_t N = A.N;
+        const int64_t Nold = std::max<int64_t>(0, n_old - m + 1);
+        if (Nold >= N) continue;
+        const int64_t a0 = (Nold / R) * R;
+        const int64_t tA = (N - a0 + R - 1) / R;
+        const int64_t cA = (N + chunk - 1) / chunk;
+        const int64_t itemsA = tA * 2 * cA;
+        const int64_t tB = (Nold + R - 1) / R;
+        const int64_t cB = (N - Nold + chunk - 1) / chunk;
+        const int64_t total = itemsA + tB * cB;
+        unsigned long long ev = 0;
+        const int64_t first = (int64_t)first_item(cum);
+        cum += (unsigned long long)total;
+        for (int64_t it = first; it < total; it += gridDim.x) {
+            int64_t i0, jbeg, jend;
+            bool left;
+            if (it < itemsA) {
+                const int64_t t = it % tA, r = it / tA;
+                const int64_t cc = r >> 1;
+                left = (r & 1) != 0;
+                i0 = a0 + t * R;
+                if (left) {
+                    jend = std::min<int64_t>(N, i0 + R - m) - cc * chunk;
+                    jbeg = std::max<int64_t>(0, jend - chunk);
+                } else {
+                    jbeg = i0 + m + cc * chunk;
+                    jend = std::min<int64_t>(N, jbeg + chunk);
+                }
             } else {
-                jbeg = i0 + m + cc * chunk;
+                const int64_t x = it - itemsA;
+                const int64_t t = x % tB, cc = x / tB;
+                i0 = t * R;
+                left = false;
+                jbeg = std::max<int64_t>(Nold, i0 + m) + cc * chunk;
                 jend = std::min<int64_t>(N, jbeg + chunk);
             }
-        } else {
-            const int64_t x = it - itemsA;
-            const int64_t t = x % tB, cc = x / tB;
-            i0 = t * R;
-            left = false;
-            jbeg = std::max<int64_t>(Nold, i0 + m) + cc * chunk;
-            jend = std::min<int64_t>(N, jbeg + chunk);
+            if (jbeg >= jend) continue;
+            ref_item<Q, HK_TILE>(A, i0, jbeg, jend, left, 2.0, 0, lds, ev);
         }
-        if (jbeg >= jend) continue;
-        ref_item<Q, HK_TILE>(A, i0, jbeg, jend, left, 2.0, 0, lds, ev);
+        if (threadIdx.x == 0 && ev)
+            atomicAdd(&s.evc[EV_REF * EV_SLOTS + (blockIdx.x & (EV_SLOTS - 1))], ev);
     }
-    if (threadIdx.x == 0 && ev)
-        atomicAdd(&s.evc[EV_REF * EV_SLOTS + (blockIdx.x & (EV_SLOTS - 1))], ev);
 }
 
-// A query at the current length: the profile becomes the round's row
-// maxima and every subsequence a live candidate (no pruning), so that
-// k_select_top, k_polish and k_round_end rank the profile, recompute the
-// best candidates exactly and write the length's top-k rows, as in a search
+// A query's candidates at every lane's length (a block each): the k + KP_EXTRA
+// rows of the smallest profile values, ties to the smaller index.  Each lane
+// of a wave holds its own smallest row, so a round of the wave's minimum costs
+// only the winner a rescan of its N / 1024 rows (a thread per bitmap word and
+// a rescan by every lane: 121 us at 30,000 points); wave 0 merges the waves'
+// lists.  The exact pass and k_round_end then write the length's rows, as in a
 // round without pruning.
-__global__ void k_stream_query(SeriesDev* S, const unsigned long long* __restrict__ prof)
+__global__ __launch_bounds__(TOPK_BLOCK) void k_stream_pick(SeriesDev* S,
+                                                            const unsigned long long* __restrict__ prof)
 {
-    const SeriesDev& s = S[0];
+    constexpr int NW = TOPK_BLOCK / 64;
+    __shared__ unsigned long long pu[NW * KP_MAX];
+    __shared__ long long pi[NW * KP_MAX];
+    const SeriesDev& s = S[blockIdx.x];
     Ctrl* c = s.ctrl;
+    if (!c->active) return;
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const int64_t N = s.n - c->m + 1;
-    const unsigned long long* p = prof + (int64_t)c->li * s.Npad;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < s.Npad;
-         i += (int64_t)gridDim.x * blockDim.x)
-        s.rho[i] = i < N ? p[i] : 0x000fffffffffffffull;
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-        c->mode = 3;
-        c->r = 0.0;
-        c->prune = 0;
-        c->thr64 = c->thr_sel = 2.0;
-        c->thr32 = 2.0f;
-        c->exact_ref = 0;
-        c->band_over = 0;
-        c->live_ref = 0xffffffffu;  // not a direct round
-        c->nlive = 0xffffffffu;
-        c->nsurv = c->ncand = 0;
-        c->done = 0;
+    const unsigned long long* __restrict__ p = prof + (int64_t)c->li * s.Npad;
+    const int kp = (int)std::min<int64_t>(N, s.k + KP_EXTRA);
+    // the smallest row of [tid, N) in steps of the block past `last`
+    auto next_of = [&](const Key& last) {
+        constexpr int U = 8;
+        Key best = {~0ull, KEY_NONE};
+        for (int64_t i0 = tid; i0 < N; i0 += U * TOPK_BLOCK) {
+            unsigned long long v[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int64_t i = i0 + (int64_t)u * TOPK_BLOCK;
+                v[u] = i < N ? p[i] : ~0ull;
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int64_t i = i0 + (int64_t)u * TOPK_BLOCK;
+                const Key x = {v[u], i};
+                if (i < N && key_less(last, x) && key_less(x, best)) best = x;
+            }
+        }
+        return best;
+    };
+    Key mine = next_of(Key{0ull, -1});
+    for (int r = 0; r < kp; ++r) {
+        const Key v = wave_min_key(mine);
+        if (lane == 0) {
+            pu[w * KP_MAX + r] = v.u;
+            pi[w * KP_MAX + r] = v.i;
+        }
+        if (mine.i == v.i && v.i != KEY_NONE && r + 1 < kp) mine = next_of(v);
     }
-    if (blockIdx.x == 0 && threadIdx.x < CAND_GROUPS) c->pcnt[threadIdx.x] = 0;
+    __syncthreads();
+    if (w != 0) return;
+    Key last = {0ull, -1};
+    for (int r = 0; r < kp; ++r) {
+        Key best = {~0ull, KEY_NONE};
+        for (int e = lane; e < NW * kp; e += 64) {
+            const int ww = e / kp, at = ww * KP_MAX + (e - ww * kp);
+            const Key x = {pu[at], pi[at]};
+            if (x.i != KEY_NONE && key_less(last, x) && key_less(x, best)) best = x;
+        }
+        best = wave_min_key(best);
+        if (lane == 0) s.cand[r] = best.i;
+        last = best;
+    }
+    if (lane == 0) {
+        c->nsurv = (uint32_t)N;
+        c->ncand = (uint32_t)kp;
+    }
 }
 
 // The exact profile of the current length as distances (Eq. (6)):
@@ -4574,27 +4733,42 @@ hipError_t launch_drift(const Batch& bt, const int64_t* total, int32_t minL, int
 // Streaming: one append's profile updates at every length (statistics,
 // helpers, band sweeps), a query's top-k rows at every length, the profile
 // of one length, and the reset of every profile.
+static void launch_stream_group(const Batch& bt, const int64_t* total, int32_t m0, int32_t maxL,
+                                hipStream_t st)
+{
+    hipLaunchKernelGGL(k_stream_group, dim3(1), dim3(64), 0, st, bt.s, bt.B, m0, maxL);
+    hipLaunchKernelGGL(k_stream_stats, dim3((unsigned int)(total[PFX_ELEM] / bt.B)), dim3(256), 0, st,
+                       bt.s, bt.B, m0, maxL);
+}
+
 template <int Q>
-static void launch_band(const Batch& bt, const SweepCfg& cfg, unsigned long long* prof,
-                        int64_t n_old, hipStream_t st)
+static void launch_band(const Batch& bt, unsigned long long* prof, int64_t n_old, int chunk,
+                        hipStream_t st)
 {
     const size_t lds = sizeof(double) * sweep_lds_doubles(bt.maxL_all, 64 * Q, (int)sizeof(double), true, HK_TILE);
-    hipLaunchKernelGGL((k_stream_band<Q>), dim3(cfg.far_grid), dim3(64), lds, st, bt.s, prof, n_old,
-                       cfg.chunk_cols);
+    hipLaunchKernelGGL((k_stream_band<Q>), dim3(STREAM_GRID), dim3(64), lds, st, bt.s, bt.B, prof, n_old,
+                       chunk);
 }
 
 hipError_t launch_stream_update(const Batch& bt, const SweepCfg& cfg, const int64_t* total,
                                 int32_t minL, int32_t maxL, unsigned long long* prof,
-                                int64_t n_old, hipStream_t st)
+                                int64_t n_old, int64_t n, hipStream_t st)
 {
-    for (int32_t m = minL; m <= maxL; ++m) {
-        hipLaunchKernelGGL(k_set_len, dim3(1), dim3(1), 0, st, bt.s, m, m == minL ? 2 : 1);
-        hipLaunchKernelGGL(k_length, dim3((unsigned int)total[PFX_ELEM]), dim3(256), 0, st, bt.s, 1,
-                           bt.pfx[PFX_ELEM]);
+    // shorter chunks until the items fill the machine (an item is a serial
+    // chain of its columns)
+    const int64_t R = 64 * (int64_t)cfg.q_ref, N = n - minL + 1;
+    const int64_t tiles = (n - n_old + R - 1) / R, old = (n_old + R - 1) / R;
+    int chunk = STREAM_CHUNK;
+    while (chunk > HK_TILE &&
+           bt.B * (tiles * ((N + chunk - 1) / chunk) + old * ((n - n_old + chunk - 1) / chunk)) <
+               STREAM_ITEMS)
+        chunk /= 2;
+    for (int32_t m = minL; m <= maxL; m += bt.B) {
+        launch_stream_group(bt, total, m, maxL, st);
         switch (cfg.q_ref) {
-        case 4: launch_band<4>(bt, cfg, prof, n_old, st); break;
-        case 8: launch_band<8>(bt, cfg, prof, n_old, st); break;
-        default: launch_band<2>(bt, cfg, prof, n_old, st); break;
+        case 4: launch_band<4>(bt, prof, n_old, chunk, st); break;
+        case 8: launch_band<8>(bt, prof, n_old, chunk, st); break;
+        default: launch_band<2>(bt, prof, n_old, chunk, st); break;
         }
     }
     return hipGetLastError();
@@ -4604,24 +4778,20 @@ hipError_t launch_stream_query(const Batch& bt, const SweepCfg& cfg, const int64
                                int32_t minL, int32_t maxL, const unsigned long long* prof,
                                hipStream_t st)
 {
-    for (int32_t m = minL; m <= maxL; ++m) {
-        hipLaunchKernelGGL(k_set_len, dim3(1), dim3(1), 0, st, bt.s, m, m == minL ? 2 : 1);
-        hipLaunchKernelGGL(k_length, dim3((unsigned int)total[PFX_ELEM]), dim3(256), 0, st, bt.s, 1,
-                           bt.pfx[PFX_ELEM]);
-        hipLaunchKernelGGL(k_stream_query, dim3(256), dim3(256), 0, st, bt.s, prof);
-        hipLaunchKernelGGL(k_select_top, dim3(1), dim3(TOPK_BLOCK), 0, st, bt.s);
-        launch_exact(bt, cfg, 1, st);
-        hipLaunchKernelGGL(k_round_end, dim3(1), dim3(END_BLOCK), 0, st, bt.s, bt.remaining,
-                           64 * cfg.q_near, 1, 0, 0.0f, 0, 1, bt.ipfx + bt.B + 1);
+    for (int32_t m = minL; m <= maxL; m += bt.B) {
+        launch_stream_group(bt, total, m, maxL, st);
+        hipLaunchKernelGGL(k_stream_pick, dim3(bt.B), dim3(TOPK_BLOCK), 0, st, bt.s, prof);
+        launch_exact(bt, cfg, 0, st);
+        hipLaunchKernelGGL(k_round_end, dim3(bt.B), dim3(END_BLOCK), 0, st, bt.s, bt.remaining,
+                           64 * cfg.q_near, 0, 0, 0.0f, 0, bt.B, bt.ipfx + bt.B + 1);
     }
     return hipGetLastError();
 }
 
-hipError_t launch_stream_profile(const Batch& bt, const int64_t* total, int32_t minL, int32_t m,
-                                 const unsigned long long* prof, double* nn, hipStream_t st)
+hipError_t launch_stream_profile(const Batch& bt, int32_t m, const unsigned long long* prof,
+                                 double* nn, hipStream_t st)
 {
-    const hipError_t e = launch_stats_to(bt, minL, m, total, st);
-    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_set_len, dim3(1), dim3(1), 0, st, bt.s, m, 0);
     hipLaunchKernelGGL(k_stream_profile, dim3(256), dim3(256), 0, st, bt.s, prof, nn);
     return hipGetLastError();
 }

@@ -121,3 +121,33 @@ def test_stream_rejects_overflow_and_nonfinite_values():
         check_against_profiles(T, out, 10, 12, 1)
     finally:
         st.close()
+
+
+@pytest.mark.parametrize("n,minL,maxL,k,pieces", [
+    (1500, 12, 46, 64, (600, 1, 899)),       # groups of 15, 15 and 5 lengths, k at its largest
+    (1500, 12, 27, 3, (200, 1300)),          # 15 lengths and one
+    (20000, 30, 55, 3, (9000, 11000)),       # groups of 13, all screened
+    (70000, 40, 44, 1, (70000,)),            # groups of three and two
+])
+def test_stream_groups_of_lengths_equal_the_search(n, minL, maxL, k, pieces):
+    """Lengths are handled several at a time: whole and partial groups, with
+    flat windows, against the one-shot search on the same points."""
+    dev = _dev()
+    from paper_2304_01660_amd import api
+    rng = np.random.default_rng([n, minL])
+    T = np.cumsum(rng.standard_normal(n))
+    for p in rng.integers(100, n - 200, 3):
+        T[p:p + 60] = T[p]
+    st = api.Stream(n, minL, maxL, k, device=0)
+    try:
+        done = 0
+        for p in pieces:
+            _say("stream groups", n, minL, maxL, done, p)
+            st.append(torch.from_numpy(T[done:done + p]).to(dev))
+            done += p
+            out = st.discords()
+            one = api.discords(torch.from_numpy(T[:done]).to(dev), minL, maxL, k)
+            for key in ("idx", "len", "nn_idx", "nn_dist"):
+                assert torch.equal(out[key], one[key]), key
+    finally:
+        st.close()
