@@ -748,16 +748,73 @@ __global__ __launch_bounds__(ADV_BLOCK) void k_advance(SeriesDev* S, int B,
 // batch.)  Rows that stay are the round's candidates.  Bound by latency: a
 // chain of dependent loads per batch, which is why a batch is wide.
 constexpr int RESCUE_TRIES = 2;
-__global__ __launch_bounds__(RESCUE_BLOCK) void k_rescue(SeriesDev* S, int B)
+// Too many failures for second chances (a new threshold altogether, e.g. the
+// first length's next r).
+__device__ __forceinline__ bool rescue_hopeless(const Ctrl* c, unsigned int total, int64_t N)
+{
+    return (int64_t)total * 2 > N && total > c->lean_max;
+}
+
+// The waves of k_rescue that each series of a batch gets (one block, a thread
+// per series): one, and its part of the others by its rows.  wpfx[b]: first
+// wave of series b.  (64 series of 10,000 to 200,000 points, per round: an even
+// share, waves bound to one list, 267 us; this share and the rows of all lists
+// in turn, 96.)
+constexpr int FAIL_ITEMS_MAXB = 1024;
+__global__ __launch_bounds__(FAIL_ITEMS_MAXB) void k_fail_items(SeriesDev* S, int B, int64_t waves,
+                                                               int64_t* wpfx)
+{
+    __shared__ long long ws[2][FAIL_ITEMS_MAXB / 64];
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    long long rows = 0, any = 0;
+    if (tid < B) {
+        const SeriesDev& s = S[tid];
+        const Ctrl* c = s.ctrl;
+        if (c->active && !c->pending && c->new_len != 2 && c->prune) {
+            unsigned int total = 0;
+#pragma unroll 16
+            for (int q = 0; q < FAIL_LISTS; ++q) total += c->nfail[q];
+            any = total > 0 ? 1 : 0;
+            rows = rescue_hopeless(c, total, s.n - c->m + 1) ? 0 : total;
+        }
+    }
+    auto scan = [&](long long v, int at, long long& before) {
+        long long x = v;
+        for (int o = 1; o < 64; o <<= 1) {
+            const long long y = __shfl_up(x, o);
+            if (lane >= o) x += y;
+        }
+        if (lane == 63) ws[at][w] = x;
+        __syncthreads();
+        long long tot = 0;
+        before = x - v;
+        for (int e = 0; e < FAIL_ITEMS_MAXB / 64; ++e) {
+            before += e < w ? ws[at][e] : 0;
+            tot += ws[at][e];
+        }
+        return tot;
+    };
+    long long before;
+    const long long all = scan(rows, 0, before);
+    const long long mine = any ? 1 + (all ? rows * (waves - B) / all : 0) : 0;
+    const long long used = scan(mine, 1, before);
+    if (tid < B) wpfx[tid] = before;
+    if (tid == 0) wpfx[B] = used;
+}
+
+__global__ __launch_bounds__(RESCUE_BLOCK) void k_rescue(SeriesDev* S, int B,
+                                                         const int64_t* __restrict__ wpfx)
 {
     const int lane = threadIdx.x & 63;
     const int sub = lane & 7, cq = lane >> 3;
     const int64_t wave = (int64_t)blockIdx.x * (RESCUE_BLOCK / 64) + (threadIdx.x >> 6);
     const int64_t nwaves = (int64_t)gridDim.x * (RESCUE_BLOCK / 64);
-    // the waves are shared out evenly among the series
-    const int64_t nper = std::max<int64_t>(1, nwaves / B);
-    const int64_t w = wave % nper;
-    for (int64_t b = wave / nper; b < B; b += nwaves / nper) {
+    // the waves are shared out by k_fail_items, without its table evenly
+    if (wpfx && wave >= wpfx[B]) return;
+    const int64_t own = wpfx ? series_of(wpfx, B, wave) : 0;
+    const int64_t nper = wpfx ? wpfx[own + 1] - wpfx[own] : std::max<int64_t>(1, nwaves / B);
+    const int64_t w = wpfx ? wave - wpfx[own] : wave % nper;
+    for (int64_t b = wpfx ? own : wave / nper; b < B; b += wpfx ? (int64_t)B : nwaves / nper) {
         const SeriesDev& s = S[b];
         Ctrl* c = s.ctrl;
         const unsigned int mine = c->nfail[lane];
@@ -767,8 +824,7 @@ __global__ __launch_bounds__(RESCUE_BLOCK) void k_rescue(SeriesDev* S, int B)
         unsigned int total = mine;
 #pragma unroll
         for (int o = 32; o >= 1; o >>= 1) total += __shfl_xor(total, o);
-        if ((int64_t)total * 2 > N && total > c->lean_max) {
-            // (a new threshold altogether, e.g. the first length's next r)
+        if (rescue_hopeless(c, total, N)) {
             if (w == 0 && lane == 0) c->nlive = 0x7fffffffu;
             continue;
         }
@@ -777,15 +833,19 @@ __global__ __launch_bounds__(RESCUE_BLOCK) void k_rescue(SeriesDev* S, int B)
         const double* __restrict__ mu = cur_mu(s, c);
         const double* __restrict__ inv = s.inv64;
         const double kill = c->thr64 + WIT_GUARD;
-        // the series' waves spread over its lists, then over a list's rows
-        // (fewer waves than lists: several lists per wave)
-        const int nl = fail_lists(s.Npad);
-        const int64_t per = std::max<int64_t>(1, nper / nl);  // waves per list
-        for (int64_t e = w; e < (nper >= nl ? per * nl : (int64_t)nl); e += nper) {
-            const int64_t list = e % nl;
-            const unsigned int cnt = (unsigned int)__builtin_amdgcn_readlane((int)mine, (int)list);
-            for (int64_t p = e / nl; p < cnt; p += per) {
-                const int64_t i = s.fail[list * cap + p];
+        // the waves take the rows in turn, numbered through the lists (lane l
+        // holds list l's end)
+        unsigned int end = mine;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const unsigned int y = __shfl_up(end, o);
+            if (lane >= o) end += y;
+        }
+        {
+            for (int64_t p = w; p < (int64_t)total; p += nper) {
+                const int list = __popcll(__ballot((int64_t)end <= p));
+                const int64_t at = p - (list ? __builtin_amdgcn_readlane((int)end, list - 1) : 0);
+                const int64_t i = s.fail[list * cap + at];
                 const double mi = mu[i], ii = inv[i];
                 // a row's witness, whatever its state (a candidate is always recomputed)
                 auto wit_of = [&](int64_t q) -> int64_t {
@@ -3792,17 +3852,26 @@ __global__ __launch_bounds__(64 * SC_WAVES, 2) void k_dense(SeriesDev* S, int B,
 // The rows handed over, by direct FP64 dot products with the eight columns of
 // each entry, eight lanes per column, one wave per entry: the best one above
 // the threshold prunes the row and becomes its witness.
-__global__ __launch_bounds__(RESCUE_BLOCK) void k_pairs(SeriesDev* S, int B)
+__global__ __launch_bounds__(RESCUE_BLOCK) void k_pairs(SeriesDev* S, int B,
+                                                        const int64_t* __restrict__ pfx)
 {
     const int lane = threadIdx.x & 63;
     const int sub = lane & 7, cq = lane >> 3;
     const int64_t wave = (int64_t)blockIdx.x * (RESCUE_BLOCK / 64) + (threadIdx.x >> 6);
     const int64_t nwaves = (int64_t)gridDim.x * (RESCUE_BLOCK / 64);
-    const int64_t nper = std::max<int64_t>(1, nwaves / B);
-    for (int64_t b = wave / nper; b < B; b += nwaves / nper) {
+    // a batch: the waves lie evenly over its row tiles (k_dense_items), and a
+    // series has those that meet its tiles (64 series: an even share 190 us
+    // per round, this 65)
+    const int64_t tiles = B == 1 ? 1 : pfx[B];
+    if (tiles == 0) return;
+    for (int64_t b = B == 1 ? 0 : series_of(pfx, B, wave * tiles / nwaves); b < B; ++b) {
+        const int64_t t0 = B == 1 ? 0 : pfx[b], t1 = B == 1 ? 1 : pfx[b + 1];
+        const int64_t first = t0 * nwaves / tiles;
+        if (first > wave) break;
         const SeriesDev& s = S[b];
         Ctrl* c = s.ctrl;
-        if (!c->active || lean_round(c) || !dense_round(c) || !c->handled) continue;
+        if (t0 == t1 || !c->active || lean_round(c) || !dense_round(c) || !c->handled) continue;
+        const int64_t nper = (t1 * nwaves - 1) / tiles - first + 1, w = wave - first;
         const int32_t m = c->m;
         const int64_t N = s.n - m + 1;
         const int64_t np = std::min<int64_t>(c->npairs, dense_pairs(s.Npad));
@@ -3810,7 +3879,7 @@ __global__ __launch_bounds__(RESCUE_BLOCK) void k_pairs(SeriesDev* S, int B)
         const double* __restrict__ mu = cur_mu(s, c);
         const double* __restrict__ inv = s.inv64;
         const double thr = c->thr64;
-        for (int64_t p = wave % nper; p < np; p += nper) {
+        for (int64_t p = w; p < np; p += nper) {
             const int2 pr = s.pairs[p];
             const int64_t i = pr.x, j = (int64_t)pr.y + cq;
             if (!((load_word(&s.alive[i >> 6]) >> (i & 63)) & 1ull)) continue;
@@ -4671,8 +4740,14 @@ hipError_t launch_round(const Batch& bt, const SweepCfg& cfg, const int64_t* tot
     hipLaunchKernelGGL(k_advance, dim3(elem), dim3(ADV_BLOCK),
                        sizeof(double) * (size_t)(ADV_BLOCK + bt.maxL_all), st, bt.s, bt.B,
                        bt.pfx[PFX_ELEM], bt.remaining);
-    if (more)
-        hipLaunchKernelGGL(k_rescue, dim3(RESCUE_GRID), dim3(RESCUE_BLOCK), 0, st, bt.s, bt.B);
+    if (more) {
+        const bool shared = bt.B > 1 && bt.B <= FAIL_ITEMS_MAXB;
+        if (shared)
+            hipLaunchKernelGGL(k_fail_items, dim3(1), dim3(FAIL_ITEMS_MAXB), 0, st, bt.s, bt.B,
+                               (int64_t)RESCUE_GRID * (RESCUE_BLOCK / 64), bt.ipfx);
+        hipLaunchKernelGGL(k_rescue, dim3(RESCUE_GRID), dim3(RESCUE_BLOCK), 0, st, bt.s, bt.B,
+                           shared ? bt.ipfx : nullptr);
+    }
     if (full)
         hipLaunchKernelGGL(k_helpers, dim3(elem), dim3(ADV_BLOCK), 0, st, bt.s, bt.B,
                            bt.pfx[PFX_ELEM]);
@@ -4698,7 +4773,8 @@ hipError_t launch_round(const Batch& bt, const SweepCfg& cfg, const int64_t* tot
         hipLaunchKernelGGL(k_dense, dim3(DENSE_GRID), dim3(64 * SC_WAVES),
                            sizeof(_Float16) * DN_ROWS * dense_stride(std::min(bt.maxL_all, DENSE_MAXM)),
                            st, bt.s, bt.B, bt.ipfx);
-        hipLaunchKernelGGL(k_pairs, dim3(RESCUE_GRID), dim3(RESCUE_BLOCK), 0, st, bt.s, bt.B);
+        hipLaunchKernelGGL(k_pairs, dim3(RESCUE_GRID), dim3(RESCUE_BLOCK), 0, st, bt.s, bt.B,
+                           bt.ipfx);
         hipLaunchKernelGGL(k_dense_top, dim3(bt.B), dim3(TOPK_BLOCK), 0, st, bt.s);
         cfg.timer->end(1, st);
     }
