@@ -336,7 +336,11 @@ int upload(palmad_ctx* ctx, const Plan& p, void* ws, const double* const* Tin, c
         s.Tin = Tin ? Tin[b] : nullptr;
         if (n_now) {
             s.n = *n_now;
-            s.T = b > 0 ? d[0].T : s.T;
+            if (b > 0) {  // the lanes share the series
+                s.T = d[0].T;
+                s.half = d[0].half;
+                s.chunk_scale = d[0].chunk_scale;
+            }
         }
         if (outs) {
             const Outputs& o = outs[n_now ? 0 : b];
@@ -508,6 +512,7 @@ int search(palmad_ctx* ctx, const Plan& p, const Opts& o, void* ws, const double
     if (rc) return rc;
     rc = prepare(ctx, bt, p, false);
     if (rc) return rc;
+    HIP_TRY(launch_half(bt, bt.B, ctx->work));
     HIP_TRY(launch_start(bt, cfg, ctx->work));
     // every issue of rounds completes a range search of at least one series
     int64_t max_checks = 2;
@@ -942,6 +947,7 @@ int palmad_range_discords(palmad_ctx* ctx, const double* T, int64_t n, int32_t m
     rc = prepare(ctx, bt, p, false);
     if (rc) return rc;
     HIP_TRY(launch_set_fixed_r(bt, r, ctx->work));
+    HIP_TRY(launch_half(bt, bt.B, ctx->work));
     HIP_TRY(launch_start(bt, cfg, ctx->work));
     HIP_TRY(launch_round(bt, cfg, p.totals, true, false, false, ctx->work));
     const int64_t N = n - m + 1;
@@ -1320,6 +1326,7 @@ int palmad_stream_append(palmad_stream* st, const double* values, int64_t count,
     }
     SweepCfg cfg = cfg_of(st->o, nullptr);
     HIP_TRY(launch_stream_append(bt, values, n_old, count, ctx->work));
+    HIP_TRY(launch_half(bt, 1, ctx->work));
     HIP_TRY(launch_stream_update(bt, cfg, st->p.totals, st->minL, st->maxL, st->prof, n_old,
                                  st->n, ctx->work));
     HIP_TRY(hipStreamSynchronize(ctx->work));

@@ -29,6 +29,8 @@ constexpr int CAND_GROUP = 16;
 constexpr int CAND_GROUPS = CAND_MAX / CAND_GROUP;
 constexpr int EXACT_COLS = 128;
 constexpr int SCREEN_COLS = 512;
+constexpr int HALF_STRIDE = SCREEN_COLS + 256 + 16;  // FP16 values kept per chunk
+constexpr int SCREEN_GROUPS = 4;  // candidate groups of a screening item (windows of up to 256)
 constexpr int EXACT_GRID = 512;
 constexpr int SCREEN_GRID = 512;  // two workgroups per CU
 constexpr int64_t SCREEN_MIN = 8192;
@@ -175,6 +177,8 @@ struct SeriesDev {
     double* part;        // its partials [pcap][CAND_GROUP][2]
     float* lbp;          // lower bounds of the screening's workgroups [lbcap][CAND_GROUP]
     float* ub;           // upper bounds [CAND_GROUPS][blocks][CAND_GROUP] (shares df64 .. rhs)
+    uint16_t* half;      // the series in FP16, by chunks (see k_half) [chunks][HALF_STRIDE]
+    double* chunk_scale; // offset and 1 / scale of every chunk [chunks][2]
     int32_t* wit;        // witness of every row (see k_advance) [Npad+64]
     double* wc;          // its covariance with the row [Npad+64]
     int2* pairs;         // a dense round's (row, first of eight columns) entries for k_pairs
@@ -203,7 +207,7 @@ struct Layout {
     int64_t n, Nmax, Npad, Tlen, nwords, pcap, lbcap;
     int32_t minL, maxL, k, L, kp;
     size_t off_T, off_mu, off_var, off_mu2, off_var2, off_h32, off_h64, off_alive, off_rho, off_rhs, off_unc,
-        off_tsel, off_tref, off_hot, off_twork, off_cand, off_part, off_lbp, off_wit, off_wc, off_hist, off_evc, off_ctrl, off_red,
+        off_tsel, off_tref, off_hot, off_twork, off_cand, off_part, off_lbp, off_half, off_scale, off_wit, off_wc, off_hist, off_evc, off_ctrl, off_red,
         off_sgm, total;
 };
 bool make_layout(int64_t n, int32_t minL, int32_t maxL, int32_t k, Layout* out);
@@ -270,6 +274,8 @@ void series_blocks(const Layout& lay, const SweepCfg& cfg, int64_t out[PFX_KINDS
 
 // ---- launchers (all asynchronous on `st`); `total[kind]` = pfx[kind][B] ----
 hipError_t launch_prepare(const Batch& bt, const int64_t* total, hipStream_t st);
+// FP16 chunks of the first `series` series (once their values are in place).
+hipError_t launch_half(const Batch& bt, int series, hipStream_t st);
 hipError_t launch_start(const Batch& bt, const SweepCfg& cfg, hipStream_t st);
 hipError_t launch_round(const Batch& bt, const SweepCfg& cfg, const int64_t* total, bool full,
                         bool dense, bool more, hipStream_t st);

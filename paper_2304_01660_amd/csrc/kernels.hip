@@ -2764,8 +2764,12 @@ constexpr int PM_XS = PM_KC + 1;  // LDS row stride of a candidate window (odd: 
 constexpr int SC_WAVES = 4;
 constexpr int SC_COLS = SCREEN_COLS;  // columns per screening chunk, EX_COLS per wave
 static_assert(SC_COLS == SC_WAVES * EX_COLS, "a wave screens one exact block");
+// (below any product: those of a stretch with a spike are off by its e_j)
+constexpr float SC_NONE = -1e30f;
 constexpr int SC_AS = PM_KC + 8;  // LDS row stride of a screened window, in halves
 constexpr int SC_SLOTS = (SC_COLS + PM_KC) / 8;  // 16-byte slots of one shifted copy
+// LDS row stride of a whole window, in halves
+__host__ __device__ constexpr int dense_stride(int m) { return ((m + 31) & ~31) + 8; }
 
 // Candidates of a series in this round (0: nothing to evaluate).
 __device__ __forceinline__ int cand_count(const SeriesDev& s, const Ctrl* c, int full)
@@ -2777,16 +2781,29 @@ __device__ __forceinline__ int cand_count(const SeriesDev& s, const Ctrl* c, int
 __device__ __forceinline__ int64_t exact_blocks(int64_t N) { return (N + EX_COLS - 1) / EX_COLS; }
 __device__ __forceinline__ int64_t screen_chunks(int64_t N) { return (N + SC_COLS - 1) / SC_COLS; }
 
-// Work items of the two kernels: (candidate group, chunk or block) of every
-// series, group-major, numbered across the batch; each workgroup takes one
-// contiguous range, so that it stays with a group's windows.  ipfx[b]: first
-// item of series b (one series needs no table).
-__device__ __forceinline__ int64_t items_of(const SeriesDev& s, int full, bool screen)
+// Candidate groups of a screening item.  Four share a chunk's operands where
+// there are items enough (staging costs as much as the products of three
+// groups), else one, whose items are shorter and more (12,000 points: 11.5 us
+// per round, with four always 26); windows past PM_KC are staged in parts, a
+// group at a time.
+constexpr int SC_GS = SCREEN_GROUPS;
+__device__ __forceinline__ int screen_groups(int B, int32_t m, int64_t ng, int64_t nch)
+{
+    return m <= PM_KC && (B > 1 || ng * nch > 2 * SCREEN_GRID) ? SC_GS : 1;
+}
+
+// Work items of the two kernels: (candidate groups, chunk) or (group, block)
+// of every series, group-major, numbered across the batch; each workgroup
+// takes one contiguous range, so that it stays with a group's windows.
+// ipfx[b]: first item of series b (one series needs no table).
+__device__ __forceinline__ int64_t items_of(const SeriesDev& s, int B, int full, bool screen)
 {
     const Ctrl* c = s.ctrl;
     const int64_t ng = (cand_count(s, c, full) + PM_G - 1) / PM_G;
     const int64_t N = s.n - c->m + 1;
-    return ng * (screen ? screen_chunks(N) : exact_blocks(N));
+    const int64_t nch = screen_chunks(N);
+    const int gs = screen_groups(B, c->m, ng, nch);
+    return screen ? (ng + gs - 1) / gs * nch : ng * exact_blocks(N);
 }
 constexpr int ITEMS_BLOCK = 1024;
 __global__ __launch_bounds__(ITEMS_BLOCK) void k_items(SeriesDev* S, int B, int full, int64_t* ipfx_s,
@@ -2799,8 +2816,8 @@ __global__ __launch_bounds__(ITEMS_BLOCK) void k_items(SeriesDev* S, int B, int 
         const int b = b0 + tid;
         long long v[2] = {0, 0}, x[2];
         if (b < B) {
-            v[0] = items_of(S[b], full, true);
-            v[1] = items_of(S[b], full, false);
+            v[0] = items_of(S[b], B, full, true);
+            v[1] = items_of(S[b], B, full, false);
         }
 #pragma unroll
         for (int q = 0; q < 2; ++q) {
@@ -2873,19 +2890,195 @@ typedef float acc4f_t __attribute__((ext_vector_type(4)));
 // it can hold its maximum, so k_exact finds the same value and the same
 // smallest argmax as over all columns.  (A split into two FP16 values per
 // operand, 2^-22 instead of 2^-11, takes three times the matrix work and
-// leaves few blocks fewer.)
+// leaves few blocks fewer.)  Eight columns of a lane share their largest e_j,
+// so that a product costs two vector operations.
+//
+// Bound by latency where a workgroup has one chunk (two loads in a chain, the
+// operands, the products), else by the LDS reads and the 64 x 512 products'
+// maxima.  The next chunk's values are fetched during the products.  (One group per item and a bound per product: 64 series 216 us
+// per round, 1,000,000 points 50 us; so 110 and 33.)
+
+// One group after the other of G (for G = 4 half the columns at a time, so
+// that the accumulators stay at 64 registers): the largest product of every
+// row over the lane's eight columns.
+template <int G, int NU>
+__device__ __forceinline__ void screen_products(const _Float16* ap, int stride, int steps,
+                                                const half8_t (*wcopy)[SC_SLOTS], int slot,
+                                                const float (&gj)[8], const int32_t* rows, int ka,
+                                                int32_t jl, int64_t N, int32_t m,
+                                                unsigned int edge, float (&mx)[4 * SC_GS])
+{
+#pragma unroll
+    for (int q = 0; q < 4 * G; ++q) mx[q] = SC_NONE;
+#pragma unroll
+    for (int hf = 0; hf < 8 / NU; ++hf) {
+        acc4f_t acc[G][NU];
+#pragma unroll
+        for (int g = 0; g < G; ++g)
+#pragma unroll
+            for (int u = 0; u < NU; ++u) acc[g][u] = (acc4f_t){0.f, 0.f, 0.f, 0.f};
+        for (int st = 0; st < steps; ++st) {
+            half8_t av[G];
+#pragma unroll
+            for (int g = 0; g < G; ++g) av[g] = *(const half8_t*)(ap + 16 * g * stride + 32 * st);
+#pragma unroll
+            for (int u = 0; u < NU; ++u) {
+                const half8_t bv = wcopy[NU * hf + u][slot + 4 * st];
+#pragma unroll
+                for (int g = 0; g < G; ++g)
+                    acc[g][u] = __builtin_amdgcn_mfma_f32_16x16x32_f16(av[g], bv, acc[g][u], 0, 0, 0);
+            }
+        }
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            if (!((edge >> g) & 1u)) {
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+#pragma unroll
+                    for (int u = 0; u < NU; ++u)
+                        mx[4 * g + r] = fmaxf(mx[4 * g + r], acc[g][u][r] * gj[NU * hf + u]);
+            } else {
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const int32_t i = rows[16 * g + 4 * ka + r];
+#pragma unroll
+                    for (int u = 0; u < NU; ++u) {
+                        const int32_t j = jl + NU * hf + u;
+                        const bool ok = (int64_t)j < N && (j <= i - m || j >= i + m);
+                        mx[4 * g + r] = fmaxf(mx[4 * g + r], ok ? acc[g][u][r] * gj[NU * hf + u] : SC_NONE);
+                    }
+                }
+            }
+        }
+    }
+}
+
+// A chunk's stretch in FP16, converted once per series (k_half): the values
+// less the chunk's offset, times its power of two, and what the wave's two
+// columns per lane need.
+struct ChunkRegs {
+    uint2 h[3];
+    double off, usw;
+    double cm[2], ci[2];
+};
+__device__ __forceinline__ void fetch_chunk(const SeriesDev& s, const double* __restrict__ mu,
+                                            const double* __restrict__ inv, int64_t ch, ChunkRegs& R)
+{
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const uint2* __restrict__ src = (const uint2*)(s.half + ch * HALF_STRIDE) + min(tid, 2 * SC_SLOTS - 1);
+#pragma unroll
+    for (int q = 0; q < 3; ++q) R.h[q] = src[q];
+    R.off = s.chunk_scale[2 * ch];
+    R.usw = s.chunk_scale[2 * ch + 1];
+    const int64_t j = ch * SC_COLS + w * EX_COLS + lane;  // (inside the padded buffers)
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        R.cm[q] = mu[j + 64 * q];
+        R.ci[q] = inv[j + 64 * q];
+    }
+}
+// Thread tid has values 4 tid .. 4 tid + 11: slot t = tid / 2 of four copies
+// (slot t of copy u: w[8 t + u .. 8 t + u + 7]).
+__device__ __forceinline__ void stage_chunk(const ChunkRegs& R, half8_t (*wcopy)[SC_SLOTS])
+{
+    const int tid = threadIdx.x;
+    if (tid >= 2 * SC_SLOTS) return;
+    const int t = tid >> 1, u0 = (tid & 1) * 4;
+    const uint32_t d[6] = {R.h[0].x, R.h[0].y, R.h[1].x, R.h[1].y, R.h[2].x, R.h[2].y};
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        uint32_t p[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int b = e + (u >> 1);
+            p[e] = (u & 1) ? __builtin_amdgcn_alignbit(d[b + 1], d[b], 16) : d[b];
+        }
+        *(uint4*)&wcopy[u0 + u][t] = make_uint4(p[0], p[1], p[2], p[3]);
+    }
+}
+// Product to correlation, and its error bound, of column q of the lane's two.
+__device__ __forceinline__ float2 chunk_column(const ChunkRegs& R, int q, int32_t m, float e0, float fl)
+{
+    const float iv = (float)(R.ci[q] * R.usw);
+    const float dn = (float)((R.cm[q] - R.off) * R.ci[q]);
+    return make_float2(iv * 0x1p-10f, 1.02f * (e0 * sqrtf(1.0f + (float)m * dn * dn) + fl * iv) + 1e-6f);
+}
+
+// The chunks of every series (blocks past a series' last one exit), so that a
+// round copies its chunks instead of scaling and converting them again: k_dense of 51,000 rows, m = 96, 200,000 points, 8.3 -> 6.5 ms (550
+// TFLOP/s).  Bound by the copy; 300,000 points 6 us.
+__global__ __launch_bounds__(256) void k_half(SeriesDev* S)
+{
+    __shared__ double rlo[4], rhi[4];
+    const SeriesDev& s = S[blockIdx.y];
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const int64_t nch = screen_chunks(s.n - s.minL + 1);
+    for (int64_t ch = blockIdx.x; ch < nch; ch += gridDim.x) {
+        constexpr int NV = (HALF_STRIDE + 255) / 256;
+        const int64_t j0 = ch * SC_COLS;
+        const int span = (int)std::min<int64_t>(SC_COLS + PM_KC, s.n - j0);
+        double v[NV], lo = f_inf<double>(), hi = -f_inf<double>();
+#pragma unroll
+        for (int q = 0; q < NV; ++q) {
+            const int t = tid + 256 * q;
+            v[q] = t < span ? s.T[j0 + t] : 0.0;
+            lo = t < span ? fmin(lo, v[q]) : lo;
+            hi = t < span ? fmax(hi, v[q]) : hi;
+        }
+#pragma unroll
+        for (int o = 32; o >= 1; o >>= 1) {
+            lo = fmin(lo, __shfl_xor(lo, o));
+            hi = fmax(hi, __shfl_xor(hi, o));
+        }
+        __syncthreads();
+        if (lane == 0) {
+            rlo[w] = lo;
+            rhi[w] = hi;
+        }
+        __syncthreads();
+        for (int q = 0; q < 4; ++q) {
+            lo = fmin(lo, rlo[q]);
+            hi = fmax(hi, rhi[q]);
+        }
+        const double off = 0.5 * (lo + hi);
+        const double range = 0.5 * (hi - lo);
+        // power of two with range * sw in (512, 1024] (1 for a constant stretch)
+        int ex = 0;
+        if (range > 0.0) (void)frexp(range, &ex);
+        const double sw = range > 0.0 ? ldexp(1.0, min(10 - ex, 900)) : 1.0;
+        _Float16* out = (_Float16*)s.half + ch * HALF_STRIDE;
+#pragma unroll
+        for (int q = 0; q < NV; ++q) {
+            const int t = tid + 256 * q;
+            if (t < HALF_STRIDE) out[t] = t < span ? (_Float16)(float)((v[q] - off) * sw) : (_Float16)0.0f;
+        }
+        if (tid == 0) {
+            s.chunk_scale[2 * ch] = off;
+            s.chunk_scale[2 * ch + 1] = 1.0 / sw;
+        }
+    }
+}
+
+hipError_t launch_half(const Batch& bt, int series, hipStream_t st)
+{
+    const int64_t nch = (bt.Nmax_all + SC_COLS - 1) / SC_COLS;
+    hipLaunchKernelGGL(k_half, dim3((unsigned int)std::min<int64_t>(2048, nch), series), dim3(256), 0, st,
+                       bt.s);
+    return hipGetLastError();
+}
+
 __global__ __launch_bounds__(64 * SC_WAVES, 2) void k_screen(SeriesDev* S, int B, int full,
                                                           const int64_t* __restrict__ ipfx)
 {
+    extern __shared__ __align__(16) _Float16 xa[];  // [PM_G SC_GS][dense_stride(m)]
     __shared__ half8_t wcopy[8][SC_SLOTS];
-    __shared__ __align__(16) _Float16 xa[PM_G * SC_AS];
-    __shared__ double cmu[PM_G], cinv[PM_G];
-    __shared__ int64_t cidx[PM_G];
-    __shared__ double rlo[SC_WAVES], rhi[SC_WAVES];
-    __shared__ float lbw[SC_WAVES][PM_G];
+    __shared__ float gjs[SC_COLS], ejs[SC_COLS];
+    __shared__ double cmu[PM_G * SC_GS], cinv[PM_G * SC_GS];
+    __shared__ int32_t rows[PM_G * SC_GS];
+    __shared__ float lbw[SC_WAVES][PM_G * SC_GS];
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const int ca = lane & 15, ka = lane >> 4;
-    const int64_t total = B == 1 ? items_of(S[0], full, true) : ipfx[B];
+    const int64_t total = B == 1 ? items_of(S[0], 1, full, true) : ipfx[B];
     const Share sh = share_of(total);
     for (int64_t it = sh.lo; it < sh.hi;) {
         const int b = B == 1 ? 0 : series_of(ipfx, B, it);
@@ -2896,13 +3089,179 @@ __global__ __launch_bounds__(64 * SC_WAVES, 2) void k_screen(SeriesDev* S, int B
         const int32_t m = c->m;
         const int64_t N = s.n - m + 1;
         const int64_t nch = screen_chunks(N), nblk = exact_blocks(N);
-        const int g = (int)((it - first) / nch);
+        const int g = (int)((it - first) / nch);  // (of SC_GS groups, or the group)
         const int64_t c0 = (it - first) - g * nch;
         const int64_t c1 = std::min<int64_t>(nch, c0 + (sh.hi - it));
         it += c1 - c0;
         const double* __restrict__ T = s.T;
         const double* __restrict__ mu = cur_mu(s, c);
         const double* __restrict__ inv = s.inv64;
+        if (m > PM_KC) continue;
+        const int gs = screen_groups(B, m, (ncand + PM_G - 1) / PM_G, nch);
+        const int ng = min(gs, (ncand + PM_G - 1) / PM_G - gs * g);
+        const int nr = PM_G * ng;
+        const int stride = dense_stride(m);
+        ChunkRegs R;
+        fetch_chunk(s, mu, inv, c0, R);
+        __syncthreads();  // (the previous item is consumed)
+        if (tid < PM_G * SC_GS) {
+            const int64_t i = s.cand[min(PM_G * gs * g + tid, ncand - 1)];
+            rows[tid] = (int32_t)i;
+            cmu[tid] = mu[i];
+            cinv[tid] = inv[i];
+        }
+        __syncthreads();
+        // the candidates' windows, centred and scaled to norm 1024 (of three
+        // groups the fourth's products are left over)
+        const int nst = ng == 3 ? PM_G * SC_GS : nr;
+#pragma unroll 1
+        for (int r0 = w; r0 < nst; r0 += 4 * SC_WAVES) {
+            constexpr int NQ = PM_KC / 64 + 1;
+            double v[4][NQ];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int64_t i = rows[r0 + SC_WAVES * u];
+#pragma unroll
+                for (int q = 0; q < NQ; ++q) {
+                    const int k = lane + 64 * q;
+                    v[u][q] = k < m ? T[i + k] : 0.0;
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int r = r0 + SC_WAVES * u;
+                const double mi = cmu[r], sc = cinv[r] * 1024.0;
+#pragma unroll
+                for (int q = 0; q < NQ; ++q) {
+                    const int k = lane + 64 * q;
+                    if (k < stride)
+                        xa[r * stride + k] =
+                            k < m ? (_Float16)(float)((v[u][q] - mi) * sc) : (_Float16)0.0f;
+                }
+            }
+        }
+        unsigned int flat = 0u;  // bit 4 g + r: row 16 g + 4 ka + r is flat
+        float lbr[4 * SC_GS];
+#pragma unroll
+        for (int q = 0; q < 4 * SC_GS; ++q) lbr[q] = -4.0f;
+#pragma unroll
+        for (int q = 0; q < 4 * SC_GS; ++q) {
+            if ((q >> 2) >= ng) break;
+            flat |= cinv[16 * (q >> 2) + 4 * ka + (q & 3)] == 0.0 ? 1u << q : 0u;
+        }
+        const float e0 = 1.05f * (2.0f * 0x1p-11f + 0x1p-22f + (float)(m + 32) * 0x1p-23f +
+                                  sqrtf((float)m) * 0x1p-23f);
+        const float fl = sqrtf((float)m) * 0x1p-13f;
+        const int steps = (m + 31) >> 5;
+        const _Float16* ap = xa + ca * stride + 8 * ka;
+        for (int64_t ch = c0; ch < c1; ++ch) {
+            const int64_t j0 = ch * SC_COLS, jb = j0 + w * EX_COLS;
+            __syncthreads();  // (the previous chunk's operands are consumed)
+            stage_chunk(R, wcopy);
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                const float2 x = chunk_column(R, q, m, e0, fl);
+                gjs[w * EX_COLS + lane + 64 * q] = x.x;
+                ejs[w * EX_COLS + lane + 64 * q] = x.y;
+            }
+            __syncthreads();
+            if (ch + 1 < c1) fetch_chunk(s, mu, inv, ch + 1, R);
+            const int64_t blk = ch * SC_WAVES + w;
+            if (blk >= nblk) continue;  // (the next barrier is the loop's first)
+            float gj[8], em = 0.0f;
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                gj[u] = gjs[w * EX_COLS + 8 * ca + u];
+                em = fmaxf(em, ejs[w * EX_COLS + 8 * ca + u]);
+            }
+            unsigned int edge = 0u;  // groups with a row at its exclusion zone
+#pragma unroll
+            for (int q = 0; q < 4 * SC_GS; ++q) {
+                if ((q >> 2) >= ng) break;
+                const int32_t i = rows[16 * (q >> 2) + 4 * ka + (q & 3)];
+                if (jb + EX_COLS > N || (jb < (int64_t)i + m && jb + EX_COLS > (int64_t)i - m))
+                    edge |= 1u << (q >> 2);
+            }
+#pragma unroll
+            for (int o = 32; o >= 16; o >>= 1) edge |= (unsigned int)__shfl_xor((int)edge, o);
+            edge = (unsigned int)__builtin_amdgcn_readfirstlane((int)edge);
+            const int slot = w * (EX_COLS / 8) + ca + ka;
+            const int32_t jl = (int32_t)jb + 8 * ca;
+            float mx[4 * SC_GS];
+            if (ng == 1)
+                screen_products<1, 8>(ap, stride, steps, wcopy, slot, gj, rows, ka, jl, N, m, edge, mx);
+            else if (ng == 2)
+                screen_products<2, 8>(ap, stride, steps, wcopy, slot, gj, rows, ka, jl, N, m, edge, mx);
+            else
+                screen_products<4, 4>(ap, stride, steps, wcopy, slot, gj, rows, ka, jl, N, m, edge, mx);
+#pragma unroll
+            for (int gi = 0; gi < SC_GS; ++gi) {
+                if (gi >= ng) break;
+                float ub[4];
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const float v = mx[4 * gi + r];
+                    lbr[4 * gi + r] = fmaxf(lbr[4 * gi + r], v - em);
+                    ub[r] = v + em;
+#pragma unroll
+                    for (int o = 8; o >= 1; o >>= 1) ub[r] = fmaxf(ub[r], __shfl_xor(ub[r], o));
+                    if ((flat >> (4 * gi + r)) & 1u) ub[r] = 4.0f;  // every block is evaluated
+                }
+                if (ca == 0)
+                    *(float4*)(s.ub + ((int64_t)(gs * g + gi) * nblk + blk) * PM_G + 4 * ka) =
+                        make_float4(ub[0], ub[1], ub[2], ub[3]);
+            }
+        }
+        // the workgroup's lower bounds of these groups
+#pragma unroll
+        for (int q = 0; q < 4 * SC_GS; ++q) {
+            if ((q >> 2) >= ng) break;
+#pragma unroll
+            for (int o = 8; o >= 1; o >>= 1) lbr[q] = fmaxf(lbr[q], __shfl_xor(lbr[q], o));
+            if (ca == 0)
+                lbw[w][16 * (q >> 2) + 4 * ka + (q & 3)] = (flat >> q) & 1u ? -4.0f : lbr[q];
+        }
+        __syncthreads();
+        if (tid < nr) {
+            float v = lbw[0][tid];
+            for (int q = 1; q < SC_WAVES; ++q) v = fmaxf(v, lbw[q][tid]);
+            const int64_t e = (int64_t)blockIdx.x - first / sh.per + g;
+            s.lbp[e * gs * PM_G + tid] = v;
+        }
+    }
+}
+
+// Windows past PM_KC points: staged in parts, a group at a time.
+__global__ __launch_bounds__(64 * SC_WAVES, 2) void k_screen_long(SeriesDev* S, int B, int full,
+                                                          const int64_t* __restrict__ ipfx)
+{
+    __shared__ __align__(16) _Float16 xa[PM_G * SC_AS];
+    __shared__ half8_t wcopy[8][SC_SLOTS];
+    __shared__ double cmu[PM_G], cinv[PM_G];
+    __shared__ int64_t cidx[PM_G];
+    __shared__ double rlo[SC_WAVES], rhi[SC_WAVES];
+    __shared__ float lbw[SC_WAVES][PM_G];
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const int ca = lane & 15, ka = lane >> 4;
+    const int64_t total = B == 1 ? items_of(S[0], 1, full, true) : ipfx[B];
+    const Share sh = share_of(total);
+    for (int64_t it = sh.lo; it < sh.hi;) {
+        const int b = B == 1 ? 0 : series_of(ipfx, B, it);
+        const int64_t first = B == 1 ? 0 : ipfx[b];
+        const SeriesDev& s = S[b];
+        const Ctrl* c = s.ctrl;
+        const int ncand = cand_count(s, c, full);
+        const int32_t m = c->m;
+        const int64_t N = s.n - m + 1;
+        const int64_t nch = screen_chunks(N), nblk = exact_blocks(N);
+        const int g = (int)((it - first) / nch);  // (of SC_GS groups, or the group)
+        const int64_t c0 = (it - first) - g * nch;
+        const int64_t c1 = std::min<int64_t>(nch, c0 + (sh.hi - it));
+        it += c1 - c0;
+        const double* __restrict__ T = s.T;
+        const double* __restrict__ mu = cur_mu(s, c);
+        const double* __restrict__ inv = s.inv64;
+        if (m <= PM_KC) continue;
         __syncthreads();
         if (tid < PM_G) {
             const int cid = PM_G * g + tid;
@@ -2923,7 +3282,6 @@ __global__ __launch_bounds__(64 * SC_WAVES, 2) void k_screen(SeriesDev* S, int B
         }
         const float e0 = 1.05f * (2.0f * 0x1p-11f + 0x1p-22f + (float)(m + 32) * 0x1p-23f +
                                   sqrtf((float)m) * 0x1p-23f);
-        const bool single = m <= PM_KC;
         auto stage_windows = [&](int kb, int kn) {
             for (int gq = w; gq < PM_G; gq += SC_WAVES) {
                 const int64_t i = cidx[gq];
@@ -2941,7 +3299,6 @@ __global__ __launch_bounds__(64 * SC_WAVES, 2) void k_screen(SeriesDev* S, int B
                 }
             }
         };
-        if (single) stage_windows(0, m);
         for (int64_t ch = c0; ch < c1; ++ch) {
             const int64_t j0 = ch * SC_COLS;
             // offset and scale of the chunk's stretch
@@ -3005,7 +3362,7 @@ __global__ __launch_bounds__(64 * SC_WAVES, 2) void k_screen(SeriesDev* S, int B
                         wcopy[u0 + u][t] = ph;
                     }
                 }
-                if (!single) stage_windows(kb, kn);
+                stage_windows(kb, kn);
                 __syncthreads();
                 const int steps = (kn + 31) >> 5;
                 const _Float16* ah = &xa[ca * SC_AS + 8 * ka];
@@ -3103,7 +3460,7 @@ __global__ __launch_bounds__(64 * EX_WAVES) void k_exact(SeriesDev* S, int B, in
     const int ca = lane & 15, ka = lane >> 4;
     double* xg = lds;                 // [PM_G][PM_XS] candidate window chunk
     double* ts = lds + PM_G * PM_XS;  // t[j0 .. j0 + EX_COLS + m + 4 EX_STEPS)
-    const int64_t total = B == 1 ? items_of(S[0], full, false) : ipfx_e[B];
+    const int64_t total = B == 1 ? items_of(S[0], 1, full, false) : ipfx_e[B];
     const Share sh = share_of(total);
     for (int64_t it = sh.lo; it < sh.hi;) {
         const int b = B == 1 ? 0 : series_of(ipfx_e, B, it);
@@ -3142,17 +3499,19 @@ __global__ __launch_bounds__(64 * EX_WAVES) void k_exact(SeriesDev* S, int B, in
             // the lower bounds the screening's workgroups left
             const int64_t nch = screen_chunks(N);
             const int64_t firsts = B == 1 ? 0 : ipfx_s[b];
-            const int64_t tots = B == 1 ? items_of(s, full, true) : ipfx_s[B];
+            const int64_t tots = B == 1 ? items_of(s, 1, full, true) : ipfx_s[B];
             const int64_t pers = (tots + screen_grid - 1) / screen_grid;
             const int64_t w0 = firsts / pers;
-            const int64_t e0 = (firsts + g * nch) / pers - w0 + g;
-            const int64_t e1 = (firsts + (g + 1) * nch - 1) / pers - w0 + g;
+            const int gs = screen_groups(B, m, (ncand + PM_G - 1) / PM_G, nch), sg = g / gs;
+            const int64_t e0 = (firsts + sg * nch) / pers - w0 + sg;
+            const int64_t e1 = (firsts + (sg + 1) * nch - 1) / pers - w0 + sg;
+            const float* lbg = s.lbp + (g - sg * gs) * PM_G + (tid & 15);
             constexpr int EN = EX_WAVES * 4;  // entries per pass of the workgroup
             for (int64_t e = e0 + (tid >> 4); e <= e1; e += 8 * EN) {
                 float v[8];
 #pragma unroll
                 for (int u = 0; u < 8; ++u)
-                    v[u] = e + u * EN <= e1 ? s.lbp[(e + u * EN) * PM_G + (tid & 15)] : -8.0f;
+                    v[u] = e + u * EN <= e1 ? lbg[(e + u * EN) * gs * PM_G] : -8.0f;
 #pragma unroll
                 for (int u = 0; u < 8; ++u) lb = fmaxf(lb, v[u]);
             }
@@ -3346,8 +3705,6 @@ __global__ __launch_bounds__(64 * EX_WAVES) void k_exact(SeriesDev* S, int B, in
 constexpr int DN_ROWS = DENSE_ROWS;      // rows per item, DN_G groups of 16
 constexpr int DN_G = DN_ROWS / 16;
 constexpr int DN_BUF = 512;              // entries buffered per workgroup
-constexpr int DN_RAW = SC_COLS + PM_KC + 8;  // series values of a chunk
-__host__ __device__ constexpr int dense_stride(int m) { return ((m + 31) & ~31) + 8; }
 
 // The rows left, ascending (one block per series); few enough of them are
 // candidates at once.  In a round without sweeps (full = 0) every series with
@@ -3440,7 +3797,7 @@ __global__ __launch_bounds__(TOPK_BLOCK) void k_dense_list(SeriesDev* S, int ful
 template <int STEPS>
 __device__ __forceinline__ void dense_item(const SeriesDev& s, Ctrl* c, int64_t tile, int seg, int segs,
                                            _Float16* dxa, half8_t (*wcopy)[SC_SLOTS], float* gjs,
-                                           double* raw, double* rlo, double* rhi, int32_t* rows,
+                                           int32_t* rows,
                                            float (*bnd)[SC_WAVES][DN_ROWS],
                                            unsigned long long* dead_p, unsigned int* npair_p,
                                            unsigned int* gbase_p, int2* buf)
@@ -3527,21 +3884,7 @@ __device__ __forceinline__ void dense_item(const SeriesDev& s, Ctrl* c, int64_t 
     const int64_t nch = screen_chunks(N);
     const int64_t ch0 = nch * seg / segs, ch1 = nch * (seg + 1) / segs;
     const int steps = (m + 31) >> 5;
-    constexpr int RAW = (SC_COLS + PM_KC + 8 + 255) / 256;  // raw values per thread
-    double rv[RAW], cm[2], ci[2];
-    auto fetch = [&](int64_t ch) {
-        const int64_t j0 = ch * SC_COLS;
-#pragma unroll
-        for (int q = 0; q < RAW; ++q) {
-            const int t = tid + 256 * q;
-            rv[q] = t < DN_RAW ? T[j0 + t] : 0.0;  // (inside the padded series)
-        }
-#pragma unroll
-        for (int q = 0; q < 2; ++q) {  // the wave's columns, two per lane
-            cm[q] = mu[j0 + w * EX_COLS + lane + 64 * q];
-            ci[q] = inv[j0 + w * EX_COLS + lane + 64 * q];
-        }
-    };
+    ChunkRegs R;
     auto flush = [&]() {  // hand the listed entries over (whole workgroup)
         const unsigned int np = min(*npair_p, (unsigned int)DN_BUF);
         if (tid == 0 && np) *gbase_p = atomicAdd(&c->npairs, np);
@@ -3552,25 +3895,10 @@ __device__ __forceinline__ void dense_item(const SeriesDev& s, Ctrl* c, int64_t 
         if (tid == 0) *npair_p = 0u;
     };
     unsigned long long ev = 0;
-    fetch(ch0);
+    fetch_chunk(s, mu, inv, ch0, R);
     for (int64_t ch = ch0; ch < ch1; ++ch) {
         const int64_t j0 = ch * SC_COLS;
         const int64_t jb = j0 + w * EX_COLS;
-        const int span = (int)std::min<int64_t>(SC_COLS + m, s.n - j0);
-        double lo = f_inf<double>(), hi = -f_inf<double>();
-#pragma unroll
-        for (int q = 0; q < RAW; ++q) {
-            const int t = tid + 256 * q;
-            if (t < span) {
-                lo = fmin(lo, rv[q]);
-                hi = fmax(hi, rv[q]);
-            }
-        }
-#pragma unroll
-        for (int o = 32; o >= 1; o >>= 1) {
-            lo = fmin(lo, __shfl_xor(lo, o));
-            hi = fmax(hi, __shfl_xor(hi, o));
-        }
         __syncthreads();  // the previous chunk's operands are consumed
         const unsigned long long dead = *dead_p;  // (written only between the next barrier and this one)
         if (dead == ~0ull) break;
@@ -3578,13 +3906,16 @@ __device__ __forceinline__ void dense_item(const SeriesDev& s, Ctrl* c, int64_t 
             __syncthreads();
             flush();
         }
-        if (lane == 0) {
-            rlo[w] = lo;
-            rhi[w] = hi;
+        stage_chunk(R, wcopy);
+        float em = 0.0f;  // largest error bound of the wave's columns
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            const float2 x = chunk_column(R, q, m, e0, fl);
+            if (jb + lane + 64 * q < N) em = fmaxf(em, x.y);
+            gjs[w * EX_COLS + lane + 64 * q] = x.x;
         }
 #pragma unroll
-        for (int q = 0; q < RAW; ++q)
-            if (tid + 256 * q < DN_RAW) raw[tid + 256 * q] = rv[q];
+        for (int o = 32; o >= 1; o >>= 1) em = fmaxf(em, __shfl_xor(em, o));
         // a dead row's window becomes zero: its products then stay far below the
         // threshold (positive by DENSE_MIN_THR)
         if (dead != seen) {
@@ -3605,44 +3936,7 @@ __device__ __forceinline__ void dense_item(const SeriesDev& s, Ctrl* c, int64_t 
                         areg[st][g] = *(const half8_t*)(ap + 16 * g * stride + 32 * st);
             fresh = false;
         }
-        for (int q = 0; q < SC_WAVES; ++q) {
-            lo = fmin(lo, rlo[q]);
-            hi = fmax(hi, rhi[q]);
-        }
-        const double off = 0.5 * (lo + hi);
-        const double range = 0.5 * (hi - lo);
-        int ex = 0;
-        if (range > 0.0) (void)frexp(range, &ex);
-        const double sw = range > 0.0 ? ldexp(1.0, min(10 - ex, 900)) : 1.0;
-        const double usw = 1.0 / sw;
-        if (tid < 2 * SC_SLOTS) {
-            const int t = tid >> 1, u0 = (tid & 1) * 4;
-            const double* src = raw + 8 * t + u0;
-            _Float16 h[11];
-#pragma unroll
-            for (int q = 0; q < 11; ++q)
-                h[q] = (_Float16)(float)fmin(2048.0, fmax(-2048.0, (src[q] - off) * sw));
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                half8_t ph;
-#pragma unroll
-                for (int q = 0; q < 8; ++q) ph[q] = h[u + q];
-                wcopy[u0 + u][t] = ph;
-            }
-        }
-        float em = 0.0f;  // largest error bound of the wave's columns
-#pragma unroll
-        for (int q = 0; q < 2; ++q) {
-            const float iv = (float)(ci[q] * usw);
-            const float dn = (float)((cm[q] - off) * ci[q]);
-            const float ej = 1.02f * (e0 * sqrtf(1.0f + (float)m * dn * dn) + fl * iv) + 1e-6f;
-            if (jb + lane + 64 * q < N) em = fmaxf(em, ej);
-            gjs[w * EX_COLS + lane + 64 * q] = iv * 0x1p-10f;
-        }
-#pragma unroll
-        for (int o = 32; o >= 1; o >>= 1) em = fmaxf(em, __shfl_xor(em, o));
-        __syncthreads();
-        if (ch + 1 < ch1) fetch(ch + 1);
+        if (ch + 1 < ch1) fetch_chunk(s, mu, inv, ch + 1, R);
         if (jb >= N) continue;  // (the next barrier is the loop's first)
         const int slot = w * (EX_COLS / 8) + ca + ka;
         const bool edge = __ballot(jb + EX_COLS > N ||
@@ -3817,9 +4111,7 @@ __global__ __launch_bounds__(64 * SC_WAVES, 2) void k_dense(SeriesDev* S, int B,
 {
     extern __shared__ _Float16 dxa[];  // [DN_ROWS][dense_stride(m)]
     __shared__ half8_t wcopy[8][SC_SLOTS];
-    __shared__ double raw[DN_RAW];
     __shared__ float gjs[SC_COLS];
-    __shared__ double rlo[SC_WAVES], rhi[SC_WAVES];
     __shared__ int32_t rows[DN_ROWS];
     __shared__ float bnd[2][SC_WAVES][DN_ROWS];
     __shared__ unsigned long long dead_s;
@@ -3837,8 +4129,7 @@ __global__ __launch_bounds__(64 * SC_WAVES, 2) void k_dense(SeriesDev* S, int B,
         Ctrl* c = s.ctrl;
         const int64_t tile = t - (B == 1 ? 0 : pfx[b]);
 #define DENSE_ITEM(ST)                                                                        \
-    dense_item<ST>(s, c, tile, seg, segs, dxa, wcopy, gjs, raw, rlo, rhi, rows, bnd, &dead_s, \
-                   &npair_s, &gbase_s, buf)
+    dense_item<ST>(s, c, tile, seg, segs, dxa, wcopy, gjs, rows, bnd, &dead_s, &npair_s, &gbase_s, buf)
         switch ((c->m + 31) >> 5) {
         case 2:
         case 3:
@@ -4712,9 +5003,15 @@ static void launch_exact(const Batch& bt, const SweepCfg& cfg, int full, hipStre
         hipLaunchKernelGGL(k_items, dim3(1), dim3(ITEMS_BLOCK), 0, st, bt.s, bt.B, full, bt.ipfx,
                            bt.ipfx + bt.B + 1);
     const bool screened = bt.Nmax_all > SCREEN_MIN;
-    if (screened)
-        hipLaunchKernelGGL(k_screen, dim3(SCREEN_GRID), dim3(64 * SC_WAVES), 0, st, bt.s, bt.B, full,
+    if (screened) {
+        const size_t wins = sizeof(_Float16) * (size_t)PM_G * SC_GS *
+                            (size_t)dense_stride(std::min<int32_t>(bt.maxL_all, PM_KC));
+        hipLaunchKernelGGL(k_screen, dim3(SCREEN_GRID), dim3(64 * SC_WAVES), wins, st, bt.s, bt.B, full,
                            bt.ipfx);
+        if (bt.maxL_all > PM_KC)
+            hipLaunchKernelGGL(k_screen_long, dim3(SCREEN_GRID), dim3(64 * SC_WAVES), 0, st, bt.s, bt.B,
+                               full, bt.ipfx);
+    }
     const size_t lds = sizeof(double) * (size_t)(PM_G * PM_XS + EX_COLS + bt.maxL_all + 4 * EX_STEPS);
     hipLaunchKernelGGL(k_exact, dim3(EXACT_GRID), dim3(64 * EX_WAVES), lds, st, bt.s, bt.B, full,
                        screened ? 1 : 0, SCREEN_GRID, bt.ipfx, bt.ipfx + bt.B + 1);
@@ -5173,7 +5470,10 @@ bool make_layout(int64_t n, int32_t minL, int32_t maxL, int32_t k, Layout* out)
     const int64_t nblk = (l.Nmax + EXACT_COLS - 1) / EXACT_COLS;
     const int64_t nch = (l.Nmax + SCREEN_COLS - 1) / SCREEN_COLS;
     l.pcap = std::min<int64_t>(EXACT_GRID, CAND_GROUPS * nblk) + 2 * CAND_GROUPS;
-    l.lbcap = std::min<int64_t>(SCREEN_GRID, CAND_GROUPS * nch) + 2 * CAND_GROUPS;
+    // groups go SCREEN_GROUPS at a time where windows are short
+    constexpr int SG = CAND_GROUPS / SCREEN_GROUPS;
+    l.lbcap = std::max<int64_t>(std::min<int64_t>(SCREEN_GRID, CAND_GROUPS * nch) + 2 * CAND_GROUPS,
+                                SCREEN_GROUPS * (std::min<int64_t>(SCREEN_GRID, SG * nch) + 2 * SG));
     const size_t hl = (size_t)(l.Npad + 64);
     size_t o = 0;
     l.off_T = o;     o = al256(o + sizeof(double) * (size_t)l.Tlen);
@@ -5198,6 +5498,8 @@ bool make_layout(int64_t n, int32_t minL, int32_t maxL, int32_t k, Layout* out)
     l.off_cand = o;  o = al256(o + sizeof(int64_t) * (size_t)CAND_MAX);
     l.off_part = o;  o = al256(o + sizeof(double) * (size_t)(2 * CAND_GROUP) * (size_t)l.pcap);
     l.off_lbp = o;   o = al256(o + sizeof(float) * (size_t)(CAND_GROUP * l.lbcap));
+    l.off_half = o;  o = al256(o + sizeof(uint16_t) * (size_t)HALF_STRIDE * (size_t)nch);
+    l.off_scale = o; o = al256(o + sizeof(double) * 2 * (size_t)nch);
     l.off_wit = o;   o = al256(o + sizeof(int32_t) * hl);
     l.off_wc = o;    o = al256(o + sizeof(double) * hl);
     l.off_hist = o;  o = al256(o + sizeof(double) * (size_t)(l.L > 0 ? l.L : 1));
@@ -5251,6 +5553,8 @@ SeriesDev carve(void* base, const Layout& l)
     s.ub = (float*)s.df64;         // free outside a round's sweeps (see make_layout)
     s.fail = (int32_t*)s.df32;     // likewise
     s.pairs = (int2*)s.df64;       // likewise (df64, dg64)
+    s.half = (uint16_t*)(p + l.off_half);
+    s.chunk_scale = (double*)(p + l.off_scale);
     s.wit = (int32_t*)(p + l.off_wit);
     s.wc = (double*)(p + l.off_wc);
     s.hist = (double*)(p + l.off_hist);
