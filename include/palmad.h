@@ -74,8 +74,8 @@ typedef struct {
                               Capped so that the longest series has at most 65536
                               (tile, chunk) items in the first pass. */
     int32_t chunk_cols;    /* columns per work item of the sweeps; 0 = 1024.  Shortened
-                              (to 128 at least) where the first pass would have too few
-                              items to fill the device. */
+                              (to 128 at least) where a pass would have too few items
+                              to fill the device. */
     uint32_t flags;        /* PALMAD_FLAG_* bits */
     int32_t rows_near;     /* row-tile height of the first selection pass: 128, 256 or
                               512; 0 = 256. */

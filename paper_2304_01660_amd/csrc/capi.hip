@@ -179,7 +179,7 @@ SweepCfg cfg_of(const Opts& o, const KernelTimer* timer)
 {
     SweepCfg c;
     c.near_cols = o.near_cols;
-    c.chunk_cols = o.chunk_cols;
+    c.near_chunk = c.chunk_cols = o.chunk_cols;
     c.guard = o.dist_bits == 64 ? 0.0f : o.guard;
     c.dist_bits = o.dist_bits;
     c.far_grid = o.far_grid;
@@ -228,7 +228,7 @@ struct Plan {
     int32_t maxL_all;
     int64_t Nmax_all;
     // first-pass width and chunk length actually used (see NEAR_ITEMS, FILL_ITEMS)
-    int near_cols, chunk_cols;
+    int near_cols, near_chunk, chunk_cols;
 };
 
 // The first selection pass launches one workgroup per (row tile, chunk) of
@@ -240,13 +240,16 @@ struct Plan {
 // go to the split pass.
 constexpr int64_t NEAR_ITEMS = 65536;
 
-// A work item is a serial chain of its chunk's columns, so where the first
-// pass has fewer items than the machine holds (about 3,500), shorter chunks
-// shorten the pass: chunk_cols is halved while that is so, down to 128
-// columns (below, an item's start costs more than its columns).  (2,000
-// points, FP64, chunks of 1024 -> 128: whole search 1,127 -> 836 us;
-// 12,347 points: 3.46 -> 3.16 ms.)
+// A work item is a serial chain of its chunk's columns, so where a pass has
+// fewer items than the machine holds (about 3,500), shorter chunks shorten it:
+// chunk_cols is halved while that is so, down to 128 columns (below, an item's
+// start costs more than its columns).  The first pass has its own chunk; the
+// other passes, whose tiles are mostly dead, count every tile.  (2,000 points,
+// FP64, chunks of 1024 -> 128: whole search 1,127 -> 836 us; 12,347 points:
+// 3.46 -> 3.16 ms.  Profile of 150,000 points with chunks of 128 13.7 ms, of
+// 1024 11.4.)
 constexpr int64_t FILL_ITEMS = 4096;
+constexpr int64_t FILL_TILE_ITEMS = 32768;
 constexpr int MIN_CHUNK = 128;
 
 void make_plan(int B, const int64_t* n, const int32_t* minL, const int32_t* maxL, int32_t k,
@@ -277,7 +280,8 @@ void make_plan(int B, const int64_t* n, const int32_t* minL, const int32_t* maxL
         const int64_t chunks = std::max<int64_t>(1, NEAR_ITEMS / std::max<int64_t>(1, tiles));
         cfg.near_cols = (int)std::min<int64_t>(cfg.near_cols, chunks * cfg.chunk_cols);
     }
-    while (cfg.chunk_cols >= 2 * MIN_CHUNK) {
+    cfg.near_chunk = cfg.chunk_cols;
+    while (cfg.near_chunk >= 2 * MIN_CHUNK) {
         int64_t items = 0;
         for (int b = 0; b < B; ++b) {
             int64_t blk[PFX_KINDS];
@@ -285,8 +289,17 @@ void make_plan(int B, const int64_t* n, const int32_t* minL, const int32_t* maxL
             items += blk[PFX_NEAR];
         }
         if (items >= FILL_ITEMS) break;
+        cfg.near_chunk /= 2;
+    }
+    while (cfg.chunk_cols >= 2 * MIN_CHUNK) {
+        int64_t items = 0;
+        for (int b = 0; b < B; ++b)
+            items += ((p->lay[b].Nmax + 127) / 128) *
+                     ((p->lay[b].Nmax + cfg.chunk_cols - 1) / cfg.chunk_cols);
+        if (items >= FILL_TILE_ITEMS) break;
         cfg.chunk_cols /= 2;
     }
+    p->near_chunk = cfg.near_chunk;
     p->near_cols = cfg.near_cols;
     p->chunk_cols = cfg.chunk_cols;
     for (int b = 0; b < B; ++b) {
@@ -504,6 +517,7 @@ int search(palmad_ctx* ctx, const Plan& p, const Opts& o, void* ws, const double
         return fail(ctx, PALMAD_EDEVICE, "injected HIP failure (PALMAD_FAULT=hip)");
     if (fault == FAULT_CONVERGE) cfg.max_attempts = 1;
     cfg.near_cols = p.near_cols;
+    cfg.near_chunk = p.near_chunk;
     cfg.chunk_cols = p.chunk_cols;
     int rc = enter(ctx, stream);
     if (rc) return rc;
@@ -936,6 +950,7 @@ int palmad_range_discords(palmad_ctx* ctx, const double* T, int64_t n, int32_t m
     Plan p;
     make_plan(1, &n, &m, &m, 1, cfg, &p);
     cfg.near_cols = p.near_cols;
+    cfg.near_chunk = p.near_chunk;
     cfg.chunk_cols = p.chunk_cols;
     rc = check_ws(ctx, workspace, ws_bytes, p.total);
     if (rc) return rc;

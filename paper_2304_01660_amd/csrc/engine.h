@@ -259,6 +259,7 @@ struct KernelTimer {
 
 struct SweepCfg {
     int near_cols;
+    int near_chunk;   // columns per item of the first pass
     int chunk_cols;
     float guard;
     int dist_bits;

@@ -4930,7 +4930,7 @@ static void launch_near(const Batch& bt, const SweepCfg& cfg, const int64_t* tot
     if (total[PFX_NEAR] == 0) return;
     cfg.timer->begin(0, st);
     hipLaunchKernelGGL((k_select_near<F, Q, WIT>), dim3((unsigned int)total[PFX_NEAR]), dim3(64), lds,
-                       st, bt.s, bt.B, bt.pfx[PFX_NEAR], cfg.near_cols, cfg.chunk_cols);
+                       st, bt.s, bt.B, bt.pfx[PFX_NEAR], cfg.near_cols, cfg.near_chunk);
     cfg.timer->end(0, st);
 }
 
@@ -5571,7 +5571,7 @@ void series_blocks(const Layout& l, const SweepCfg& cfg, int64_t out[PFX_KINDS])
     // chunks of the first pass: near_cols (or a dense round's), at most every column
     const int64_t wide = l.Nmax <= DENSE_NEAR_MAXN ? std::max(cfg.near_cols, DENSE_NEAR) : cfg.near_cols;
     const int64_t span = std::min<int64_t>(wide, l.Nmax);
-    const int64_t nsub = (span + cfg.chunk_cols - 1) / cfg.chunk_cols;
+    const int64_t nsub = (span + cfg.near_chunk - 1) / cfg.near_chunk;
     out[PFX_ELEM] = (l.Npad + 64 + 255) / 256;
     out[PFX_NEAR] = ((l.Nmax + rn - 1) / rn) * nsub;
     out[PFX_TSEL] = ((l.Nmax + rf - 1) / rf + 255) / 256;
