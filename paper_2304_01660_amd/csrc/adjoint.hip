@@ -56,81 +56,190 @@ __device__ void adj_window_stats(const double* T, int64_t p, int32_t m, double* 
     sg = sqrt(adj_block_sum(q, sh) / (double)m);
 }
 
-// Partial nearest neighbour of reported row q against the 256 columns of
-// block x: (max rho, smallest argmax j).
+// Partial nearest neighbours of up to ADJ_ROWS reported rows against
+// ADJ_SPAN blocks of 256 columns: (max rho, smallest argmax j) per row and
+// block.  Consecutive rows of one length (a search reports k of each) share a
+// column's mean and deviation and the reads of its window, R at a time; every
+// value is the same as for a row alone.  Bound by the LDS reads, of a row's
+// value for two columns, and the FP64 operations, 3 + R per offset and column.  (325 rows, five per length of 96
+// to 160, 200,000 columns: a row and 256 columns per workgroup 3.36 ms, so
+// 1.80 ms.)
+constexpr int ADJ_ROWS = 16;  // rows per workgroup
+constexpr int ADJ_RUN = 8;    // most rows sharing a column
+constexpr int ADJ_SPAN = 4;
+
+// Sums of squares v and products c of the C column windows t + 256 e, less
+// their means, with R centred rows xs (stride doubles apart).
+template <int R, int C>
+__device__ __forceinline__ void adj_dots(const double* t, const double* xs, int stride, int32_t m,
+                                         const double (&mu)[C], double (&v)[C],
+                                         double (&c)[C][ADJ_RUN])
+{
+    double c0[C][R], c1[C][R], vv[C];
+#pragma unroll
+    for (int e = 0; e < C; ++e) {
+        vv[e] = 0.0;
+#pragma unroll
+        for (int r = 0; r < R; ++r) c0[e][r] = c1[e][r] = 0.0;
+    }
+    int k = 0;
+    for (; k + 1 < m; k += 2) {
+        double d0[C], d1[C];
+#pragma unroll
+        for (int e = 0; e < C; ++e) {
+            d0[e] = t[ADJ_BLOCK * e + k] - mu[e];
+            d1[e] = t[ADJ_BLOCK * e + k + 1] - mu[e];
+            vv[e] = fma(d0[e], d0[e], vv[e]);
+            vv[e] = fma(d1[e], d1[e], vv[e]);
+        }
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const double x0 = xs[r * stride + k], x1 = xs[r * stride + k + 1];
+#pragma unroll
+            for (int e = 0; e < C; ++e) {
+                c0[e][r] = fma(x0, d0[e], c0[e][r]);
+                c1[e][r] = fma(x1, d1[e], c1[e][r]);
+            }
+        }
+    }
+    if (k < m) {
+#pragma unroll
+        for (int e = 0; e < C; ++e) {
+            const double d0 = t[ADJ_BLOCK * e + k] - mu[e];
+            vv[e] = fma(d0, d0, vv[e]);
+#pragma unroll
+            for (int r = 0; r < R; ++r) c0[e][r] = fma(xs[r * stride + k], d0, c0[e][r]);
+        }
+    }
+#pragma unroll
+    for (int e = 0; e < C; ++e) {
+        v[e] = vv[e];
+#pragma unroll
+        for (int r = 0; r < R; ++r) c[e][r] = c0[e][r] + c1[e][r];
+    }
+}
+
+template <int C>
 __global__ __launch_bounds__(ADJ_BLOCK) void k_adj_rows(const double* __restrict__ T, int64_t n,
-                                                        const int64_t* __restrict__ idx,
+                                                        int64_t K, const int64_t* __restrict__ idx,
                                                         const int32_t* __restrict__ len,
-                                                        const Ctrl* ctrl, double* part,
-                                                        int64_t nblk)
+                                                        const Ctrl* ctrl, double* part, int64_t nblk,
+                                                        int max_run, int stride)
 {
     extern __shared__ double lds[];
     __shared__ double sh[8];
-    __shared__ double rv[ADJ_BLOCK / 64];
-    __shared__ long long rj[ADJ_BLOCK / 64];
-    const int q = blockIdx.y;
-    const int64_t i = idx[q];
-    const int32_t m = len[q];
-    const int64_t N = n - m + 1;
-    const int64_t j0 = (int64_t)blockIdx.x * ADJ_BLOCK;
+    __shared__ double rv[C][ADJ_RUN][ADJ_BLOCK / 64];
+    __shared__ long long rj[C][ADJ_RUN][ADJ_BLOCK / 64];
     const int tid = threadIdx.x;
-    double best = -1e300;
-    long long bj = 0x7fffffffffffffffll;
-    const bool row_ok = m >= 3 && m <= ctrl->m && i >= 0 && i < N;  // ctrl->m holds max length
-    if (row_ok && j0 < N) {
-        double* xs = lds;              // centred window of row i, padded
-        double* ts = lds + (m + 64);   // T[j0 .. j0 + 256 + m + 64)
-        double mui, sgi;
-        adj_window_stats(T, i, m, sh, mui, sgi);
-        for (int k = tid; k < m + 64; k += ADJ_BLOCK) xs[k] = k < m ? T[i + k] - mui : 0.0;
-        for (int t = tid; t < ADJ_BLOCK + m + 64; t += ADJ_BLOCK) ts[t] = T[j0 + t];
-        __syncthreads();
-        const double feps = ctrl->flat_eps;
-        const bool flat_i = sgi <= feps;
-        const int64_t j = j0 + tid;
-        if (j < N && (j <= i - m || j >= i + m)) {
-            const double* t = ts + tid;
-            double s = 0.0;
-            for (int k = 0; k < m; ++k) s += t[k];
-            const double muj = s / (double)m;
-            double v = 0.0, c0 = 0.0, c1 = 0.0;
-            for (int k = 0; k < m; ++k) {
-                const double dk = t[k] - muj;
-                v = fma(dk, dk, v);
-                if (k & 1) c1 = fma(xs[k], dk, c1);
-                else c0 = fma(xs[k], dk, c0);
-            }
-            const double sgj = sqrt(v / (double)m);
-            const bool flat_j = sgj <= feps;
-            double rho;
-            if (flat_i || flat_j) rho = (flat_i && flat_j) ? 1.0 : 0.0;
-            else rho = fmin(1.0, fmax(-1.0, (c0 + c1) / ((double)m * sgi * sgj)));
-            best = rho;
-            bj = j;
+    const int64_t q0 = (int64_t)blockIdx.y * ADJ_ROWS, q1 = std::min<int64_t>(K, q0 + ADJ_ROWS);
+    const int64_t x0 = (int64_t)blockIdx.x * ADJ_SPAN, x1 = std::min<int64_t>(nblk, x0 + ADJ_SPAN);
+    const double feps = ctrl->flat_eps;
+    double* ts = lds;                          // T[j0 .. j0 + 256 C + m)
+    double* xs = lds + (ADJ_BLOCK * C + stride);  // centred windows, stride apart
+    for (int64_t q = q0; q < q1;) {
+        const int32_t m = len[q];
+        int run = 1;
+        while (run < max_run && q + run < q1 && len[q + run] == m) ++run;
+        const int64_t N = n - m + 1;
+        const bool len_ok = m >= 3 && m <= ctrl->m;  // ctrl->m holds max length
+        double sgi[ADJ_RUN];
+        int64_t ii[ADJ_RUN];
+        unsigned int ok = 0u;
+#pragma unroll
+        for (int r = 0; r < ADJ_RUN; ++r) {
+            ii[r] = 0;
+            sgi[r] = 0.0;
+            if (r >= run || !len_ok) continue;
+            ii[r] = idx[q + r];
+            if (ii[r] < 0 || ii[r] >= N) continue;
+            ok |= 1u << r;
+            double mui;
+            adj_window_stats(T, ii[r], m, sh, mui, sgi[r]);
+            for (int k = tid; k < m; k += ADJ_BLOCK) xs[r * stride + k] = T[ii[r] + k] - mui;
         }
-    }
-    for (int o = 32; o >= 1; o >>= 1) {
-        const double v = __shfl_xor(best, o);
-        const long long jj = __shfl_xor(bj, o);
-        if (v > best || (v == best && jj < bj)) {
-            best = v;
-            bj = jj;
-        }
-    }
-    if ((tid & 63) == 0) {
-        rv[tid >> 6] = best;
-        rj[tid >> 6] = bj;
-    }
-    __syncthreads();
-    if (tid == 0) {
-        for (int w = 1; w < ADJ_BLOCK / 64; ++w)
-            if (rv[w] > best || (rv[w] == best && rj[w] < bj)) {
-                best = rv[w];
-                bj = rj[w];
+        for (int64_t x = x0; x < x1; x += C) {
+            const int64_t j0 = x * ADJ_BLOCK;
+            double best[C][ADJ_RUN];
+#pragma unroll
+            for (int e = 0; e < C; ++e)
+#pragma unroll
+                for (int r = 0; r < ADJ_RUN; ++r) best[e][r] = -1e300;
+            __syncthreads();  // the previous blocks and run are consumed
+            if (ok && j0 < N) {
+                for (int t = tid; t < ADJ_BLOCK * C + m; t += ADJ_BLOCK) ts[t] = j0 + t < n ? T[j0 + t] : 0.0;
+                __syncthreads();
+                const double* t = ts + tid;
+                double mu[C], v[C], c[C][ADJ_RUN];
+#pragma unroll
+                for (int e = 0; e < C; ++e) mu[e] = 0.0;
+                for (int k = 0; k < m; ++k)
+#pragma unroll
+                    for (int e = 0; e < C; ++e) mu[e] += t[ADJ_BLOCK * e + k];
+#pragma unroll
+                for (int e = 0; e < C; ++e) mu[e] /= (double)m;
+                switch (run) {
+                case 1: adj_dots<1, C>(t, xs, stride, m, mu, v, c); break;
+                case 2: adj_dots<2, C>(t, xs, stride, m, mu, v, c); break;
+                case 3: adj_dots<3, C>(t, xs, stride, m, mu, v, c); break;
+                case 4: adj_dots<4, C>(t, xs, stride, m, mu, v, c); break;
+                case 5: adj_dots<5, C>(t, xs, stride, m, mu, v, c); break;
+                case 6: adj_dots<6, C>(t, xs, stride, m, mu, v, c); break;
+                case 7: adj_dots<7, C>(t, xs, stride, m, mu, v, c); break;
+                default: adj_dots<8, C>(t, xs, stride, m, mu, v, c); break;
+                }
+#pragma unroll
+                for (int e = 0; e < C; ++e) {
+                    const int64_t j = j0 + ADJ_BLOCK * e + tid;
+                    const double sgj = sqrt(v[e] / (double)m);
+                    const bool flat_j = sgj <= feps;
+#pragma unroll
+                    for (int r = 0; r < ADJ_RUN; ++r) {
+                        if (r >= run || !((ok >> r) & 1u)) continue;
+                        if (j >= N || !(j <= ii[r] - m || j >= ii[r] + m)) continue;
+                        const bool flat_i = sgi[r] <= feps;
+                        best[e][r] = flat_i || flat_j
+                                         ? (flat_i && flat_j ? 1.0 : 0.0)
+                                         : fmin(1.0, fmax(-1.0, c[e][r] / ((double)m * sgi[r] * sgj)));
+                    }
+                }
             }
-        const int64_t slot = ((int64_t)q * nblk + blockIdx.x) * 2;
-        part[slot] = best;
-        part[slot + 1] = bj == 0x7fffffffffffffffll ? 1e300 : (double)bj;  // 1e300: none
+#pragma unroll
+            for (int e = 0; e < C; ++e)
+#pragma unroll
+                for (int r = 0; r < ADJ_RUN; ++r) {
+                    if (r >= run) break;
+                    double b = best[e][r];
+                    long long bj = b > -1e299 ? (long long)(j0 + ADJ_BLOCK * e + tid) : 0x7fffffffffffffffll;
+                    for (int o = 32; o >= 1; o >>= 1) {
+                        const double vv = __shfl_xor(b, o);
+                        const long long jj = __shfl_xor(bj, o);
+                        if (vv > b || (vv == b && jj < bj)) {
+                            b = vv;
+                            bj = jj;
+                        }
+                    }
+                    if ((tid & 63) == 0) {
+                        rv[e][r][tid >> 6] = b;
+                        rj[e][r][tid >> 6] = bj;
+                    }
+                }
+            __syncthreads();
+            const int r = tid & (ADJ_RUN - 1), e = tid / ADJ_RUN;
+            if (e < C && r < run && x + e < x1) {
+                double b = rv[e][r][0];
+                long long bj = rj[e][r][0];
+                for (int w = 1; w < ADJ_BLOCK / 64; ++w)
+                    if (rv[e][r][w] > b || (rv[e][r][w] == b && rj[e][r][w] < bj)) {
+                        b = rv[e][r][w];
+                        bj = rj[e][r][w];
+                    }
+                const int64_t slot = ((q + r) * nblk + x + e) * 2;
+                part[slot] = b;
+                part[slot + 1] = bj == 0x7fffffffffffffffll ? 1e300 : (double)bj;  // 1e300: none
+            }
+        }
+        __syncthreads();  // (the next run's windows take this one's place)
+        q += run;
     }
 }
 
@@ -210,9 +319,15 @@ hipError_t launch_adjoint(const double* Tpad, int64_t n, int64_t K, int32_t maxm
                           int64_t* jstar, hipStream_t st)
 {
     if (K <= 0) return hipSuccess;
-    const size_t lds = sizeof(double) * (size_t)(2 * (maxm + 64) + ADJ_BLOCK);
-    hipLaunchKernelGGL(k_adj_rows, dim3((unsigned int)nblk, (unsigned int)K), dim3(ADJ_BLOCK), lds,
-                       st, Tpad, n, idx, len, ctrl, part, nblk);
+    // as many rows of one length as fit 64 KB beside the columns' values, and
+    // two columns per thread, which share the rows' reads, while those fit
+    const int stride = maxm + 1, cols = maxm <= 2048 ? 2 : 1;
+    const int max_run = std::max(1, std::min(ADJ_RUN, (8000 - ADJ_BLOCK * cols - stride) / stride));
+    const size_t lds = sizeof(double) * (size_t)(ADJ_BLOCK * cols + (max_run + 1) * stride);
+    hipLaunchKernelGGL(cols == 2 ? k_adj_rows<2> : k_adj_rows<1>,
+                       dim3((unsigned int)((nblk + ADJ_SPAN - 1) / ADJ_SPAN),
+                            (unsigned int)((K + ADJ_ROWS - 1) / ADJ_ROWS)),
+                       dim3(ADJ_BLOCK), lds, st, Tpad, n, K, idx, len, ctrl, part, nblk, max_run, stride);
     hipLaunchKernelGGL(k_adj_scatter, dim3((unsigned int)K), dim3(ADJ_BLOCK), 0, st, Tpad, idx, len,
                        gin, ctrl, part, nblk, grad, jstar);
     return hipGetLastError();

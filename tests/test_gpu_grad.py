@@ -180,3 +180,28 @@ def test_config5_gradient():
         compared += 1
     _say("config5 FD compared", compared, "kinks", kinks)
     assert compared >= 48, (compared, kinks)
+
+
+@pytest.mark.parametrize("n,runs,maxm", [
+    (1500, [(20, 9), (21, 1), (20, 8), (23, 2), (2, 1), (20, 17)], 40),   # runs past 8 rows and past 16
+    (511 + 24, [(24, 5), (25, 5), (26, 5), (27, 1)], 27),                 # 512 columns, then fewer
+    (6300, [(2049, 3), (2050, 1)], 2050),                                 # one column per thread
+])
+def test_backward_of_runs_of_rows_matches_the_oracle(n, runs, maxm):
+    """Consecutive rows of one length share their columns' statistics."""
+    dev = _dev()
+    from paper_2304_01660_amd import api
+    T = synth.small_random(323, n, "rw")
+    rng = np.random.default_rng([n, maxm])
+    ln = np.array([m for m, c in runs for _ in range(c)], np.int32)
+    idx = np.array([rng.integers(0, n - max(m, 3) + 1) for m in ln], np.int64)
+    w = rng.standard_normal(len(ln))
+    _say("grad runs", n, runs)
+    gT, nnj = api.discords_backward(torch.from_numpy(T).to(dev), torch.from_numpy(idx).to(dev),
+                                    torch.from_numpy(ln).to(dev), torch.from_numpy(w).to(dev),
+                                    maxm=maxm, return_nn_idx=True)
+    nnj = nnj.cpu().numpy()
+    ok = ln >= 3
+    assert np.all(nnj[~ok] == -1)
+    ref = _oracle_grad(T, idx[ok], ln[ok], nnj[ok], w[ok])
+    np.testing.assert_allclose(gT.cpu().numpy(), ref, rtol=1e-8, atol=1e-10 * np.abs(ref).max())
