@@ -61,9 +61,9 @@ __device__ void adj_window_stats(const double* T, int64_t p, int32_t m, double* 
 // block.  Consecutive rows of one length (a search reports k of each) share a
 // column's mean and deviation and the reads of its window, R at a time; every
 // value is the same as for a row alone.  Bound by the LDS reads, of a row's
-// value for two columns, and the FP64 operations, 3 + R per offset and column.  (325 rows, five per length of 96
-// to 160, 200,000 columns: a row and 256 columns per workgroup 3.36 ms, so
-// 1.80 ms.)
+// value for two columns, and the FP64 operations, 3 + R per offset and column.
+// (325 rows, five per length of 96 to 160, 200,000 columns: a row and 256
+// columns per workgroup 3.36 ms, so 1.80 ms.)
 constexpr int ADJ_ROWS = 16;  // rows per workgroup
 constexpr int ADJ_RUN = 8;    // most rows sharing a column
 constexpr int ADJ_SPAN = 4;

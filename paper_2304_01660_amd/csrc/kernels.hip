@@ -4297,6 +4297,13 @@ __global__ __launch_bounds__(TOPK_BLOCK) void k_dense_top(SeriesDev* S)
 // MERLIN's r otherwise, and set up the series' next range search.  A round
 // without sweeps (full = 0) that turned out to need them is left pending.
 constexpr int END_BLOCK = 1024;
+static_assert(END_BLOCK >= CAND_MAX, "a thread per candidate");
+// Candidates per reported row above which the k largest are found in k rounds
+// of the block's maximum instead of by every candidate's rank: a round costs
+// two barriers and a reduction, a rank two LDS reads per candidate.  (64
+// series with up to a thousand candidates each: k_round_end 41 us per round
+// by ranks, so 15; 12,000 points 18.6, so 17.)
+constexpr int RANK_PER_ROUND = 64;
 __global__ __launch_bounds__(END_BLOCK) void k_round_end(SeriesDev* S, int32_t* rem, int hot_rows,
                                                           int full, int more, float guard,
                                                           int max_attempts, int B,
@@ -4306,6 +4313,8 @@ __global__ __launch_bounds__(END_BLOCK) void k_round_end(SeriesDev* S, int32_t* 
     __shared__ double nn_s[CAND_MAX];
     __shared__ long long id_s[CAND_MAX];
     __shared__ long long jj_s[CAND_MAX];
+    __shared__ unsigned long long ku_s[END_BLOCK / 64];
+    __shared__ long long ki_s[END_BLOCK / 64];
     __shared__ unsigned int nvalid_s;
     const SeriesDev& s = S[blockIdx.x];
     Ctrl* c = s.ctrl;
@@ -4413,10 +4422,42 @@ __global__ __launch_bounds__(END_BLOCK) void k_round_end(SeriesDev* S, int32_t* 
     const bool redo = !lean && c->band_over != 0;
     const bool ok = ns >= (unsigned int)k && kp >= k && !redo;
     const int nv = kp >= k ? (int)nvalid_s : 0;
-    if (ok && tid < nv) {
-        const int t = tid;
-        const double nt = nn_s[t];
-        const long long it = id_s[t];
+    auto write_row = [&](int t, int rank) {
+        const int64_t row = (int64_t)li * k + rank;
+        if (s.idx) {
+            s.idx[row] = id_s[t];
+            s.len[row] = m;
+            s.nn[row] = nn_s[t];
+            s.nnidx[row] = jj_s[t];
+        }
+        if (rank == k - 1) s.hist[li] = nn_s[t];
+    };
+    if (ok && RANK_PER_ROUND * k < nv) {
+        // the largest distance (ties: smallest index) k times; distances are not
+        // negative, so their bits order as they do
+        Key mine = {~0ull, KEY_NONE};
+        if (tid < nv) mine = Key{~(unsigned long long)__double_as_longlong(nn_s[tid]), id_s[tid]};
+        for (int r = 0; r < k; ++r) {
+            const Key v = wave_min_key(mine);
+            if (lane == 0) {
+                ku_s[w] = v.u;
+                ki_s[w] = v.i;
+            }
+            __syncthreads();
+            Key first = {ku_s[0], ki_s[0]};
+            for (int q = 1; q < END_BLOCK / 64; ++q) {
+                const Key x = {ku_s[q], ki_s[q]};
+                if (key_less(x, first)) first = x;
+            }
+            if (mine.i == first.i) {
+                write_row(tid, r);
+                mine = Key{~0ull, KEY_NONE};
+            }
+            __syncthreads();
+        }
+    } else if (ok && tid < nv) {
+        const double nt = nn_s[tid];
+        const long long it = id_s[tid];
         int rank = 0;
 #pragma unroll 8
         for (int e = 0; e < nv; ++e) {
@@ -4424,16 +4465,7 @@ __global__ __launch_bounds__(END_BLOCK) void k_round_end(SeriesDev* S, int32_t* 
             const long long ie = id_s[e];
             rank += (ne > nt || (ne == nt && ie < it)) ? 1 : 0;
         }
-        if (rank < k) {
-            const int64_t row = (int64_t)li * k + rank;
-            if (s.idx) {
-                s.idx[row] = id_s[t];
-                s.len[row] = m;
-                s.nn[row] = nn_s[t];
-                s.nnidx[row] = jj_s[t];
-            }
-            if (rank == k - 1) s.hist[li] = nn_s[t];
-        }
+        if (rank < k) write_row(tid, rank);
     }
     __syncthreads();
     if (tid == 0) {
