@@ -38,16 +38,16 @@ FP64_PEAK_TFLOPS = 78.6
 # for the covariance update, one multiply by 1/(sqrt(m) sigma_j), one compare
 # (selection) or max (refinement).
 OPS_PER_EVAL = 4
-# Algorithmic HBM bytes of the per-length statistics step per subsequence
-# and length: the series value (8), mean and sigma read and written (32),
-# three FP32 helpers (12), two bitmaps (1/4, rounded into the 52).
-LENGTH_BYTES_PER_SUBSEQ = 52
+# Algorithmic HBM bytes of the per-length step per subsequence and length: the
+# series value (8), mean and variance read and written (32), the inverse
+# deviation (8), the witness (4) and its covariance read and written (16).
+LENGTH_BYTES_PER_SUBSEQ = 68
 KERNEL_NAMES = {
     "select_near": "k_select_near",
-    "select_far": "k_select_far",
+    "select_far": "k_select_far, k_dense",
     "refine": "k_refine",
-    "polish": "k_polish",
-    "length": "k_length",
+    "polish": "k_screen, k_exact",
+    "length": "k_advance, k_rescue",
     "select_band": "k_select_band",
 }
 CLASS_NAMES = ("select_near", "select_far", "refine", "polish", "length", "select_band")
@@ -187,7 +187,7 @@ def check_golden(out, golden):
 
 
 def search_leg(api, torch, dev, w, tuned, steps, warmup):
-    """Time the full search (production path: graph replay, no events), then
+    """Time the full search (production path: no events), then
     the same steps with HIP events around every kernel class on the
     library's stream."""
     T = torch.from_numpy(w.T).to(dev)
@@ -275,7 +275,7 @@ def batched_vs_plain(api, synth, tuning, torch, dev, reps: int, retune: bool):
     length range of 51 lengths, top-1): one batched call against a loop of
     single-series calls over the same series.  The batched call uses tile
     geometry from the autotuner (tuned on the batch, outside the timing); the
-    loop gets the best of: default geometry with graph replay, default
+    loop gets the best of: default geometry with the graph flag clear, default
     geometry with direct launches, and the tuned geometry."""
     ws = synth.config4()
     vals = [torch.from_numpy(w.T).to(dev) for w in ws]

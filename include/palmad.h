@@ -432,8 +432,7 @@ void palmad_stream_destroy(palmad_stream* st);
  * the same options, but the workspace is a static device array of
  * PALMAD_STATIC_WORKSPACE_BYTES bytes held by each GPU the library runs on
  * until the process ends (its address is taken once per device by
- * palmad_create()).  The call allocates no device memory and launches every
- * kernel directly (no graph is instantiated).
+ * palmad_create()).  The call allocates no device memory.
  *
  *   T ... count, stats, stream  as palmad_discords().
  * Returns PALMAD_EWORKSPACE when palmad_workspace_size() for these

@@ -7,7 +7,7 @@
 // block; one "round" performs one range search (one DRAG call, Alg. 2) for
 // every series that still has work, each at its own length and attempt.  All
 // geometry and state are read from device descriptors, so a round is a fixed
-// sequence of launches that can be captured once in a hipGraph.
+// sequence of launches.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -18,7 +18,7 @@ namespace palmad {
 
 constexpr int WAVE = 64;
 constexpr int R_MAX = 512;   // tallest row tile (64 lanes x 8 rows)
-constexpr int KP_EXTRA = 4;  // candidates polished beyond k
+constexpr int KP_EXTRA = 4;  // candidates evaluated beyond k
 constexpr int K_MAX = 64;
 constexpr int KP_MAX = K_MAX + KP_EXTRA;
 // The exact pass: most candidates of one round, taken in groups; columns per

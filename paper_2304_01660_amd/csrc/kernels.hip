@@ -28,6 +28,11 @@
 //     step, flushed to the candidate bitmap every 64 columns with one atomic.
 //   * Long scans are split into column chunks fed from a device work list in
 //     nearest-first order, so the critical path is one chunk, not one row.
+//   * Most range searches sweep nothing: every row carries the neighbour that
+//     pruned it to the next length (k_advance, k_rescue), and the few rows left
+//     are bounded against every column on the FP16 matrix cores (k_screen) and
+//     decided in FP64 (k_exact).  Where thousands of rows are left, k_dense
+//     bounds them in the same way.
 //   * Every kernel serves a batch of series: flat block indices map to
 //     (series, block) through host-built prefix tables, the queued passes
 //     drain each series' work list in turn, and all per-series geometry and
@@ -2546,7 +2551,7 @@ __device__ __forceinline__ Key wave_min_key(Key k)
     return k;
 }
 
-// The round's range discords and the candidates to polish (one block per
+// The round's range discords and the exact pass's candidates (one block per
 // series).  After a refinement sweep: count the subsequences still alive
 // (the range discords of this range search), pick the k + KP_EXTRA with the
 // smallest refined correlation (largest distance; ties: smaller index).  Each
@@ -2693,7 +2698,7 @@ __global__ __launch_bounds__(TOPK_BLOCK) void k_select_top(SeriesDev* S)
         if (!exact) {
             // Every row whose key is within 2g of the k-th smallest may hold
             // one of the k smallest exact values (keys are within g of
-            // exact): all of them are polished, up to KP_MAX; beyond that
+            // exact): all of them are evaluated, up to KP_MAX; beyond that
             // the round is repeated with exact refinement.
             const double g = c->thr_sel - c->thr64;
             const unsigned long long ub = ord_of(dbl_of(kth_s) + 2.0 * g);
