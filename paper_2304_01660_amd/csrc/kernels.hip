@@ -3010,8 +3010,9 @@ __device__ __forceinline__ float2 chunk_column(const ChunkRegs& R, int q, int32_
 }
 
 // The chunks of every series (blocks past a series' last one exit), so that a
-// round copies its chunks instead of scaling and converting them again: k_dense of 51,000 rows, m = 96, 200,000 points, 8.3 -> 6.5 ms (550
-// TFLOP/s).  Bound by the copy; 300,000 points 6 us.
+// round copies its chunks instead of scaling and converting them again
+// (k_dense of 51,000 rows, m = 96, 200,000 points: 8.3 -> 6.5 ms).  Bound by
+// the copy; 1,000,000 points 8.8 us.
 __global__ __launch_bounds__(256) void k_half(SeriesDev* S)
 {
     __shared__ double rlo[4], rhi[4];
@@ -3704,9 +3705,9 @@ __global__ __launch_bounds__(64 * EX_WAVES) void k_exact(SeriesDev* S, int B, in
 // (k_dense_top).  Heatmaps report every range discord's exact maximum, and
 // windows past 256 points leave no room for the operands: both sweep.
 // Measured against sweeps: 200,000 points, m = 96, 51,000 range discords: the
-// round's sweeps 14 ms, this 8.4 ms (430 TFLOP/s); 64 series of 10,000 to
-// 200,000 points: the search 480 ms, now 175; 100,000 points, lengths 90-140:
-// 8.4 ms, now 7.2.
+// round's sweeps 14 ms, this 5.7 ms (620 TFLOP/s); 64 series of 10,000 to
+// 200,000 points: the search 480 ms, with dense rounds 175; 100,000 points,
+// lengths 64-128: 8.4 ms, then 7.2.
 constexpr int DN_ROWS = DENSE_ROWS;      // rows per item, DN_G groups of 16
 constexpr int DN_G = DN_ROWS / 16;
 constexpr int DN_BUF = 512;              // entries buffered per workgroup
@@ -3788,8 +3789,10 @@ __global__ __launch_bounds__(TOPK_BLOCK) void k_dense_list(SeriesDev* S, int ful
 // One item: DN_ROWS listed rows against one segment of the columns, four waves
 // of 128 columns each per chunk of 512.  A wave computes a 64 x 128 tile of
 // products in parts (128 accumulators do not fit two waves per SIMD); for
-// windows of 33 to 128 points (STEPS = 4) the rows' operands stay in registers
-// for the whole item, so that eight matrix instructions take two LDS reads;
+// windows of 33 to 128 points (STEPS operand steps of 32) the rows' operands
+// stay in registers for the whole item, as many as the window needs, so that
+// eight matrix instructions take two LDS reads (200,000 points, m = 96: four
+// steps kept for every window 6.5 ms, three 5.7);
 // from LDS (STEPS = 0, every other window) they take six, which is as long as
 // the products.  The next chunk's series values are fetched during the
 // products.  Bound by the matrix cores (2 m flops per pair) and, for short
@@ -3937,8 +3940,7 @@ __device__ __forceinline__ void dense_item(const SeriesDev& s, Ctrl* c, int64_t 
             for (int st = 0; st < STEPS; ++st)
 #pragma unroll
                 for (int g = 0; g < DN_G; ++g)
-                    if (st < steps)
-                        areg[st][g] = *(const half8_t*)(ap + 16 * g * stride + 32 * st);
+                    areg[st][g] = *(const half8_t*)(ap + 16 * g * stride + 32 * st);
             fresh = false;
         }
         if (ch + 1 < ch1) fetch_chunk(s, mu, inv, ch + 1, R);
@@ -3961,7 +3963,6 @@ __device__ __forceinline__ void dense_item(const SeriesDev& s, Ctrl* c, int64_t 
             if (STEPS) {
 #pragma unroll
                 for (int st = 0; st < STEPS; ++st) {
-                    if (st >= steps) break;
 #pragma unroll
                     for (int u = 0; u < NU; ++u) {
                         const half8_t bv = wcopy[NU * hf + u][slot + 4 * st];
@@ -4136,8 +4137,8 @@ __global__ __launch_bounds__(64 * SC_WAVES, 2) void k_dense(SeriesDev* S, int B,
 #define DENSE_ITEM(ST)                                                                        \
     dense_item<ST>(s, c, tile, seg, segs, dxa, wcopy, gjs, rows, bnd, &dead_s, &npair_s, &gbase_s, buf)
         switch ((c->m + 31) >> 5) {
-        case 2:
-        case 3:
+        case 2: DENSE_ITEM(2); break;
+        case 3: DENSE_ITEM(3); break;
         case 4: DENSE_ITEM(4); break;
         default: DENSE_ITEM(0); break;
         }
