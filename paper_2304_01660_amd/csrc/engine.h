@@ -31,7 +31,11 @@ constexpr int EXACT_COLS = 128;
 constexpr int SCREEN_COLS = 512;
 constexpr int HALF_STRIDE = SCREEN_COLS + 256 + 16;  // FP16 values kept per chunk
 constexpr int SCREEN_GROUPS = 4;  // candidate groups of a screening item (windows of up to 256)
-constexpr int EXACT_GRID = 512;
+// Workgroups of the exact pass: two per CU; a batch's marked blocks lie together
+// more unevenly than one series' (64 series: 512 workgroups 128 us per round,
+// 1024 109; 1,000,000 points 22.5, 27).
+constexpr int EXACT_GRID = 512, EXACT_GRID_BATCH = 1024;
+__host__ __device__ constexpr int exact_grid(int B) { return B == 1 ? EXACT_GRID : EXACT_GRID_BATCH; }
 constexpr int SCREEN_GRID = 512;  // two workgroups per CU
 constexpr int64_t SCREEN_MIN = 8192;
 // A round without sweeps takes at most LEAN_PAIRS (rows, columns) pairs.

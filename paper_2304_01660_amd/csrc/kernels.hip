@@ -4362,7 +4362,7 @@ __global__ __launch_bounds__(END_BLOCK) void k_round_end(SeriesDev* S, int32_t* 
         const int64_t first = B == 1 ? 0 : ipfx_e[blockIdx.x];
         const int64_t total =
             B == 1 ? (int64_t)((kp + CAND_GROUP - 1) / CAND_GROUP) * nblk : ipfx_e[B];
-        const int64_t per = (total + EXACT_GRID - 1) / EXACT_GRID;
+        const int64_t per = (total + exact_grid(B) - 1) / exact_grid(B);
         for (int cid = tid / tpc; cid < kp; cid += END_BLOCK / tpc) {
             double best = -f_inf<double>(), bj = 1e300;
             const int g = cid / CAND_GROUP;
@@ -5051,7 +5051,7 @@ static void launch_exact(const Batch& bt, const SweepCfg& cfg, int full, hipStre
                                full, bt.ipfx);
     }
     const size_t lds = sizeof(double) * (size_t)(PM_G * PM_XS + EX_COLS + bt.maxL_all + 4 * EX_STEPS);
-    hipLaunchKernelGGL(k_exact, dim3(EXACT_GRID), dim3(64 * EX_WAVES), lds, st, bt.s, bt.B, full,
+    hipLaunchKernelGGL(k_exact, dim3(exact_grid(bt.B)), dim3(64 * EX_WAVES), lds, st, bt.s, bt.B, full,
                        screened ? 1 : 0, SCREEN_GRID, bt.ipfx, bt.ipfx + bt.B + 1);
     cfg.timer->end(3, st);
 }
@@ -5507,7 +5507,7 @@ bool make_layout(int64_t n, int32_t minL, int32_t maxL, int32_t k, Layout* out)
     l.nwords = l.Npad / 64 + 1;
     const int64_t nblk = (l.Nmax + EXACT_COLS - 1) / EXACT_COLS;
     const int64_t nch = (l.Nmax + SCREEN_COLS - 1) / SCREEN_COLS;
-    l.pcap = std::min<int64_t>(EXACT_GRID, CAND_GROUPS * nblk) + 2 * CAND_GROUPS;
+    l.pcap = std::min<int64_t>(EXACT_GRID_BATCH, CAND_GROUPS * nblk) + 2 * CAND_GROUPS;
     // groups go SCREEN_GROUPS at a time where windows are short
     constexpr int SG = CAND_GROUPS / SCREEN_GROUPS;
     l.lbcap = std::max<int64_t>(std::min<int64_t>(SCREEN_GRID, CAND_GROUPS * nch) + 2 * CAND_GROUPS,
