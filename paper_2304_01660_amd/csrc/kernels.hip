@@ -4329,8 +4329,11 @@ __global__ __launch_bounds__(END_BLOCK) void k_round_end(SeriesDev* S, int32_t* 
         if (tid == 0 && c->error) atomicAdd(&rem[REM_ERROR], 1);  // stays visible in later rounds
         return;
     }
-    const bool lean = lean_round(c);
-    if (!full && !lean && !c->handled) {
+    // the round's kind, read before any barrier: next_range rewrites the control
+    // block at the end, and a wave that read it there could take another branch
+    // (with barriers in it) than the thread that runs next_range
+    const bool lean = lean_round(c), handled = c->handled != 0;
+    if (!full && !lean && !handled) {
         if (tid == 0) {
             c->pending = 1;
             if (c->dense == DENSE_NO && dense_allowed(s, c)) c->dense = DENSE_LEFT;
@@ -4499,7 +4502,7 @@ __global__ __launch_bounds__(END_BLOCK) void k_round_end(SeriesDev* S, int32_t* 
             c->done = 0;
         }
     }
-    if (full && !lean && !c->handled) {
+    if (full && !lean && !handled) {
         // Hot tiles of hot_rows rows, in ascending order (the first HOT_MAX of
         // them): those that still hold survivors or whose first-pass items swept
         // at least N / HOT_FRAC columns this round.  The next sweep's first
@@ -4546,6 +4549,7 @@ __global__ __launch_bounds__(END_BLOCK) void k_round_end(SeriesDev* S, int32_t* 
             c->hot_r = hot_rows;
         }
     }
+    __syncthreads();  // (nothing of the round is read past this point)
     if (more && tid == 0) next_range(s, c, guard, max_attempts, rem);
 }
 
