@@ -4115,7 +4115,7 @@ __global__ __launch_bounds__(ITEMS_BLOCK) void k_dense_items(SeriesDev* S, int B
 __global__ __launch_bounds__(64 * SC_WAVES, 2) void k_dense(SeriesDev* S, int B,
                                                             const int64_t* __restrict__ pfx)
 {
-    extern __shared__ _Float16 dxa[];  // [DN_ROWS][dense_stride(m)]
+    extern __shared__ __align__(16) _Float16 dxa[];  // [DN_ROWS][dense_stride(m)]
     __shared__ half8_t wcopy[8][SC_SLOTS];
     __shared__ float gjs[SC_COLS];
     __shared__ int32_t rows[DN_ROWS];
