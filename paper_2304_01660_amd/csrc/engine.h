@@ -62,7 +62,12 @@ constexpr int DENSE_GRID = 512;
 constexpr int DENSE_MAXM = 256;
 constexpr int DENSE_NEAR = 16384;             // columns of its first pass at the second range,
 constexpr int64_t DENSE_NEAR_MAXN = 131072;   // for series of at most so many subsequences
-__host__ __device__ constexpr int64_t dense_pairs(int64_t Npad) { return 2 * Npad; }
+// (the counter has 32 bits and runs past the list by what the workgroups hold
+// when it fills, a few million entries at most)
+__host__ __device__ constexpr int64_t dense_pairs(int64_t Npad)
+{
+    return 2 * Npad < ((int64_t)1 << 31) ? 2 * Npad : (int64_t)1 << 31;
+}
 // Streaming series: lengths handled together so that one launch holds about
 // STREAM_ROWS rows, an odd number of at most STREAM_LANES; the profile
 // update's longest chunk of columns, the items it should have, and its
@@ -134,6 +139,7 @@ struct Ctrl {
     int32_t dense;     // kind of dense round (DENSE_*)
     int32_t handled;   // 1: this round's rows went through k_dense_list
     uint32_t ndense, npairs;  // its listed rows, entries for k_pairs
+    uint32_t lost;     // 1: the entries did not fit, and the round gives up
     int32_t pending;   // 1: the range search waits for a round with sweeps
     uint32_t lean_max; // most rows of a round without sweeps
     int32_t heat_m;    // length whose heatmap row k_heat writes (0: none)

@@ -138,6 +138,11 @@ __device__ __forceinline__ unsigned long long load_word(const unsigned long long
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+__device__ __forceinline__ unsigned int load_flag(const uint32_t* p)
+{
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 __device__ __forceinline__ double wave_sum(double v)
 {
 #pragma unroll
@@ -222,10 +227,16 @@ __device__ __forceinline__ void set_sel_thresholds(Ctrl* c, float guard)
 
 // A round that bounds every row left, by a short first pass (DENSE_SWEEP) or by
 // the witnesses (DENSE_LEFT), instead of sweeping on (see k_dense).
-enum { DENSE_NO = 0, DENSE_SWEEP, DENSE_OFF, DENSE_LEFT };
+// DENSE_OFF: not at this length; DENSE_NEVER: not again in this call (the bounds
+// of this series decide too little).
+enum { DENSE_NO = 0, DENSE_SWEEP, DENSE_OFF, DENSE_LEFT, DENSE_NEVER };
 __device__ __forceinline__ bool dense_round(const Ctrl* c)
 {
     return c->dense == DENSE_SWEEP || c->dense == DENSE_LEFT;
+}
+__device__ __forceinline__ bool dense_off(const Ctrl* c)
+{
+    return c->dense == DENSE_OFF || c->dense == DENSE_NEVER;
 }
 // Columns of the short first pass: most rows of the second range (r = sqrt(m))
 // fall within a few thousand columns where they fall at all; from the third
@@ -284,12 +295,12 @@ __device__ void begin_range(const SeriesDev& s, Ctrl* c, float guard)
     if (c->new_len) {
         c->flat_min = 0x7fffffffffffffffll;
         c->flat_max = -1;
-        c->dense = DENSE_NO;
+        if (c->dense != DENSE_NEVER) c->dense = DENSE_NO;
     }
     c->handled = 0;
     // from the second range of the first length on (long series: the third;
     // there the second leaves few rows to sweep and many columns to bound)
-    if (c->dense != DENSE_OFF)
+    if (!dense_off(c))
         c->dense = c->mode == 0 && c->attempt >= (N <= DENSE_NEAR_MAXN ? 1 : 2) &&
                            s.heat == nullptr && m <= DENSE_MAXM && c->thr64 >= DENSE_MIN_THR
                        ? DENSE_SWEEP
@@ -3719,7 +3730,7 @@ constexpr int DN_BUF = 512;              // entries buffered per workgroup
 __device__ __forceinline__ bool dense_allowed(const SeriesDev& s, const Ctrl* c)
 {
     return c->prune && c->nlive != 0x7fffffffu && s.heat == nullptr && c->m <= DENSE_MAXM &&
-           c->thr64 >= DENSE_MIN_THR && c->dense != DENSE_OFF;
+           c->thr64 >= DENSE_MIN_THR && !dense_off(c);
 }
 __global__ __launch_bounds__(TOPK_BLOCK) void k_dense_list(SeriesDev* S, int full)
 {
@@ -3773,6 +3784,7 @@ __global__ __launch_bounds__(TOPK_BLOCK) void k_dense_list(SeriesDev* S, int ful
         c->handled = 1;
         c->rows_near += base;
         c->npairs = 0;
+        c->lost = 0;
         if (base <= lean_max) {
             c->dense = DENSE_NO;
             c->live_ref = base;  // a direct round
@@ -3808,7 +3820,7 @@ __device__ __forceinline__ void dense_item(const SeriesDev& s, Ctrl* c, int64_t 
                                            int32_t* rows,
                                            float (*bnd)[SC_WAVES][DN_ROWS],
                                            unsigned long long* dead_p, unsigned int* npair_p,
-                                           unsigned int* gbase_p, int2* buf)
+                                           unsigned int* gbase_p, unsigned int* lost_p, int2* buf)
 {
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const int ca = lane & 15, ka = lane >> 4;
@@ -3821,10 +3833,15 @@ __device__ __forceinline__ void dense_item(const SeriesDev& s, Ctrl* c, int64_t 
     const float thr = (float)c->thr64;
     const int stride = dense_stride(m);
     __syncthreads();  // (the previous item is consumed)
-    if (tid == 0) *npair_p = 0u;
+    const int64_t room = dense_pairs(s.Npad);
+    if (tid == 0) {
+        *npair_p = 0u;
+        *lost_p = load_flag(&c->lost);
+    }
     if (tid < DN_ROWS)
         rows[tid] = s.fail[std::min<int64_t>(tile * DN_ROWS + tid, (int64_t)nrow - 1)];
     __syncthreads();
+    if (*lost_p) return;
     // the rows' windows, centred and scaled to norm 1024
 #pragma unroll 1
     for (int r0 = w; r0 < DN_ROWS; r0 += 4 * SC_WAVES) {
@@ -3895,10 +3912,13 @@ __device__ __forceinline__ void dense_item(const SeriesDev& s, Ctrl* c, int64_t 
     ChunkRegs R;
     auto flush = [&]() {  // hand the listed entries over (whole workgroup)
         const unsigned int np = min(*npair_p, (unsigned int)DN_BUF);
-        if (tid == 0 && np) *gbase_p = atomicAdd(&c->npairs, np);
+        if (tid == 0 && np) {
+            *gbase_p = atomicAdd(&c->npairs, np);
+            if ((int64_t)*gbase_p + np > room) atomicOr(&c->lost, 1u);
+        }
         __syncthreads();
         for (unsigned int q = tid; q < np; q += 64 * SC_WAVES)
-            if ((int64_t)*gbase_p + q < dense_pairs(s.Npad)) s.pairs[*gbase_p + q] = buf[q];
+            if ((int64_t)*gbase_p + q < room) s.pairs[*gbase_p + q] = buf[q];
         __syncthreads();
         if (tid == 0) *npair_p = 0u;
     };
@@ -3908,8 +3928,9 @@ __device__ __forceinline__ void dense_item(const SeriesDev& s, Ctrl* c, int64_t 
         const int64_t j0 = ch * SC_COLS;
         const int64_t jb = j0 + w * EX_COLS;
         __syncthreads();  // the previous chunk's operands are consumed
-        const unsigned long long dead = *dead_p;  // (written only between the next barrier and this one)
-        if (dead == ~0ull) break;
+        // (both written only between the next barrier and this one)
+        const unsigned long long dead = *dead_p;
+        if (dead == ~0ull || *lost_p) break;
         if (*npair_p > DN_BUF / 2) {
             __syncthreads();
             flush();
@@ -3924,8 +3945,9 @@ __device__ __forceinline__ void dense_item(const SeriesDev& s, Ctrl* c, int64_t 
         }
 #pragma unroll
         for (int o = 32; o >= 1; o >>= 1) em = fmaxf(em, __shfl_xor(em, o));
-        // a dead row's window becomes zero: its products then stay far below the
-        // threshold (positive by DENSE_MIN_THR)
+        // a dead row's window becomes zero: its products then stay below the
+        // threshold (positive by DENSE_MIN_THR); with a wide bound they pass the
+        // test below all the same, which leaves the dead rows out
         if (dead != seen) {
             for (unsigned long long d = (dead & ~seen) & (0x1111111111111111ull << w); d; d &= d - 1ull) {
                 const int r = __ffsll((long long)d) - 1;
@@ -3944,6 +3966,7 @@ __device__ __forceinline__ void dense_item(const SeriesDev& s, Ctrl* c, int64_t 
             fresh = false;
         }
         if (ch + 1 < ch1) fetch_chunk(s, mu, inv, ch + 1, R);
+        if (tid == 0) *lost_p = load_flag(&c->lost);
         if (jb >= N) continue;  // (the next barrier is the loop's first)
         const int slot = w * (EX_COLS / 8) + ca + ka;
         const bool edge = __ballot(jb + EX_COLS > N ||
@@ -4031,15 +4054,16 @@ __device__ __forceinline__ void dense_item(const SeriesDev& s, Ctrl* c, int64_t 
                 float v = mx[0];
 #pragma unroll
                 for (int e = 1; e < 4 * DN_G; ++e) v = q == e ? mx[e] : v;
-                if (!(v + em > thr)) continue;
                 const int rr = 16 * (q >> 2) + 4 * ka + (q & 3);
+                if (!(v + em > thr) || ((dead >> rr) & 1ull)) continue;
                 const int2 pr = make_int2(rows[rr], (int32_t)jb + 8 * ca);
                 const unsigned int p = atomicAdd(npair_p, 1u);
                 if (p < (unsigned int)DN_BUF) {
                     buf[p] = pr;
                 } else {  // (buffer full)
                     const unsigned int gp = atomicAdd(&c->npairs, 1u);
-                    if ((int64_t)gp < dense_pairs(s.Npad)) s.pairs[gp] = pr;
+                    if ((int64_t)gp < room) s.pairs[gp] = pr;
+                    else if ((int64_t)gp == room) atomicOr(&c->lost, 1u);
                 }
                 if (v - em > thr) atomicOr(dead_p, 1ull << rr);  // surely closer than r
             }
@@ -4121,7 +4145,7 @@ __global__ __launch_bounds__(64 * SC_WAVES, 2) void k_dense(SeriesDev* S, int B,
     __shared__ int32_t rows[DN_ROWS];
     __shared__ float bnd[2][SC_WAVES][DN_ROWS];
     __shared__ unsigned long long dead_s;
-    __shared__ unsigned int npair_s, gbase_s;
+    __shared__ unsigned int npair_s, gbase_s, lost_s;
     __shared__ int2 buf[DN_BUF];
     const int64_t tiles = B == 1 ? dense_tiles(S[0].ctrl) : pfx[B];
     if (tiles == 0) return;
@@ -4135,7 +4159,7 @@ __global__ __launch_bounds__(64 * SC_WAVES, 2) void k_dense(SeriesDev* S, int B,
         Ctrl* c = s.ctrl;
         const int64_t tile = t - (B == 1 ? 0 : pfx[b]);
 #define DENSE_ITEM(ST)                                                                        \
-    dense_item<ST>(s, c, tile, seg, segs, dxa, wcopy, gjs, rows, bnd, &dead_s, &npair_s, &gbase_s, buf)
+    dense_item<ST>(s, c, tile, seg, segs, dxa, wcopy, gjs, rows, bnd, &dead_s, &npair_s, &gbase_s, &lost_s, buf)
         switch ((c->m + 31) >> 5) {
         case 2: DENSE_ITEM(2); break;
         case 3: DENSE_ITEM(3); break;
@@ -4167,7 +4191,7 @@ __global__ __launch_bounds__(RESCUE_BLOCK) void k_pairs(SeriesDev* S, int B,
         if (first > wave) break;
         const SeriesDev& s = S[b];
         Ctrl* c = s.ctrl;
-        if (t0 == t1 || !c->active || lean_round(c) || !dense_round(c) || !c->handled) continue;
+        if (t0 == t1 || !c->active || lean_round(c) || !dense_round(c) || !c->handled || c->lost) continue;
         const int64_t nper = (t1 * nwaves - 1) / tiles - first + 1, w = wave - first;
         const int32_t m = c->m;
         const int64_t N = s.n - m + 1;
@@ -4256,7 +4280,7 @@ __global__ __launch_bounds__(TOPK_BLOCK) void k_dense_top(SeriesDev* S)
         c->nsurv = ns;
         c->ncand = 0;
     }
-    const bool lost = (int64_t)c->npairs > dense_pairs(s.Npad);
+    const bool lost = c->lost != 0;
     if (ns < (unsigned int)k && !lost) return;
     Key kth = {0ull, -1};
     for (int r = 0; r < k && !lost; ++r) {
@@ -4290,7 +4314,7 @@ __global__ __launch_bounds__(TOPK_BLOCK) void k_dense_top(SeriesDev* S)
     if (tid == 0) {
         if (lost || nc_s > (unsigned int)CAND_MAX) {
             c->band_over = 1;  // the range again, with sweeps
-            c->dense = DENSE_OFF;
+            c->dense = lost ? DENSE_NEVER : DENSE_OFF;
         } else {
             c->ncand = nc_s;
         }

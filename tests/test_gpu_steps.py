@@ -1,0 +1,105 @@
+"""Series whose level jumps (a noisy periodic signal, switched on and off): a
+chunk of the screening holds both levels, so its FP16 values resolve the signal
+poorly and the error bound decides little.  A dense round then hands over more
+pairs than its list holds; it gives up, the sweeps decide, and no later length
+of the call tries again.  Heatmaps never take a dense round: every row and
+count equals theirs, and the first length's distances are checked in FP64."""
+
+import math
+import sys
+
+import numpy as np
+import pytest
+
+from parity_helpers import close_ed
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+KEYS = ("idx", "len", "nn_dist", "nn_idx", "count")
+FAR = 1  # kernel class of the split selection pass and of k_dense
+
+
+def _dev():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    return torch.device("cuda:0")
+
+
+def _say(*a):
+    print("[case]", *a, file=sys.stderr, flush=True)
+
+
+def stepped(n, m, jump, seed):
+    """A sine of twice the noise's power; levels 0 and `jump` deviations of the
+    noise in turn, 150 to 600 points each."""
+    rng = np.random.default_rng([seed, n])
+    T = 2.0 * np.sin(2.0 * np.pi * np.arange(n) / (0.8 * m)) + rng.standard_normal(n)
+    p, on = 0, False
+    while p < n:
+        q = p + int(rng.integers(150, 600))
+        T[p:q] += jump if on else 0.0
+        p, on = q, not on
+    return T
+
+
+def _profile(T, m):
+    """Largest correlation of every window with a non-self match, in FP64."""
+    w = T.unfold(0, m, 1)
+    w = w - w.mean(1, keepdim=True)
+    w = w / w.norm(dim=1, keepdim=True)
+    N = w.shape[0]
+    col = torch.arange(N, device=T.device)
+    out = []
+    for a in range(0, N, 2048):
+        r = w[a:a + 2048] @ w.t().contiguous()
+        r[(col[None, :] - col[a:a + 2048, None]).abs() < m] = -2.0
+        out.append(r.max(1).values)
+    return torch.cat(out).clamp(-1.0, 1.0)
+
+
+@pytest.mark.parametrize("jump", [500.0, 1000.0, 3000.0])
+@pytest.mark.parametrize("n", [9000, 20011])
+@pytest.mark.parametrize("dist_bits", [32, 64])
+def test_a_dense_round_that_cannot_decide_gives_up(dist_bits, n, jump):
+    from paper_2304_01660_amd import api
+    dev = _dev()
+    minL, maxL, k = 64, 68, 2
+    _say("steps", dist_bits, n, jump)
+    T = torch.from_numpy(stepped(n, minL, jump, 11)).to(dev)
+    # every first pass covers all columns, so the class FAR holds k_dense alone
+    opts = dict(dist_bits=dist_bits, near_cols=1 << 30, return_stats=True)
+    plain = api.discords(T, minL, maxL, k, **opts)
+    swept = api.discord_heatmap(T, minL, maxL, k, **opts)
+    for key in KEYS:
+        assert torch.equal(plain[key], swept[key]), key
+    rho = _profile(T, minL)
+    d = torch.sqrt(2.0 * minL * (1.0 - rho)).cpu().numpy()
+    r = float(swept["range"][0])
+    assert np.all(close_ed(plain["nn_dist"][:k].cpu().numpy(), np.sort(d)[::-1][:k], minL))
+    if not close_ed(d, np.full_like(d, r), minL).any():
+        assert int(plain["count"][0]) == int((d >= r).sum())
+    # one range search more than the sweeps need: the round that gave up (FP32
+    # sweeps repeat a range search of their own where their guard band is wide)
+    if dist_bits == 64:
+        assert plain["stats"]["range_searches"] <= swept["stats"]["range_searches"] + 1
+    # and it gave up early: its rows (about all of them at r = sqrt(m) / 2)
+    # against a part of the columns
+    N = n - minL + 1
+    left = int((d >= r).sum())
+    assert math.isclose(r, math.sqrt(minL) / 2) and left > 1024
+    if n > 16384:
+        assert plain["stats"]["kernel_evals"][FAR] < 0.5 * left * N
+
+
+def test_a_batch_of_stepped_series_equals_single_searches():
+    from paper_2304_01660_amd import api
+    dev = _dev()
+    vals = [torch.from_numpy(stepped(n, 64, j, 12)).to(dev)
+            for n, j in ((9000, 1000.0), (1200, 500.0), (12000, 0.0), (8300, 3000.0))]
+    _say("steps batch")
+    res = api.discords_batched(vals, [64] * 4, [67] * 4, 2)
+    for b in range(4):
+        one = api.discords(vals[b], 64, 67, 2)
+        for key in KEYS:
+            assert torch.equal(res[b][key], one[key]), (b, key)
