@@ -140,6 +140,8 @@ struct Ctrl {
     int32_t handled;   // 1: this round's rows went through k_dense_list
     uint32_t ndense, npairs;  // its listed rows, entries for k_pairs
     uint32_t lost;     // 1: the entries did not fit, and the round gives up
+    uint32_t cand_at, cand_total;  // its candidates taken so far, of all (0: one pass)
+    int32_t thrown;    // 1: a dense round's candidates were too many
     int32_t pending;   // 1: the range search waits for a round with sweeps
     uint32_t lean_max; // most rows of a round without sweeps
     int32_t heat_m;    // length whose heatmap row k_heat writes (0: none)

@@ -248,6 +248,18 @@ __device__ __forceinline__ int dense_near(const Ctrl* c) { return c->attempt == 
 constexpr double DENSE_LEFT_WORK = 2.5e11;
 constexpr double DENSE_MIN_THR = 0.2;  // smallest threshold of a dense round
 
+// Candidates of a dense round: those whose bounds do not tell them from the k
+// best, usually some hundred, on a noisy series a few thousand.  More than
+// CAND_MAX go through the exact pass in parts, each with the k best so far; a
+// part costs 0.1 ms at 20,000 points and 0.4 at 500,000, the same range again
+// with sweeps 0.5 and 20 to 90.
+__device__ __forceinline__ unsigned int dense_cands(int64_t N)
+{
+    return (unsigned int)CAND_MAX * (unsigned int)std::min<int64_t>(16, std::max<int64_t>(2, N / 32768));
+}
+// The round goes on with the next part of its candidates, and does nothing else.
+__device__ __forceinline__ bool taking_parts(const Ctrl* c) { return c->cand_at > 0; }
+
 __device__ void begin_range(const SeriesDev& s, Ctrl* c, float guard)
 {
     const int li = c->li;
@@ -970,7 +982,7 @@ __global__ __launch_bounds__(ADV_BLOCK) void k_helpers(SeriesDev* S, int B,
     const int b = series_of(pfx, B, blockIdx.x);
     const SeriesDev& s = S[b];
     Ctrl* c = s.ctrl;
-    if (!c->active || lean_round(c)) return;
+    if (!c->active || lean_round(c) || taking_parts(c)) return;  // (the candidates stand in s.fail)
     const int64_t lb = blockIdx.x - pfx[b];
     const int64_t i = lb * (int64_t)ADV_BLOCK + threadIdx.x;
     const int32_t m = c->m;
@@ -2107,7 +2119,7 @@ __global__ __launch_bounds__(64) void k_select_band(SeriesDev* S, int B, const i
     const int b = series_of(pfx, B, blockIdx.x);
     const SeriesDev& s = S[b];
     Ctrl* c = s.ctrl;
-    if (!c->active || !c->prune || lean_round(c)) return;
+    if (!c->active || !c->prune || lean_round(c) || taking_parts(c)) return;
     const SweepArgs<F> A = args_of<F>(s, c);
     const int32_t m = A.m;
     const int64_t i0 = (int64_t)(blockIdx.x - pfx[b]) * BAND_S;
@@ -3737,7 +3749,7 @@ __global__ __launch_bounds__(TOPK_BLOCK) void k_dense_list(SeriesDev* S, int ful
     __shared__ unsigned int wsum[TOPK_BLOCK / 64];
     const SeriesDev& s = S[blockIdx.x];
     Ctrl* c = s.ctrl;
-    if (!c->active || lean_round(c)) return;
+    if (!c->active || lean_round(c) || taking_parts(c)) return;
     if (!dense_round(c) && (full || !dense_allowed(s, c))) return;
     if (!full && c->dense == DENSE_SWEEP) return;  // its first pass has not run
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
@@ -3785,6 +3797,7 @@ __global__ __launch_bounds__(TOPK_BLOCK) void k_dense_list(SeriesDev* S, int ful
         c->rows_near += base;
         c->npairs = 0;
         c->lost = 0;
+        c->cand_total = 0;
         if (base <= lean_max) {
             c->dense = DENSE_NO;
             c->live_ref = base;  // a direct round
@@ -4122,7 +4135,7 @@ __device__ __forceinline__ void dense_item(const SeriesDev& s, Ctrl* c, int64_t 
 // Row tiles of a series' list.
 __device__ __forceinline__ int64_t dense_tiles(const Ctrl* c)
 {
-    return c->active && !lean_round(c) && dense_round(c) && c->handled
+    return c->active && !lean_round(c) && dense_round(c) && c->handled && !taking_parts(c)
                ? ((int64_t)c->ndense + DN_ROWS - 1) / DN_ROWS
                : 0;
 }
@@ -4210,7 +4223,8 @@ __global__ __launch_bounds__(RESCUE_BLOCK) void k_pairs(SeriesDev* S, int B,
         if (first > wave) break;
         const SeriesDev& s = S[b];
         Ctrl* c = s.ctrl;
-        if (t0 == t1 || !c->active || lean_round(c) || !dense_round(c) || !c->handled || c->lost) continue;
+        if (t0 == t1 || !c->active || lean_round(c) || !dense_round(c) || !c->handled) continue;
+        if (taking_parts(c) || c->lost) continue;
         const int64_t nper = (t1 * nwaves - 1) / tiles - first + 1, w = wave - first;
         const int32_t m = c->m;
         const int64_t N = s.n - m + 1;
@@ -4256,7 +4270,8 @@ __global__ __launch_bounds__(RESCUE_BLOCK) void k_pairs(SeriesDev* S, int B,
 // After a dense round (one block per series): the number of range discords,
 // and as candidates every one whose lower bound does not exceed the k-th
 // smallest upper bound (rhs, rho: upper and lower bounds of the largest
-// correlation).  The k-th smallest by k rounds of the block's minimum, each
+// correlation); more than an exact pass takes are listed in s.fail, as the
+// bounds do not outlive the screening.  The k-th smallest by k rounds of the block's minimum, each
 // thread holding its own; only the winner looks for its next.
 __global__ __launch_bounds__(TOPK_BLOCK) void k_dense_top(SeriesDev* S)
 {
@@ -4266,7 +4281,7 @@ __global__ __launch_bounds__(TOPK_BLOCK) void k_dense_top(SeriesDev* S)
     __shared__ unsigned int cnt_s, nc_s;
     const SeriesDev& s = S[blockIdx.x];
     Ctrl* c = s.ctrl;
-    if (!c->active || lean_round(c) || !dense_round(c) || !c->handled) return;
+    if (!c->active || lean_round(c) || !dense_round(c) || !c->handled || taking_parts(c)) return;
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const int64_t nw = (s.n - c->m + 1 + 63) / 64;
     const int k = s.k;
@@ -4326,16 +4341,22 @@ __global__ __launch_bounds__(TOPK_BLOCK) void k_dense_top(SeriesDev* S)
                 if (s.rho[i] <= kth.u) {
                     const unsigned int slot = atomicAdd(&nc_s, 1u);
                     if (slot < (unsigned int)CAND_MAX) s.cand[slot] = i;
+                    s.fail[slot] = (int32_t)i;
                 }
             }
         });
     __syncthreads();
     if (tid == 0) {
-        if (lost || nc_s > (unsigned int)CAND_MAX) {
+        if (lost || nc_s > dense_cands(s.n - c->m + 1)) {
             c->band_over = 1;  // the range again, with sweeps
-            c->dense = lost ? DENSE_NEVER : DENSE_OFF;
+            c->dense = lost || c->thrown ? DENSE_NEVER : DENSE_OFF;
+            c->thrown = 1;
         } else {
-            c->ncand = nc_s;
+            c->ncand = min(nc_s, (unsigned int)CAND_MAX);
+            if (nc_s > (unsigned int)CAND_MAX) {
+                c->cand_total = nc_s;
+                c->cand_at = CAND_MAX;
+            }
         }
     }
 }
@@ -4365,6 +4386,7 @@ __global__ __launch_bounds__(END_BLOCK) void k_round_end(SeriesDev* S, int32_t* 
     __shared__ unsigned long long ku_s[END_BLOCK / 64];
     __shared__ long long ki_s[END_BLOCK / 64];
     __shared__ unsigned int nvalid_s;
+    __shared__ long long next_s[K_MAX];
     const SeriesDev& s = S[blockIdx.x];
     Ctrl* c = s.ctrl;
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
@@ -4376,6 +4398,8 @@ __global__ __launch_bounds__(END_BLOCK) void k_round_end(SeriesDev* S, int32_t* 
     // block at the end, and a wave that read it there could take another branch
     // (with barriers in it) than the thread that runs next_range
     const bool lean = lean_round(c), handled = c->handled != 0;
+    const unsigned int cand_at = handled ? c->cand_at : 0u, cand_total = c->cand_total;
+    const bool parts_left = cand_at > 0 && cand_at < cand_total;
     if (!full && !lean && !handled) {
         if (tid == 0) {
             c->pending = 1;
@@ -4469,13 +4493,17 @@ __global__ __launch_bounds__(END_BLOCK) void k_round_end(SeriesDev* S, int32_t* 
     }
     __syncthreads();
     const unsigned int ns = direct ? (kp >= k ? nvalid_s : (lean ? c->nlive : c->nsurv)) : c->nsurv;
-    // the candidates could not be narrowed to KP_MAX: same r again, with both
-    // sides of every tile refined exactly
+    // the candidates could not be narrowed: same r again, after sweeps with
+    // both sides of every tile refined exactly, after a dense round with sweeps
     const bool redo = !lean && c->band_over != 0;
     const bool ok = ns >= (unsigned int)k && kp >= k && !redo;
     const int nv = kp >= k ? (int)nvalid_s : 0;
     auto write_row = [&](int t, int rank) {
         const int64_t row = (int64_t)li * k + rank;
+        if (parts_left) {
+            next_s[rank] = id_s[t];
+            return;
+        }
         if (s.idx) {
             s.idx[row] = id_s[t];
             s.len[row] = m;
@@ -4520,14 +4548,28 @@ __global__ __launch_bounds__(END_BLOCK) void k_round_end(SeriesDev* S, int32_t* 
         if (rank < k) write_row(tid, rank);
     }
     __syncthreads();
+    if (parts_left) {  // the k best so far and the next part of the candidates
+        const unsigned int take = min(cand_total - cand_at, (unsigned int)(CAND_MAX - k));
+        for (unsigned int e = tid; e < k + take; e += END_BLOCK)
+            s.cand[e] = e < (unsigned int)k ? next_s[e] : (long long)s.fail[cand_at + e - k];
+        if (tid < CAND_GROUPS) c->pcnt[tid] = 0;
+        if (tid == 0) {
+            c->ncand = k + take;
+            c->cand_at = cand_at + take;
+            c->pending = 1;
+            atomicAdd(&rem[REM_LEFT], 1);
+        }
+        return;
+    }
     if (tid == 0) {
+        c->cand_at = 0;
         c->rounds += 1;
         c->nsurv = ns;
         if (lean) {
             c->rows_near += c->nlive;
             c->rows_far += c->nlive;
         }
-        c->exact_ref = redo ? 1 : 0;
+        c->exact_ref = redo && !handled ? 1 : 0;
         c->pending = 0;
         // (a heatmap row of a round that refined: the bitmap's rows, by k_heat)
         c->heat_m = ok && !direct ? m : 0;

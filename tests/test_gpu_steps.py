@@ -103,3 +103,42 @@ def test_a_batch_of_stepped_series_equals_single_searches():
         one = api.discords(vals[b], 64, 67, 2)
         for key in KEYS:
             assert torch.equal(res[b][key], one[key]), (b, key)
+
+
+@pytest.mark.parametrize("jump", [90.0, 110.0, 130.0, 150.0])
+def test_candidates_of_a_dense_round_beyond_one_exact_pass(jump):
+    """Jumps of about a hundred deviations: the bounds still tell range discords
+    from the rest, but leave one to several thousand rows that may be among the
+    k best, up to and past what the exact pass takes in parts."""
+    from paper_2304_01660_amd import api
+    dev = _dev()
+    T = torch.from_numpy(stepped(20011, 64, jump, 3)).to(dev)
+    for k in (2, 64):  # a part carries the k best so far
+        _say("parts", jump, k)
+        plain = api.discords(T, 64, 66, k)
+        swept = api.discord_heatmap(T, 64, 66, k)
+        for key in KEYS:
+            assert torch.equal(plain[key], swept[key]), (k, key)
+    vals = [torch.from_numpy(stepped(n, 64, j, 3)).to(dev)
+            for n, j in ((20011, jump), (9000, 0.0), (16011, 1000.0), (14000, jump))]
+    res = api.discords_batched(vals, [64] * 4, [66] * 4, 2)
+    for b in range(4):
+        one = api.discord_heatmap(vals[b], 64, 66, 2)
+        for key in KEYS:
+            assert torch.equal(res[b][key], one[key]), (b, key)
+
+
+def test_a_long_series_throws_no_dense_round_away():
+    """Beats between quiet baselines, half a million points: between one and
+    three thousand candidates at several lengths."""
+    from paper_2304_01660_amd import api, synth
+    dev = _dev()
+    n, minL, maxL, k = 487755, 38, 42, 5
+    T, _ = synth.ecg_like(np.random.default_rng([3, n, 43]), n, 5, maxL=43)
+    T = torch.from_numpy(synth.fp32_canonical(T)).to(dev)
+    _say("parts", n)
+    plain = api.discords(T, minL, maxL, k, dist_bits=64, return_stats=True)
+    swept = api.discord_heatmap(T, minL, maxL, k, dist_bits=64, return_stats=True)
+    for key in KEYS:
+        assert torch.equal(plain[key], swept[key]), key
+    assert plain["stats"]["range_searches"] == swept["stats"]["range_searches"]
