@@ -456,20 +456,23 @@ int prepare(palmad_ctx* ctx, const Batch& bt, const Plan& p, bool wait = true)
     return rc ? rc : check_finite(ctx, p);
 }
 
-// Rounds without sweeps issued per host check: a finished series makes
-// every kernel of a round return at once, so a few rounds past the end cost
-// little, while each check is a device-to-host copy and a stream
-// synchronisation.
+// Rounds issued per host check where the next ones are likely of one kind: a
+// series that needs another kind waits, and a finished one makes every kernel
+// return at once, so a round too many costs little, while each check is a
+// device-to-host copy and a stream synchronisation.
 constexpr int ROUNDS_PER_CHECK = 4;
 
-// One round with sweeps or dense ones, or ROUNDS_PER_CHECK rounds without.  (Launched
+// Up to ROUNDS_PER_CHECK rounds without sweeps, or with them where a series'
+// last length needed them too; else one, as after the first length's the next
+// are of another kind.  No more than there are lengths left.  (Launched
 // directly: a round is a few kernels of 5-60 us, so the host stays ahead of
 // the device, and a captured graph, bound to one workspace, measured the same
 // on it and cost its capture, 0.4 ms, on every other.)
 int run_rounds(palmad_ctx* ctx, const Batch& bt, const SweepCfg& cfg, const Plan& p, bool full,
-               bool dense)
+               bool steady, bool dense, int lengths)
 {
-    const int rounds = full || dense || cfg.timer->on ? 1 : ROUNDS_PER_CHECK;
+    const bool one = (full && !steady) || dense || cfg.timer->on;
+    const int rounds = one ? 1 : std::min(ROUNDS_PER_CHECK, std::max(1, lengths));
     for (int r = 0; r < rounds; ++r)
         HIP_TRY(launch_round(bt, cfg, p.totals, full, dense, true, ctx->work));
     return PALMAD_OK;
@@ -528,13 +531,15 @@ int search(palmad_ctx* ctx, const Plan& p, const Opts& o, void* ws, const double
     if (rc) return rc;
     HIP_TRY(launch_half(bt, bt.B, ctx->work));
     HIP_TRY(launch_start(bt, cfg, ctx->work));
-    // every issue of rounds completes a range search of at least one series
+    // of two issues of rounds at least one completes a range search of some
+    // series or takes a part of its candidates (at most sixteen)
     int64_t max_checks = 2;
-    for (int b = 0; b < p.B; ++b) max_checks += (int64_t)p.lay[b].L * cfg.max_attempts * 2;
-    bool full = true, dense = false;  // the first length has no witnesses yet
+    for (int b = 0; b < p.B; ++b) max_checks += (int64_t)p.lay[b].L * (cfg.max_attempts * 2 + 32);
+    bool full = true, steady = false, dense = false;  // the first length has no witnesses yet
+    int lengths = 1;
     for (int64_t check = 0;; ++check) {
         if (check > max_checks) return fail(ctx, PALMAD_EDEVICE, "search did not terminate");
-        rc = run_rounds(ctx, bt, cfg, p, full, dense);
+        rc = run_rounds(ctx, bt, cfg, p, full, steady, dense, lengths);
         if (rc) return rc;
         rc = read_counters(ctx, bt);
         if (!rc) rc = check_finite(ctx, p);
@@ -546,6 +551,8 @@ int search(palmad_ctx* ctx, const Plan& p, const Opts& o, void* ws, const double
                         ctx->pinned[REM_ERROR], cfg.max_attempts);
         if (ctx->pinned[REM_LEFT] == 0) break;
         full = ctx->pinned[REM_SWEEP] > 0;
+        steady = ctx->pinned[REM_STEADY] > 0;
+        lengths = ctx->pinned[REM_LENGTHS];
         dense = ctx->pinned[REM_DENSE] > 0;
     }
     const double secs =

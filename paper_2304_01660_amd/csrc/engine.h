@@ -98,11 +98,11 @@ constexpr int EV_SLOTS = 64;
 enum { EV_NEAR = 0, EV_FAR = 1, EV_REF = 2, EV_POL = 3, EV_BAND = 4 };
 
 // Host counters of a round: series with work left, series in error, series
-// waiting (for a round with sweeps or a dense one), series whose next range
-// search needs sweeps (the first length's and those waiting for them), series
-// whose next one is a dense round; then, once per call, series holding NaN or
-// Inf and the first of them.
-enum { REM_LEFT = 0, REM_ERROR, REM_PENDING, REM_SWEEP, REM_DENSE, REM_COUNT };
+// whose next range search needs sweeps (the first length's, those waiting for
+// them and those whose last one did), those whose last two did, series whose
+// next one is a dense round, most lengths left; then, once per call, series holding NaN
+// or Inf and the first of them.
+enum { REM_LEFT = 0, REM_ERROR, REM_SWEEP, REM_STEADY, REM_DENSE, REM_LENGTHS, REM_COUNT };
 enum { REM_BAD = REM_COUNT, REM_BAD_SERIES, REM_TOTAL };
 
 // Device-resident control block of one series (the MERLIN state of Alg. 1
@@ -142,7 +142,8 @@ struct Ctrl {
     uint32_t lost;     // 1: the entries did not fit, and the round gives up
     uint32_t cand_at, cand_total;  // its candidates taken so far, of all (0: one pass)
     int32_t thrown;    // 1: a dense round's candidates were too many
-    int32_t pending;   // 1: the range search waits for a round with sweeps
+    int32_t pending;   // 1: the range search waits for a round of another kind
+    int32_t sweeps;    // how the last range search past the first length swept (SWEEPS_*)
     uint32_t lean_max; // most rows of a round without sweeps
     int32_t heat_m;    // length whose heatmap row k_heat writes (0: none)
     // work lists of the current round (built by k_tiles, read by the queued passes)

@@ -319,6 +319,17 @@ __device__ void begin_range(const SeriesDev& s, Ctrl* c, float guard)
                        : DENSE_NO;
 }
 
+// A length whose rows left are too many for the exact pass, and for which a
+// dense round is no choice (dense_allowed), is followed by others of its kind
+// (heatmaps of noisy series, windows past 256 points): its series asks for
+// sweeps at once instead of waiting for them in a round that can only find that
+// out.  SWEEPS_MANY: the range discords alone were too many, so that second
+// chances cannot make the round one without sweeps; SWEEPS_AGAIN: the one before
+// swept too, and the host issues several such rounds at once.  (Heatmap of 14,098 points,
+// eleven lengths, 1,675 to 2,275 range discords at six of
+// them: 4.2 ms, so 3.5.)
+enum { SWEEPS_NO = 0, SWEEPS_FEW = 1, SWEEPS_MANY = 2, SWEEPS_AGAIN = 4 };
+
 // The next range search of a series (one thread): the first length, the next
 // one after a success, or the same length again with the r that k_round_end
 // lowered.
@@ -355,8 +366,10 @@ __device__ void next_range(const SeriesDev& s, Ctrl* c, float guard, int max_att
     c->active = 1;
     begin_range(s, c, guard);
     atomicAdd(&rem[REM_LEFT], 1);
-    if (c->li == 0) atomicAdd(&rem[REM_SWEEP], 1);
+    if (c->li == 0 || c->sweeps) atomicAdd(&rem[REM_SWEEP], 1);
+    if (c->sweeps & SWEEPS_AGAIN) atomicAdd(&rem[REM_STEADY], 1);
     if (dense_round(c)) atomicAdd(&rem[REM_DENSE], 1);
+    atomicMax(&rem[REM_LENGTHS], s.maxL - c->m + 1);
 }
 
 // Before the first round of a search.
@@ -777,10 +790,10 @@ __global__ __launch_bounds__(ADV_BLOCK) void k_advance(SeriesDev* S, int B,
 // chain of dependent loads per batch, which is why a batch is wide.
 constexpr int RESCUE_TRIES = 2;
 // Too many failures for second chances (a new threshold altogether, e.g. the
-// first length's next r).
+// first length's next r), or too many range discords among them.
 __device__ __forceinline__ bool rescue_hopeless(const Ctrl* c, unsigned int total, int64_t N)
 {
-    return (int64_t)total * 2 > N && total > c->lean_max;
+    return ((int64_t)total * 2 > N || (c->sweeps & SWEEPS_MANY)) && total > c->lean_max;
 }
 
 // The waves of k_rescue that each series of a batch gets (one block, a thread
@@ -4392,6 +4405,7 @@ __global__ __launch_bounds__(END_BLOCK) void k_round_end(SeriesDev* S, int32_t* 
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     if (!c->active) {
         if (tid == 0 && c->error) atomicAdd(&rem[REM_ERROR], 1);  // stays visible in later rounds
+        if (tid == 0) c->heat_m = 0;
         return;
     }
     // the round's kind, read before any barrier: next_range rewrites the control
@@ -4400,12 +4414,14 @@ __global__ __launch_bounds__(END_BLOCK) void k_round_end(SeriesDev* S, int32_t* 
     const bool lean = lean_round(c), handled = c->handled != 0;
     const unsigned int cand_at = handled ? c->cand_at : 0u, cand_total = c->cand_total;
     const bool parts_left = cand_at > 0 && cand_at < cand_total;
-    if (!full && !lean && !handled) {
+    // (a dense round in a launch without dense kernels waits too)
+    const bool swept = full && !dense_round(c);
+    if (!swept && !lean && !handled) {
         if (tid == 0) {
             c->pending = 1;
             if (c->dense == DENSE_NO && dense_allowed(s, c)) c->dense = DENSE_LEFT;
             atomicAdd(&rem[REM_LEFT], 1);
-            atomicAdd(&rem[REM_PENDING], 1);
+            atomicMax(&rem[REM_LENGTHS], s.maxL - c->m + 1);
             if (c->dense != DENSE_LEFT) atomicAdd(&rem[REM_SWEEP], 1);
             if (dense_round(c)) atomicAdd(&rem[REM_DENSE], 1);
         }
@@ -4558,6 +4574,7 @@ __global__ __launch_bounds__(END_BLOCK) void k_round_end(SeriesDev* S, int32_t* 
             c->cand_at = cand_at + take;
             c->pending = 1;
             atomicAdd(&rem[REM_LEFT], 1);
+            atomicMax(&rem[REM_LENGTHS], s.maxL - m + 1);
         }
         return;
     }
@@ -4571,6 +4588,10 @@ __global__ __launch_bounds__(END_BLOCK) void k_round_end(SeriesDev* S, int32_t* 
         }
         c->exact_ref = redo && !handled ? 1 : 0;
         c->pending = 0;
+        const int was = c->sweeps ? SWEEPS_AGAIN : 0;
+        c->sweeps = li == 0 || lean || handled || dense_allowed(s, c)
+                        ? SWEEPS_NO
+                        : was | (ns > c->lean_max ? SWEEPS_MANY : SWEEPS_FEW);
         // (a heatmap row of a round that refined: the bitmap's rows, by k_heat)
         c->heat_m = ok && !direct ? m : 0;
         if (ok) {
@@ -4587,7 +4608,7 @@ __global__ __launch_bounds__(END_BLOCK) void k_round_end(SeriesDev* S, int32_t* 
             c->done = 0;
         }
     }
-    if (full && !lean && !handled) {
+    if (swept && !lean && !handled) {
         // Hot tiles of hot_rows rows, in ascending order (the first HOT_MAX of
         // them): those that still hold survivors or whose first-pass items swept
         // at least N / HOT_FRAC columns this round.  The next sweep's first

@@ -142,3 +142,34 @@ def test_a_long_series_throws_no_dense_round_away():
     for key in KEYS:
         assert torch.equal(plain[key], swept[key]), key
     assert plain["stats"]["range_searches"] == swept["stats"]["range_searches"]
+
+
+@pytest.mark.parametrize("n, minL, maxL, call", [(14098, 36, 46, "heatmap"), (9000, 300, 306, "heatmap"),
+                                                 (20011, 64, 72, "search")])
+def test_lengths_that_sweep_ask_for_it_at_once(monkeypatch, n, minL, maxL, call):
+    """A heatmap whose lengths keep more range discords than the exact pass
+    takes, windows past 256 points, and a search whose dense rounds gave up: a
+    round is issued per range search and for the first change of kind, not one
+    more per length that finds out that it needs sweeps."""
+    from paper_2304_01660_amd import _lib, api, synth
+    dev = _dev()
+    if call == "search":
+        T = stepped(n, minL, 1000.0, 11)
+    else:
+        T, _ = synth.ecg_like(np.random.default_rng([3, n, maxL]), n, 5, maxL=maxL)
+    T = torch.from_numpy(T).to(dev)
+    plain = _lib.make_options
+
+    def timed(*a, **kw):  # with timing a launch of rounds is one round
+        o = plain(*a, **kw)
+        o.flags |= _lib.FLAG_TIME_KERNELS
+        return o
+
+    monkeypatch.setattr(_lib, "make_options", timed)
+    f = api.discord_heatmap if call == "heatmap" else api.discords
+    _say("sweeping lengths", call, n, minL)
+    out = f(T, minL, maxL, 5, return_stats=True)
+    st = out["stats"]
+    issued = st["kernel_launches"][4]
+    _say(st["range_searches"], "range searches", issued, "rounds", out["count"].tolist())
+    assert issued <= st["range_searches"] + 3
