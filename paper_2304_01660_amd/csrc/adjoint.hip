@@ -56,17 +56,18 @@ __device__ void adj_window_stats(const double* T, int64_t p, int32_t m, double* 
     sg = sqrt(adj_block_sum(q, sh) / (double)m);
 }
 
-// Partial nearest neighbours of up to ADJ_ROWS reported rows against
-// ADJ_SPAN blocks of 256 columns: (max rho, smallest argmax j) per row and
+// Partial nearest neighbours of up to `rows` reported rows against `span`
+// blocks of 256 columns (launch_adjoint): (max rho, smallest argmax j) per row and
 // block.  Consecutive rows of one length (a search reports k of each) share a
 // column's mean and deviation and the reads of its window, R at a time; every
 // value is the same as for a row alone.  Bound by the LDS reads, of a row's
 // value for two columns, and the FP64 operations, 3 + R per offset and column.
 // (325 rows, five per length of 96 to 160, 200,000 columns: a row and 256
 // columns per workgroup 3.36 ms, so 1.80 ms.)
-constexpr int ADJ_ROWS = 16;  // rows per workgroup
+constexpr int ADJ_ROWS = 16;  // most rows per workgroup
 constexpr int ADJ_RUN = 8;    // most rows sharing a column
-constexpr int ADJ_SPAN = 4;
+constexpr int ADJ_SPAN = 4;   // most blocks of columns
+constexpr int64_t ADJ_FILL = 2048;  // workgroups wanted: eight per CU
 
 // Sums of squares v and products c of the C column windows t + 256 e, less
 // their means, with R centred rows xs (stride doubles apart).
@@ -124,15 +125,15 @@ __global__ __launch_bounds__(ADJ_BLOCK) void k_adj_rows(const double* __restrict
                                                         int64_t K, const int64_t* __restrict__ idx,
                                                         const int32_t* __restrict__ len,
                                                         const Ctrl* ctrl, double* part, int64_t nblk,
-                                                        int max_run, int stride)
+                                                        int rows, int span, int max_run, int stride)
 {
     extern __shared__ double lds[];
     __shared__ double sh[8];
     __shared__ double rv[C][ADJ_RUN][ADJ_BLOCK / 64];
     __shared__ long long rj[C][ADJ_RUN][ADJ_BLOCK / 64];
     const int tid = threadIdx.x;
-    const int64_t q0 = (int64_t)blockIdx.y * ADJ_ROWS, q1 = std::min<int64_t>(K, q0 + ADJ_ROWS);
-    const int64_t x0 = (int64_t)blockIdx.x * ADJ_SPAN, x1 = std::min<int64_t>(nblk, x0 + ADJ_SPAN);
+    const int64_t q0 = (int64_t)blockIdx.y * rows, q1 = std::min<int64_t>(K, q0 + rows);
+    const int64_t x0 = (int64_t)blockIdx.x * span, x1 = std::min<int64_t>(nblk, x0 + span);
     const double feps = ctrl->flat_eps;
     double* ts = lds;                          // T[j0 .. j0 + 256 C + m)
     double* xs = lds + (ADJ_BLOCK * C + stride);  // centred windows, stride apart
@@ -319,15 +320,33 @@ hipError_t launch_adjoint(const double* Tpad, int64_t n, int64_t K, int32_t maxm
                           int64_t* jstar, hipStream_t st)
 {
     if (K <= 0) return hipSuccess;
-    // as many rows of one length as fit 64 KB beside the columns' values, and
     // two columns per thread, which share the rows' reads, while those fit
-    const int stride = maxm + 1, cols = maxm <= 2048 ? 2 : 1;
-    const int max_run = std::max(1, std::min(ADJ_RUN, (8000 - ADJ_BLOCK * cols - stride) / stride));
+    const int stride = maxm + 1;
+    int cols = maxm <= 2048 ? 2 : 1, rows = ADJ_ROWS, span = ADJ_SPAN;
+    // Rows and columns that share a workgroup save reads and operations, but a
+    // small problem then leaves the device idle behind a few serial workgroups:
+    // the shares are cut until there are ADJ_FILL of them, the columns' first
+    // (that costs the least).  (Whole call, full shares and these: 8,000 points
+    // and 33 rows of different lengths 0.64 and 0.19 ms; 50,000 points and 33
+    // rows 0.66 and 0.28; 12,000 points and 99 rows, three per length, 0.44 and
+    // 0.24.  4096 workgroups are too many: 50,000 points and 325 rows 0.71 ms
+    // with 2048, 0.86.)
+    const auto groups = [&] { return ((nblk + span - 1) / span) * ((K + rows - 1) / rows); };
+    while (groups() < ADJ_FILL) {
+        if (span > cols) span /= 2;
+        else if (rows > 1) rows /= 2;
+        else if (cols > 1) cols = span = 1;
+        else break;
+    }
+    // as many rows of one length as fit 64 KB beside the columns' values
+    const int max_run = std::max(
+        1, std::min({ADJ_RUN, rows, (8000 - ADJ_BLOCK * cols - stride) / stride}));
     const size_t lds = sizeof(double) * (size_t)(ADJ_BLOCK * cols + (max_run + 1) * stride);
     hipLaunchKernelGGL(cols == 2 ? k_adj_rows<2> : k_adj_rows<1>,
-                       dim3((unsigned int)((nblk + ADJ_SPAN - 1) / ADJ_SPAN),
-                            (unsigned int)((K + ADJ_ROWS - 1) / ADJ_ROWS)),
-                       dim3(ADJ_BLOCK), lds, st, Tpad, n, K, idx, len, ctrl, part, nblk, max_run, stride);
+                       dim3((unsigned int)((nblk + span - 1) / span),
+                            (unsigned int)((K + rows - 1) / rows)),
+                       dim3(ADJ_BLOCK), lds, st, Tpad, n, K, idx, len, ctrl, part, nblk, rows, span,
+                       max_run, stride);
     hipLaunchKernelGGL(k_adj_scatter, dim3((unsigned int)K), dim3(ADJ_BLOCK), 0, st, Tpad, idx, len,
                        gin, ctrl, part, nblk, grad, jstar);
     return hipGetLastError();

@@ -205,3 +205,32 @@ def test_backward_of_runs_of_rows_matches_the_oracle(n, runs, maxm):
     assert np.all(nnj[~ok] == -1)
     ref = _oracle_grad(T, idx[ok], ln[ok], nnj[ok], w[ok])
     np.testing.assert_allclose(gT.cpu().numpy(), ref, rtol=1e-8, atol=1e-10 * np.abs(ref).max())
+
+
+@pytest.mark.parametrize("n,K", [
+    (300, 1),        # one column per thread, a row and a block per workgroup
+    (12000, 33),     # two columns per thread, two blocks, a row
+    (6000, 603),     # four rows
+    (12000, 601),    # eight
+    (12000, 1603),   # sixteen rows, four blocks
+])
+def test_backward_shares_of_every_size_match_the_oracle(n, K):
+    """The shares of a workgroup shrink with the problem: the neighbours of
+    sampled rows and the gradient of all, against the oracle."""
+    dev = _dev()
+    from paper_2304_01660_amd import api
+    T = synth.small_random(324, n, "rw")
+    rng = np.random.default_rng([n, K])
+    ln = (40 + np.arange(K) // 5 % 9).astype(np.int32)  # runs of five
+    idx = np.array([rng.integers(0, n - m + 1) for m in ln], np.int64)
+    w = rng.standard_normal(K)
+    _say("grad shares", n, K)
+    gT, nnj = api.discords_backward(torch.from_numpy(T).to(dev), torch.from_numpy(idx).to(dev),
+                                    torch.from_numpy(ln).to(dev), torch.from_numpy(w).to(dev),
+                                    maxm=48, return_nn_idx=True)
+    nnj = nnj.cpu().numpy()
+    for q in rng.choice(K, size=min(K, 24), replace=False):
+        d, j = oracle.nn_row(T, int(ln[q]), int(idx[q]))
+        assert int(nnj[q]) == j, (q, int(nnj[q]), j)
+    ref = _oracle_grad(T, idx, ln, nnj, w)
+    np.testing.assert_allclose(gT.cpu().numpy(), ref, rtol=1e-8, atol=1e-10 * np.abs(ref).max())
