@@ -79,7 +79,9 @@ typedef struct {
     uint32_t flags;        /* PALMAD_FLAG_* bits */
     int32_t rows_near;     /* row-tile height of the first selection pass: 128, 256 or
                               512; 0 = 256. */
-    int32_t rows_far;      /* row-tile height of the split selection pass; 0 = as near. */
+    int32_t rows_far;      /* row-tile height of the split selection pass; 0 = as near;
+                              where both are 0, a long series whose range discords are
+                              many is swept in FP32 with 512. */
     int32_t rows_refine;   /* row-tile height of the refinement pass; 0 = 128. */
     int32_t far_grid;      /* workgroups of the split passes (1..65536); 0 = 2048. */
     int32_t band_pass;     /* 1: before the first selection pass, test every

@@ -188,6 +188,7 @@ SweepCfg cfg_of(const Opts& o, const KernelTimer* timer)
     const int ref_rows = o.rows_refine ? o.rows_refine : 128;
     c.q_near = near_rows / 64;
     c.q_far = far_rows / 64;
+    c.far_open = o.rows_near == 0 && o.rows_far == 0;
     c.q_ref = ref_rows / 64;
     c.max_attempts = MAX_ATTEMPTS;
     c.band = o.band_pass;
@@ -469,12 +470,12 @@ constexpr int ROUNDS_PER_CHECK = 4;
 // the device, and a captured graph, bound to one workspace, measured the same
 // on it and cost its capture, 0.4 ms, on every other.)
 int run_rounds(palmad_ctx* ctx, const Batch& bt, const SweepCfg& cfg, const Plan& p, bool full,
-               bool steady, bool dense, int lengths)
+               bool steady, bool wit, bool dense, int lengths)
 {
     const bool one = (full && !steady) || dense || cfg.timer->on;
     const int rounds = one ? 1 : std::min(ROUNDS_PER_CHECK, std::max(1, lengths));
     for (int r = 0; r < rounds; ++r)
-        HIP_TRY(launch_round(bt, cfg, p.totals, full, dense, true, ctx->work));
+        HIP_TRY(launch_round(bt, cfg, p.totals, full, dense, true, wit, ctx->work));
     return PALMAD_OK;
 }
 
@@ -535,11 +536,11 @@ int search(palmad_ctx* ctx, const Plan& p, const Opts& o, void* ws, const double
     // series or takes a part of its candidates (at most sixteen)
     int64_t max_checks = 2;
     for (int b = 0; b < p.B; ++b) max_checks += (int64_t)p.lay[b].L * (cfg.max_attempts * 2 + 32);
-    bool full = true, steady = false, dense = false;  // the first length has no witnesses yet
+    bool full = true, steady = false, wit = true, dense = false;  // the first length has no witnesses yet
     int lengths = 1;
     for (int64_t check = 0;; ++check) {
         if (check > max_checks) return fail(ctx, PALMAD_EDEVICE, "search did not terminate");
-        rc = run_rounds(ctx, bt, cfg, p, full, steady, dense, lengths);
+        rc = run_rounds(ctx, bt, cfg, p, full, steady, wit, dense, lengths);
         if (rc) return rc;
         rc = read_counters(ctx, bt);
         if (!rc) rc = check_finite(ctx, p);
@@ -552,6 +553,7 @@ int search(palmad_ctx* ctx, const Plan& p, const Opts& o, void* ws, const double
         if (ctx->pinned[REM_LEFT] == 0) break;
         full = ctx->pinned[REM_SWEEP] > 0;
         steady = ctx->pinned[REM_STEADY] > 0;
+        wit = ctx->pinned[REM_WITNESS] > 0;
         lengths = ctx->pinned[REM_LENGTHS];
         dense = ctx->pinned[REM_DENSE] > 0;
     }
@@ -971,7 +973,7 @@ int palmad_range_discords(palmad_ctx* ctx, const double* T, int64_t n, int32_t m
     HIP_TRY(launch_set_fixed_r(bt, r, ctx->work));
     HIP_TRY(launch_half(bt, bt.B, ctx->work));
     HIP_TRY(launch_start(bt, cfg, ctx->work));
-    HIP_TRY(launch_round(bt, cfg, p.totals, true, false, false, ctx->work));
+    HIP_TRY(launch_round(bt, cfg, p.totals, true, false, false, false, ctx->work));
     const int64_t N = n - m + 1;
     HIP_TRY(launch_range_out(bt, N, (unsigned long long*)alive, nn_dist, ctx->work));
     const Ctrl* c = (const Ctrl*)((char*)workspace + p.base[0] + p.lay[0].off_ctrl);

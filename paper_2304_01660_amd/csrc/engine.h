@@ -78,6 +78,14 @@ constexpr int STREAM_LANES = 15;
 constexpr int STREAM_CHUNK = 2048;
 constexpr int64_t STREAM_ITEMS = 4096;
 constexpr int STREAM_GRID = 16384;
+// A search's sweeps that keep no witnesses (SWEEPS_MANY) prune little, and the
+// FP32 split pass of a long series then takes tiles of 512 rows where the caller
+// leaves the height open: a taller tile costs less per pair, but a tile that
+// thins out is swept for its last row.  (White noise, 300,000 points, per length
+// 14.2 ms with 256 rows, 7.0 with 512; searches and range searches that thin
+// out, 300,000 ECG-like points: 2.04 and 0.76 ms with 256, 2.23 and 0.83 with
+// 512.)
+constexpr int64_t FAR_TALL_MIN = 65536;
 constexpr int RESCUE_GRID = 2048, RESCUE_BLOCK = 256;
 constexpr int TOPK_BLOCK = 1024;
 constexpr int RED_BLOCKS = 256;   // series reductions: blocks of 256 threads
@@ -99,10 +107,10 @@ enum { EV_NEAR = 0, EV_FAR = 1, EV_REF = 2, EV_POL = 3, EV_BAND = 4 };
 
 // Host counters of a round: series with work left, series in error, series
 // whose next range search needs sweeps (the first length's, those waiting for
-// them and those whose last one did), those whose last two did, series whose
-// next one is a dense round, most lengths left; then, once per call, series holding NaN
+// them and those whose last one did), those whose last two did, those of them
+// that want the witnesses kept, series whose next one is a dense round, most lengths left; then, once per call, series holding NaN
 // or Inf and the first of them.
-enum { REM_LEFT = 0, REM_ERROR, REM_SWEEP, REM_STEADY, REM_DENSE, REM_LENGTHS, REM_COUNT };
+enum { REM_LEFT = 0, REM_ERROR, REM_SWEEP, REM_STEADY, REM_WITNESS, REM_DENSE, REM_LENGTHS, REM_COUNT };
 enum { REM_BAD = REM_COUNT, REM_BAD_SERIES, REM_TOTAL };
 
 // Device-resident control block of one series (the MERLIN state of Alg. 1
@@ -278,6 +286,7 @@ struct SweepCfg {
     int dist_bits;
     int far_grid;              // workgroups of the queued passes
     int q_near, q_far, q_ref;  // rows per lane of each pass's tiles (2, 4 or 8)
+    bool far_open;             // the caller left the heights of the selection's tiles open
     int max_attempts;          // range searches allowed per length (MAX_ATTEMPTS)
     int band;                  // 1: diagonal band pre-pass before the first selection pass
     const KernelTimer* timer;
@@ -292,7 +301,7 @@ hipError_t launch_prepare(const Batch& bt, const int64_t* total, hipStream_t st)
 hipError_t launch_half(const Batch& bt, int series, hipStream_t st);
 hipError_t launch_start(const Batch& bt, const SweepCfg& cfg, hipStream_t st);
 hipError_t launch_round(const Batch& bt, const SweepCfg& cfg, const int64_t* total, bool full,
-                        bool dense, bool more, hipStream_t st);
+                        bool dense, bool more, bool wit, hipStream_t st);
 hipError_t launch_set_fixed_r(const Batch& bt, double r, hipStream_t st);
 hipError_t launch_range_out(const Batch& bt, int64_t N, unsigned long long* alive_out,
                             double* nn_out, hipStream_t st);

@@ -323,11 +323,13 @@ __device__ void begin_range(const SeriesDev& s, Ctrl* c, float guard)
 // dense round is no choice (dense_allowed), is followed by others of its kind
 // (heatmaps of noisy series, windows past 256 points): its series asks for
 // sweeps at once instead of waiting for them in a round that can only find that
-// out.  SWEEPS_MANY: the range discords alone were too many, so that second
-// chances cannot make the round one without sweeps; SWEEPS_AGAIN: the one before
-// swept too, and the host issues several such rounds at once.  (Heatmap of 14,098 points,
-// eleven lengths, 1,675 to 2,275 range discords at six of
-// them: 4.2 ms, so 3.5.)
+// out.  SWEEPS_MANY: the range discords alone were too many, so that neither
+// second chances nor fresh witnesses can make the next round one without sweeps,
+// and its sweeps, for which a witness is 1.5 operations more per pair, keep
+// none; SWEEPS_AGAIN: the one before swept too, and the host issues several
+// such rounds at once.  (Heatmap of 14,098 points, eleven lengths, 1,675 to
+// 2,275 range discords at six of them: 4.2 ms, so 3.5; white noise, 300,000
+// points, m = 50 to 53, 1,600 to 3,000 range discords: 82 ms with witnesses throughout, so 76.)
 enum { SWEEPS_NO = 0, SWEEPS_FEW = 1, SWEEPS_MANY = 2, SWEEPS_AGAIN = 4 };
 
 // The next range search of a series (one thread): the first length, the next
@@ -367,6 +369,7 @@ __device__ void next_range(const SeriesDev& s, Ctrl* c, float guard, int max_att
     begin_range(s, c, guard);
     atomicAdd(&rem[REM_LEFT], 1);
     if (c->li == 0 || c->sweeps) atomicAdd(&rem[REM_SWEEP], 1);
+    if (c->li == 0 || (c->sweeps & SWEEPS_FEW)) atomicAdd(&rem[REM_WITNESS], 1);
     if (c->sweeps & SWEEPS_AGAIN) atomicAdd(&rem[REM_STEADY], 1);
     if (dense_round(c)) atomicAdd(&rem[REM_DENSE], 1);
     atomicMax(&rem[REM_LENGTHS], s.maxL - c->m + 1);
@@ -2126,7 +2129,8 @@ __device__ __forceinline__ void band_hits(const F (&mg)[BAND_Q], unsigned int (&
 }
 
 template <typename F>
-__global__ __launch_bounds__(64) void k_select_band(SeriesDev* S, int B, const int64_t* __restrict__ pfx)
+__global__ __launch_bounds__(64) void k_select_band(SeriesDev* S, int B, const int64_t* __restrict__ pfx,
+                                                   int wit)
 {
     extern __shared__ double lds[];
     const int b = series_of(pfx, B, blockIdx.x);
@@ -2260,7 +2264,7 @@ __global__ __launch_bounds__(64) void k_select_band(SeriesDev* S, int B, const i
         for (int q = 0; q < BAND_Q; ++q) {
             const unsigned int v = __builtin_bitreverse32(km[q]);
             // every hit is a witness of both its subsequences
-            for (unsigned int h = v; h; h &= h - 1u) {
+            for (unsigned int h = wit ? v : 0u; h; h &= h - 1u) {
                 const int32_t t = t0 + __ffs((int)h) - 1;
                 const int32_t i = (int32_t)i0 + t, j = (int32_t)j0 + t + BAND_Q * lane + q;
                 A.wit[i] = ~j;
@@ -4422,7 +4426,10 @@ __global__ __launch_bounds__(END_BLOCK) void k_round_end(SeriesDev* S, int32_t* 
             if (c->dense == DENSE_NO && dense_allowed(s, c)) c->dense = DENSE_LEFT;
             atomicAdd(&rem[REM_LEFT], 1);
             atomicMax(&rem[REM_LENGTHS], s.maxL - c->m + 1);
-            if (c->dense != DENSE_LEFT) atomicAdd(&rem[REM_SWEEP], 1);
+            if (c->dense != DENSE_LEFT) {
+                atomicAdd(&rem[REM_SWEEP], 1);
+                atomicAdd(&rem[REM_WITNESS], 1);
+            }
             if (dense_round(c)) atomicAdd(&rem[REM_DENSE], 1);
         }
         return;
@@ -5113,7 +5120,8 @@ static void launch_select(const Batch& bt, const SweepCfg& cfg, const int64_t* t
     if (cfg.band && total[PFX_BAND] > 0) {
         cfg.timer->begin(5, st);
         hipLaunchKernelGGL((k_select_band<F>), dim3((unsigned int)total[PFX_BAND]), dim3(64),
-                           band_lds_bytes(bt.maxL_all, (int)sizeof(F)), st, bt.s, bt.B, bt.pfx[PFX_BAND]);
+                           band_lds_bytes(bt.maxL_all, (int)sizeof(F)), st, bt.s, bt.B, bt.pfx[PFX_BAND],
+                           WIT ? 1 : 0);
         cfg.timer->end(5, st);
     }
     switch (cfg.q_near) {
@@ -5176,9 +5184,10 @@ hipError_t launch_start(const Batch& bt, const SweepCfg& cfg, hipStream_t st)
 // One round: every series with work does one range search at its current
 // length (a fixed launch sequence; all parameters come from the device).
 // Without `full` the sweeps are left out: a series that needs them waits for
-// the next full round.  more = 0: a bare range search.
+// the next full round.  more = 0: a bare range search.  wit: the sweeps keep
+// the witnesses of what they prune.
 hipError_t launch_round(const Batch& bt, const SweepCfg& cfg, const int64_t* total, bool full,
-                        bool dense, bool more, hipStream_t st)
+                        bool dense, bool more, bool wit, hipStream_t st)
 {
     const unsigned int elem = (unsigned int)total[PFX_ELEM];
     cfg.timer->begin(4, st);
@@ -5199,13 +5208,16 @@ hipError_t launch_round(const Batch& bt, const SweepCfg& cfg, const int64_t* tot
     cfg.timer->end(4, st);
     if (full) {
         hipLaunchKernelGGL(k_guard, dim3(bt.B), dim3(GUARD_BLOCK), 0, st, bt.s, cfg.guard);
-        if (more) {
+        if (wit) {
             if (cfg.dist_bits == 64) launch_select<double, true>(bt, cfg, total, st);
             else launch_select<float, true>(bt, cfg, total, st);
             launch_refine_q<true>(bt, cfg, total, st);
         } else {
+            // (the table of selection tiles is built for the lower tiles, which are more)
+            SweepCfg tall = cfg;
+            if (more && cfg.far_open && bt.Nmax_all >= FAR_TALL_MIN) tall.q_far = 8;
             if (cfg.dist_bits == 64) launch_select<double, false>(bt, cfg, total, st);
-            else launch_select<float, false>(bt, cfg, total, st);
+            else launch_select<float, false>(bt, tall, total, st);
             launch_refine_q<false>(bt, cfg, total, st);
         }
         hipLaunchKernelGGL(k_select_top, dim3(bt.B), dim3(TOPK_BLOCK), 0, st, bt.s);

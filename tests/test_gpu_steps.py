@@ -173,3 +173,30 @@ def test_lengths_that_sweep_ask_for_it_at_once(monkeypatch, n, minL, maxL, call)
     issued = st["kernel_launches"][4]
     _say(st["range_searches"], "range searches", issued, "rounds", out["count"].tolist())
     assert issued <= st["range_searches"] + 3
+
+
+@pytest.mark.parametrize("n, band", [(30000, 1), (66000, 0)])
+def test_sweeps_without_witnesses_find_the_range_discords(n, band):
+    """White noise with windows past 256 points: thousands of range discords at
+    every length, so that from the third on the sweeps keep no witnesses (in
+    tiles of 512 rows where the series is long): every length's range discords
+    and distances in FP64, and the same rows without a heatmap."""
+    from paper_2304_01660_amd import api
+    dev = _dev()
+    minL, maxL, k = 300, 304, 3
+    T = torch.from_numpy(np.random.default_rng([66, n]).standard_normal(n)).to(dev)
+    _say("no witnesses", n, band)
+    heat = api.discord_heatmap(T, minL, maxL, k, band_pass=band)
+    plain = api.discords(T, minL, maxL, k, band_pass=band)
+    for key in KEYS:
+        assert torch.equal(heat[key], plain[key]), key
+    assert int(heat["count"][1:].min()) > 1024
+    for m in range(minL, maxL + 1):
+        P = torch.sqrt(2.0 * m * (1.0 - _profile(T, m))).cpu().numpy()
+        row = heat["heat"][m - minL, :n - m + 1].cpu().numpy()
+        r = float(heat["range"][m - minL])
+        far = ~close_ed(P, np.full_like(P, r), m)
+        np.testing.assert_array_equal((row > 0.0)[far], (P >= r)[far])
+        member = row > 0.0
+        assert np.all(close_ed(np.sqrt(2.0 * m * row[member]), P[member], m))
+        assert int(member.sum()) == int(heat["count"][m - minL])
