@@ -189,10 +189,19 @@ SweepCfg cfg_of(const Opts& o, const KernelTimer* timer)
     c.q_near = near_rows / 64;
     c.q_far = far_rows / 64;
     c.far_open = o.rows_near == 0 && o.rows_far == 0;
+    c.may_dense = false;
     c.q_ref = ref_rows / 64;
     c.max_attempts = MAX_ATTEMPTS;
     c.band = o.band_pass;
     c.timer = timer;
+    return c;
+}
+
+// ... of a search without a heatmap, which may take dense rounds.
+SweepCfg search_cfg(const Opts& o)
+{
+    SweepCfg c = cfg_of(o, nullptr);
+    c.may_dense = true;
     return c;
 }
 
@@ -232,20 +241,13 @@ struct Plan {
     int near_cols, near_chunk, chunk_cols;
 };
 
-// The first selection pass launches one workgroup per (row tile, chunk) of
-// every series, most of which find their tile dead and exit; past a few
-// tens of thousands of them per series their dispatch costs more than the
-// queued split pass, which draws only live tiles' chunks.  The first-pass
-// width is therefore capped so that the largest series has at most
-// NEAR_ITEMS of them (at least one chunk per tile); the remaining columns
-// go to the split pass.
-constexpr int64_t NEAR_ITEMS = 65536;
-
 // A work item is a serial chain of its chunk's columns, so where a pass has
 // fewer items than the machine holds (about 3,500), shorter chunks shorten it:
 // chunk_cols is halved while that is so, down to 128 columns (below, an item's
 // start costs more than its columns).  The first pass has its own chunk; the
-// other passes, whose tiles are mostly dead, count every tile.  (2,000 points,
+// other passes, whose tiles are mostly dead, count every tile.  The chunks that
+// only a dense round's wider first pass has are not counted: in every other
+// round they exit at once.  (2,000 points,
 // FP64, chunks of 1024 -> 128: whole search 1,127 -> 836 us; 12,347 points:
 // 3.46 -> 3.16 ms.  Profile of 150,000 points with chunks of 128 13.7 ms, of
 // 1024 11.4.)
@@ -284,9 +286,11 @@ void make_plan(int B, const int64_t* n, const int32_t* minL, const int32_t* maxL
     cfg.near_chunk = cfg.chunk_cols;
     while (cfg.near_chunk >= 2 * MIN_CHUNK) {
         int64_t items = 0;
+        SweepCfg plain = cfg;
+        plain.may_dense = false;
         for (int b = 0; b < B; ++b) {
             int64_t blk[PFX_KINDS];
-            series_blocks(p->lay[b], cfg, blk);
+            series_blocks(p->lay[b], plain, blk);
             items += blk[PFX_NEAR];
         }
         if (items >= FILL_ITEMS) break;
@@ -613,7 +617,7 @@ void make_probe(int B, const int64_t* n, const int32_t* minL, const int32_t* max
         pr->lrows += L;
     }
     make_plan(B, pr->n.data(), pr->lo.data(), pr->hi.data(), k,
-              cfg_of(default_opts(), nullptr), &pr->plan);
+              search_cfg(default_opts()), &pr->plan);
     pr->off_out = pr->plan.total;
     pr->total = pr->off_out + al256((size_t)pr->rows * (8 + 4 + 8 + 8) + (size_t)pr->lrows * 4 + 1024);
 }
@@ -625,7 +629,7 @@ int time_probe(palmad_ctx* ctx, const Probe& pr, int32_t k, const Opts& o, void*
                void* stream, double* best)
 {
     Plan p;  // the prefix tables depend on the tile geometry
-    make_plan(pr.plan.B, pr.n.data(), pr.lo.data(), pr.hi.data(), k, cfg_of(o, nullptr), &p);
+    make_plan(pr.plan.B, pr.n.data(), pr.lo.data(), pr.hi.data(), k, search_cfg(o), &p);
     const int rc0 = check_grid(ctx, p);
     if (rc0) return rc0;
     double bs = 1e300;
@@ -801,7 +805,7 @@ int palmad_discords(palmad_ctx* ctx, const double* T, int64_t n, int32_t minL, i
     rc = read_opts(ctx, opts, &o);
     if (rc) return rc;
     Plan p;
-    make_plan(1, &n, &minL, &maxL, k, cfg_of(o, nullptr), &p);
+    make_plan(1, &n, &minL, &maxL, k, search_cfg(o), &p);
     rc = check_ws(ctx, workspace, ws_bytes, p.total);
     if (rc) return rc;
     const Outputs out = {idx, len, nn_dist, nn_idx, count};
@@ -822,7 +826,7 @@ int palmad_discords_static(palmad_ctx* ctx, const double* T, int64_t n, int32_t 
     rc = read_opts(ctx, opts, &o);
     if (rc) return rc;
     Plan p;
-    make_plan(1, &n, &minL, &maxL, k, cfg_of(o, nullptr), &p);
+    make_plan(1, &n, &minL, &maxL, k, search_cfg(o), &p);
     if (p.total > (size_t)PALMAD_STATIC_WORKSPACE_BYTES)
         return fail(ctx, PALMAD_EWORKSPACE,
                     "this search needs %zu bytes of workspace; the static workspace holds %zu "
@@ -898,7 +902,7 @@ int palmad_batched_workspace_size(int32_t B, const int64_t* offsets, const int32
     rc = read_opts(nullptr, opts, &o);
     if (rc) return rc;
     Plan p;
-    make_plan(B, n.data(), minL, maxL, k, cfg_of(o, nullptr), &p);
+    make_plan(B, n.data(), minL, maxL, k, search_cfg(o), &p);
     rc = check_grid(nullptr, p);
     if (rc) return rc;
     *bytes = p.total;
@@ -921,7 +925,7 @@ int palmad_discords_batched(palmad_ctx* ctx, const double* values, const int64_t
     rc = read_opts(ctx, opts, &o);
     if (rc) return rc;
     Plan p;
-    make_plan(B, n.data(), minL, maxL, k, cfg_of(o, nullptr), &p);
+    make_plan(B, n.data(), minL, maxL, k, search_cfg(o), &p);
     rc = check_grid(ctx, p);
     if (rc) return rc;
     rc = check_ws(ctx, workspace, ws_bytes, p.total);

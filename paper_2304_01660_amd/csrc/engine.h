@@ -278,6 +278,15 @@ struct KernelTimer {
     }
 };
 
+// The first selection pass launches one workgroup per (row tile, chunk) of
+// every series, most of which find their tile dead and exit; past a few
+// tens of thousands of them per series their dispatch costs more than the
+// queued split pass, which draws only live tiles' chunks.  The first-pass
+// width is therefore capped so that the largest series has at most
+// NEAR_ITEMS of them (at least one chunk per tile); the remaining columns
+// go to the split pass, or, in a dense round, to the bounds.
+constexpr int64_t NEAR_ITEMS = 65536;
+
 struct SweepCfg {
     int near_cols;
     int near_chunk;   // columns per item of the first pass
@@ -286,6 +295,7 @@ struct SweepCfg {
     int dist_bits;
     int far_grid;              // workgroups of the queued passes
     int q_near, q_far, q_ref;  // rows per lane of each pass's tiles (2, 4 or 8)
+    bool may_dense;            // the call may take dense rounds, whose first pass can be wider
     bool far_open;             // the caller left the heights of the selection's tiles open
     int max_attempts;          // range searches allowed per length (MAX_ATTEMPTS)
     int band;                  // 1: diagonal band pre-pass before the first selection pass

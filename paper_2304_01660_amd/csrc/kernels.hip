@@ -5728,12 +5728,17 @@ SeriesDev carve(void* base, const Layout& l)
 void series_blocks(const Layout& l, const SweepCfg& cfg, int64_t out[PFX_KINDS])
 {
     const int rn = 64 * cfg.q_near, rf = 64 * cfg.q_far, rr = 64 * cfg.q_ref;
-    // chunks of the first pass: near_cols (or a dense round's), at most every column
-    const int64_t wide = l.Nmax <= DENSE_NEAR_MAXN ? std::max(cfg.near_cols, DENSE_NEAR) : cfg.near_cols;
-    const int64_t span = std::min<int64_t>(wide, l.Nmax);
-    const int64_t nsub = (span + cfg.near_chunk - 1) / cfg.near_chunk;
+    // chunks of the first pass: near_cols, at most every column; a dense round's
+    // as far as the cap allows (its bounds cover every column in any case)
+    const int64_t tiles = (l.Nmax + rn - 1) / rn;
+    const auto chunks = [&](int64_t cols) {
+        return (std::min(cols, l.Nmax) + cfg.near_chunk - 1) / cfg.near_chunk;
+    };
+    int64_t nsub = chunks(cfg.near_cols);
+    if (cfg.may_dense && l.Nmax <= DENSE_NEAR_MAXN && l.minL <= DENSE_MAXM)
+        nsub = std::max(nsub, std::min(chunks(DENSE_NEAR), NEAR_ITEMS / tiles));
     out[PFX_ELEM] = (l.Npad + 64 + 255) / 256;
-    out[PFX_NEAR] = ((l.Nmax + rn - 1) / rn) * nsub;
+    out[PFX_NEAR] = tiles * nsub;
     out[PFX_TSEL] = ((l.Nmax + rf - 1) / rf + 255) / 256;
     out[PFX_TREF] = ((l.Nmax + rr - 1) / rr + 255) / 256;
     out[PFX_BAND] = (l.Nmax + BAND_S - 1) / BAND_S;

@@ -200,3 +200,20 @@ def test_sweeps_without_witnesses_find_the_range_discords(n, band):
         member = row > 0.0
         assert np.all(close_ed(np.sqrt(2.0 * m * row[member]), P[member], m))
         assert int(member.sum()) == int(heat["count"][m - minL])
+
+
+@pytest.mark.parametrize("chunk", [64, 128, 1024])
+def test_the_first_pass_of_a_dense_round_may_be_cut(chunk):
+    """Tiles of 128 rows and chunks of 64 columns: a dense round's first pass of
+    16,384 columns would take 200,000 workgroups, past the cap; the bounds cover
+    what it leaves out."""
+    from paper_2304_01660_amd import api, synth
+    dev = _dev()
+    rng = np.random.default_rng([100, 100000])
+    T, _ = synth.inject_bursts(rng, synth.random_walk(rng, 100000), 5, maxL=66)
+    T = torch.from_numpy(synth.fp32_canonical(T)).to(dev)
+    _say("first pass", chunk)
+    plain = api.discords(T, 64, 66, 3, rows_near=128, chunk_cols=chunk)
+    swept = api.discord_heatmap(T, 64, 66, 3)
+    for key in KEYS:
+        assert torch.equal(plain[key], swept[key]), key
