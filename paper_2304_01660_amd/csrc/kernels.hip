@@ -1560,12 +1560,19 @@ __device__ __forceinline__ void sel_block_full(F (&C)[Q], const F (&a)[Q], const
 }
 
 // WIT: keep the witnesses of the rows and columns it prunes (a search; a bare
-// range search has no next length and saves the instructions).
-template <typename F, int Q, bool WIT>
+// range search has no next length and saves the instructions): WIT_INLINE with
+// every pair, 1.5 operations on four, for the first pass, where most blocks
+// prune; WIT_REPLAY by a second run over a block in which something fell, for the
+// split pass, where few do.  (Split pass of a first length, 300,000 points: white
+// noise, m = 50, 13.4 ms inline, 9.1 so; a periodic signal whose level jumps, of
+// which the FP32 sweeps prune nothing, m = 64, 16.0 and 9.9.)
+enum { WIT_OFF = 0, WIT_INLINE, WIT_REPLAY };
+template <typename F, int Q, int WIT>
 __device__ void sel_item(const SweepArgs<F>& A, int64_t i0, int64_t jbeg, int64_t jend, F thr,
                          double* lds, unsigned long long& evals, uint32_t* work)
 {
     constexpr int R = 64 * Q;
+    constexpr bool INL = WIT == WIT_INLINE;
     i0 = uniform_i64(i0);
     jbeg = uniform_i64(jbeg);
     jend = uniform_i64(jend);
@@ -1630,7 +1637,7 @@ __device__ void sel_item(const SweepArgs<F>& A, int64_t i0, int64_t jbeg, int64_
             cm = fmax(cm, mg[q]);
         }
         const unsigned long long bal = uniform64(__ballot(cm > F(0)));
-        if (!WIT) {
+        if (WIT == WIT_OFF) {
             kill_columns(A.alive, jbeg, bal ? 1ull : 0ull);
         } else if (bal != 0ull) {
             int32_t wcol = 0;
@@ -1660,21 +1667,36 @@ __device__ void sel_item(const SweepArgs<F>& A, int64_t i0, int64_t jbeg, int64_
             const unsigned long long word = load_word(&A.alive[rbase >> 6]);
             unsigned long long colbits = 0ull;
             int32_t wcol = 0;
-            F bm[Q];
+            F bm[Q], C0[Q];
 #pragma unroll
-            for (int q = 0; q < Q; ++q) bm[q] = f_low<F>();
+            for (int q = 0; q < Q; ++q) {
+                bm[q] = f_low<F>();
+                C0[q] = C[q];
+            }
             const bool full = (j - (i0 + R - 1)) >= m;
             if (Q <= 4 && full && nst == 64)  // taller tiles: the general path keeps fewer registers
-                sel_block_full<F, Q, WIT>(C, a, b, nth, rm, bm, hb, row0, colbits, wcol);
+                sel_block_full<F, Q, INL>(C, a, b, nth, rm, bm, hb, row0, colbits, wcol);
             else if (full)
-                sel_block<F, Q, false, WIT>(A, j, nst, C, a, b, nth, rm, bm, ri, hb, row0, colbits, wcol);
+                sel_block<F, Q, false, INL>(A, j, nst, C, a, b, nth, rm, bm, ri, hb, row0, colbits, wcol);
             else
-                sel_block<F, Q, true, WIT>(A, j, nst, C, a, b, nth, rm, bm, ri, hb, row0, colbits, wcol);
-            if (!WIT) {
+                sel_block<F, Q, true, INL>(A, j, nst, C, a, b, nth, rm, bm, ri, hb, row0, colbits, wcol);
+            if (WIT == WIT_OFF) {
                 kill_columns(A.alive, j, colbits);
             } else if (colbits != 0ull) {
                 // only columns still alive: the others keep the witness they have
                 colbits &= live_columns(A.alive, j);
+                unsigned long long fell = colbits;
+                if (WIT == WIT_REPLAY) {
+#pragma unroll
+                    for (int q = 0; q < Q; ++q) fell |= uniform64(__ballot(rm[q] > F(0))) & ~dm[q];
+                }
+                if (WIT == WIT_REPLAY && fell != 0ull) {
+                    F rm0[Q];
+                    unsigned long long cb = 0ull;
+#pragma unroll
+                    for (int q = 0; q < Q; ++q) rm0[q] = f_low<F>();
+                    sel_block<F, Q, true, true>(A, j, nst, C0, a, b, nth, rm0, bm, ri, hb, row0, cb, wcol);
+                }
                 if ((colbits >> lane) & 1ull) A.wit[j + lane] = ~wcol;
                 row_witness(bm, j);
                 kill_columns(A.alive, j, colbits);
@@ -2297,7 +2319,7 @@ __global__ __launch_bounds__(64) void k_select_band(SeriesDev* S, int B, const i
 // First selection pass: every row tile's nearest near_cols columns, split
 // into chunks of `chunk` columns that run concurrently; each stops as soon
 // as the whole tile is dead.
-template <typename F, int Q, bool WIT>
+template <typename F, int Q, int WIT>
 __global__ __launch_bounds__(64) void k_select_near(SeriesDev* S, int B,
                                                     const int64_t* __restrict__ pfx, int near_cols,
                                                     int chunk)
@@ -2361,7 +2383,7 @@ __global__ __launch_bounds__(64) void k_select_near(SeriesDev* S, int B,
 // from each series' counter; a workgroup drains the series in rotated order.
 // The FP32 two-row tile fits 128 registers, so four waves share a SIMD
 // (three otherwise): the pass is bound by how many items are resident.
-template <typename F, int Q, bool WIT>
+template <typename F, int Q, int WIT>
 __global__ __launch_bounds__(64, (sizeof(F) == 4 && Q <= 2) ? 4 : 1) void k_select_far(
     SeriesDev* S, int B, int near_cols, int chunk, int near_rows)
 {
@@ -4418,6 +4440,7 @@ __global__ __launch_bounds__(END_BLOCK) void k_round_end(SeriesDev* S, int32_t* 
     const bool lean = lean_round(c), handled = c->handled != 0;
     const unsigned int cand_at = handled ? c->cand_at : 0u, cand_total = c->cand_total;
     const bool parts_left = cand_at > 0 && cand_at < cand_total;
+    const bool lost = handled && c->lost != 0;
     // (a dense round in a launch without dense kernels waits too)
     const bool swept = full && !dense_round(c);
     if (!swept && !lean && !handled) {
@@ -4518,6 +4541,8 @@ __global__ __launch_bounds__(END_BLOCK) void k_round_end(SeriesDev* S, int32_t* 
     const unsigned int ns = direct ? (kp >= k ? nvalid_s : (lean ? c->nlive : c->nsurv)) : c->nsurv;
     // the candidates could not be narrowed: same r again, after sweeps with
     // both sides of every tile refined exactly, after a dense round with sweeps
+    // (exactly too where the bounds were lost: the level jumps that widen them
+    // widen the FP32 guard band, and its sweeps would be repeated in turn)
     const bool redo = !lean && c->band_over != 0;
     const bool ok = ns >= (unsigned int)k && kp >= k && !redo;
     const int nv = kp >= k ? (int)nvalid_s : 0;
@@ -4593,7 +4618,7 @@ __global__ __launch_bounds__(END_BLOCK) void k_round_end(SeriesDev* S, int32_t* 
             c->rows_near += c->nlive;
             c->rows_far += c->nlive;
         }
-        c->exact_ref = redo && !handled ? 1 : 0;
+        c->exact_ref = redo && (!handled || lost) ? 1 : 0;
         c->pending = 0;
         const int was = c->sweeps ? SWEEPS_AGAIN : 0;
         c->sweeps = li == 0 || lean || handled || dense_allowed(s, c)
@@ -5084,7 +5109,7 @@ static void launch_near(const Batch& bt, const SweepCfg& cfg, const int64_t* tot
     const size_t lds = sizeof(double) * sweep_lds_doubles(bt.maxL_all, 64 * Q, (int)sizeof(F), false);
     if (total[PFX_NEAR] == 0) return;
     cfg.timer->begin(0, st);
-    hipLaunchKernelGGL((k_select_near<F, Q, WIT>), dim3((unsigned int)total[PFX_NEAR]), dim3(64), lds,
+    hipLaunchKernelGGL((k_select_near<F, Q, WIT ? WIT_INLINE : WIT_OFF>), dim3((unsigned int)total[PFX_NEAR]), dim3(64), lds,
                        st, bt.s, bt.B, bt.pfx[PFX_NEAR], cfg.near_cols, cfg.near_chunk);
     cfg.timer->end(0, st);
 }
@@ -5096,7 +5121,7 @@ static void launch_far(const Batch& bt, const SweepCfg& cfg, const int64_t* tota
     hipLaunchKernelGGL(k_tiles, dim3((unsigned int)total[PFX_TSEL]), dim3(TILES_BLOCK), 0, st, bt.s, bt.B,
                        bt.pfx[PFX_TSEL], 64 * Q, 0, cfg.near_cols, cfg.chunk_cols, 64 * cfg.q_near);
     cfg.timer->begin(1, st);
-    hipLaunchKernelGGL((k_select_far<F, Q, WIT>), dim3(cfg.far_grid), dim3(64), lds, st, bt.s, bt.B,
+    hipLaunchKernelGGL((k_select_far<F, Q, WIT ? WIT_REPLAY : WIT_OFF>), dim3(cfg.far_grid), dim3(64), lds, st, bt.s, bt.B,
                        cfg.near_cols, cfg.chunk_cols, 64 * cfg.q_near);
     cfg.timer->end(1, st);
 }
