@@ -607,11 +607,20 @@ __global__ void k_length(SeriesDev* S, int B, const int64_t* __restrict__ pfx)
 // length, mostly) does a round sweep.
 //
 // Soundness: a row is pruned only by an FP64 correlation above thr64 by more
-// than WIT_GUARD; rows nearer to the threshold are left to the exact pass.  C
-// starts from a direct dot product (or the exact pass's value), and m sigma^2
-// never shrinks as m grows, so the relative rounding of the chained updates
-// stays of the order m 2^-53, four orders below the guard.
+// than a guard; rows nearer to the threshold are left to the exact pass.  C
+// starts from a direct dot product (or the exact pass's value).  The chain adds
+// what its means are off by, to first order: after S lengths a mean of values
+// up to M is off by at most e = (m + 2 S) u M (u = 2^-53; the first sum, then two
+// roundings per length), and as the products' other factors are the deviations
+// that make up m sigma^2, rho is off by at most e_i / sigma_i + e_j / sigma_j for
+// S <= m.  With M <= |mu| + sqrt(m) sigma that is
+//     3 m u (|mu_i| / sigma_i + |mu_j| / sigma_j + 2 sqrt(m)),
+// 1e-11 for a walk of 10^6 steps, but past 1e-9 where the series lies 10^4 to 10^5
+// times its windows' deviations from zero (windows of 128 points at 4e7 times
+// were seen 6e-8 off): WIT_GUARD, or that where it is more.  A direct product's
+// error is of second order in e, far below either.
 constexpr double WIT_GUARD = 1e-9;
+constexpr double WIT_DRIFT = 3.0;
 constexpr int32_t WIT_NONE = (int32_t)0x80000000;  // j >= 0: C known; ~j: C to be computed
 
 __device__ __forceinline__ double inv_of(double var, double sqm, double feps)
@@ -749,7 +758,9 @@ __global__ __launch_bounds__(ADV_BLOCK) void k_advance(SeriesDev* S, int B,
                     s.wc[i] = C;
                 }
             }
-            dead = prune && pair_rho(C, ii, ij) > kill;
+            const double rho = pair_rho(C, ii, ij);
+            const double drift = fma(fabs(mi), ii, fma(fabs(mj), ij, 2.0)) * (WIT_DRIFT * 0x1p-53);
+            dead = prune && rho > kill && rho > fma(drift, (double)m * sqm, c->thr64);
         } else {  // no longer a window, or now a self match
             s.wit[i] = WIT_NONE;
         }
