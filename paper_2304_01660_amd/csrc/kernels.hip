@@ -668,7 +668,7 @@ __device__ __forceinline__ double direct_cov(const double* __restrict__ T, int64
 // length at a smaller r only repeats the test.  rem: the round's host
 // counters restart.
 constexpr int ADV_BLOCK = 256;
-__global__ __launch_bounds__(ADV_BLOCK) void k_advance(SeriesDev* S, int B,
+__global__ __launch_bounds__(ADV_BLOCK, 8) void k_advance(SeriesDev* S, int B,
                                                        const int64_t* __restrict__ pfx, int32_t* rem)
 {
     extern __shared__ double ts[];  // ADV_BLOCK + maxL values
@@ -760,7 +760,7 @@ __global__ __launch_bounds__(ADV_BLOCK) void k_advance(SeriesDev* S, int B,
             }
             const double rho = pair_rho(C, ii, ij);
             const double drift = fma(fabs(mi), ii, fma(fabs(mj), ij, 2.0)) * (WIT_DRIFT * 0x1p-53);
-            dead = prune && rho > kill && rho > fma(drift, (double)m * sqm, c->thr64);
+            dead = prune && rho > kill && rho - c->thr64 > drift * (gb.m * sqm);
         } else {  // no longer a window, or now a self match
             s.wit[i] = WIT_NONE;
         }
