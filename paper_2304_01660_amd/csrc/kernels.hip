@@ -4542,8 +4542,11 @@ __global__ __launch_bounds__(END_BLOCK) void k_round_end(SeriesDev* S, int32_t* 
                 }
                 if (more && j >= 0) {  // the nearest neighbour is the best witness
                     const double ij = s.inv64[j];
-                    s.wit[i] = (int32_t)j;
-                    s.wc[i] = ii > 0.0 && ij > 0.0 ? best / (ii * ij) : 0.0;
+                    // (a flat window's correlation is a convention, not its
+                    // covariance: ~j has that computed at the next length)
+                    const bool known = ii > 0.0 && ij > 0.0;
+                    s.wit[i] = known ? (int32_t)j : ~(int32_t)j;
+                    if (known) s.wc[i] = best / (ii * ij);
                 }
             }
         }

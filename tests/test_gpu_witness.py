@@ -197,3 +197,34 @@ def test_many_range_discords_match_the_heatmaps_sweeps(N, minL):
     res = api.discords_batched([Td, Td[:n - 1].contiguous()], [minL] * 2, [minL + 2] * 2, k)
     for key in ("idx", "len", "nn_dist", "nn_idx", "count"):
         assert torch.equal(res[0][key], plain[key]), key
+
+
+@pytest.mark.parametrize("seed", [4, 35, 52])
+def test_a_window_flat_at_one_length_starts_its_witness_anew(seed):
+    """White noise with one stretch of 200 values around 1e-12: its window is
+    flat at m = 200, where its correlation with window 0 counts as 0, and just
+    above the flat threshold at m = 201, where half of either window's variance
+    is its last value and the rest correlates -1, so that the two do not
+    correlate.  The window is one of the 64 discords there."""
+    from paper_2304_01660_amd import api
+    dev = _dev()
+    m, k = 200, 64
+    rng = np.random.default_rng([seed, m])
+    T = rng.standard_normal(1200 + m)
+    p = 700
+    w, s = T[:m] - T[:m].mean(), T[:m].std()
+    last = np.sqrt(m * (m + 1) / m)  # f d^2 = m s^2, f = m / (m + 1)
+    T[m] = T[:m].mean() + last * s
+    T[p:p + m] = -w / s * 0.9e-12
+    T[p + m] = last * 0.9e-12
+    _, _, _, flat = bf.znorm_windows(T, m)
+    assert flat.sum() == 1 and flat[p] and not bf.znorm_windows(T, m + 1)[3].any()
+    _say("flat then not", seed)
+    out = api.discord_heatmap(torch.from_numpy(T).to(dev), m, m + 1, k)
+    P = _profile(T, m + 1, dev)
+    r = float(out["range"][1])
+    assert P[p] > np.sort(P)[-k]
+    far = ~close_ed(P, np.full_like(P, r), m + 1)
+    member = out["heat"].cpu().numpy()[1, :P.shape[0]] > 0.0
+    np.testing.assert_array_equal(member[far], (P >= r)[far])
+    assert p in out["idx"].cpu().numpy()[k:]
