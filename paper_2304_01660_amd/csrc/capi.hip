@@ -1010,6 +1010,14 @@ int palmad_window_stats(palmad_ctx* ctx, const double* T, int64_t n, int32_t min
     rc = enter(ctx, stream);
     if (rc) return rc;
     int32_t* bad = (int32_t*)workspace;
+    // the kernel reads the series where the caller left it, unless an output
+    // lies over it
+    const auto over = [&](const double* p) { return p < T + n && T < p + (n - m + 1); };
+    if (over(mu) || over(sigma)) {
+        double* copy = (double*)((char*)workspace + 256);
+        HIP_TRY(hipMemcpyAsync(copy, T, sizeof(double) * (size_t)n, hipMemcpyDeviceToDevice, ctx->work));
+        T = copy;
+    }
     HIP_TRY(launch_check_finite(T, n, bad, ctx->work));
     HIP_TRY(launch_window_stats(T, n, minL, m, bad, mu, sigma, ctx->work));
     HIP_TRY(hipMemcpyAsync(ctx->pinned, bad, sizeof(int32_t), hipMemcpyDeviceToHost, ctx->work));

@@ -301,3 +301,28 @@ def test_extreme_spread_contrast_stays_exact():
     _say("spread contrast")
     out = api.discords(torch.from_numpy(T).to(dev), 32, 34, 3, dist_bits=32)
     _check_against_profiles(T, out, 32, 34, 3)
+
+
+@pytest.mark.parametrize("into", ["mu", "sigma"])
+@pytest.mark.parametrize("shift", [0, 1000000])
+def test_window_stats_written_over_the_series(shift, into):
+    """An output may lie over the input, whole or in part: `shift` values on,
+    what the first workgroups write is read by ones that start much later."""
+    import ctypes
+    from paper_2304_01660_amd import _lib, api
+    dev = _dev()
+    n, minL, m = 3000000, 100, 140
+    T = torch.from_numpy(np.random.default_rng(9).standard_normal(n)).to(dev)
+    mu, sg = api.window_stats(T, minL, m)
+    N = n - m + 1
+    buf = torch.zeros(n + shift, dtype=torch.float64, device=dev)
+    buf[:n] = T
+    other = torch.empty(N, dtype=torch.float64, device=dev)
+    ws = torch.empty(api.workspace_size(n, minL, m, 1), dtype=torch.uint8, device=dev)
+    over = buf[shift:shift + N]
+    out = [over, other] if into == "mu" else [other, over]
+    _say("window_stats over the series", shift, into)
+    _lib.check(_lib.lib().palmad_window_stats(
+        api.context(0), buf.data_ptr(), n, minL, m, ws.data_ptr(), ws.numel(), out[0].data_ptr(),
+        out[1].data_ptr(), ctypes.c_void_p(torch.cuda.current_stream(dev).cuda_stream)))
+    assert torch.equal(out[0], mu) and torch.equal(out[1], sg)
