@@ -385,6 +385,9 @@ int upload(palmad_ctx* ctx, const Plan& p, void* ws, const double* const* Tin, c
     bt->remaining = (int32_t*)((char*)ws + p.off_rem);
     bt->ipfx = (int64_t*)((char*)ws + p.off_ipfx);
     bt->heat = outs && outs[0].heat;
+    int64_t chunks = 0;
+    for (const Layout& l : p.lay) chunks += (l.Nmax + SCREEN_COLS - 1) / SCREEN_COLS;
+    bt->large = p.B > 1 && chunks > 2 * SCREEN_GRID ? 1 : 0;
     bt->sums = (unsigned long long*)((char*)ws + p.off_sums);
     return PALMAD_OK;
 }

@@ -31,11 +31,12 @@ constexpr int EXACT_COLS = 128;
 constexpr int SCREEN_COLS = 512;
 constexpr int HALF_STRIDE = SCREEN_COLS + 256 + 16;  // FP16 values kept per chunk
 constexpr int SCREEN_GROUPS = 4;  // candidate groups of a screening item (windows of up to 256)
-// Workgroups of the exact pass: two per CU; a batch's marked blocks lie together
-// more unevenly than one series' (64 series: 512 workgroups 128 us per round,
-// 1024 109; 1,000,000 points 22.5, 27).
+// Workgroups of the exact pass: two per CU; a large batch's marked blocks lie
+// together more unevenly than one series' (64 series: 512 workgroups 128 us per
+// round, 1024 109; 1,000,000 points 22.5, 27; batches of two to eight series of
+// 12,000 points up to 5 % slower with 1024).  large: Batch::large.
 constexpr int EXACT_GRID = 512, EXACT_GRID_BATCH = 1024;
-__host__ __device__ constexpr int exact_grid(int B) { return B == 1 ? EXACT_GRID : EXACT_GRID_BATCH; }
+__host__ __device__ constexpr int exact_grid(int large) { return large ? EXACT_GRID_BATCH : EXACT_GRID; }
 constexpr int SCREEN_GRID = 512;  // two workgroups per CU
 constexpr int64_t SCREEN_MIN = 8192;
 // A round without sweeps takes at most LEAN_PAIRS (rows, columns) pairs.
@@ -253,6 +254,7 @@ struct Batch {
     int64_t Nmax_all;                // most subsequences of any series
     int64_t* ipfx;                   // device [2][B+1]: first exact-pass items of each series
     bool heat;                       // the search writes a discord heatmap
+    int32_t large;                   // 1: several series with more screening chunks than workgroups hold
     int32_t* remaining;              // device [REM_TOTAL]
     unsigned long long* sums;        // device [9]: counters summed over the batch
 };

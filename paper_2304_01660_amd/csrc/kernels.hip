@@ -2860,31 +2860,33 @@ __device__ __forceinline__ int64_t exact_blocks(int64_t N) { return (N + EX_COLS
 __device__ __forceinline__ int64_t screen_chunks(int64_t N) { return (N + SC_COLS - 1) / SC_COLS; }
 
 // Candidate groups of a screening item.  Four share a chunk's operands where
-// there are items enough (staging costs as much as the products of three
-// groups), else one, whose items are shorter and more (12,000 points: 11.5 us
-// per round, with four always 26); windows past PM_KC are staged in parts, a
+// there are items enough, in the series or in the batch (staging costs as much
+// as the products of three groups), else one, whose items are shorter and more
+// (12,000 points: 11.5 us per round, with four always 26; batches of two to
+// sixteen series of 12,000 to 30,000 points, m = 120: 3 to 10 % less time than
+// with four in every batch); windows past PM_KC are staged in parts, a
 // group at a time.
 constexpr int SC_GS = SCREEN_GROUPS;
-__device__ __forceinline__ int screen_groups(int B, int32_t m, int64_t ng, int64_t nch)
+__device__ __forceinline__ int screen_groups(int large, int32_t m, int64_t ng, int64_t nch)
 {
-    return m <= PM_KC && (B > 1 || ng * nch > 2 * SCREEN_GRID) ? SC_GS : 1;
+    return m <= PM_KC && (large || ng * nch > 2 * SCREEN_GRID) ? SC_GS : 1;
 }
 
 // Work items of the two kernels: (candidate groups, chunk) or (group, block)
 // of every series, group-major, numbered across the batch; each workgroup
 // takes one contiguous range, so that it stays with a group's windows.
 // ipfx[b]: first item of series b (one series needs no table).
-__device__ __forceinline__ int64_t items_of(const SeriesDev& s, int B, int full, bool screen)
+__device__ __forceinline__ int64_t items_of(const SeriesDev& s, int large, int full, bool screen)
 {
     const Ctrl* c = s.ctrl;
     const int64_t ng = (cand_count(s, c, full) + PM_G - 1) / PM_G;
     const int64_t N = s.n - c->m + 1;
     const int64_t nch = screen_chunks(N);
-    const int gs = screen_groups(B, c->m, ng, nch);
+    const int gs = screen_groups(large, c->m, ng, nch);
     return screen ? (ng + gs - 1) / gs * nch : ng * exact_blocks(N);
 }
 constexpr int ITEMS_BLOCK = 1024;
-__global__ __launch_bounds__(ITEMS_BLOCK) void k_items(SeriesDev* S, int B, int full, int64_t* ipfx_s,
+__global__ __launch_bounds__(ITEMS_BLOCK) void k_items(SeriesDev* S, int B, int large, int full, int64_t* ipfx_s,
                                                        int64_t* ipfx_e)
 {
     __shared__ long long ws[2][ITEMS_BLOCK / 64];
@@ -2894,8 +2896,8 @@ __global__ __launch_bounds__(ITEMS_BLOCK) void k_items(SeriesDev* S, int B, int 
         const int b = b0 + tid;
         long long v[2] = {0, 0}, x[2];
         if (b < B) {
-            v[0] = items_of(S[b], B, full, true);
-            v[1] = items_of(S[b], B, full, false);
+            v[0] = items_of(S[b], large, full, true);
+            v[1] = items_of(S[b], large, full, false);
         }
 #pragma unroll
         for (int q = 0; q < 2; ++q) {
@@ -3146,7 +3148,7 @@ hipError_t launch_half(const Batch& bt, int series, hipStream_t st)
     return hipGetLastError();
 }
 
-__global__ __launch_bounds__(64 * SC_WAVES, 2) void k_screen(SeriesDev* S, int B, int full,
+__global__ __launch_bounds__(64 * SC_WAVES, 2) void k_screen(SeriesDev* S, int B, int large, int full,
                                                           const int64_t* __restrict__ ipfx)
 {
     extern __shared__ __align__(16) _Float16 xa[];  // [PM_G SC_GS][dense_stride(m)]
@@ -3157,7 +3159,7 @@ __global__ __launch_bounds__(64 * SC_WAVES, 2) void k_screen(SeriesDev* S, int B
     __shared__ float lbw[SC_WAVES][PM_G * SC_GS];
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const int ca = lane & 15, ka = lane >> 4;
-    const int64_t total = B == 1 ? items_of(S[0], 1, full, true) : ipfx[B];
+    const int64_t total = B == 1 ? items_of(S[0], 0, full, true) : ipfx[B];
     const Share sh = share_of(total);
     for (int64_t it = sh.lo; it < sh.hi;) {
         const int b = B == 1 ? 0 : series_of(ipfx, B, it);
@@ -3176,7 +3178,7 @@ __global__ __launch_bounds__(64 * SC_WAVES, 2) void k_screen(SeriesDev* S, int B
         const double* __restrict__ mu = cur_mu(s, c);
         const double* __restrict__ inv = s.inv64;
         if (m > PM_KC) continue;
-        const int gs = screen_groups(B, m, (ncand + PM_G - 1) / PM_G, nch);
+        const int gs = screen_groups(large, m, (ncand + PM_G - 1) / PM_G, nch);
         const int ng = min(gs, (ncand + PM_G - 1) / PM_G - gs * g);
         const int nr = PM_G * ng;
         const int stride = dense_stride(m);
@@ -3311,7 +3313,7 @@ __global__ __launch_bounds__(64 * SC_WAVES, 2) void k_screen(SeriesDev* S, int B
 }
 
 // Windows past PM_KC points: staged in parts, a group at a time.
-__global__ __launch_bounds__(64 * SC_WAVES, 2) void k_screen_long(SeriesDev* S, int B, int full,
+__global__ __launch_bounds__(64 * SC_WAVES, 2) void k_screen_long(SeriesDev* S, int B, int large, int full,
                                                           const int64_t* __restrict__ ipfx)
 {
     __shared__ __align__(16) _Float16 xa[PM_G * SC_AS];
@@ -3322,7 +3324,7 @@ __global__ __launch_bounds__(64 * SC_WAVES, 2) void k_screen_long(SeriesDev* S, 
     __shared__ float lbw[SC_WAVES][PM_G];
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const int ca = lane & 15, ka = lane >> 4;
-    const int64_t total = B == 1 ? items_of(S[0], 1, full, true) : ipfx[B];
+    const int64_t total = B == 1 ? items_of(S[0], 0, full, true) : ipfx[B];
     const Share sh = share_of(total);
     for (int64_t it = sh.lo; it < sh.hi;) {
         const int b = B == 1 ? 0 : series_of(ipfx, B, it);
@@ -3522,7 +3524,7 @@ __global__ __launch_bounds__(64 * SC_WAVES, 2) void k_screen_long(SeriesDev* S, 
 // and their latency counts.  With `screened` only the marked blocks run.  One
 // (max rho, argmax j) partial per candidate, group and workgroup, in the
 // order the workgroups finish (slots from one counter per group).
-__global__ __launch_bounds__(64 * EX_WAVES) void k_exact(SeriesDev* S, int B, int full, int screened,
+__global__ __launch_bounds__(64 * EX_WAVES) void k_exact(SeriesDev* S, int B, int large, int full, int screened,
                                                          int screen_grid,
                                                          const int64_t* __restrict__ ipfx_s,
                                                          const int64_t* __restrict__ ipfx_e)
@@ -3539,7 +3541,7 @@ __global__ __launch_bounds__(64 * EX_WAVES) void k_exact(SeriesDev* S, int B, in
     const int ca = lane & 15, ka = lane >> 4;
     double* xg = lds;                 // [PM_G][PM_XS] candidate window chunk
     double* ts = lds + PM_G * PM_XS;  // t[j0 .. j0 + EX_COLS + m + 4 EX_STEPS)
-    const int64_t total = B == 1 ? items_of(S[0], 1, full, false) : ipfx_e[B];
+    const int64_t total = B == 1 ? items_of(S[0], 0, full, false) : ipfx_e[B];
     const Share sh = share_of(total);
     for (int64_t it = sh.lo; it < sh.hi;) {
         const int b = B == 1 ? 0 : series_of(ipfx_e, B, it);
@@ -3578,10 +3580,10 @@ __global__ __launch_bounds__(64 * EX_WAVES) void k_exact(SeriesDev* S, int B, in
             // the lower bounds the screening's workgroups left
             const int64_t nch = screen_chunks(N);
             const int64_t firsts = B == 1 ? 0 : ipfx_s[b];
-            const int64_t tots = B == 1 ? items_of(s, 1, full, true) : ipfx_s[B];
+            const int64_t tots = B == 1 ? items_of(s, 0, full, true) : ipfx_s[B];
             const int64_t pers = (tots + screen_grid - 1) / screen_grid;
             const int64_t w0 = firsts / pers;
-            const int gs = screen_groups(B, m, (ncand + PM_G - 1) / PM_G, nch), sg = g / gs;
+            const int gs = screen_groups(large, m, (ncand + PM_G - 1) / PM_G, nch), sg = g / gs;
             const int64_t e0 = (firsts + sg * nch) / pers - w0 + sg;
             const int64_t e1 = (firsts + (sg + 1) * nch - 1) / pers - w0 + sg;
             const float* lbg = s.lbp + (g - sg * gs) * PM_G + (tid & 15);
@@ -4426,7 +4428,7 @@ static_assert(END_BLOCK >= CAND_MAX, "a thread per candidate");
 constexpr int RANK_PER_ROUND = 64;
 __global__ __launch_bounds__(END_BLOCK) void k_round_end(SeriesDev* S, int32_t* rem, int hot_rows,
                                                           int full, int more, float guard,
-                                                          int max_attempts, int B,
+                                                          int max_attempts, int B, int large,
                                                           const int64_t* __restrict__ ipfx_e)
 {
     // the valid candidates, nvalid_s of them
@@ -4489,7 +4491,7 @@ __global__ __launch_bounds__(END_BLOCK) void k_round_end(SeriesDev* S, int32_t* 
         const int64_t first = B == 1 ? 0 : ipfx_e[blockIdx.x];
         const int64_t total =
             B == 1 ? (int64_t)((kp + CAND_GROUP - 1) / CAND_GROUP) * nblk : ipfx_e[B];
-        const int64_t per = (total + exact_grid(B) - 1) / exact_grid(B);
+        const int64_t per = (total + exact_grid(large) - 1) / exact_grid(large);
         for (int cid = tid / tpc; cid < kp; cid += END_BLOCK / tpc) {
             double best = -f_inf<double>(), bj = 1e300;
             const int g = cid / CAND_GROUP;
@@ -5195,21 +5197,22 @@ static void launch_exact(const Batch& bt, const SweepCfg& cfg, int full, hipStre
 {
     cfg.timer->begin(3, st);
     if (bt.B > 1)
-        hipLaunchKernelGGL(k_items, dim3(1), dim3(ITEMS_BLOCK), 0, st, bt.s, bt.B, full, bt.ipfx,
+        hipLaunchKernelGGL(k_items, dim3(1), dim3(ITEMS_BLOCK), 0, st, bt.s, bt.B, bt.large, full, bt.ipfx,
                            bt.ipfx + bt.B + 1);
     const bool screened = bt.Nmax_all > SCREEN_MIN;
     if (screened) {
         const size_t wins = sizeof(_Float16) * (size_t)PM_G * SC_GS *
                             (size_t)dense_stride(std::min<int32_t>(bt.maxL_all, PM_KC));
-        hipLaunchKernelGGL(k_screen, dim3(SCREEN_GRID), dim3(64 * SC_WAVES), wins, st, bt.s, bt.B, full,
-                           bt.ipfx);
+        hipLaunchKernelGGL(k_screen, dim3(SCREEN_GRID), dim3(64 * SC_WAVES), wins, st, bt.s, bt.B, bt.large,
+                           full, bt.ipfx);
         if (bt.maxL_all > PM_KC)
             hipLaunchKernelGGL(k_screen_long, dim3(SCREEN_GRID), dim3(64 * SC_WAVES), 0, st, bt.s, bt.B,
-                               full, bt.ipfx);
+                               bt.large, full, bt.ipfx);
     }
     const size_t lds = sizeof(double) * (size_t)(PM_G * PM_XS + EX_COLS + bt.maxL_all + 4 * EX_STEPS);
-    hipLaunchKernelGGL(k_exact, dim3(exact_grid(bt.B)), dim3(64 * EX_WAVES), lds, st, bt.s, bt.B, full,
-                       screened ? 1 : 0, SCREEN_GRID, bt.ipfx, bt.ipfx + bt.B + 1);
+    hipLaunchKernelGGL(k_exact, dim3(exact_grid(bt.large)), dim3(64 * EX_WAVES), lds, st, bt.s, bt.B,
+                       bt.large, full, screened ? 1 : 0, SCREEN_GRID, bt.ipfx,
+                       bt.ipfx + bt.B + 1);
     cfg.timer->end(3, st);
 }
 
@@ -5277,7 +5280,7 @@ hipError_t launch_round(const Batch& bt, const SweepCfg& cfg, const int64_t* tot
     launch_exact(bt, cfg, full ? 1 : 0, st);
     hipLaunchKernelGGL(k_round_end, dim3(bt.B), dim3(END_BLOCK), 0, st, bt.s, bt.remaining,
                        64 * cfg.q_near, full ? 1 : 0, more ? 1 : 0, cfg.guard, cfg.max_attempts, bt.B,
-                       bt.ipfx + bt.B + 1);
+                       bt.large, bt.ipfx + bt.B + 1);
     if (full && bt.heat)
         hipLaunchKernelGGL(k_heat, dim3(elem), dim3(ADV_BLOCK), 0, st, bt.s, bt.B, bt.pfx[PFX_ELEM]);
     return hipGetLastError();
@@ -5355,7 +5358,7 @@ hipError_t launch_stream_query(const Batch& bt, const SweepCfg& cfg, const int64
         hipLaunchKernelGGL(k_stream_pick, dim3(bt.B), dim3(TOPK_BLOCK), 0, st, bt.s, prof);
         launch_exact(bt, cfg, 0, st);
         hipLaunchKernelGGL(k_round_end, dim3(bt.B), dim3(END_BLOCK), 0, st, bt.s, bt.remaining,
-                           64 * cfg.q_near, 0, 0, 0.0f, 0, bt.B, bt.ipfx + bt.B + 1);
+                           64 * cfg.q_near, 0, 0, 0.0f, 0, bt.B, bt.large, bt.ipfx + bt.B + 1);
     }
     return hipGetLastError();
 }

@@ -228,3 +228,22 @@ def test_a_window_flat_at_one_length_starts_its_witness_anew(seed):
     member = out["heat"].cpu().numpy()[1, :P.shape[0]] > 0.0
     np.testing.assert_array_equal(member[far], (P >= r)[far])
     assert p in out["idx"].cpu().numpy()[k:]
+
+
+@pytest.mark.parametrize("sizes", [(9000, 8500), (12000, 300, 30000, 9001, 700), (300000, 9500, 260000)])
+def test_batches_small_and_large_equal_single_searches(sizes):
+    """The screening takes candidate groups one at a time or four, and the exact
+    pass 512 or 1024 workgroups, by the batch's chunks: up to 1024 of 512 columns
+    and beyond."""
+    from paper_2304_01660_amd import api
+    dev = _dev()
+    vals = [torch.from_numpy(_series("ecg" if q % 2 else "rw", n, 810 + q)).to(dev)
+            for q, n in enumerate(sizes)]
+    lo = [30 + 20 * q for q in range(len(sizes))]
+    hi = [a + 6 for a in lo]
+    _say("batch chunks", sizes)
+    res = api.discords_batched(vals, lo, hi, 3)
+    for b, T in enumerate(vals):
+        one = api.discords(T, lo[b], hi[b], 3)
+        for key in ("idx", "len", "nn_dist", "nn_idx", "count"):
+            assert torch.equal(res[b][key], one[key]), (b, key)
