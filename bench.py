@@ -44,9 +44,9 @@ OPS_PER_EVAL = 4
 LENGTH_BYTES_PER_SUBSEQ = 68
 KERNEL_NAMES = {
     "select_near": "k_select_near",
-    "select_far": "k_select_far, k_dense",
+    "select_far": "k_select_far",
     "refine": "k_refine",
-    "polish": "k_screen, k_exact",
+    "polish": "k_screen, k_exact, k_dense",
     "length": "k_advance, k_rescue",
     "select_band": "k_select_band",
 }
@@ -275,8 +275,7 @@ def batched_vs_plain(api, synth, tuning, torch, dev, reps: int, retune: bool):
     length range of 51 lengths, top-1): one batched call against a loop of
     single-series calls over the same series.  The batched call uses tile
     geometry from the autotuner (tuned on the batch, outside the timing); the
-    loop gets the best of: default geometry with the graph flag clear, default
-    geometry with direct launches, and the tuned geometry."""
+    loop gets the better of default and tuned geometry."""
     ws = synth.config4()
     vals = [torch.from_numpy(w.T).to(dev) for w in ws]
     lo = [w.minL for w in ws]
@@ -302,9 +301,9 @@ def batched_vs_plain(api, synth, tuning, torch, dev, reps: int, retune: bool):
     wss = [torch.empty(api.workspace_size(w.n, w.minL, w.maxL, 1), dtype=torch.uint8, device=dev)
            for w in ws]
     plain = {}
-    variants = {"default_graph": dict(graphs=True), "default_direct": dict(graphs=False)}
+    variants = {"default": {}}
     if tuned:
-        variants["tuned_graph"] = dict(tuned)
+        variants["tuned"] = dict(tuned)
     for name, kw in variants.items():
         for b, w in enumerate(ws):  # warm-up
             api.discords(vals[b], w.minL, w.maxL, 1, workspace=wss[b], **kw)
@@ -667,7 +666,7 @@ def main():
         "higher_is_better": True,
         "scaling": "weak",
         "vs_baseline": None,
-        "dtype": "f32+f64",
+        "dtype": "f32+f64 (bounds: f16)",
         "data": "synthetic",
         "config": {
             "workload": w.name,

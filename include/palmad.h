@@ -63,8 +63,11 @@ typedef enum {
 /* Options; a zero-initialised struct selects the defaults. */
 typedef struct {
     int32_t dist_bits;     /* 32: FP32 selection sweep (statistics, refinement and
-                              reported distances stay FP64); 64: FP64 throughout.
-                              0 = 32. */
+                              reported distances stay FP64); 64: FP64 sweeps.
+                              0 = 32.  With either, rounds without sweeps and dense
+                              rounds bound correlations on the FP16 matrix cores,
+                              with proved errors; what a bound leaves open, and
+                              every value reported, is FP64. */
     float guard;           /* correlation guard band of the FP32 selection sweep:
                               a pair prunes only if its FP32 correlation exceeds the
                               threshold by more than this.  <= 0 = 1.25e-4. */
@@ -104,7 +107,8 @@ enum {
     PALMAD_KERNEL_SELECT_NEAR = 0, /* first selection pass of every row tile */
     PALMAD_KERNEL_SELECT_FAR = 1,  /* split selection pass over the remaining columns */
     PALMAD_KERNEL_REFINE = 2,      /* refinement pass (exact FP64 nearest neighbour) */
-    PALMAD_KERNEL_POLISH = 3,      /* direct FP64 distances of the top candidates */
+    PALMAD_KERNEL_POLISH = 3,      /* direct FP64 distances of the top candidates (counted), and
+                                      the matrix-core bounds before them: screening, dense rounds */
     PALMAD_KERNEL_LENGTH = 4,      /* per-length statistics, helpers and round resets */
     PALMAD_KERNEL_SELECT_BAND = 5, /* diagonal band pre-pass of the first selection pass */
     PALMAD_KERNEL_CLASSES = 6
@@ -112,7 +116,8 @@ enum {
 
 /* Per-call counters (host struct, filled when the call returns). */
 typedef struct {
-    uint64_t evals_select;   /* pair correlations evaluated by selection passes */
+    uint64_t evals_select;   /* pair correlations evaluated by selection passes, or bounded
+                                by dense rounds (in no class of kernel_evals) */
     uint64_t evals_refine;   /* pair correlations evaluated by refinement passes */
     uint64_t evals_polish;   /* pair distances evaluated by the exact FP64 pass */
     uint64_t range_searches; /* selection+refinement rounds (DRAG calls), all lengths */

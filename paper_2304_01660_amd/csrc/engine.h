@@ -102,9 +102,10 @@ constexpr int HOT_FRAC = 8;
 
 // Pair-evaluation counters: EV_SLOTS slots per class, so that the many
 // work items of a launch add to different addresses.
-constexpr int EV_CLASSES = 5;  // first selection pass, split pass, refinement, exact pass, band pre-pass
+constexpr int EV_CLASSES = 6;  // first selection pass, split pass, refinement, exact pass, band
+                               // pre-pass, bounds of dense rounds
 constexpr int EV_SLOTS = 64;
-enum { EV_NEAR = 0, EV_FAR = 1, EV_REF = 2, EV_POL = 3, EV_BAND = 4 };
+enum { EV_NEAR = 0, EV_FAR = 1, EV_REF = 2, EV_POL = 3, EV_BAND = 4, EV_DENSE = 5 };
 
 // Host counters of a round: series with work left, series in error, series
 // whose next range search needs sweeps (the first length's, those waiting for

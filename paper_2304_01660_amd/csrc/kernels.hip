@@ -288,7 +288,7 @@ __device__ void begin_range(const SeriesDev& s, Ctrl* c, float guard)
     const double r = c->r;
     c->prune = r > 0.0 ? 1 : 0;
     c->thr64 = r > 0.0 ? 1.0 - r * r / (2.0 * (double)m) : 2.0;
-    // a new length's contrast is measured by k_length and k_guard, which
+    // a new length's contrast is measured by k_helpers and k_guard, which
     // then resets the selection thresholds; a repeat keeps the current length's
     if (c->new_len) c->gam2 = 0.0;
     set_sel_thresholds(c, guard);
@@ -454,8 +454,8 @@ __device__ __forceinline__ void grow_stats(double t, const GrowBy& g, double mu0
     var = g.fm * (v0 + div_by(d * d, g.m, g.rm));
 }
 
-// Block extremes of the window spreads (every block of k_length at a new
-// length): the largest and smallest sigma of the block's non-flat windows.
+// Block extremes of the window spreads (every block of k_helpers, and of
+// k_length in the diagnostics): the largest and smallest sigma of the block's non-flat windows.
 __device__ void spread_extremes(const SeriesDev& s, int64_t lb, double smax, double smin)
 {
     __shared__ double rmax[4], rmin[4];
@@ -482,7 +482,7 @@ __device__ void spread_extremes(const SeriesDev& s, int64_t lb, double smax, dou
 }
 
 // The spread contrast of a new length and the round's selection thresholds
-// (one block per series, after k_length): over every block of 256 windows,
+// (one block per series, after k_helpers): over every block of 256 windows,
 // the largest spread of the two blocks on either side (a superset of the
 // R_MAX - 1 windows a recurrence chain passes on each side) over the block's
 // smallest spread, squared (see sel_guard).
@@ -2965,7 +2965,11 @@ typedef float acc4f_t __attribute__((ext_vector_type(4)));
 // by Cauchy-Schwarz on |x| = 1 and |w_j - off|: e0 holds the two roundings
 // (2^-11 each) and the FP32 accumulation (one rounding of 2^-23 per product),
 // floor the smallest normal FP16 value (should the matrix cores flush
-// subnormals), all rounded up.  A candidate's lower bound is the largest
+// subnormals), all rounded up.  (Measured on the device: the instruction's sums
+// of 32 to 512 products of random, cancelling, offset, widely spread and
+// subnormal values are off by at most 4.7 x 2^-23 of the products' absolute
+// sum, where the bound allows the number of products + 32; subnormal values are
+// kept.)  A candidate's lower bound is the largest
 // rho~ - e_j over all columns; only blocks whose largest rho~ + e_j reaches
 // it can hold its maximum, so k_exact finds the same value and the same
 // smallest argmax as over all columns.  (A split into two FP16 values per
@@ -3991,7 +3995,7 @@ __device__ __forceinline__ void dense_item(const SeriesDev& s, Ctrl* c, int64_t 
         __syncthreads();
         if (tid == 0) *npair_p = 0u;
     };
-    unsigned long long ev = 0;
+    unsigned int ev = 0, left = DN_ROWS;  // rows times blocks, rows not dead
     fetch_chunk(s, mu, inv, ch0, R);
     for (int64_t ch = ch0; ch < ch1; ++ch) {
         const int64_t j0 = ch * SC_COLS;
@@ -4022,6 +4026,7 @@ __device__ __forceinline__ void dense_item(const SeriesDev& s, Ctrl* c, int64_t 
                 for (int k = lane; k < stride; k += 64) dxa[r * stride + k] = (_Float16)0.0f;
             }
             seen = dead;
+            left = (unsigned int)(DN_ROWS - __popcll(uniform64(dead)));
             fresh = true;
         }
         __syncthreads();
@@ -4152,7 +4157,7 @@ __device__ __forceinline__ void dense_item(const SeriesDev& s, Ctrl* c, int64_t 
                 if (hand && v - em > thr) atomicOr(dead_p, 1ull << rr);  // surely closer than r
             }
         }
-        ev += (unsigned long long)DN_ROWS * EX_COLS;
+        ev += left;
     }
     __syncthreads();
     flush();
@@ -4181,7 +4186,8 @@ __device__ __forceinline__ void dense_item(const SeriesDev& s, Ctrl* c, int64_t 
         }
     }
     if (lane == 0 && ev)
-        atomicAdd(&s.evc[EV_FAR * EV_SLOTS + ((blockIdx.x + w) & (EV_SLOTS - 1))], ev);
+        atomicAdd(&s.evc[EV_DENSE * EV_SLOTS + ((blockIdx.x + w) & (EV_SLOTS - 1))],
+                  (unsigned long long)ev * EX_COLS);
 }
 
 // Row tiles of a series' list.
@@ -5193,9 +5199,8 @@ static void launch_refine_q(const Batch& bt, const SweepCfg& cfg, const int64_t*
 
 // The exact pass over the rounds' candidates.  Up to SCREEN_MIN subsequences
 // a launch of the screening costs more than the blocks it saves.
-static void launch_exact(const Batch& bt, const SweepCfg& cfg, int full, hipStream_t st)
+static void launch_exact(const Batch& bt, int full, hipStream_t st)
 {
-    cfg.timer->begin(3, st);
     if (bt.B > 1)
         hipLaunchKernelGGL(k_items, dim3(1), dim3(ITEMS_BLOCK), 0, st, bt.s, bt.B, bt.large, full, bt.ipfx,
                            bt.ipfx + bt.B + 1);
@@ -5213,7 +5218,6 @@ static void launch_exact(const Batch& bt, const SweepCfg& cfg, int full, hipStre
     hipLaunchKernelGGL(k_exact, dim3(exact_grid(bt.large)), dim3(64 * EX_WAVES), lds, st, bt.s, bt.B,
                        bt.large, full, screened ? 1 : 0, SCREEN_GRID, bt.ipfx,
                        bt.ipfx + bt.B + 1);
-    cfg.timer->end(3, st);
 }
 
 hipError_t launch_start(const Batch& bt, const SweepCfg& cfg, hipStream_t st)
@@ -5264,8 +5268,8 @@ hipError_t launch_round(const Batch& bt, const SweepCfg& cfg, const int64_t* tot
         }
         hipLaunchKernelGGL(k_select_top, dim3(bt.B), dim3(TOPK_BLOCK), 0, st, bt.s);
     }
+    cfg.timer->begin(3, st);
     if (dense) {
-        cfg.timer->begin(1, st);
         hipLaunchKernelGGL(k_dense_list, dim3(bt.B), dim3(TOPK_BLOCK), 0, st, bt.s, full ? 1 : 0);
         if (bt.B > 1)
             hipLaunchKernelGGL(k_dense_items, dim3(1), dim3(ITEMS_BLOCK), 0, st, bt.s, bt.B, bt.ipfx);
@@ -5275,9 +5279,9 @@ hipError_t launch_round(const Batch& bt, const SweepCfg& cfg, const int64_t* tot
         hipLaunchKernelGGL(k_pairs, dim3(RESCUE_GRID), dim3(RESCUE_BLOCK), 0, st, bt.s, bt.B,
                            bt.ipfx);
         hipLaunchKernelGGL(k_dense_top, dim3(bt.B), dim3(TOPK_BLOCK), 0, st, bt.s);
-        cfg.timer->end(1, st);
     }
-    launch_exact(bt, cfg, full ? 1 : 0, st);
+    launch_exact(bt, full ? 1 : 0, st);
+    cfg.timer->end(3, st);
     hipLaunchKernelGGL(k_round_end, dim3(bt.B), dim3(END_BLOCK), 0, st, bt.s, bt.remaining,
                        64 * cfg.q_near, full ? 1 : 0, more ? 1 : 0, cfg.guard, cfg.max_attempts, bt.B,
                        bt.large, bt.ipfx + bt.B + 1);
@@ -5356,7 +5360,7 @@ hipError_t launch_stream_query(const Batch& bt, const SweepCfg& cfg, const int64
     for (int32_t m = minL; m <= maxL; m += bt.B) {
         launch_stream_group(bt, total, m, maxL, st);
         hipLaunchKernelGGL(k_stream_pick, dim3(bt.B), dim3(TOPK_BLOCK), 0, st, bt.s, prof);
-        launch_exact(bt, cfg, 0, st);
+        launch_exact(bt, 0, st);
         hipLaunchKernelGGL(k_round_end, dim3(bt.B), dim3(END_BLOCK), 0, st, bt.s, bt.remaining,
                            64 * cfg.q_near, 0, 0, 0.0f, 0, bt.B, bt.large, bt.ipfx + bt.B + 1);
     }
@@ -5444,7 +5448,7 @@ __global__ __launch_bounds__(1024) void k_sum_stats(SeriesDev* S, int B, unsigne
             for (int o = 32; o >= 1; o >>= 1) v[e] += __shfl_xor(v[e], o);
         if (lane == 0) {
             const Ctrl* c = s.ctrl;
-            atomicAdd(&acc[0], v[EV_NEAR] + v[EV_FAR] + v[EV_BAND]);
+            atomicAdd(&acc[0], v[EV_NEAR] + v[EV_FAR] + v[EV_BAND] + v[EV_DENSE]);
             atomicAdd(&acc[1], v[EV_REF]);
             atomicAdd(&acc[2], v[EV_POL]);
             atomicAdd(&acc[3], c->rounds);

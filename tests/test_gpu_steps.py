@@ -17,7 +17,6 @@ pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
 
 KEYS = ("idx", "len", "nn_dist", "nn_idx", "count")
-FAR = 1  # kernel class of the split selection pass and of k_dense
 
 
 def _dev():
@@ -67,7 +66,8 @@ def test_a_dense_round_that_cannot_decide_gives_up(dist_bits, n, jump):
     minL, maxL, k = 64, 68, 2
     _say("steps", dist_bits, n, jump)
     T = torch.from_numpy(stepped(n, minL, jump, 11)).to(dev)
-    # every first pass covers all columns, so the class FAR holds k_dense alone
+    # every first pass covers all columns, so what the selection evaluates beside
+    # it are the bounds of dense rounds
     opts = dict(dist_bits=dist_bits, near_cols=1 << 30, return_stats=True)
     plain = api.discords(T, minL, maxL, k, **opts)
     swept = api.discord_heatmap(T, minL, maxL, k, **opts)
@@ -89,7 +89,9 @@ def test_a_dense_round_that_cannot_decide_gives_up(dist_bits, n, jump):
     left = int((d >= r).sum())
     assert math.isclose(r, math.sqrt(minL) / 2) and left > 1024
     if n > 16384:
-        assert plain["stats"]["kernel_evals"][FAR] < 0.5 * left * N
+        st = plain["stats"]
+        assert st["kernel_evals"][1] == 0
+        assert 0 < st["evals_select"] - st["kernel_evals"][0] < 0.5 * left * N
 
 
 def test_a_batch_of_stepped_series_equals_single_searches():
