@@ -209,6 +209,7 @@ __device__ __forceinline__ unsigned long long pair_count(long long ilo, long lon
 // guard (default 1.25e-4).  A series with an extreme spread contrast thus
 // gets a wide band (the selection sweep prunes less, the FP64 refinement
 // decides), never an unsound one.
+constexpr double WIDE_BAND = 0.01;  // more rows within it of the k-th best than are candidates
 constexpr double GUARD_PER_CONTRAST2 = 4.0 * 0x1p-24 * 22.62741699796952;  // 4 u sqrt(512)
 
 __device__ __forceinline__ double sel_guard(const Ctrl* c, float guard)
@@ -4563,8 +4564,11 @@ __global__ __launch_bounds__(END_BLOCK) void k_round_end(SeriesDev* S, int32_t* 
     const unsigned int ns = direct ? (kp >= k ? nvalid_s : (lean ? c->nlive : c->nsurv)) : c->nsurv;
     // the candidates could not be narrowed: same r again, after sweeps with
     // both sides of every tile refined exactly, after a dense round with sweeps
-    // (exactly too where the bounds were lost: the level jumps that widen them
-    // widen the FP32 guard band, and its sweeps would be repeated in turn)
+    // (exactly too where the FP32 guard band is wide, as level jumps make it
+    // that also lose a dense round: its sweeps would be repeated in turn.  300,000
+    // points with jumps 160 -> 109 ms; refining both sides where the band is
+    // narrow costs as much again: 600,000 points without jumps 65 ms, 46 on the
+    // left alone)
     const bool redo = !lean && c->band_over != 0;
     const bool ok = ns >= (unsigned int)k && kp >= k && !redo;
     const int nv = kp >= k ? (int)nvalid_s : 0;
@@ -4640,7 +4644,7 @@ __global__ __launch_bounds__(END_BLOCK) void k_round_end(SeriesDev* S, int32_t* 
             c->rows_near += c->nlive;
             c->rows_far += c->nlive;
         }
-        c->exact_ref = redo && (!handled || lost) ? 1 : 0;
+        c->exact_ref = redo && (!handled || (lost && c->thr_sel - c->thr64 > WIDE_BAND)) ? 1 : 0;
         c->pending = 0;
         const int was = c->sweeps ? SWEEPS_AGAIN : 0;
         c->sweeps = li == 0 || lean || handled || dense_allowed(s, c)
