@@ -324,9 +324,10 @@ __device__ void begin_range(const SeriesDev& s, Ctrl* c, float guard)
 // dense round is no choice (dense_allowed), is followed by others of its kind
 // (heatmaps of noisy series, windows past 256 points): its series asks for
 // sweeps at once instead of waiting for them in a round that can only find that
-// out.  SWEEPS_MANY: the range discords alone were too many, so that neither
-// second chances nor fresh witnesses can make the next round one without sweeps,
-// and its sweeps, for which a witness is 1.5 operations more per pair, keep
+// out.  SWEEPS_MANY: the range discords alone were too many (for a dense round,
+// where that is possible, half of all rows), so that neither second chances nor
+// fresh witnesses can make the next round one without sweeps, and its sweeps,
+// for which a witness is 1.5 operations more per pair, keep
 // none; SWEEPS_AGAIN: the one before swept too, and the host issues several
 // such rounds at once.  (Heatmap of 14,098 points, eleven lengths, 1,675 to
 // 2,275 range discords at six of them: 4.2 ms, so 3.5; white noise, 300,000
@@ -3796,10 +3797,14 @@ constexpr int DN_BUF = 512;              // entries buffered per workgroup
 // candidates at once.  In a round without sweeps (full = 0) every series with
 // too many rows left for that is taken here, unless its witnesses failed
 // altogether.
+__device__ __forceinline__ bool dense_possible(const SeriesDev& s, const Ctrl* c)
+{
+    return c->prune && s.heat == nullptr && c->m <= DENSE_MAXM && c->thr64 >= DENSE_MIN_THR &&
+           !dense_off(c);
+}
 __device__ __forceinline__ bool dense_allowed(const SeriesDev& s, const Ctrl* c)
 {
-    return c->prune && c->nlive != 0x7fffffffu && s.heat == nullptr && c->m <= DENSE_MAXM &&
-           c->thr64 >= DENSE_MIN_THR && !dense_off(c);
+    return c->nlive != 0x7fffffffu && dense_possible(s, c);
 }
 __global__ __launch_bounds__(TOPK_BLOCK) void k_dense_list(SeriesDev* S, int full)
 {
@@ -4649,7 +4654,10 @@ __global__ __launch_bounds__(END_BLOCK) void k_round_end(SeriesDev* S, int32_t* 
         const int was = c->sweeps ? SWEEPS_AGAIN : 0;
         c->sweeps = li == 0 || lean || handled || dense_allowed(s, c)
                         ? SWEEPS_NO
-                        : was | (ns > c->lean_max ? SWEEPS_MANY : SWEEPS_FEW);
+                        : was | ((dense_possible(s, c) ? (int64_t)ns * 2 > s.n - m + 1
+                                                       : ns > c->lean_max)
+                                     ? SWEEPS_MANY
+                                     : SWEEPS_FEW);
         // (a heatmap row of a round that refined: the bitmap's rows, by k_heat)
         c->heat_m = ok && !direct ? m : 0;
         if (ok) {

@@ -219,3 +219,23 @@ def test_the_first_pass_of_a_dense_round_may_be_cut(chunk):
     swept = api.discord_heatmap(T, 64, 66, 3)
     for key in KEYS:
         assert torch.equal(plain[key], swept[key]), key
+
+
+def test_a_length_whose_witnesses_all_fail_does_not_end_dense_rounds():
+    """Short windows of a noisy beat train: most rows are range discords of the
+    first length, so that the second length's witnesses fail and it sweeps; the
+    lengths after it take dense rounds again, which refine nothing."""
+    from paper_2304_01660_amd import api, synth
+    dev = _dev()
+    n, minL, maxL, k = 260000, 26, 36, 8
+    T, _ = synth.ecg_like(np.random.default_rng([3, n, maxL]), n, 5, maxL=maxL)
+    T = torch.from_numpy(synth.fp32_canonical(T)).to(dev)
+    _say("failed witnesses", n)
+    plain = api.discords(T, minL, maxL, k, return_stats=True)
+    swept = api.discord_heatmap(T, minL, maxL, k, return_stats=True)
+    for key in KEYS:
+        assert torch.equal(plain[key], swept[key]), key
+    two = api.discords(T, minL, minL + 1, k, return_stats=True)
+    _say([x["stats"]["evals_refine"] for x in (two, plain, swept)], plain["count"].tolist())
+    # no more refinement than the first two lengths' beside one length's sweep
+    assert plain["stats"]["evals_refine"] <= 2 * two["stats"]["evals_refine"] + n * n // 4
