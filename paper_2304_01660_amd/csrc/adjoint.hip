@@ -62,19 +62,25 @@ __device__ void adj_window_stats(const double* T, int64_t p, int32_t m, double* 
 // column's mean and deviation and the reads of its window, R at a time; every
 // value is the same as for a row alone.  Bound by the LDS reads, of a row's
 // value for two columns, and the FP64 operations, 3 + R per offset and column.
-// (325 rows, five per length of 96 to 160, 200,000 columns: a row and 256
-// columns per workgroup 3.36 ms, so 1.80 ms.)
+// Held to 128 registers, four waves per SIMD: with a row's state and results in
+// registers it took 204, and rows that share nothing ran slower than one at a
+// time.  (Whole call, a row and 256 columns per workgroup, with 204 registers,
+// so: 325 rows, five per length of 96 to 160, 200,000 columns 3.40, 2.00, 1.55 ms;
+// 129 rows of different lengths 1.80, 2.37, 1.75.)
 constexpr int ADJ_ROWS = 16;  // most rows per workgroup
 constexpr int ADJ_RUN = 8;    // most rows sharing a column
 constexpr int ADJ_SPAN = 4;   // most blocks of columns
 constexpr int64_t ADJ_FILL = 2048;  // workgroups wanted: eight per CU
 
-// Sums of squares v and products c of the C column windows t + 256 e, less
-// their means, with R centred rows xs (stride doubles apart).
+// The C column windows t + 256 e, less their means, against R centred rows xs
+// (stride doubles apart): sums of squares and products, then each row's largest
+// correlation over the wave's columns and the first column that has it.
 template <int R, int C>
-__device__ __forceinline__ void adj_dots(const double* t, const double* xs, int stride, int32_t m,
-                                         const double (&mu)[C], double (&v)[C],
-                                         double (&c)[C][ADJ_RUN])
+__device__ __forceinline__ void adj_columns(const double* t, const double* xs, int stride, int32_t m,
+                                            const double (&mu)[C], int64_t N, int64_t j0, double feps,
+                                            unsigned int ok, const double* sgi, const long long* ii,
+                                            double (*rv)[ADJ_RUN][ADJ_BLOCK / 64],
+                                            long long (*rj)[ADJ_RUN][ADJ_BLOCK / 64])
 {
     double c0[C][R], c1[C][R], vv[C];
 #pragma unroll
@@ -112,16 +118,36 @@ __device__ __forceinline__ void adj_dots(const double* t, const double* xs, int 
             for (int r = 0; r < R; ++r) c0[e][r] = fma(xs[r * stride + k], d0, c0[e][r]);
         }
     }
+    const int tid = threadIdx.x;
 #pragma unroll
     for (int e = 0; e < C; ++e) {
-        v[e] = vv[e];
+        const int64_t j = j0 + ADJ_BLOCK * e + tid;
+        const double sgj = sqrt(vv[e] / (double)m);
+        const bool flat_j = sgj <= feps;
 #pragma unroll
-        for (int r = 0; r < R; ++r) c[e][r] = c0[e][r] + c1[e][r];
+        for (int r = 0; r < R; ++r) {
+            const long long i = ii[r];
+            const double si = sgi[r];
+            const bool flat_i = si <= feps;
+            double b = -1e300;
+            if (((ok >> r) & 1u) && j < N && (j <= i - m || j >= i + m))
+                b = flat_i || flat_j ? (flat_i && flat_j ? 1.0 : 0.0)
+                                     : fmin(1.0, fmax(-1.0, (c0[e][r] + c1[e][r]) / ((double)m * si * sgj)));
+            // (columns ascend with the lane: the first lane that has the maximum)
+            double top = b;
+#pragma unroll
+            for (int o = 32; o >= 1; o >>= 1) top = fmax(top, __shfl_xor(top, o));
+            const int first = __ffsll((long long)__ballot(b == top)) - 1;
+            if ((tid & 63) == 0) {
+                rv[e][r][tid >> 6] = top;
+                rj[e][r][tid >> 6] = top > -1e299 ? (long long)(j + first) : 0x7fffffffffffffffll;
+            }
+        }
     }
 }
 
 template <int C>
-__global__ __launch_bounds__(ADJ_BLOCK) void k_adj_rows(const double* __restrict__ T, int64_t n,
+__global__ __launch_bounds__(ADJ_BLOCK, 4) void k_adj_rows(const double* __restrict__ T, int64_t n,
                                                         int64_t K, const int64_t* __restrict__ idx,
                                                         const int32_t* __restrict__ len,
                                                         const Ctrl* ctrl, double* part, int64_t nblk,
@@ -131,6 +157,8 @@ __global__ __launch_bounds__(ADJ_BLOCK) void k_adj_rows(const double* __restrict
     __shared__ double sh[8];
     __shared__ double rv[C][ADJ_RUN][ADJ_BLOCK / 64];
     __shared__ long long rj[C][ADJ_RUN][ADJ_BLOCK / 64];
+    __shared__ double sgi[ADJ_RUN];
+    __shared__ long long ii[ADJ_RUN];
     const int tid = threadIdx.x;
     const int64_t q0 = (int64_t)blockIdx.y * rows, q1 = std::min<int64_t>(K, q0 + rows);
     const int64_t x0 = (int64_t)blockIdx.x * span, x1 = std::min<int64_t>(nblk, x0 + span);
@@ -143,34 +171,27 @@ __global__ __launch_bounds__(ADJ_BLOCK) void k_adj_rows(const double* __restrict
         while (run < max_run && q + run < q1 && len[q + run] == m) ++run;
         const int64_t N = n - m + 1;
         const bool len_ok = m >= 3 && m <= ctrl->m;  // ctrl->m holds max length
-        double sgi[ADJ_RUN];
-        int64_t ii[ADJ_RUN];
         unsigned int ok = 0u;
-#pragma unroll
-        for (int r = 0; r < ADJ_RUN; ++r) {
-            ii[r] = 0;
-            sgi[r] = 0.0;
-            if (r >= run || !len_ok) continue;
-            ii[r] = idx[q + r];
-            if (ii[r] < 0 || ii[r] >= N) continue;
+        for (int r = 0; r < run && len_ok; ++r) {
+            const int64_t i = idx[q + r];
+            if (i < 0 || i >= N) continue;
             ok |= 1u << r;
-            double mui;
-            adj_window_stats(T, ii[r], m, sh, mui, sgi[r]);
-            for (int k = tid; k < m; k += ADJ_BLOCK) xs[r * stride + k] = T[ii[r] + k] - mui;
+            double mui, sg;
+            adj_window_stats(T, i, m, sh, mui, sg);
+            for (int k = tid; k < m; k += ADJ_BLOCK) xs[r * stride + k] = T[i + k] - mui;
+            if (tid == 0) {
+                ii[r] = i;
+                sgi[r] = sg;
+            }
         }
         for (int64_t x = x0; x < x1; x += C) {
             const int64_t j0 = x * ADJ_BLOCK;
-            double best[C][ADJ_RUN];
-#pragma unroll
-            for (int e = 0; e < C; ++e)
-#pragma unroll
-                for (int r = 0; r < ADJ_RUN; ++r) best[e][r] = -1e300;
             __syncthreads();  // the previous blocks and run are consumed
             if (ok && j0 < N) {
                 for (int t = tid; t < ADJ_BLOCK * C + m; t += ADJ_BLOCK) ts[t] = j0 + t < n ? T[j0 + t] : 0.0;
                 __syncthreads();
                 const double* t = ts + tid;
-                double mu[C], v[C], c[C][ADJ_RUN];
+                double mu[C];
 #pragma unroll
                 for (int e = 0; e < C; ++e) mu[e] = 0.0;
                 for (int k = 0; k < m; ++k)
@@ -178,52 +199,22 @@ __global__ __launch_bounds__(ADJ_BLOCK) void k_adj_rows(const double* __restrict
                     for (int e = 0; e < C; ++e) mu[e] += t[ADJ_BLOCK * e + k];
 #pragma unroll
                 for (int e = 0; e < C; ++e) mu[e] /= (double)m;
+#define ADJ_COLUMNS(R) adj_columns<R, C>(t, xs, stride, m, mu, N, j0, feps, ok, sgi, ii, rv, rj)
                 switch (run) {
-                case 1: adj_dots<1, C>(t, xs, stride, m, mu, v, c); break;
-                case 2: adj_dots<2, C>(t, xs, stride, m, mu, v, c); break;
-                case 3: adj_dots<3, C>(t, xs, stride, m, mu, v, c); break;
-                case 4: adj_dots<4, C>(t, xs, stride, m, mu, v, c); break;
-                case 5: adj_dots<5, C>(t, xs, stride, m, mu, v, c); break;
-                case 6: adj_dots<6, C>(t, xs, stride, m, mu, v, c); break;
-                case 7: adj_dots<7, C>(t, xs, stride, m, mu, v, c); break;
-                default: adj_dots<8, C>(t, xs, stride, m, mu, v, c); break;
+                case 1: ADJ_COLUMNS(1); break;
+                case 2: ADJ_COLUMNS(2); break;
+                case 3: ADJ_COLUMNS(3); break;
+                case 4: ADJ_COLUMNS(4); break;
+                case 5: ADJ_COLUMNS(5); break;
+                case 6: ADJ_COLUMNS(6); break;
+                case 7: ADJ_COLUMNS(7); break;
+                default: ADJ_COLUMNS(8); break;
                 }
-#pragma unroll
-                for (int e = 0; e < C; ++e) {
-                    const int64_t j = j0 + ADJ_BLOCK * e + tid;
-                    const double sgj = sqrt(v[e] / (double)m);
-                    const bool flat_j = sgj <= feps;
-#pragma unroll
-                    for (int r = 0; r < ADJ_RUN; ++r) {
-                        if (r >= run || !((ok >> r) & 1u)) continue;
-                        if (j >= N || !(j <= ii[r] - m || j >= ii[r] + m)) continue;
-                        const bool flat_i = sgi[r] <= feps;
-                        best[e][r] = flat_i || flat_j
-                                         ? (flat_i && flat_j ? 1.0 : 0.0)
-                                         : fmin(1.0, fmax(-1.0, c[e][r] / ((double)m * sgi[r] * sgj)));
-                    }
-                }
+#undef ADJ_COLUMNS
+            } else if (tid < C * ADJ_RUN * (ADJ_BLOCK / 64)) {
+                (&rv[0][0][0])[tid] = -1e300;
+                (&rj[0][0][0])[tid] = 0x7fffffffffffffffll;
             }
-#pragma unroll
-            for (int e = 0; e < C; ++e)
-#pragma unroll
-                for (int r = 0; r < ADJ_RUN; ++r) {
-                    if (r >= run) break;
-                    double b = best[e][r];
-                    long long bj = b > -1e299 ? (long long)(j0 + ADJ_BLOCK * e + tid) : 0x7fffffffffffffffll;
-                    for (int o = 32; o >= 1; o >>= 1) {
-                        const double vv = __shfl_xor(b, o);
-                        const long long jj = __shfl_xor(bj, o);
-                        if (vv > b || (vv == b && jj < bj)) {
-                            b = vv;
-                            bj = jj;
-                        }
-                    }
-                    if ((tid & 63) == 0) {
-                        rv[e][r][tid >> 6] = b;
-                        rj[e][r][tid >> 6] = bj;
-                    }
-                }
             __syncthreads();
             const int r = tid & (ADJ_RUN - 1), e = tid / ADJ_RUN;
             if (e < C && r < run && x + e < x1) {
@@ -327,9 +318,9 @@ hipError_t launch_adjoint(const double* Tpad, int64_t n, int64_t K, int32_t maxm
     // small problem then leaves the device idle behind a few serial workgroups:
     // the shares are cut until there are ADJ_FILL of them, the columns' first
     // (that costs the least).  (Whole call, full shares and these: 8,000 points
-    // and 33 rows of different lengths 0.64 and 0.19 ms; 50,000 points and 33
-    // rows 0.66 and 0.28; 12,000 points and 99 rows, three per length, 0.44 and
-    // 0.24.  4096 workgroups are too many: 50,000 points and 325 rows 0.71 ms
+    // and 33 rows of different lengths 0.64 and 0.24 ms; 50,000 points and 33
+    // rows 0.66 and 0.29; 12,000 points and 99 rows, three per length, 0.44 and
+    // 0.27.  4096 workgroups are too many: 50,000 points and 325 rows 0.71 ms
     // with 2048, 0.86.)
     const auto groups = [&] { return ((nblk + span - 1) / span) * ((K + rows - 1) / rows); };
     while (groups() < ADJ_FILL) {
