@@ -561,7 +561,7 @@ int search(palmad_ctx* ctx, const Plan& p, const Opts& o, void* ws, const double
         full = ctx->pinned[REM_SWEEP] > 0;
         steady = ctx->pinned[REM_STEADY] > 0;
         wit = ctx->pinned[REM_WITNESS] > 0;
-        lengths = ctx->pinned[REM_LENGTHS];
+        lengths = ctx->pinned[REM_LEFT];
         dense = ctx->pinned[REM_DENSE] > 0;
     }
     const double secs =

@@ -107,12 +107,12 @@ constexpr int EV_CLASSES = 6;  // first selection pass, split pass, refinement, 
 constexpr int EV_SLOTS = 64;
 enum { EV_NEAR = 0, EV_FAR = 1, EV_REF = 2, EV_POL = 3, EV_BAND = 4, EV_DENSE = 5 };
 
-// Host counters of a round: series with work left, series in error, series
-// whose next range search needs sweeps (the first length's, those waiting for
-// them and those whose last one did), those whose last two did, those of them
-// that want the witnesses kept, series whose next one is a dense round, most lengths left; then, once per call, series holding NaN
-// or Inf and the first of them.
-enum { REM_LEFT = 0, REM_ERROR, REM_SWEEP, REM_STEADY, REM_WITNESS, REM_DENSE, REM_LENGTHS, REM_COUNT };
+// Host counters of a round: most lengths left to any series, series in error,
+// series whose next range search needs sweeps (the first length's, those
+// waiting for them and those whose last one did), those whose last two did,
+// those that want the witnesses kept, series whose next one is a dense round;
+// then, once per call, series holding NaN or Inf and the first of them.
+enum { REM_LEFT = 0, REM_ERROR, REM_SWEEP, REM_STEADY, REM_WITNESS, REM_DENSE, REM_COUNT };
 enum { REM_BAD = REM_COUNT, REM_BAD_SERIES, REM_TOTAL };
 
 // Device-resident control block of one series (the MERLIN state of Alg. 1

@@ -369,12 +369,11 @@ __device__ void next_range(const SeriesDev& s, Ctrl* c, float guard, int max_att
     c->done = 0;
     c->active = 1;
     begin_range(s, c, guard);
-    atomicAdd(&rem[REM_LEFT], 1);
+    atomicMax(&rem[REM_LEFT], s.maxL - c->m + 1);
     if (c->li == 0 || c->sweeps) atomicAdd(&rem[REM_SWEEP], 1);
     if (c->li == 0 || (c->sweeps & SWEEPS_FEW)) atomicAdd(&rem[REM_WITNESS], 1);
     if (c->sweeps & SWEEPS_AGAIN) atomicAdd(&rem[REM_STEADY], 1);
     if (dense_round(c)) atomicAdd(&rem[REM_DENSE], 1);
-    atomicMax(&rem[REM_LENGTHS], s.maxL - c->m + 1);
 }
 
 // Before the first round of a search.
@@ -4463,17 +4462,21 @@ __global__ __launch_bounds__(END_BLOCK) void k_round_end(SeriesDev* S, int32_t* 
     // block at the end, and a wave that read it there could take another branch
     // (with barriers in it) than the thread that runs next_range
     const bool lean = lean_round(c), handled = c->handled != 0;
-    const unsigned int cand_at = handled ? c->cand_at : 0u, cand_total = c->cand_total;
-    const bool parts_left = cand_at > 0 && cand_at < cand_total;
-    const bool lost = handled && c->lost != 0;
+    const unsigned int cand_at = c->cand_at, cand_total = c->cand_total;
+    const bool parts_left = handled && cand_at > 0 && cand_at < cand_total;
+    const bool lost = c->lost != 0;
+    // (what the tail needs too: each load there would be a memory latency more)
+    const bool may_dense = dense_possible(s, c), hopeless = c->nlive == 0x7fffffffu;
+    const bool wide = c->thr_sel - c->thr64 > WIDE_BAND;
+    const unsigned int lean_max = c->lean_max;
+    const int swept_before = c->sweeps;
     // (a dense round in a launch without dense kernels waits too)
     const bool swept = full && !dense_round(c);
     if (!swept && !lean && !handled) {
         if (tid == 0) {
             c->pending = 1;
             if (c->dense == DENSE_NO && dense_allowed(s, c)) c->dense = DENSE_LEFT;
-            atomicAdd(&rem[REM_LEFT], 1);
-            atomicMax(&rem[REM_LENGTHS], s.maxL - c->m + 1);
+            atomicMax(&rem[REM_LEFT], s.maxL - c->m + 1);
             if (c->dense != DENSE_LEFT) {
                 atomicAdd(&rem[REM_SWEEP], 1);
                 atomicAdd(&rem[REM_WITNESS], 1);
@@ -4636,8 +4639,7 @@ __global__ __launch_bounds__(END_BLOCK) void k_round_end(SeriesDev* S, int32_t* 
             c->ncand = k + take;
             c->cand_at = cand_at + take;
             c->pending = 1;
-            atomicAdd(&rem[REM_LEFT], 1);
-            atomicMax(&rem[REM_LENGTHS], s.maxL - m + 1);
+            atomicMax(&rem[REM_LEFT], s.maxL - m + 1);
         }
         return;
     }
@@ -4649,15 +4651,12 @@ __global__ __launch_bounds__(END_BLOCK) void k_round_end(SeriesDev* S, int32_t* 
             c->rows_near += c->nlive;
             c->rows_far += c->nlive;
         }
-        c->exact_ref = redo && (!handled || (lost && c->thr_sel - c->thr64 > WIDE_BAND)) ? 1 : 0;
+        c->exact_ref = redo && (!handled || (lost && wide)) ? 1 : 0;
         c->pending = 0;
-        const int was = c->sweeps ? SWEEPS_AGAIN : 0;
-        c->sweeps = li == 0 || lean || handled || dense_allowed(s, c)
+        const bool many = may_dense ? (int64_t)ns * 2 > s.n - m + 1 : ns > lean_max;
+        c->sweeps = li == 0 || lean || handled || (may_dense && !hopeless)
                         ? SWEEPS_NO
-                        : was | ((dense_possible(s, c) ? (int64_t)ns * 2 > s.n - m + 1
-                                                       : ns > c->lean_max)
-                                     ? SWEEPS_MANY
-                                     : SWEEPS_FEW);
+                        : (swept_before ? SWEEPS_AGAIN : 0) | (many ? SWEEPS_MANY : SWEEPS_FEW);
         // (a heatmap row of a round that refined: the bitmap's rows, by k_heat)
         c->heat_m = ok && !direct ? m : 0;
         if (ok) {
@@ -4721,7 +4720,8 @@ __global__ __launch_bounds__(END_BLOCK) void k_round_end(SeriesDev* S, int32_t* 
             c->hot_r = hot_rows;
         }
     }
-    __syncthreads();  // (nothing of the round is read past this point)
+    // (the other waves read nothing of the control block after the barrier above
+    // thread 0's part; one more here would wait for its stores)
     if (more && tid == 0) next_range(s, c, guard, max_attempts, rem);
 }
 
