@@ -11,6 +11,9 @@ representative synthetic series of that bucket.  :func:`options_for` returns
 the entry of the bucket holding (n, m) -- or, when no bucket holds it, of
 the nearest bucket in (log n, log m) -- so every input gets tuned geometry.
 :func:`batch_options` returns the entry tuned on the 64-series batch.
+The stored entries were tuned when every range search swept; the seconds in
+their reports are of that program, and most inputs now sweep at their first
+length only.
 
 ``python -m paper_2304_01660_amd.tuning [OUT] [--only 0,5,batch]`` re-runs
 the autotuner for every bucket (or the listed ones) on the current GPU and
