@@ -369,11 +369,14 @@ __device__ void next_range(const SeriesDev& s, Ctrl* c, float guard, int max_att
     c->done = 0;
     c->active = 1;
     begin_range(s, c, guard);
-    atomicMax(&rem[REM_LEFT], s.maxL - c->m + 1);
-    if (c->li == 0 || c->sweeps) atomicAdd(&rem[REM_SWEEP], 1);
-    if (c->li == 0 || (c->sweeps & SWEEPS_FEW)) atomicAdd(&rem[REM_WITNESS], 1);
-    if (c->sweeps & SWEEPS_AGAIN) atomicAdd(&rem[REM_STEADY], 1);
-    if (dense_round(c)) atomicAdd(&rem[REM_DENSE], 1);
+    // (read before the first atomic: after one each would be a load of its own)
+    const int left = s.maxL - c->m + 1, sweeps = c->li == 0 ? (int)SWEEPS_FEW : c->sweeps;
+    const bool dense = dense_round(c);
+    atomicMax(&rem[REM_LEFT], left);
+    if (sweeps) atomicAdd(&rem[REM_SWEEP], 1);
+    if (sweeps & SWEEPS_FEW) atomicAdd(&rem[REM_WITNESS], 1);
+    if (sweeps & SWEEPS_AGAIN) atomicAdd(&rem[REM_STEADY], 1);
+    if (dense) atomicAdd(&rem[REM_DENSE], 1);
 }
 
 // Before the first round of a search.
